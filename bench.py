@@ -75,9 +75,9 @@ def source_sha(files):
     return h.hexdigest()
 
 
-ADJOINT_KERNEL = {"fp32": "cgemm_f32_kernel<GM_STORE>", "fp32_3m": "cgemm3m_kernel<GM_STORE, 0>",
+ADJOINT_KERNEL = {"fp32": "cgemm_kernel<GM_STORE, 4M>", "fp32_3m": "cgemm_kernel<GM_STORE, 3M>",
                   "bf16x3": "cgemm_bf16x3_kernel<GM_STORE>"}
-LINE_KERNEL = {"fp32": "cgemm_f32_kernel<GM_LINE>", "fp32_3m": "cgemm3m_kernel<GM_LINE, 0>",
+LINE_KERNEL = {"fp32": "cgemm_kernel<GM_LINE, 4M>", "fp32_3m": "cgemm_kernel<GM_LINE, 3M>",
                "bf16x3": "cgemm_bf16x3_kernel<GM_LINE>"}
 FORM_FLOPS = {"fp32": "four-product FP32, 8 m n k", "fp32_3m": "three-product FP32, 6 m n k",
               "bf16x3": "BF16 hi+lo split, 24 m n k in BF16"}
@@ -93,9 +93,9 @@ def precision_info(tl, name):
 
 
 TRAFFIC_RECORDS = {   # (precision, line-search form, product kind) -> (counter summary, kernel sources)
-    ("fp32_3m", "tile_grad", "gemm_line"): ("cgemm3m_line_traffic_tile.json", ("cgemm3m.hip", "gemm_common.hpp")),
+    ("fp32_3m", "tile_grad", "gemm_line"): ("cgemm3m_line_traffic_tile.json", ("cgemm.hip", "gemm_common.hpp")),
     ("fp32_3m", "tile_grad", "gemm_adjoint"): ("cgemm3m_adjoint_traffic_tile.json",
-                                               ("cgemm3m.hip", "gemm_common.hpp")),
+                                               ("cgemm.hip", "gemm_common.hpp")),
     ("bf16x3", "tile_grad", "gemm_line"): ("cgemm_bf16_line_traffic.json", ("cgemm_bf16.hip", "gemm_common.hpp")),
 }
 
@@ -846,8 +846,8 @@ def measure_workload(tl, torch, args, wl, inputs, steps, warmup, prec, line_prod
     dom = kernel_table(kt_dom)[dom_kind]
     dom_name = {"gemm_line": LINE_KERNEL[args.precision] + " ([a|b] = D [X1|X2], dense line search)",
                 "gemm_adjoint": ADJOINT_KERNEL[args.precision] + " (W = D^H r)",
-                "line_tile": "cgemm3m_kernel<GM_STORE|GM_LINE, 1> (tile-form line-search stages)",
-                "grad_tile": "cgemm3m_kernel<GM_STORE, 1|2> (tile-form gradient products)",
+                "line_tile": "cgemm_kernel<GM_STORE|GM_LINE, 3M, tile stage> (tile-form line-search stages)",
+                "grad_tile": "cgemm_kernel<GM_STORE, 3M, tile stage> (tile-form gradient products)",
                 "gemm_resid": "r = D X - U", "resid_tile": "tile-form residual product"}[dom_kind]
     mode = ("tile_grad" if n_tgrad else "tile") if n_tile else "dense"
     traffic = (measured_traffic(nfreq, wl.name, args.precision, mode, dom_kind) if nstreams == 1 else None)

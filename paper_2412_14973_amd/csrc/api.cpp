@@ -479,8 +479,7 @@ void assign_parts(Tables &T, int pstride) {
 
 int partial_stride(const Tables &T, int64_t nrp, int64_t nsp) {
     int ps = std::max(T.tseg_max, T.rseg_per_prob);
-    ps = std::max(ps, gemm_partials_per_problem(GM_LINE, (int)nsp, (int)nrp) / 5);
-    ps = std::max(ps, gemm_partials_per_problem(GM_RESID, (int)nsp, (int)nrp));
+    ps = std::max(ps, gemm_partial_slots((int)nsp, (int)nrp));
     return std::max(ps, 1);
 }
 
@@ -541,7 +540,8 @@ Ws carve(char *base, int op, int nprob, int64_t ldk, int64_t lds, int64_t theta_
         w.u = (float *)take(tz);
         w.cen = (float *)take(tz);
     }
-    w.partials = (double *)take((size_t)nprob * pstride * std::max(5, 6 * m1) * sizeof(double));
+    // sums per slot: one (objective) or, in a solve, up to five (line search) and 6 m1 (Gram pass)
+    w.partials = (double *)take((size_t)nprob * pstride * (op >= 2 ? std::max(5, 6 * m1) : 1) * sizeof(double));
     w.sc = (SolveScalars *)take((size_t)nprob * sizeof(SolveScalars));
     w.tables = take(tbytes);
     w.bytes = o;
@@ -1014,13 +1014,7 @@ template <typename T> std::vector<T> pick(const T *a, const std::vector<int> &id
 int ws_bytes_grouped(int op, int count, const tlrmdd_plan *plans, const tlrmdd_opts *opts, size_t *bytes,
                      std::vector<size_t> *parts = nullptr);
 
-// A second stream with its fork / join events for a run (see Run::side), or none.
-struct SideStream {
-    hipStream_t s = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-};
-
-// Runs impl(sub-batch arrays, workspace slice, bytes, stream, side stream) for every sub-batch: the first on
+// Runs impl(sub-batch arrays, workspace slice, bytes, stream) for every sub-batch: the first on
 // `stream`, the others on pool streams that wait for `stream` first and are waited for at the end.
 template <typename Impl>
 int run_grouped(int op, int count, const tlrmdd_plan *plans, const void *const *D, const void *const *U,
@@ -1033,19 +1027,12 @@ int run_grouped(int op, int count, const tlrmdd_plan *plans, const void *const *
     int st = ws_bytes_grouped(op, count, plans, opts, &need, &parts);
     if (st) return st;
     if (!workspace || ws_bytes < need) return fail(TLRMDD_WORKSPACE, "workspace too small");
-    // S sub-batches: S - 1 pool streams forked with event S - 1 and joined with events 0 .. S - 2;
-    // one sub-batch: a pool stream serves as the run's side stream (events S and S + 1 fork and join it)
+    // S sub-batches: S - 1 pool streams forked with event S - 1 and joined with events 0 .. S - 2
     CallStreams cs;
-    if ((st = pool_get(S == 1 ? 1 : S - 1, S + 2, stream, cs))) return st;
+    if (S > 1 && (st = pool_get(S - 1, S, stream, cs))) return st;
     const std::vector<hipStream_t> &ps = cs.st;
     const std::vector<hipEvent_t> &ev = cs.ev;
-    SideStream side;
-    if (S == 1) {
-        side.s = ps[0];
-        side.fork = ev[S];
-        side.join = ev[S + 1];
-    }
-    HIP_TRY(hipEventRecord(ev[S - 1], stream));
+    if (S > 1) HIP_TRY(hipEventRecord(ev[S - 1], stream));
     for (int k = 0; k < S - 1; ++k) HIP_TRY(hipStreamWaitEvent(ps[k], ev[S - 1], 0));
     char *base = static_cast<char *>(workspace);
     int first_err = TLRMDD_OK;
@@ -1057,7 +1044,7 @@ int run_grouped(int op, int count, const tlrmdd_plan *plans, const void *const *
         const std::vector<double *> gf = pick(fhist, m);
         const int k = (int)(g % S);
         const int e = impl((int)m.size(), gp.data(), gd.data(), gu.data(), gt.data(), gf.data(), base, parts[g],
-                           k == 0 ? stream : ps[k - 1], S == 1 ? &side : nullptr);
+                           k == 0 ? stream : ps[k - 1]);
         if (e && !first_err) first_err = e;
         base += align256(parts[g]);
     }
@@ -1200,6 +1187,7 @@ struct Ctx {
     hipStream_t s;
     bool bf16 = false;          // BF16 hi+lo split products
     bool p3m = false;           // FP32 products in the three-real-product form
+    bool split = false;         // dense FP32 products with the contraction split over waves (gemm_split_k)
     int64_t xspace = 0;         // complex64 elements of X space per problem (1 or 2 ldk x ldk)
 
     int form() const { return bf16 ? F_BF16X3 : p3m ? F_3M : F_4M; }
@@ -1211,11 +1199,30 @@ struct Ctx {
     int64_t lo_words() const { return xspace; }
 };
 
+// The contraction of a dense FP32 product is split over the four waves of a workgroup where a wave for every
+// 32 x 32 block would fill the chip's 1024 SIMDs fewer than eight times: below that the last round and the
+// few waves per SIMD cost more than the sums over the waves (one problem, three products, us for r = D X - U,
+// D^H r and [a | b], split against a wave per block: 512^2 16, 15, 24 against 38, 35, 63; 1024^2 59, 57, 107
+// against 70, 69, 121; 2304^2 560, 559, 1086 against 635, 637, 1228; 4096 x 2048 1518, 1579, 3050 against
+// 1503, 1537, 2957; where a batch fills the chip anyway the split is 2 to 4 % slower). The order of the sums
+// changes with it, so the choice looks at the problem's own sizes only: its results do not depend on its batch.
+constexpr int64_t SPLIT_MAX_BLOCKS = 8191;
+bool gemm_split_k(int64_t nr, int64_t ns) {
+    return ((nr + 31) / 32) * ((std::max(nr, ns) + 31) / 32) <= SPLIT_MAX_BLOCKS;
+}
+
+void set_precision(Ctx &c, int precision) {
+    c.bf16 = precision == TLRMDD_BF16X3;
+    c.p3m = precision == TLRMDD_FP32_3M;
+    c.split = gemm_split_k(c.nr, c.ns);
+}
+
 int fin(const Ctx &c, FinArgs f, const int32_t *counts, int ucount, int nsum) {
     f.partials = c.w.partials;
     f.pstride = c.pstride;
     f.counts = counts;
     f.ucount = ucount;
+    if (f.nfirst == 0) f.ucount2 = ucount;   // one count for all problems
     f.nsum = nsum;
     HIP_TRY(launch_finalize(f, c.nprob, c.s));
     return TLRMDD_OK;
@@ -1252,9 +1259,9 @@ int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64
     g.E = U; g.lde = ldu; g.sE = sU;
     g.partials = c.w.partials; g.sP = (int64_t)c.pstride;   // one sum per workgroup
     g.M = (int)c.lds; g.N = (int)c.ldk; g.K = (int)round_up(c.nr, GEMM_BK);
-    g.Me = (int)c.ns; g.Ne = (int)c.nr;
+    g.Me = g.Mt = (int)c.ns; g.Ne = g.Nt = (int)c.nr;
     HIP_TRY(timed(TLRMDD_K_GEMM_RESID, c.s, wk, [&] {
-        return c.p3m ? launch_cgemm3m(GM_RESID, g, c.nprob, c.s) : launch_cgemm(GM_RESID, g, c.nprob, c.s);
+        return launch_cgemm(GM_RESID, g, c.nprob, c.s, GR_DENSE, c.p3m, c.split);
     }));
     return TLRMDD_OK;
 }
@@ -1278,12 +1285,13 @@ int gemm_adjoint(const Ctx &c, const float2 *r, float2 *W, int64_t sW) {
         return TLRMDD_OK;
     }
     GemmArgs g = gemm_args();
-    g.A = c.w.DHs; g.lda = c.lds; g.sA = c.ldk * c.lds;
+    g.A = c.w.Ds; g.lda = c.ldk; g.sA = c.lds * c.ldk;   // read transposed and conjugated
     g.B = r; g.ldb = c.ldk; g.sB = c.lds * c.ldk;
     g.C = W; g.ldc = c.ldk; g.sC = sW;
     g.M = (int)c.ldk; g.N = (int)c.ldk; g.K = (int)round_up(c.ns, GEMM_BK);
+    g.Mt = g.Nt = (int)c.nr;
     HIP_TRY(timed(TLRMDD_K_GEMM_ADJOINT, c.s, wk, [&] {
-        return c.p3m ? launch_cgemm3m(GM_STORE, g, c.nprob, c.s) : launch_cgemm(GM_STORE, g, c.nprob, c.s);
+        return launch_cgemm(GM_STORE, g, c.nprob, c.s, GR_ADJOINT, c.p3m, c.split);
     }));
     return TLRMDD_OK;
 }
@@ -1315,8 +1323,9 @@ int gemm_line(const Ctx &c, const float2 *X1, const float2 *X2, int64_t sX) {
     g.E = c.w.r; g.lde = c.ldk; g.sE = c.lds * c.ldk;
     g.partials = c.w.partials; g.sP = (int64_t)c.pstride * 5;
     g.M = (int)c.lds; g.N = (int)c.ldk; g.K = (int)round_up(c.nr, GEMM_BK);
+    g.Mt = (int)c.ns; g.Nt = (int)c.nr;
     HIP_TRY(timed(TLRMDD_K_GEMM_LINE, c.s, wk, [&] {
-        return c.p3m ? launch_cgemm3m(GM_LINE, g, c.nprob, c.s) : launch_cgemm(GM_LINE, g, c.nprob, c.s);
+        return launch_cgemm(GM_LINE, g, c.nprob, c.s, GR_DENSE, c.p3m, c.split);
     }));
     return TLRMDD_OK;
 }
@@ -1331,6 +1340,7 @@ int split_r_transpose(const Ctx &c) {
 
 // staging of D for problem p (padded; split planes in BF16 mode): reads D, writes D and D^H
 int stage(const Ctx &c, int p, const float2 *D, bool with_dh) {
+    with_dh = with_dh && c.bf16;   // the FP32 adjoint product reads D itself
     const Work wk = bytes_work((with_dh ? 24.0 : 16.0) * (double)c.ns * (double)c.nr);
     if (c.bf16) {
         uint32_t *dh = c.dsw() + (int64_t)p * 2 * c.lds * c.ldk;
@@ -1348,8 +1358,13 @@ int stage(const Ctx &c, int p, const float2 *D, bool with_dh) {
     return TLRMDD_OK;
 }
 
-int resid_tiles(const Ctx &c) { return gemm_partials_per_problem(GM_RESID, (int)c.lds, (int)c.ldk); }
-int line_tiles(const Ctx &c) { return gemm_partials_per_problem(GM_LINE, (int)c.lds, (int)c.ldk) / 5; }
+// partial-sum slots that the products of `mode` fill per problem: those of the FP32 kernel, or (dense
+// products in BF16 mode) one per 128 x 128 (GM_LINE: 128 x 64) tile
+int partial_slots(const Ctx &c, int mode, bool tile_form = false) {
+    if (c.bf16 && !tile_form)
+        return (int)(c.lds / GEMM_BM) * (int)(c.ldk / (mode == GM_LINE ? GEMM_BN / 2 : GEMM_BN));
+    return gemm_partial_slots((int)c.lds, (int)c.ldk);
+}
 
 // The whole solve, for one problem or a batch of equal-shape problems.
 // One run of the solver over `nprob` problems of one shape: tables, workspace views, staged operands
@@ -1374,10 +1389,6 @@ struct Run {
     int n_adj = 0;                   // problems before the tile-form gradient ranges (adjoint product)
     std::vector<double> theta_pre;   // complex unknowns of problems 0 .. p - 1 (true sizes)
     std::vector<double> asm_pre, asm_dir_pre, grad_pre;   // tile-product complex flops, likewise
-    // a second stream (default priority) on which the tile-form gradient runs beside the adjoint
-    // product of the other problems, and the events that fork it from and join it to c.s
-    hipStream_t side = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
 };
 
 // The context of problems p0 .. p0 + np - 1 of a run for the line-search products (complex64 operands
@@ -1399,10 +1410,8 @@ Ctx line_ctx(const Ctx &c, int p0, int np) {
 // Stage 1 of a tile range: pack the factor blocks of theta and of the direction `dir`, then
 // Pcol_(p,j) = [D_:,i A_dir(ij) ... | D_:,i A_th(ij) ...] (see LineTile), or the direction half only
 // (dir_only: the theta half is carried by P_th += step P_p in ranges with the tile-form gradient)
-int tile_stage1(Run &R, const LineSeg &sg, const float *dir, bool dir_only = false, bool theta_only = false,
-                hipStream_t stream = nullptr) {
-    Ctx c = line_ctx(R.c, sg.p0, sg.np);
-    if (stream) c.s = stream;
+int tile_stage1(Run &R, const LineSeg &sg, const float *dir, bool dir_only = false, bool theta_only = false) {
+    const Ctx c = line_ctx(R.c, sg.p0, sg.np);
     const LineTile &L = sg.lt;
     const LineClass &lc = L.lc;
     const int64_t NA = L.NA, d = lc.d, nt = lc.nt;
@@ -1424,18 +1433,17 @@ int tile_stage1(Run &R, const LineSeg &sg, const float *dir, bool dir_only = fal
     const double h = (dir_only || theta_only) ? 1.0 : 2.0;   // halves formed
     const Work wk = gemm_work(F_3M, 8.0 * ns * dd * ks * h, 8.0 * (ns * nr * np + dd * ks * h + ns * ks * h));
     HIP_TRY(timed(TLRMDD_K_LINE_TILE, c.s, wk, [&] {
-        return launch_cgemm3m(GM_STORE, g1, (int)(c.nprob * nt), c.s, GR_TILE);
+        return launch_cgemm(GM_STORE, g1, (int)(c.nprob * nt), c.s, GR_TILE, true, false);
     }));
     return TLRMDD_OK;
 }
 
 // [a | b] = D [X1 | X2] with the five line-search sums for the problems of a tile range (see LineTile).
 // dir_only: stage 1 forms the direction half only (the theta half is current, see tile_pcol_update).
-int line_products_tile(Run &R, const LineSeg &sg, bool dir_only = false, hipStream_t stream = nullptr) {
-    int st = tile_stage1(R, sg, R.c.w.p, dir_only, false, stream);
+int line_products_tile(Run &R, const LineSeg &sg, bool dir_only = false) {
+    int st = tile_stage1(R, sg, R.c.w.p, dir_only);
     if (st) return st;
-    Ctx c = line_ctx(R.c, sg.p0, sg.np);
-    if (stream) c.s = stream;
+    const Ctx c = line_ctx(R.c, sg.p0, sg.np);
     const LineTile &L = sg.lt;
     const LineClass &lc = L.lc;
     const int64_t NA = L.NA, d = lc.d, nt = lc.nt;
@@ -1445,7 +1453,7 @@ int line_products_tile(Run &R, const LineSeg &sg, bool dir_only = false, hipStre
     g2.C = c.w.a; g2.C2 = c.w.b; g2.ldc = c.ldk; g2.sC = c.lds * c.ldk; g2.sC2 = d;
     g2.E = c.w.r; g2.lde = c.ldk; g2.sE = c.lds * c.ldk; g2.sE2 = d;
     g2.partials = c.w.partials; g2.sP = (int64_t)c.pstride * 5;
-    g2.sP2 = (c.lds / GEMM_BM) * (d / (GEMM_BN / 2)) * 5;   // the line tiles of one tile column
+    g2.sP2 = gemm_partial_slots((int)c.lds, (int)d) * 5;   // those of one tile column
     g2.M = (int)c.lds; g2.N = (int)d; g2.K = (int)NA;
     g2.K2 = (int)(nt * lc.kpad);   // b: the direction half of Pcol only
     g2.nz2 = (int)nt;
@@ -1454,7 +1462,7 @@ int line_products_tile(Run &R, const LineSeg &sg, bool dir_only = false, hipStre
         const Work wk = gemm_work(F_3M, 24.0 * ns * dd * ks,
                                   8.0 * (2.0 * ns * ks + 2.0 * ks * dd + 3.0 * ns * nr * np));
         HIP_TRY(timed(TLRMDD_K_LINE_TILE, c.s, wk, [&] {
-            return launch_cgemm3m(GM_LINE, g2, (int)(c.nprob * nt), c.s, GR_TILE);
+            return launch_cgemm(GM_LINE, g2, (int)(c.nprob * nt), c.s, GR_TILE, true, false);
         }));
     }
     return TLRMDD_OK;
@@ -1462,9 +1470,8 @@ int line_products_tile(Run &R, const LineSeg &sg, bool dir_only = false, hipStre
 
 // Gradient of the problems of a tile range in tile form (see GRAD_TILE_MAX_COST), into g. Needs the
 // theta half of Pcol for the current theta.
-int tile_gradient(Run &R, const LineSeg &sg, float *g, hipStream_t stream) {
-    Ctx c = line_ctx(R.c, sg.p0, sg.np);
-    c.s = stream;
+int tile_gradient(Run &R, const LineSeg &sg, float *g) {
+    const Ctx c = line_ctx(R.c, sg.p0, sg.np);
     const LineTile &L = sg.lt;
     const LineClass &lc = L.lc;
     const int64_t NA = L.NA, d = lc.d, nt = lc.nt, kp = lc.kpad, Wg = L.Wg;
@@ -1483,7 +1490,7 @@ int tile_gradient(Run &R, const LineSeg &sg, float *g, hipStream_t stream) {
     g1.nz2 = (int)nt;
     HIP_TRY(timed(TLRMDD_K_GRAD_TILE, c.s,
                   gemm_work(F_3M, 8.0 * ns * dd * ks, 8.0 * (ns * nr * np + dd * ks + ns * ks)), [&] {
-                      return launch_cgemm3m(GM_STORE, g1, (int)(c.nprob * nt), c.s, GR_TILE);
+                      return launch_cgemm(GM_STORE, g1, (int)(c.nprob * nt), c.s, GR_TILE, true, false);
                   }));
     // G2 and G3 in one launch of the transposed-A / conjugated-B role, per (p, tile x, part q):
     //   set 0: GBT_(p,x,q) = r_p[q Kc ..., x d ...]^T conj(Pcol_th(p,x)[q Kc ...])
@@ -1498,7 +1505,7 @@ int tile_gradient(Run &R, const LineSeg &sg, float *g, hipStream_t stream) {
     g3.nz2 = (int)(nt * KS * 2); g3.nz3 = KS; g3.nz4 = 2;
     HIP_TRY(timed(TLRMDD_K_GRAD_TILE, c.s,
                   gemm_work(F_3M, 16.0 * ns * dd * ks, 8.0 * (2.0 * ns * nr * np + 2.0 * ns * ks + 2.0 * dd * ks)),
-                  [&] { return launch_cgemm3m(GM_STORE, g3, (int)(c.nprob * nt * KS * 2), c.s, GR_TILE_TA_CB); }));
+                  [&] { return launch_cgemm(GM_STORE, g3, (int)(c.nprob * nt * KS * 2), c.s, GR_TILE_TA_CB, true, false); }));
     // every gradient entry (d ksum of them) from 2 KS partial planes
     HIP_TRY(timed(TLRMDD_K_LINE_PACK, c.s, bytes_work(8.0 * (2.0 * KS + 1.0) * dd * ks), [&] {
         return launch_tlr_grad(L.gitems, L.ngitems, L.GA, L.GBT, KS, d * Wg, Wg, true, (float2 *)g, c.s);
@@ -1524,14 +1531,14 @@ int tile_resid(Run &R, const LineSeg &sg) {
     g.C = c0.w.r + sg.p0 * rs; g.ldc = c0.ldk; g.sC = rs; g.sC2 = d;
     g.E = c0.w.Us + sg.p0 * rs; g.lde = c0.ldk; g.sE = rs; g.sE2 = d;
     g.partials = c0.w.partials + (int64_t)sg.p0 * c0.pstride; g.sP = c0.pstride;
-    g.sP2 = (c0.lds / GEMM_BM) * (d / GEMM_BN);   // the residual tiles of one tile column
+    g.sP2 = gemm_partial_slots((int)c0.lds, (int)d);   // those of one tile column
     g.M = (int)c0.lds; g.N = (int)d; g.K = (int)(nt * kp);
     g.Me = (int)c0.ns; g.Ne = (int)d;             // E's columns are local to the tile column
     g.nz2 = (int)nt;
     const double ks = L.ksum, dd = (double)d, ns = (double)c0.ns, nr = (double)c0.nr, np = sg.np;
     const Work wk = gemm_work(F_3M, 8.0 * ns * dd * ks, 8.0 * (ns * ks + dd * ks + 2.0 * ns * nr * np));
     HIP_TRY(timed(TLRMDD_K_RESID_TILE, c0.s, wk, [&] {
-        return launch_cgemm3m(GM_RESID, g, (int)(sg.np * nt), c0.s, GR_TILE);
+        return launch_cgemm(GM_RESID, g, (int)(sg.np * nt), c0.s, GR_TILE, true, false);
     }));
     return TLRMDD_OK;
 }
@@ -1558,15 +1565,18 @@ int clear_plane_padding(Run &R) {
 }
 
 // record < 0: no f-history entry
-int fin_f(Run &R, int record, double lam, int nsum_parts) {
+// nfirst, first_parts: another number of partial sums for the problems before nfirst
+int fin_f(Run &R, int record, double lam, int nsum_parts, int nfirst = 0, int first_parts = 0) {
     FinArgs f = fin_args(FIN_F, R.c.w.sc);
+    f.nfirst = nfirst;
+    f.ucount2 = nsum_parts;
     if (record >= 0) {
         f.fhist = R.single ? nullptr : R.c.D.fhist;
         f.fhist0 = R.fhist0;
         f.t = record;
     }
     f.lam = lam;
-    return fin(R.c, f, nullptr, nsum_parts, 1);
+    return fin(R.c, f, nullptr, nfirst ? first_parts : nsum_parts, 1);
 }
 
 // r = D C(theta) - U afresh: assembly and the dense product for the problems before the tile-form
@@ -1591,7 +1601,7 @@ int objective_fresh(Run &R, int record, double lam) {
         if (sg.tile && sg.lt.lc.grad)
             if ((e = tile_resid(R, sg))) return e;
     if ((e = split_r_transpose(c))) return e;
-    return fin_f(R, record, lam, resid_tiles(c));
+    return fin_f(R, record, lam, partial_slots(c, GM_RESID, true), R.n_adj, partial_slots(c, GM_RESID));
 }
 
 int run_setup(Run &R, int op, int nprob, const tlrmdd_plan *plans, const void *const *D, const void *const *U,
@@ -1685,8 +1695,7 @@ int run_setup(Run &R, int op, int nprob, const tlrmdd_plan *plans, const void *c
     R.fhist0 = R.single ? fhist[0] : nullptr;
     R.xstride = 2 * c.ldk * c.ldk;   // per-problem X-space stride
     R.rstride = c.lds * c.ldk;
-    c.bf16 = opts->precision == TLRMDD_BF16X3;
-    c.p3m = opts->precision == TLRMDD_FP32_3M;
+    set_precision(c, opts->precision);
     c.xspace = R.xstride;
     R.X1 = c.w.XW;
     R.X2 = c.w.XW + c.ldk * c.ldk;
@@ -1742,17 +1751,11 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
     for (int t = 0; t < iters; ++t) {
         // gradient from the tracked residual (eqs. DXLR): W = D^H r and the tile blocks of W' for the
         // problems before the tile-form gradient ranges, the tile form for those
-        // (the two parts write disjoint problems' gradients; with a side stream they run side by side)
-        const bool overlap = R.side && R.n_adj > 0 && R.n_adj < c.nprob;
-        hipStream_t gs = s;
-        if (overlap) {
-            HIP_TRY(hipEventRecord(R.fork, s));
-            HIP_TRY(hipStreamWaitEvent(R.side, R.fork, 0));
-            gs = R.side;
-        }
+        // (one after the other: either part fills the chip, and side by side on two streams their operands
+        // push each other out of the caches - 16 problems of 1024^2, 11.1 ms a solve against 10.0)
         for (const LineSeg &sg : R.segs)
             if (sg.tile && sg.lt.lc.grad)
-                if ((st = tile_gradient(R, sg, R.gcur, gs))) return st;
+                if ((st = tile_gradient(R, sg, R.gcur))) return st;
         if (R.n_adj > 0) {
             const Ctx ca = R.n_adj == c.nprob ? c : line_ctx(c, 0, R.n_adj);
             if ((st = gemm_adjoint(ca, c.w.r, R.X1, R.xstride))) return st;
@@ -1763,10 +1766,6 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
                 return launch_grad(c.D.tiles, c.D.grad_items, ng, c.D.probs, R.X1, (const float2 *)c.w.th,
                                    (float2 *)R.gcur, s);
             }));
-        }
-        if (overlap) {
-            HIP_TRY(hipEventRecord(R.join, R.side));
-            HIP_TRY(hipStreamWaitEvent(s, R.join, 0));
         }
         if (lam != 0.0) HIP_TRY(launch_reg_grad(c.D.tsegs, nt, R.gcur, c.w.th, cen, (float)(2.0 * lam), s));
         // direction: steepest descent first, then L-BFGS in vector-free form (Gram pass, two-loop
@@ -1811,38 +1810,26 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
             HIP_TRY(launch_pen(c.D.tsegs, nt, c.w.th, cen, c.w.p, c.w.partials, s));
             if ((st = fin(c, fin_args(FIN_LAMTERMS, c.w.sc), c.D.tcount, 0, 2))) return st;
         }
-        // With a side stream and several tile ranges, the tile ranges alternate between it and s once
-        // the dense ranges' product is enqueued, so that the small launches of two tile classes fill
-        // each other's last rounds of workgroups; the side stream is joined before the line sums.
-        int ntile = 0;
-        for (const LineSeg &sg : R.segs) ntile += sg.tile ? 1 : 0;
-        const bool tile_overlap = R.side && ntile > 1;
-        bool forked = false;
-        int itile = 0;
         for (const LineSeg &sg : R.segs) {
             // ranges with the tile-form gradient carry P_th from step to step (formed afresh with every
             // residual recompute, so its rounding accumulates over no more iterations than the tracked
             // residual's): stage 1 forms the direction half only where the halves fill whole tiles
             const bool dir_only = sg.tile && sg.lt.lc.grad && (sg.lt.lc.nt * sg.lt.lc.kpad) % GEMM_BN == 0;
-            if (sg.tile && tile_overlap && !forked) {
-                HIP_TRY(hipEventRecord(R.fork, s));
-                HIP_TRY(hipStreamWaitEvent(R.side, R.fork, 0));
-                forked = true;
-            }
-            if (sg.tile) st = line_products_tile(R, sg, dir_only, (tile_overlap && (itile++ & 1) == 0) ? R.side : s);
+            if (sg.tile) st = line_products_tile(R, sg, dir_only);
             else if (sg.np == c.nprob) st = gemm_line(c, R.X1, R.X2, R.xstride);
             else st = gemm_line(line_ctx(c, sg.p0, sg.np), R.X1 + sg.p0 * R.xstride, R.X2 + sg.p0 * R.xstride,
                                 R.xstride);
             if (st) return st;
         }
-        if (forked) {
-            HIP_TRY(hipEventRecord(R.join, R.side));
-            HIP_TRY(hipStreamWaitEvent(s, R.join, 0));
-        }
         {
+            // the dense-form problems come before the tile ranges
             FinArgs f = fin_args(FIN_LINE, c.w.sc);
             f.lam = lam;
-            if ((st = fin(c, f, nullptr, line_tiles(c), 5))) return st;
+            f.nfirst = 0;
+            for (const LineSeg &sg : R.segs)
+                if (!sg.tile) f.nfirst = std::max(f.nfirst, sg.p0 + sg.np);
+            f.ucount2 = partial_slots(c, GM_LINE, true);
+            if ((st = fin(c, f, nullptr, f.nfirst ? partial_slots(c, GM_LINE) : f.ucount2, 5))) return st;
         }
         // updates
         HIP_TRY(timed(TLRMDD_K_THETA_UPDATE, s,
@@ -1881,15 +1868,10 @@ int run_finish(Run &R, const tlrmdd_plan *plans, void *const *theta) {
 
 int solve_impl(int nprob, const tlrmdd_plan *plans, const void *const *D, const void *const *U,
                void *const *theta, const tlrmdd_opts *opts, double *const *fhist, void *workspace,
-               size_t ws_bytes, hipStream_t s, const SideStream *side = nullptr) {
+               size_t ws_bytes, hipStream_t s) {
     Run R;
     int st = run_setup(R, 2, nprob, plans, D, U, theta, opts, fhist, workspace, ws_bytes, s);
     if (st) return st;
-    if (side) {
-        R.side = side->s;
-        R.fork = side->fork;
-        R.join = side->join;
-    }
     const double lam = opts->lambda;
     if (lam != 0.0) {
         HIP_TRY(launch_pen(R.c.D.tsegs, R.nt, R.c.w.th, nullptr, nullptr, R.c.w.partials, s));
@@ -1916,16 +1898,11 @@ int check_admm(const tlrmdd_admm_opts *a) {
 // device. f-history: data misfit at the start and after every X-update.
 int admm_impl(int nprob, const tlrmdd_plan *plans, const void *const *D, const void *const *U,
               void *const *theta, const tlrmdd_admm_opts *aopts, double *const *fhist, void *workspace,
-              size_t ws_bytes, hipStream_t s, const SideStream *side = nullptr) {
+              size_t ws_bytes, hipStream_t s) {
     int st = check_admm(aopts);
     if (st) return st;
     Run R;
     if ((st = run_setup(R, 3, nprob, plans, D, U, theta, &aopts->inner, fhist, workspace, ws_bytes, s))) return st;
-    if (side) {
-        R.side = side->s;
-        R.fork = side->fork;
-        R.join = side->join;
-    }
     Ctx &c = R.c;
     if ((st = objective_fresh(R, -1, 0.0))) return st;
     auto record = [&](int k) -> int {
@@ -1972,8 +1949,7 @@ int tlrmdd_forward(tlrmdd_plan plan, const void *D, const void *U, const void *t
     c.w = carve((char *)workspace, 0, 1, c.ldk, c.lds, theta_span(plan->H.theta_size), 1, c.pstride, 0);
     if (c.w.bytes > ws_bytes) return fail(TLRMDD_WORKSPACE, "workspace too small");
     c.D = plan->D;
-    c.bf16 = precision == TLRMDD_BF16X3;
-    c.p3m = precision == TLRMDD_FP32_3M;
+    set_precision(c, precision);
     c.xspace = c.ldk * c.ldk;
     if (c.ldk != c.nr) HIP_TRY(launch_fill_zero(c.w.XW, (size_t)c.ldk * c.ldk * sizeof(float2), stream));
     if ((st = stage(c, 0, (const float2 *)D, false))) return st;
@@ -1983,7 +1959,7 @@ int tlrmdd_forward(tlrmdd_plan plan, const void *D, const void *U, const void *t
     if ((st = gemm_resid(c, c.w.XW, 0, (const float2 *)U, c.nr, 0, c.w.r))) return st;
     FinArgs f = fin_args(FIN_F_OUT, c.w.sc);
     f.fout = f_dev;
-    if ((st = fin(c, f, nullptr, resid_tiles(c), 1))) return st;
+    if ((st = fin(c, f, nullptr, partial_slots(c, GM_RESID), 1))) return st;
     if (r_out) HIP_TRY(launch_copy2d(c.w.r, c.ldk, (float2 *)r_out, c.nr, c.ns, c.nr, stream));
     if (X_out) {
         if (c.bf16)   // the X space holds split planes: re-assemble X in complex64 for the caller
@@ -2012,8 +1988,7 @@ int tlrmdd_grad(tlrmdd_plan plan, const void *D, const void *U, const void *thet
     c.w = carve((char *)workspace, 1, 1, c.ldk, c.lds, theta_span(plan->H.theta_size), 1, c.pstride, 0);
     if (c.w.bytes > ws_bytes) return fail(TLRMDD_WORKSPACE, "workspace too small");
     c.D = plan->D;
-    c.bf16 = precision == TLRMDD_BF16X3;
-    c.p3m = precision == TLRMDD_FP32_3M;
+    set_precision(c, precision);
     c.xspace = c.ldk * c.ldk;
     if (c.ldk != c.nr) HIP_TRY(launch_fill_zero(c.w.XW, (size_t)c.ldk * c.ldk * sizeof(float2), stream));
     if ((st = stage(c, 0, (const float2 *)D, true))) return st;
@@ -2025,7 +2000,7 @@ int tlrmdd_grad(tlrmdd_plan plan, const void *D, const void *U, const void *thet
     if (f_dev) {
         FinArgs f = fin_args(FIN_F_OUT, c.w.sc);
         f.fout = f_dev;
-        if ((st = fin(c, f, nullptr, resid_tiles(c), 1))) return st;
+        if ((st = fin(c, f, nullptr, partial_slots(c, GM_RESID), 1))) return st;
     }
     // the assembled X is dead once r exists: W = D^H r reuses its storage
     if ((st = gemm_adjoint(c, c.w.r, c.w.XW, 0))) return st;
@@ -2051,8 +2026,7 @@ int tlrmdd_adjoint(tlrmdd_plan plan, const void *D, const void *U, void *X_out, 
     c.w = carve((char *)workspace, 1, 1, c.ldk, c.lds, theta_span(plan->H.theta_size), 1, c.pstride, 0);
     if (c.w.bytes > ws_bytes) return fail(TLRMDD_WORKSPACE, "workspace too small");
     c.D = plan->D;
-    c.bf16 = precision == TLRMDD_BF16X3;
-    c.p3m = precision == TLRMDD_FP32_3M;
+    set_precision(c, precision);
     c.xspace = c.ldk * c.ldk;
     if ((st = stage(c, 0, (const float2 *)D, true))) return st;
     // U takes the place of the residual: padded copy with zero padding, then W = D^H U
@@ -2174,8 +2148,8 @@ int tlrmdd_admm_batched(int count, const tlrmdd_plan *plans, const void *const *
         return admm_impl(count, plans, D, U, theta_inout, opts, f_hist_dev, workspace, ws_bytes, stream);
     return run_grouped(3, count, plans, D, U, theta_inout, &opts->inner, f_hist_dev, workspace, ws_bytes, stream,
                        [&](int n, const tlrmdd_plan *p, const void *const *d, const void *const *u, void *const *t,
-                           double *const *f, void *w, size_t b, hipStream_t s, const SideStream *side) {
-                           return admm_impl(n, p, d, u, t, opts, f, w, b, s, side);
+                           double *const *f, void *w, size_t b, hipStream_t s) {
+                           return admm_impl(n, p, d, u, t, opts, f, w, b, s);
                        });
 }
 
@@ -2191,8 +2165,8 @@ int tlrmdd_solve_batched(int count, const tlrmdd_plan *plans, const void *const 
         return solve_impl(count, plans, D, U, theta_inout, opts, f_hist_dev, workspace, ws_bytes, stream);
     return run_grouped(2, count, plans, D, U, theta_inout, opts, f_hist_dev, workspace, ws_bytes, stream,
                        [&](int n, const tlrmdd_plan *p, const void *const *d, const void *const *u, void *const *t,
-                           double *const *f, void *w, size_t b, hipStream_t s, const SideStream *side) {
-                           return solve_impl(n, p, d, u, t, opts, f, w, b, s, side);
+                           double *const *f, void *w, size_t b, hipStream_t s) {
+                           return solve_impl(n, p, d, u, t, opts, f, w, b, s);
                        });
 }
 
@@ -2696,7 +2670,7 @@ TlrWs tlr_carve(char *base, const TlrHost &T, int64_t lds, int64_t ldk) {
     w.B = (float2 *)take((size_t)N * T.K2p * T.dp * c8);
     w.Pcol = (float2 *)take((size_t)N * lds * T.K2p * c8);
     w.R = (float2 *)take((size_t)N * lds * T.dp * c8);
-    w.partials = (double *)take((size_t)N * (lds / GEMM_BM) * (T.dp / GEMM_BN) * sizeof(double));
+    w.partials = (double *)take((size_t)N * gemm_partial_slots((int)lds, (int)T.dp) * sizeof(double));
     w.sc = (SolveScalars *)take(sizeof(SolveScalars));
     w.pa = (PackItem *)take(T.packA.size() * sizeof(PackItem));
     w.pb = (PackItem *)take(T.packB.size() * sizeof(PackItem));
@@ -2741,7 +2715,7 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
     HIP_TRY(launch_stage_d((const float2 *)D, ns, nr, w.Ds, ldk, nullptr, lds, s));
     HIP_TRY(launch_tlr_pack(w.pa, (int)T.packA.size(), (const float2 *)theta, w.A, s));
     HIP_TRY(launch_tlr_pack(w.pb, (int)T.packB.size(), (const float2 *)theta, w.B, s));
-    const int64_t tiles2 = (lds / GEMM_BM) * (T.dp / GEMM_BN);
+    const int64_t tiles2 = gemm_partial_slots((int)lds, (int)T.dp);
     for (const auto &run : T.runs) {   // stage 1: P_i = D_:,i A_i
         const int i0 = run.first, cnt = run.second - run.first + 1, di = H.d[i0];
         GemmArgs g = gemm_args();
@@ -2749,7 +2723,7 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
         g.B = w.A + i0 * T.Kpmax * T.K1p; g.ldb = T.K1p; g.sB = T.Kpmax * T.K1p;
         g.C = w.P + i0 * lds * T.K1p; g.ldc = T.K1p; g.sC = lds * T.K1p;
         g.M = (int)lds; g.N = (int)T.K1p; g.K = (int)round_up(di, GEMM_BK);
-        HIP_TRY(launch_cgemm(GM_STORE, g, cnt, s));
+        HIP_TRY(launch_cgemm(GM_STORE, g, cnt, s, GR_DENSE, false, false));
     }
     HIP_TRY(launch_tlr_gather(w.gi, (int)T.gather.size(), w.P, w.Pcol, lds, s));
     for (const auto &run : T.runs) {   // stage 2: r_:,j = Pcol_j B_j - U_:,j
@@ -2762,13 +2736,13 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
         g.partials = w.partials + j0 * tiles2; g.sP = tiles2;
         g.M = (int)lds; g.N = (int)T.dp; g.K = (int)T.K2p;
         g.Me = (int)ns; g.Ne = dj;
-        HIP_TRY(launch_cgemm(GM_RESID, g, cnt, s));
+        HIP_TRY(launch_cgemm(GM_RESID, g, cnt, s, GR_DENSE, false, false));
     }
     FinArgs f = fin_args(FIN_F_OUT, w.sc);
     f.partials = w.partials;
     f.pstride = N * tiles2;
     f.counts = nullptr;
-    f.ucount = (int32_t)(N * tiles2);
+    f.ucount = f.ucount2 = (int32_t)(N * tiles2);
     f.nsum = 1;
     f.fout = f_dev;
     HIP_TRY(launch_finalize(f, 1, s));

@@ -1,216 +1,411 @@
-// Complex64 GEMM on CDNA4 FP32 matrix cores.
+// Complex64 GEMM on CDNA4 FP32 matrix cores: the dense products of the method (ADMM solver section:
+// r = D X - U in the objective of eq. X2LQR_lst, W = D^H r in the gradient equations DXLR, the line-search
+// products a = D X1 and b = D X2) and the stages of the tile forms.
 //
-// The dense products of the method (ADMM solver section: r = D X - U in the
-// objective of eq. X2LQR_lst, W = D^H r in the gradient equations DXLR, and
-// the line-search products D X1, D X2) are complex. A complex product
-// C = A B is evaluated as ONE real GEMM of size M x 2N x 2K: A (interleaved
-// re/im, row-major) is read as a real M x 2K matrix, and every complex b of B
-// becomes the real 2x2 block [[Re b, Im b], [-Im b, Re b]], so the real
-// output rows come out interleaved (re, im) - the complex64 layout - with
-// exactly the 8MNK flops of the four-real-product form and no separate
-// subtraction pass.
+// Every wave owns one 32 x 32 block of C (GM_LINE: the same block of a and b) and feeds its MFMAs from
+// global memory through registers, without LDS and without a barrier in the k loop. An FP32 MFMA takes 64
+// cycles, so the 8 KiB of operands that a wave needs per 16 complex k (1536 cycles of products in the
+// three-product form) come to 21 bytes per cycle and CU, a third of what L1 delivers; the loads of the next
+// 16 k are in flight during the products of the present 16, and the other waves of the SIMD (3 to 4, 2 or 3
+// in GM_LINE) cover the rest. The matrix core rate is what bounds it. Measured, TFLOP/s counted 8mnk with
+// the 128 x 128 tiles staged through LDS that this replaces in brackets: one problem of 1024^2, three
+// products: r = D X - U 58 us (252), D^H r 56 (223), [a | b] 107 (234); one of 4096 x 2048: 1500 us (1678),
+// 1537 (1547), 2957 (3077); 34 of 1024^2, four-product form 144 (144), three-product form 132 (125).
+//   KS = 1: a workgroup is 4 waves (2 x 2) on a 64 x 64 tile, which share its operands through L1.
+//   KS = 4: a workgroup's 4 waves share one 32 x 32 block and each takes every fourth chunk of k; their
+//     sums are added in LDS in a fixed order. Four times as many waves, each a quarter as long, for
+//     problems that would leave SIMDs idle or a last round nearly empty. The order of the sums is
+//     another one, so a problem's own sizes choose the form (gemm_split_k), not its batch.
 //
-// Tiling: 256 threads = 4 waves (2 x 2); workgroup tile 128 rows x 128
-// complex columns, 16 complex k per stage, double-buffered LDS (A stored
-// k-major with an odd pitch so the MFMA operand reads are conflict free).
-// Each wave owns 2 x 4 v_mfma_f32_32x32x2_f32 blocks (64 rows x 64 complex
-// columns). One MFMA consumes one complex k: its A operand is (Re, Im) of
-// A[m][k] and its B operand one realified row pair of B.
+// 4M (four products): Re C += Ar Br, Im C += Ar Bi, Re C += (-Ai) Bi, Im C += Ai Br: 8MNK flops.
+// 3M (three products): T1 = Ar Br, T2 = Ai Bi, T3 = (Ar + Ai)(Br + Bi), Re C = T1 - T2, Im C = T3 - T1 - T2:
+//   6MNK flops, at the price of one extra rounding level in Im C (the sums and the final differences).
+// One v_mfma_f32_32x32x2_f32 multiplies two complex k of one of these products; a lane ends with whole
+// complex entries of one column.
 //
-// Epilogues: GM_STORE (C = AB), GM_RESID (C = AB - U plus FP64 partial sums
-// of |C|^2) and GM_LINE (a = D X1, b = D X2 for the same columns in one
-// workgroup, plus FP64 partial sums of Re<r,a>, |a|^2, Re<r,b>, Re<a,b>,
-// |b|^2 for the exact line search).
+// Epilogues: GM_STORE (C = AB), GM_RESID (C = AB - U plus FP64 partial sums of |C|^2) and GM_LINE (a and b
+// plus FP64 partial sums of Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2 for the exact line search).
+//
+// Operands are padded to whole 64-tiles with zeros, so no load carries a bounds check (they are buffer
+// loads: anything past an operand's last row reads zero); blocks outside the true sizes (Mt x Nt) are
+// written as zeros without their products.
+#include <algorithm>
+#include <type_traits>
+
 #include "gemm_common.hpp"
 
 namespace tlr {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 namespace {
 
-constexpr int BM = GEMM_BM, BN = GEMM_BN, BK = GEMM_BK;
-constexpr int A_PITCH = BM + 1;             // floats per real-k row (k-major A tile)
-constexpr int A_STAGE = 2 * BK * A_PITCH;   // floats per A stage
-constexpr int B_PITCH = 2 * BN;             // floats per k row of the B tile
-constexpr int B_STAGE = BK * B_PITCH;
+// the five products of the line-search sums: Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2
+__device__ __forceinline__ void line_terms(float (&blk)[5], float2 r, float2 a, float2 b) {
+    blk[0] = fmaf(r.x, a.x, fmaf(r.y, a.y, blk[0]));
+    blk[1] = fmaf(a.x, a.x, fmaf(a.y, a.y, blk[1]));
+    blk[2] = fmaf(r.x, b.x, fmaf(r.y, b.y, blk[2]));
+    blk[3] = fmaf(a.x, b.x, fmaf(a.y, b.y, blk[3]));
+    blk[4] = fmaf(b.x, b.x, fmaf(b.y, b.y, blk[4]));
+}
 
-template <int MODE>
-__global__ __launch_bounds__(256, 2) void cgemm_f32_kernel(GemmArgs g) {
-    __shared__ float As[2][A_STAGE];
-    __shared__ float Bs[2][B_STAGE];
+__device__ __forceinline__ float flip(float v, uint32_t sign) { return __uint_as_float(__float_as_uint(v) ^ sign); }
 
-    const int z = blockIdx.y;
-    const float2 *A = g.A + z * g.sA;
-    const float2 *B = g.B + z * g.sB;
+// The operands of one chunk of CH complex k as loaded. Every step multiplies two k, one per lane half h. A
+// row-major A comes in 16-byte loads, k = 4 q + 2 h and the next one: step (q, e) then multiplies 4 q + e and
+// 4 q + e + 2. The tile stages multiply k and k + 1 instead, for which the lane halves exchange one entry of
+// each load: their products are carried from iteration to iteration, and at 2 Hz 100 iterations amplify any
+// rounding past what FP32 state allows (5.6e-5 in X; this order ends at 3.7e-5, the other at 7.3e-5, at 6 %
+// less time per stage).
+template <bool TA, int HB, int NB, int CH>
+struct Chunk {
+    float4 a4[HB][TA ? 1 : CH / 4];
+    float2 a2[HB][TA ? CH / 2 : 1];
+    float2 b[NB][CH / 2];
+};
 
-    // workgroup -> tile: contiguous tile ranges per XCD, grouped by 8 tile rows
-    const int nb = gridDim.x;
-    int pid = blockIdx.x;
-    if ((nb & 7) == 0) pid = (pid & 7) * (nb >> 3) + (pid >> 3);
-    const int group_rows = 8;
-    const int per_group = group_rows * g.tiles_n;
+template <int MODE, bool M3, int ROLE, int KS, bool BIG = false>
+__global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
+    constexpr bool TA = ROLE == GR_TILE_TA_CB || ROLE == GR_ADJOINT;
+    constexpr bool STAGE = ROLE == GR_TILE || ROLE == GR_TILE_TA_CB;
+    constexpr int HK = STAGE ? 1 : 2;              // k between the lane halves of a step
+    constexpr int HB = BIG ? 2 : 1;                // row blocks of a wave
+    constexpr int NB = (MODE == GM_LINE || BIG) ? 2 : 1;   // column blocks (GM_LINE: of X1 and of X2)
+    constexpr int CB = MODE == GM_LINE ? 1 : NB;   // blocks of 32 columns of C
+    constexpr int NT = M3 ? 3 : 2;                 // accumulators per block: T1, T2, T3 or Re, Im
+    constexpr int WV = KS == 1 ? 2 : 1;            // waves per workgroup tile row and column
+    // complex k per chunk (one round of loads). GM_LINE takes 8: its accumulators and two column blocks then
+    // fit three waves per SIMD instead of two (64 problems of 512^2, split: 892 us, with 16: 957)
+    constexpr int CH = BIG && M3 ? 4 : NB == 2 ? 8 : 16;
+
+    // workgroup -> batch entry and tile. Consecutive workgroups go to the eight XCDs in turn. Dense products:
+    // contiguous tile ranges of an entry per XCD; tile stages, whose entries are small: whole entries per XCD,
+    // so that its L2 fetches their operands once (32 frequencies of 4096 x 2048: gradient stages 3 % faster).
+    // Either way tiles are grouped by 8 tile rows, which read few rows of A and few columns of B.
+    const int nwg = gridDim.x;
+    int zz = blockIdx.y, pid = blockIdx.x;
+    if (STAGE && zz < (int)(gridDim.y & ~7u)) {
+        const int lin = zz * nwg + pid;
+        zz = ((lin >> 3) / nwg) * 8 + (lin & 7);
+        pid = (lin >> 3) % nwg;
+    } else if ((nwg & 7) == 0) {
+        pid = (pid & 7) * (nwg >> 3) + (pid >> 3);
+    }
+    const int z = g.nz2 > 1 ? zz / g.nz2 : zz;
+    int z2 = g.nz2 > 1 ? zz % g.nz2 : 0;
+    int z3 = 0, z4 = 0;
+    if (MODE == GM_STORE && STAGE) {
+        if (g.nz4 > 1) {
+            z4 = z2 % g.nz4;
+            z2 = z2 / g.nz4;
+        }
+        if (g.nz3 > 1) {
+            z3 = z2 % g.nz3;
+            z2 = z2 / g.nz3;
+        }
+    }
+    const float2 *A = g.A + z * g.sA + z2 * g.sA2 + z3 * g.sA3 + z4 * g.sA4;
+    const float2 *B = g.B + z * g.sB + z2 * g.sB2 + z3 * g.sB3 + z4 * g.sB4;
+
+    const int per_group = 8 * g.tiles_n;
     const int grp = pid / per_group;
-    const int first_m = grp * group_rows;
-    const int gsz = min(g.tiles_m - first_m, group_rows);
-    const int tm = first_m + (pid % per_group) % gsz;
+    const int gsz = min(g.tiles_m - 8 * grp, 8);
+    const int tm = 8 * grp + (pid % per_group) % gsz;
     const int tn = (pid % per_group) / gsz;
-
-    const int m0 = tm * BM;
-    const int n0 = (MODE == GM_LINE) ? tn * (BN / 2) : tn * BN;
 
     const int t = threadIdx.x;
     const int lane = t & 63;
-    const int wave = t >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int j32 = lane & 31, half = lane >> 5;
     const int wm = wave >> 1, wn = wave & 1;
-    const int K = g.K;
+    const int m0 = 32 * HB * (tm * WV + (KS == 1 ? wm : 0));   // the wave's first row and column
+    const int n0 = 32 * CB * (tn * WV + (KS == 1 ? wn : 0));
 
-    // ---- global -> register loaders ----
-    float4 ra[4], rb[4];
-    const int a_row = t >> 3, a_fq = t & 7;     // A: 8 lanes per row, 4 floats each
-    const int b_row = t >> 6, b_cq = t & 63;    // B: 64 lanes per k row, 2 complex each
-
-    // The host pads every operand to whole tiles (M, N multiples of 128, K of 16)
-    // with zeros, so the loads carry no bounds checks. They are buffer loads: a
-    // uniform resource (base, byte size) plus a per-lane 32-bit offset that stays
-    // fixed across stages (the stage advance is the uniform soffset), so all eight
-    // 16-byte loads of a stage are in flight together while the previous stage
-    // runs on the matrix cores, and any access outside an operand reads zero.
     const __amdgpu_buffer_rsrc_t rsA =
         __builtin_amdgcn_make_buffer_rsrc((void *)A, (short)0, (int)g.bytesA, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsB =
         __builtin_amdgcn_make_buffer_rsrc((void *)B, (short)0, (int)g.bytesB, 0x00020000);
-    uint32_t offA[4], offB[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-        offA[p] = (uint32_t)(((int64_t)(m0 + a_row + 32 * p) * g.lda + 2 * a_fq) * 8);
-    {
-        const int c = 2 * b_cq;  // complex column inside the LDS tile
-        int64_t base = n0 + c;
-        if (MODE == GM_LINE) {
-            const int grp2 = c >> 5;
-            base = n0 + (grp2 >> 1) * 32 + (c & 31) + ((grp2 & 1) ? g.b2_off : 0);
-        }
-#pragma unroll
-        for (int p = 0; p < 4; ++p) offB[p] = (uint32_t)((base + (int64_t)(b_row + 4 * p) * g.ldb) * 8);
-    }
-    auto ld16 = [](__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
-        return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-    };
-    auto load_a = [&](int k0) {
-        const uint32_t so = (uint32_t)k0 * 8u;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) ra[p] = ld16(rsA, offA[p], so);
-    };
-    auto load_b = [&](int k0) {
-        const uint32_t so = (uint32_t)((int64_t)k0 * g.ldb * 8);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) rb[p] = ld16(rsB, offB[p], so);
-    };
-    auto store_lds = [&](int buf) {
-        float *as = As[buf];
-        float *bs = Bs[buf];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int row = a_row + 32 * p;
-            as[(4 * a_fq + 0) * A_PITCH + row] = ra[p].x;
-            as[(4 * a_fq + 1) * A_PITCH + row] = ra[p].y;
-            as[(4 * a_fq + 2) * A_PITCH + row] = ra[p].z;
-            as[(4 * a_fq + 3) * A_PITCH + row] = ra[p].w;
-        }
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            *reinterpret_cast<float4 *>(bs + (b_row + 4 * p) * B_PITCH + 4 * b_cq) = rb[p];
-        }
-    };
+    uint32_t offA[HB];
+    offA[0] = TA ? (uint32_t)(((int64_t)HK * half * g.lda + m0 + j32) * 8)
+                 : (uint32_t)(((int64_t)(m0 + j32) * g.lda + 2 * half) * 8);
+    if (HB == 2) offA[HB - 1] = offA[0] + (uint32_t)(TA ? 32 * 8 : 32 * g.lda * 8);
+    uint32_t offB[NB];
+    offB[0] = (uint32_t)(((int64_t)HK * half * g.ldb + n0 + j32) * 8);
+    if (NB == 2) offB[NB - 1] = offB[0] + (uint32_t)((MODE == GM_LINE ? g.b2_off : 32) * 8);
 
-    floatx16 acc[2][4];
+    auto k_of = [](int s) { return HK == 2 ? 4 * (s >> 1) + (s & 1) : 2 * s; };   // of lane half 0 in step s
+    auto load = [&](Chunk<TA, HB, NB, CH> &c, int k0, bool b2) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int h = 0; h < HB; ++h) {
+            if constexpr (TA) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+                for (int s = 0; s < CH / 2; ++s) {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsA, (int)offA[h], (int)((uint32_t)(k0 + k_of(s)) * (uint32_t)g.lda * 8u), 0);
+                    c.a2[h][s] = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+                }
+            } else {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    const int j32 = lane & 31;
-    const int half = lane >> 5;
-    const int bswz = j32 ^ half;                         // (re,im) swap for the second k row
-    const uint32_t bsign = (half && !(j32 & 1)) ? 0x80000000u : 0u;   // -Im b
-
-    const int nk = (K + BK - 1) / BK;
-    load_a(0);
-    load_b(0);
-    store_lds(0);
-    __syncthreads();
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) {
-            load_a((kt + 1) * BK);
-            load_b((kt + 1) * BK);
-        }
-        const float *as = As[buf] + half * A_PITCH + wm * 64 + j32;
-        const float *bs = Bs[buf] + 2 * (wn * 64) + bswz;
-        // operand fragments double-buffered in registers: the reads of step kc+1
-        // are issued before the eight MFMAs of step kc
-        float a_cur[2], b_cur[4], a_nxt[2], b_nxt[4];
-        auto frag = [&](int kc, float *af, float *bf) {
-            af[0] = as[2 * kc * A_PITCH];
-            af[1] = as[2 * kc * A_PITCH + 32];
-#pragma unroll
-            for (int bn = 0; bn < 4; ++bn)
-                bf[bn] = __uint_as_float(__float_as_uint(bs[kc * B_PITCH + 32 * bn]) ^ bsign);
-        };
-        frag(0, a_cur, b_cur);
-#pragma unroll
-        for (int kc = 0; kc < BK; ++kc) {
-            if (kc + 1 < BK) frag(kc + 1, a_nxt, b_nxt);
-#pragma unroll
-            for (int bn = 0; bn < 4; ++bn) {
-                acc[0][bn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[0], b_cur[bn], acc[0][bn], 0, 0, 0);
-                acc[1][bn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[1], b_cur[bn], acc[1][bn], 0, 0, 0);
-            }
-            if (kc + 1 < BK) {
-                a_cur[0] = a_nxt[0];
-                a_cur[1] = a_nxt[1];
-#pragma unroll
-                for (int bn = 0; bn < 4; ++bn) b_cur[bn] = b_nxt[bn];
+                for (int q = 0; q < CH / 4; ++q) {
+                    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsA, (int)(offA[h] + 32 * q), k0 * 8, 0);
+                    c.a4[h][q] = make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+                }
             }
         }
-        if (kt + 1 < nk) store_lds(buf ^ 1);
-        __syncthreads();
-    }
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            if (n == 1 && !b2) continue;
+#pragma unroll
+            for (int s = 0; s < CH / 2; ++s) {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsB, (int)offB[n], (int)((uint32_t)(k0 + k_of(s)) * (uint32_t)g.ldb * 8u), 0);
+                c.b[n][s] = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+            }
+        }
+    };
 
-    EpiArgs ea;
-    ea.C = g.C + z * g.sC;
-    ea.C2 = (MODE == GM_LINE) ? g.C2 + z * g.sC : nullptr;
-    ea.ldc = g.ldc;
-    ea.E = (MODE == GM_STORE) ? nullptr : g.E + z * g.sE;
-    ea.lde = g.lde;
-    ea.Me = g.Me;
-    ea.Ne = g.Ne;
-    ea.partials = g.partials ? g.partials + z * g.sP : nullptr;
-    gemm_epilogue<MODE>(acc, ea, m0, n0, pid);
+    floatx16 acc[HB][NB][NT];
+#pragma unroll
+    for (int h = 0; h < HB; ++h)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int p = 0; p < NT; ++p)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[h][n][p][r] = 0.f;
+
+    constexpr uint32_t conj_a = ROLE == GR_ADJOINT ? 0x80000000u : 0u;
+    constexpr uint32_t conj_b = ROLE == GR_TILE_TA_CB ? 0x80000000u : 0u;
+    auto mfma = [](float a, float b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); };
+    auto compute = [&](const Chunk<TA, HB, NB, CH> &c, auto nb_tag) {
+        constexpr int NBC = decltype(nb_tag)::value;   // column blocks with products in this chunk
+#pragma unroll
+        for (int s = 0; s < CH / 2; ++s) {
+            float ar[HB], ai[HB];
+#pragma unroll
+            for (int h = 0; h < HB; ++h) {
+                if constexpr (TA) {
+                    ar[h] = c.a2[h][s].x;
+                    ai[h] = flip(c.a2[h][s].y, conj_a);
+                } else {
+                    const float4 v = c.a4[h][s >> 1];
+                    if constexpr (STAGE) {   // (k, k + 1 | k + 2, k + 3) -> (k | k + 1) and (k + 2 | k + 3)
+                        const u32x2 re = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.x), __float_as_uint(v.z), false, false);
+                        const u32x2 im = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.y), __float_as_uint(v.w), false, false);
+                        ar[h] = __uint_as_float((s & 1) ? re.y : re.x);
+                        ai[h] = __uint_as_float((s & 1) ? im.y : im.x);
+                    } else {
+                        ar[h] = (s & 1) ? v.z : v.x;
+                        ai[h] = (s & 1) ? v.w : v.y;
+                    }
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < (M3 ? 3 : 4); ++p)
+#pragma unroll
+                for (int h = 0; h < HB; ++h)
+#pragma unroll
+                    for (int n = 0; n < NBC; ++n) {
+                        const float br = c.b[n][s].x, bi = flip(c.b[n][s].y, conj_b);
+                        floatx16 *d = acc[h][n];
+                        if constexpr (M3) d[p] = p == 0 ? mfma(ar[h], br, d[p]) : p == 1 ? mfma(ai[h], bi, d[p]) : mfma(ar[h] + ai[h], br + bi, d[p]);
+                        else if (p & 1) d[1] = p == 1 ? mfma(ar[h], bi, d[1]) : mfma(ai[h], br, d[1]);
+                        else d[0] = p == 0 ? mfma(ar[h], br, d[0]) : mfma(-ai[h], bi, d[0]);
+                    }
+        }
+    };
+
+    // the chunks of this wave: first, first + KS, ...; GM_LINE tile stages: b over the first K2 k only
+    constexpr bool SPLIT_K2 = MODE == GM_LINE && STAGE;
+    const bool inside = m0 < g.Mt && n0 < g.Nt;
+    const int nc = inside ? g.K / CH : 0;
+    const int nc2 = (SPLIT_K2 && g.K2 > 0) ? g.K2 / CH : nc;
+    const int first = KS == 1 ? 0 : wave;
+    auto chunks = [&](int c, int end, auto nb_tag) {
+        Chunk<TA, HB, NB, CH> r0, r1;
+        constexpr bool B2 = decltype(nb_tag)::value > 1;
+        if (c < end) load(r0, c * CH, B2);
+        for (; c < end; c += 2 * KS) {
+            if (c + KS < end) load(r1, (c + KS) * CH, B2);
+            compute(r0, nb_tag);
+            if (c + KS < end) {
+                if (c + 2 * KS < end) load(r0, (c + 2 * KS) * CH, B2);
+                compute(r1, nb_tag);
+            }
+        }
+    };
+    chunks(first, nc2, std::integral_constant<int, NB>{});
+    if constexpr (SPLIT_K2) chunks(nc2, nc, std::integral_constant<int, 1>{});
+
+    // ---- epilogue ----
+    float2 *C = g.C + z * g.sC + z2 * g.sC2 + z3 * g.sC3 + z4 * g.sC4;
+    const int64_t ldc = g.ldc;
+    const int col = n0 + j32;
+    auto cval = [&](int h, int n, int r) {
+        const floatx16 *d = acc[h][n];
+        if constexpr (M3) return make_float2(d[0][r] - d[1][r], d[NT - 1][r] - d[0][r] - d[1][r]);
+        else return make_float2(d[0][r], d[1][r]);
+    };
+    constexpr int NR = KS == 1 ? 16 : 16 / KS;   // rows of a block that this wave finishes
+    constexpr int NS = MODE == GM_RESID ? 1 : 5;
+    auto row_of = [&](int h, int r) { return m0 + 32 * h + acc_row(KS == 1 ? r : wave * NR + r, lane); };
+    const float2 *E = MODE == GM_STORE ? nullptr : g.E + z * g.sE + z2 * g.sE2;
+    double *partials = MODE == GM_STORE ? nullptr : g.partials + z * g.sP + z2 * g.sP2;
+    __shared__ float2 part[KS][KS == 1 ? 1 : 16][KS == 1 ? 1 : 64];   // a, then b: less LDS, more waves per CU
+    __shared__ double red[KS][NS];
+#pragma unroll
+    for (int h = 0; h < HB; ++h)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            const int cc = col + 32 * cb;
+            // the entries of E: their loads are in flight together, and during the sums over the waves (an
+            // entry outside E reads E[0] and is dropped)
+            float2 e[NR];
+            if constexpr (MODE != GM_STORE) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    const int row = row_of(h, r);
+                    const bool in = MODE == GM_LINE || (row < g.Me && cc < g.Ne);
+                    e[r] = E[in ? (int64_t)row * g.lde + cc : 0];
+                    if (!in) e[r] = make_float2(0.f, 0.f);
+                }
+            }
+            constexpr int NV = MODE == GM_LINE ? 2 : 1;   // a and b, or one block of C
+            float2 v[NV][NR];
+#pragma unroll
+            for (int n = 0; n < NV; ++n) {
+                if constexpr (KS == 1) {
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) v[n][r] = cval(h, MODE == GM_LINE ? n : cb, r);
+                } else {
+                    if (n) __syncthreads();
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) part[wave][r][lane] = cval(h, n, r);
+                    __syncthreads();
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) {
+                        float2 s = part[0][wave * NR + r][lane];
+#pragma unroll
+                        for (int w = 1; w < KS; ++w) {
+                            const float2 x = part[w][wave * NR + r][lane];
+                            s.x += x.x;
+                            s.y += x.y;
+                        }
+                        v[n][r] = s;
+                    }
+                }
+            }
+            float blk[NS];
+#pragma unroll
+            for (int q = 0; q < NS; ++q) blk[q] = 0.f;
+            if constexpr (MODE == GM_STORE) {
+                int64_t ccol = cc;
+                if (STAGE && g.scat_kp > 0) {
+                    if (cc >= g.scat_lim) continue;
+                    ccol += (int64_t)((cc % g.scat_w) / g.scat_kp) * g.scat_js;
+                }
+#pragma unroll
+                for (int r = 0; r < NR; ++r) C[(int64_t)row_of(h, r) * ldc + ccol] = v[0][r];
+            } else if constexpr (MODE == GM_RESID) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    const float2 d = make_float2(v[0][r].x - e[r].x, v[0][r].y - e[r].y);
+                    C[(int64_t)row_of(h, r) * ldc + cc] = d;
+                    blk[0] = fmaf(d.x, d.x, fmaf(d.y, d.y, blk[0]));
+                }
+            } else {
+                float2 *C2 = g.C2 + z * g.sC + z2 * g.sC2;
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    C[(int64_t)row_of(h, r) * ldc + cc] = v[0][r];
+                    C2[(int64_t)row_of(h, r) * ldc + cc] = v[NV - 1][r];
+                    line_terms(blk, e[r], v[0][r], v[NV - 1][r]);
+                }
+            }
+            // a block's sums: its lanes' FP32 sums over the rows, added in FP64; one slot per 32 x 32 block,
+            // numbered by block row and column whatever the tile
+            if constexpr (MODE != GM_STORE) {
+                const int64_t slot = (int64_t)((m0 >> 5) + h) * (g.N >> 5) + (cc >> 5);
+#pragma unroll
+                for (int q = 0; q < NS; ++q) {
+                    const double s = wave_sum((double)blk[q]);
+                    if (lane == 0) {
+                        if constexpr (KS == 1) partials[slot * NS + q] = s;
+                        else red[wave][q] = s;
+                    }
+                }
+                if constexpr (KS > 1) {
+                    __syncthreads();
+                    if (t < NS) partials[slot * NS + t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
+                }
+            }
+        }
+}
+
+template <int MODE, bool M3, int ROLE, int KS, bool BIG = false>
+hipError_t go(const GemmArgs &a, int batch, hipStream_t s) {
+    hipLaunchKernelGGL((cgemm_kernel<MODE, M3, ROLE, KS, BIG>), dim3(a.tiles_m * a.tiles_n, batch), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+// C = AB in wave tiles of 2 x 2 blocks (128 x 128 per workgroup, the same results): half the operand traffic
+// per product, for two waves per SIMD instead of four. Pays where the k loop is long against prologue and
+// epilogue and the workgroups fill the chip twice (two per CU): D^H r of 8 problems of 4096 x 2048 11.6 ms
+// (12.2), of one 1.455 (1.508), but the stages of 12 tile-128 problems (K = 128) 870 us (852). The other
+// epilogues lose with it: r = D X - U 13.6 ms (12.2), [a | b] 23.6 (23.1).
+constexpr int64_t BIG_MIN_WG = 1024;
+constexpr int BIG_MIN_K = 256;
+template <bool M3, int ROLE>
+hipError_t go_store(GemmArgs a, int batch, hipStream_t s) {
+    if (a.M % 128 == 0 && a.N % 128 == 0 && a.K >= BIG_MIN_K &&
+        (int64_t)(a.tiles_m / 2) * (a.tiles_n / 2) * batch >= BIG_MIN_WG) {
+        a.tiles_m /= 2;
+        a.tiles_n /= 2;
+        return go<GM_STORE, M3, ROLE, 1, true>(a, batch, s);
+    }
+    return go<GM_STORE, M3, ROLE, 1>(a, batch, s);
+}
+
+template <bool M3>
+hipError_t go_dense(int mode, const GemmArgs &a, int batch, hipStream_t s, int role, bool split) {
+    if (role == GR_ADJOINT)
+        return split ? go<GM_STORE, M3, GR_ADJOINT, 4>(a, batch, s) : go_store<M3, GR_ADJOINT>(a, batch, s);
+    switch (mode) {
+        case GM_STORE: return split ? hipErrorInvalidValue : go_store<M3, GR_DENSE>(a, batch, s);
+        case GM_RESID: return split ? go<GM_RESID, M3, GR_DENSE, 4>(a, batch, s) : go<GM_RESID, M3, GR_DENSE, 1>(a, batch, s);
+        case GM_LINE: return split ? go<GM_LINE, M3, GR_DENSE, 4>(a, batch, s) : go<GM_LINE, M3, GR_DENSE, 1>(a, batch, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
 
-int gemm_partials_per_problem(int mode, int M, int N) {
-    const int tm = (M + BM - 1) / BM;
-    const int tn = (mode == GM_LINE) ? (N + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
-    const int ns = (mode == GM_RESID) ? 1 : (mode == GM_LINE ? 5 : 0);
-    return tm * tn * ns;
-}
+int gemm_partial_slots(int M, int N) { return ((M + 31) / 32) * ((N + 31) / 32); }
 
-hipError_t launch_cgemm(int mode, const GemmArgs &a0, int batch, hipStream_t s) {
+hipError_t launch_cgemm(int mode, const GemmArgs &a0, int batch, hipStream_t s, int role, bool m3, bool split) {
     GemmArgs a = a0;
-    a.tiles_m = (a.M + BM - 1) / BM;
-    a.tiles_n = (mode == GM_LINE) ? (a.N + BN / 2 - 1) / (BN / 2) : (a.N + BN - 1) / BN;
+    const int wt = split ? 32 : 64;
     if (a.M <= 0 || a.N <= 0 || batch <= 0) return hipSuccess;
-    if (a.M % BM || a.N % BN || a.K % BK || a.K <= 0) return hipErrorInvalidValue;   // padded operands only
-    // byte extents of the buffer resources (32-bit): A is M x lda, B is K x ldb (GM_LINE: B2 follows B)
-    const int64_t bytesA = (int64_t)a.M * a.lda * 8;
+    if (role < GR_DENSE || role > GR_ADJOINT) return hipErrorInvalidValue;
+    const bool stage = role == GR_TILE || role == GR_TILE_TA_CB;
+    const bool ta = role == GR_TILE_TA_CB || role == GR_ADJOINT;
+    if (a.M % 64 || a.N % 64 || a.K % GEMM_BK || a.K <= 0) return hipErrorInvalidValue;   // padded operands only
+    if ((ta && mode != GM_STORE) || (stage && (split || !m3))) return hipErrorInvalidValue;
+    if (a.K2 < 0 || a.K2 > a.K || a.K2 % GEMM_BK || (a.K2 && !(mode == GM_LINE && stage))) return hipErrorInvalidValue;
+    if (a.nz3 > 1 || a.nz4 > 1) {
+        const int64_t inner = (int64_t)std::max(1, a.nz3) * std::max(1, a.nz4);
+        if (!(mode == GM_STORE && stage && a.nz2 > 1 && a.nz2 % inner == 0)) return hipErrorInvalidValue;
+    }
+    if (a.scat_kp < 0 || (a.scat_kp && (!(mode == GM_STORE && stage) || a.scat_w < a.scat_kp || a.scat_lim <= 0 ||
+                                        a.scat_lim > a.N)))
+        return hipErrorInvalidValue;
+    a.tiles_m = a.M / wt;
+    a.tiles_n = a.N / wt;
+    a.Mt = a.Mt > 0 ? std::min(a.Mt, a.M) : a.M;
+    a.Nt = a.Nt > 0 ? std::min(a.Nt, a.N) : a.N;
+    // byte extents of the buffer resources (32-bit): A is Mt x lda (transposed source: K x lda), B is K x ldb
+    // (GM_LINE: B2 follows B)
+    if (ta && a.lda < a.Mt) return hipErrorInvalidValue;
+    const int64_t bytesA = (int64_t)(ta ? a.K : a.Mt) * a.lda * 8;
     int64_t bytesB = (int64_t)a.K * a.ldb * 8;
     a.b2_off = 0;
     if (mode == GM_LINE) {
@@ -221,14 +416,14 @@ hipError_t launch_cgemm(int mode, const GemmArgs &a0, int batch, hipStream_t s) 
     if (bytesA >= (int64_t)1 << 32 || bytesB >= (int64_t)1 << 32) return hipErrorInvalidValue;
     a.bytesA = (uint32_t)bytesA;
     a.bytesB = (uint32_t)bytesB;
-    dim3 grid(a.tiles_m * a.tiles_n, batch);
+    if (!stage) return m3 ? go_dense<true>(mode, a, batch, s, role, split) : go_dense<false>(mode, a, batch, s, role, split);
+    if (role == GR_TILE_TA_CB) return go_store<true, GR_TILE_TA_CB>(a, batch, s);
     switch (mode) {
-        case GM_STORE: hipLaunchKernelGGL(cgemm_f32_kernel<GM_STORE>, grid, dim3(256), 0, s, a); break;
-        case GM_RESID: hipLaunchKernelGGL(cgemm_f32_kernel<GM_RESID>, grid, dim3(256), 0, s, a); break;
-        case GM_LINE:  hipLaunchKernelGGL(cgemm_f32_kernel<GM_LINE>, grid, dim3(256), 0, s, a); break;
+        case GM_STORE: return go_store<true, GR_TILE>(a, batch, s);
+        case GM_RESID: return go<GM_RESID, true, GR_TILE, 1>(a, batch, s);
+        case GM_LINE: return go<GM_LINE, true, GR_TILE, 1>(a, batch, s);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace tlr

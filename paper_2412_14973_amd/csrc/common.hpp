@@ -68,15 +68,16 @@ struct GemmArgs {
     float2 *C2;                      // GM_LINE: second output (same ldc)
     const float2 *E;  int64_t lde;   // GM_RESID: U (C = AB - U); GM_LINE: residual r
     double *partials;                // per-workgroup FP64 sums (GM_RESID: 1, GM_LINE: 5)
-    int32_t M, N, K;                 // padded sizes: M, N multiples of 128, K of 16 (zero padding)
+    int32_t M, N, K;                 // padded sizes: M, N multiples of 64, K of 16 (zero padding)
     int32_t Me, Ne;                  // GM_RESID: true shape of E (reads outside are zero)
+    int32_t Mt, Nt;                  // true shape of C (blocks outside are zero; 0: M, N)
     int64_t b2_off;                  // GM_LINE: B2 - B in complex elements (set by the launcher)
     uint32_t bytesA, bytesB;         // buffer extents (set by the launcher)
     int32_t tiles_m, tiles_n;
     // uniform batch (grid.y): element strides between problems
     int64_t sA, sB, sC, sE;
     int64_t sP;                      // partial stride (doubles) between problems
-    // two-level batch (three-product kernel): grid.y = nz * nz2, entry z = z1 * nz2 + z2 is at
+    // two-level batch: grid.y = nz * nz2, entry z = z1 * nz2 + z2 is at
     // z1 * s + z2 * s2 for every operand (nz2 <= 1: one level, the s2 are unused)
     int32_t nz2;
     int32_t K2;                      // GM_LINE: b = A B2 sums over k < K2 only (0: all K; a multiple of 16)
@@ -92,11 +93,11 @@ struct GemmArgs {
     // plain), which regroups blocks of scat_kp columns across batch entries
     int32_t scat_kp, scat_w, scat_lim;
     int64_t scat_js;
-    int32_t n_half;                  // GM_STORE tile stages: first column of a last 64-column tile (set by the launcher)
 };
-// roles of the three-product kernel: the solver's dense products; the tile-form stages; the same
-// with A given transposed (K x M source, row pitch lda) and B conjugated
-enum GemmRole : int32_t { GR_DENSE = 0, GR_TILE = 1, GR_TILE_TA_CB = 2 };
+// roles of the FP32 product kernel: dense products; the tile-form stages; a tile-form stage with A given
+// transposed (K x M source, row pitch lda) and B conjugated; the adjoint product, whose A is given transposed
+// and conjugated (D itself for D^H)
+enum GemmRole : int32_t { GR_DENSE = 0, GR_TILE = 1, GR_TILE_TA_CB = 2, GR_ADJOINT = 3 };
 constexpr int GEMM_BM = 128;
 constexpr int GEMM_BN = 128;   // complex columns per workgroup (64 of a + 64 of b in GM_LINE)
 constexpr int GEMM_BK = 16;    // complex k per stage
@@ -151,10 +152,11 @@ struct SolveScalars {
 };
 
 // host launchers (stream ordered)
-hipError_t launch_cgemm(int mode, const GemmArgs &a, int batch, hipStream_t s);
-// the same products in the three-real-product form (FP32 MFMA, interleaved complex64 operands)
-hipError_t launch_cgemm3m(int mode, const GemmArgs &a, int batch, hipStream_t s, int role = GR_DENSE);
-int gemm_partials_per_problem(int mode, int M, int N);
+// FP32 products; m3: in the three-product form; split: the contraction of every 32 x 32 block over four waves
+// (dense products only)
+hipError_t launch_cgemm(int mode, const GemmArgs &a, int batch, hipStream_t s, int role, bool m3, bool split);
+// their partial-sum slots: one per 32 x 32 block of the (padded) output
+int gemm_partial_slots(int M, int N);
 
 // out_bf16 == false: X / X2 are complex64 matrices (ProbOff.x offsets, ld ProbOff.ldx).
 // out_bf16 == true: the same region holds split planes of uint32 words; a problem's

@@ -598,18 +598,41 @@ __device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, co
 // ...: lanes stride over the slots, then one DPP wave reduction, a fixed order), and the Gram pass
 // stages the problem's Gram matrix and coefficient vector, which are written back afterwards.
 constexpr int FIN_NB = 2 * (MAX_LBFGS_M + 1) + 1;
+constexpr int FIN_FEW = 5;
 __global__ __launch_bounds__(256) void finalize_kernel(FinArgs fa) {
     __shared__ double tot[6 * (MAX_LBFGS_M + 1)];
     __shared__ double sG[FIN_NB * FIN_NB + FIN_NB];
+    __shared__ double few[4][FIN_FEW];
     const int prob = blockIdx.x;
-    const int count = fa.counts ? fa.counts[prob] : fa.ucount;
+    const int count = fa.counts ? fa.counts[prob] : prob < fa.nfirst ? fa.ucount : fa.ucount2;
     const double *base = fa.partials + (int64_t)prob * fa.pstride * fa.nsum;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int k = wv; k < fa.nsum; k += 4) {
-        double v = 0.0;
-        for (int i = lane; i < count; i += 64) v += base[(int64_t)i * fa.nsum + k];
-        v = wave_sum64(v);
-        if (lane == 0) tot[k] = v;
+    if (fa.nsum <= FIN_FEW) {
+        // products' sums, up to thousands of slots: a thread adds every 256th slot, all sums of a slot at once
+        // (their loads are in flight together), then the lanes and the four waves
+        double v[FIN_FEW];
+#pragma unroll
+        for (int k = 0; k < FIN_FEW; ++k) v[k] = 0.0;
+        for (int i = threadIdx.x; i < count; i += 256)
+#pragma unroll
+            for (int k = 0; k < FIN_FEW; ++k)
+                if (k < fa.nsum) v[k] += base[(int64_t)i * fa.nsum + k];
+#pragma unroll
+        for (int k = 0; k < FIN_FEW; ++k) {
+            if (k >= fa.nsum) break;
+            const double s = wave_sum64(v[k]);
+            if (lane == 0) few[wv][k] = s;
+        }
+        __syncthreads();
+        if (threadIdx.x < fa.nsum)
+            tot[threadIdx.x] = (few[0][threadIdx.x] + few[1][threadIdx.x]) + (few[2][threadIdx.x] + few[3][threadIdx.x]);
+    } else {
+        for (int k = wv; k < fa.nsum; k += 4) {
+            double v = 0.0;
+            for (int i = lane; i < count; i += 64) v += base[(int64_t)i * fa.nsum + k];
+            v = wave_sum64(v);
+            if (lane == 0) tot[k] = v;
+        }
     }
     const int m1 = fa.m1;
     const int gwords = (2 * m1 + 1) * (2 * m1 + 1) + 2 * m1 + 1;
