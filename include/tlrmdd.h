@@ -292,9 +292,11 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
  * (Hyper-parameter selection and initialization; the examples' rank study.)
  * X is a reference solution: device, nr x nr complex64, symmetric, in the
  * receiver order of the solve (Hilbert). Tiles of size d cover nr with a
- * ragged last tile. Every tile X_ij, i >= j, is decomposed in FP64 on the GPU
- * by one-sided Jacobi (round-robin pairs, sweeps until no pair is rotated,
- * at most 30). Tile sizes up to 1024.
+ * ragged last tile. Every tile X_ij, i >= j, is decomposed in FP64 on the GPU:
+ * the warm start by one-sided Jacobi (round-robin pairs, sweeps until no pair is
+ * rotated, at most 30); the ranks from a Householder bidiagonal and its singular
+ * value counts, or by Jacobi too where a tile has more than 512 rows or X a value
+ * that is not finite. Tile sizes up to 1024.
  *
  * tlrmdd_tile_ranks: v0 = largest singular value over all tiles; the rank of a
  * tile is the number of its singular values >= eps * v0 (0 possible; all of

@@ -2380,7 +2380,7 @@ SvdWs svd_carve(char *base, const SvdHost &S, int nitems) {
 int svd_run(const SvdHost &S, const SvdWs &w, const float2 *X, int64_t ldx, hipStream_t s) {
     const int nt = (int)S.tiles.size();
     const int npairs = (int)S.pair_tile.size();
-    HIP_TRY(launch_svd_gather(w.tiles, nt, X, ldx, w.W, w.V, s));
+    HIP_TRY(launch_svd_gather(w.tiles, nt, X, ldx, w.W, w.V, nullptr, s));
     HIP_TRY(launch_fill_zero(w.flags, 2 * sizeof(int32_t), s));
     bool converged = npairs == 0;
     for (int sw = 0; sw < SVD_MAX_SWEEPS && !converged; ++sw) {
@@ -2400,12 +2400,42 @@ int svd_run(const SvdHost &S, const SvdWs &w, const float2 *X, int64_t ldx, hipS
     return TLRMDD_OK;
 }
 
-int svd_upload(const SvdHost &S, const SvdWs &w, const std::vector<WarmItem> *items, hipStream_t s) {
+// jacobi: the tables of the rotations too
+int svd_upload(const SvdHost &S, const SvdWs &w, const std::vector<WarmItem> *items, hipStream_t s,
+               bool jacobi = true) {
     Upload up;
     up.add(w.tiles, S.tiles.data(), S.tiles.size() * sizeof(SvdTile));
-    up.add(w.pair_tile, S.pair_tile.data(), S.pair_tile.size() * sizeof(int32_t));
+    if (jacobi) up.add(w.pair_tile, S.pair_tile.data(), S.pair_tile.size() * sizeof(int32_t));
     if (items) up.add(w.items, items->data(), items->size() * sizeof(WarmItem));
     return up.commit(s);
+}
+
+// Ranks and v0 from bidiagonals (bidiag.hip) instead of Jacobi rotations, which only the singular vectors need:
+// finite tiles of at most BIDIAG_MAX_M rows; done = false leaves the rest to svd_run (a tile with a value that is
+// not finite, where the rotations still give the other columns' values; larger tiles, whose two reads and one write
+// per step of one workgroup would take as long as the rotations spread over the chip).
+int svd_counts(const SvdHost &S, const SvdWs &w, const float2 *X, int64_t ldx, double eps, std::vector<int32_t> &k,
+               double &v0, bool &done, hipStream_t s) {
+    int mmax = 0;
+    for (const SvdTile &t : S.tiles) mmax = std::max(mmax, t.m);
+    if (mmax > BIDIAG_MAX_M) return TLRMDD_OK;
+    const int nt = (int)S.tiles.size();
+    int st = svd_upload(S, w, nullptr, s, false);
+    if (st) return st;
+    HIP_TRY(launch_fill_zero(w.flags, 2 * sizeof(int32_t), s));
+    if (!bidiag_in_lds(mmax)) HIP_TRY(launch_svd_gather(w.tiles, nt, X, ldx, w.W, nullptr, w.flags, s));
+    HIP_TRY(launch_bidiag(w.tiles, nt, mmax, X, ldx, w.W, w.sig, w.flags, s));
+    HIP_TRY(launch_svd_counts(w.tiles, nt, w.W, w.sig, eps, w.kout, w.v0, s));
+    // kout, v0 and the flags lie one after the other: one copy
+    std::vector<char> out((char *)(w.flags + 1) - (char *)w.kout);
+    HIP_TRY(hipMemcpyAsync(out.data(), w.kout, out.size(), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    int32_t nonfinite = 0;
+    std::memcpy(&nonfinite, out.data() + ((char *)w.flags - (char *)w.kout), sizeof(nonfinite));
+    std::memcpy(&v0, out.data() + ((char *)w.v0 - (char *)w.kout), sizeof(v0));
+    std::memcpy(k.data(), out.data(), k.size() * sizeof(int32_t));
+    done = nonfinite == 0;
+    return TLRMDD_OK;
 }
 
 int check_rank_args(const void *X, int64_t nr, int32_t d, double eps) {
@@ -2425,14 +2455,18 @@ int tile_ranks_impl(const void *X, int64_t nr, int32_t d, double eps, std::vecto
     const SvdHost S = svd_grid(nr, d, false);
     const SvdWs w = svd_carve((char *)workspace, S, 0);
     if (w.bytes > ws_bytes) return fail(TLRMDD_WORKSPACE, "workspace too small");
-    if ((st = svd_upload(S, w, nullptr, s))) return st;
-    if ((st = svd_run(S, w, (const float2 *)X, nr, s))) return st;
-    HIP_TRY(launch_svd_rank(w.tiles, (int)S.tiles.size(), w.sig, S.nS, eps, w.kout, w.v0, s));
     std::vector<int32_t> k(S.tiles.size());
     double v = 0.0;
-    HIP_TRY(hipMemcpyAsync(k.data(), w.kout, k.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&v, w.v0, sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    bool done = false;
+    if ((st = svd_counts(S, w, (const float2 *)X, nr, eps, k, v, done, s))) return st;
+    if (!done) {
+        if ((st = svd_upload(S, w, nullptr, s))) return st;
+        if ((st = svd_run(S, w, (const float2 *)X, nr, s))) return st;
+        HIP_TRY(launch_svd_rank(w.tiles, (int)S.tiles.size(), w.sig, S.nS, eps, w.kout, w.v0, s));
+        HIP_TRY(hipMemcpyAsync(k.data(), w.kout, k.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(&v, w.v0, sizeof(double), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+    }
     const int N = (int)split_sizes(nr, d).size();
     koff.clear();
     kdiag.assign(N, 0);

@@ -1,0 +1,442 @@
+// Singular-value counts of the tiles in FP64 for the rank / tile-size estimate (Hyper-parameter selection and
+// initialization; the examples' rank study): k = #{sigma >= eps v0} per tile, without the singular vectors.
+//
+// Every tile is reduced to a real bidiagonal B by Householder reflections (Golub-Kahan, |d_i| and |e_i| only,
+// which is all that its singular values depend on), and singular values are counted on B by the signs of the
+// stationary quotient-difference recurrence of B^T B - t^2 (Fernando and Parlett's form of Sturm's count).
+// v0 comes from the same count by repeated subdivision of the interval that holds the largest one. All of it is
+// backward stable in FP64: a count is exact for singular values further than a few n 1e-16 v0 from t.
+//
+// One workgroup per tile. Step k: the reflection u of column k; all columns c > k take the right reflection
+// of step k - 1, A -= zt v^H, and the left one, A -= conj(tau) u (u^H A), in one pass (32 lanes per column, its
+// rows in registers); the reflection v of row k; zt = tau A v in a second, reading pass (a wave per column, its
+// rows over the lanes). Two reads and one write of the trailing matrix and five barriers per step: what bounds
+// it is the latency of the phases in small tiles (2.7 us a step at 64 rows, LDS) and the one CU's path to L2 in
+// large ones (11 us a step at 128 rows, 17 at 256; the traffic alone is 1.7 and 7). Tiles up to 64 rows are held
+// in LDS and read from X once. Tile sizes 64, 128 and 256 of a 1024 x 1024 matrix: 0.23 + 1.4 + 4.3 ms, 6.0 ms in
+// all, where one-sided Jacobi with a launch per round of rotations took 48.6 ms (6104 launches of 8 us).
+#include "svd.hpp"
+
+#include "common.hpp"
+
+namespace tlr {
+namespace {
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+__device__ __forceinline__ double2 fma_c(double2 a, double2 b, double2 c) {   // a b + c
+    return make_double2(fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y)));
+}
+__device__ __forceinline__ double2 conj_c(double2 a) { return make_double2(a.x, -a.y); }
+__device__ __forceinline__ double2 neg_c(double2 a) { return make_double2(-a.x, -a.y); }
+
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// sum over the 16 lanes of a DPP row, in every lane: pairs, quads, halves, the row (a fixed order)
+__device__ __forceinline__ double sum16(double v) {
+    v += dpp<0xB1>(v);    // quad_perm 1 0 3 2
+    v += dpp<0x4E>(v);    // quad_perm 2 3 0 1
+    v += dpp<0x141>(v);   // row_half_mirror
+    v += dpp<0x140>(v);   // row_mirror
+    return v;
+}
+// the other half's value of a pair of rows of 16 lanes, and of the wave's two halves of 32
+__device__ __forceinline__ double swap16(double v) {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    const bool odd = threadIdx.x & 16;
+    return __longlong_as_double(((long long)(odd ? hi[0] : hi[1]) << 32) | (odd ? lo[0] : lo[1]));
+}
+__device__ __forceinline__ double sum32(double v) {
+    v = sum16(v);
+    return v + swap16(v);
+}
+__device__ __forceinline__ double sum64(double v) {
+    v = sum32(v);
+    return v + __shfl_xor(v, 32, 64);
+}
+
+// reflection I - tau v v^H (v_0 = 1) that takes (alpha, x) to (beta, 0), beta real
+struct Reflect {
+    double beta;
+    double2 tau, scale;   // v = scale x below alpha
+};
+__device__ __forceinline__ Reflect reflect(double2 alpha, double xnorm2) {
+    Reflect h;
+    if (xnorm2 == 0.0 && alpha.y == 0.0) {
+        h.beta = alpha.x;
+        h.tau = h.scale = make_double2(0.0, 0.0);
+        return h;
+    }
+    const double nrm = sqrt(fma(alpha.x, alpha.x, fma(alpha.y, alpha.y, xnorm2)));
+    h.beta = alpha.x >= 0.0 ? -nrm : nrm;
+    h.tau = make_double2((h.beta - alpha.x) / h.beta, -alpha.y / h.beta);
+    const double2 d = make_double2(alpha.x - h.beta, alpha.y);
+    const double q = 1.0 / (d.x * d.x + d.y * d.y);
+    h.scale = make_double2(d.x * q, -d.y * q);
+    return h;
+}
+
+__device__ __forceinline__ double recip(double p) {   // two Newton steps on the hardware's estimate
+    double r = __builtin_amdgcn_rcp(p);
+    r = fma(fma(-p, r, 1.0), r, r);
+    return fma(fma(-p, r, 1.0), r, r);
+}
+
+// how many singular values of the bidiagonal are >= t (d2, e2: squares, scaled with t so that the largest is of
+// the order of 1: no step over- or underflows)
+__device__ __forceinline__ int at_least(const double *d2, const double *e2, int n, double t) {
+    if (!(t > 0.0)) return n;
+    const double t2 = t * t;
+    double s = -t2;
+    int below = 0;
+    for (int i = 0; i < n; ++i) {
+        double p = d2[i] + s;
+        below += p < 0.0 ? 1 : 0;
+        if (fabs(p) < 1e-200) p = p < 0.0 ? -1e-200 : 1e-200;
+        s = fma(s, e2[i] * recip(p), -t2);   // e2[n - 1] = 0
+    }
+    return n - below;
+}
+// the power of two that brings v to [1/2, 1)
+__device__ __forceinline__ double scale_of(double v) { return v > 0.0 ? ldexp(1.0, -ilogb(v) - 1) : 1.0; }
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// A tile in L2 through buffer instructions: an offset past its end reads zero and writes nothing, so every
+// access of a pass is unconditional and they are all in flight together.
+struct TileMem {
+    __amdgpu_buffer_rsrc_t rs;
+    __device__ double2 get(uint32_t off) const {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
+        return make_double2(__hiloint2double(v.y, v.x), __hiloint2double(v.w, v.z));
+    }
+    __device__ void put(uint32_t off, double2 x) const {
+        const u32x4 v = {(unsigned)__double2loint(x.x), (unsigned)__double2hiint(x.x), (unsigned)__double2loint(x.y),
+                         (unsigned)__double2hiint(x.y)};
+        __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)off, 0, 0);
+    }
+};
+// a tile in LDS, the same offsets
+struct TileLds {
+    double2 *a;
+    __device__ double2 get(uint32_t off) const { return a[min(off >> 4, last)]; }
+    __device__ void put(uint32_t off, double2 x) const {
+        if ((off >> 4) < last) a[off >> 4] = x;
+    }
+    uint32_t last;   // entries; a[last] is zero
+};
+constexpr uint32_t OUTSIDE = 0xfffffff0u;
+
+// NT threads, tiles up to MMAX rows; RES: the tile lives in LDS and is read from X, else in W
+template <int MMAX, int NT, bool RES>
+__global__ __launch_bounds__(NT) void bidiag_kernel(const SvdTile *__restrict__ tiles, const float2 *__restrict__ X,
+                                                    int64_t ldx, double2 *__restrict__ W, double *__restrict__ d2out,
+                                                    int32_t *__restrict__ nonfinite) {
+    constexpr int NW = NT / 64, NG = NT / 32;   // waves; groups of 32 lanes
+    constexpr int MR = MMAX / 32;               // rows per lane of a group
+    constexpr int ML = (MMAX + 63) / 64;        // rows per lane of a wave
+    __shared__ double2 sA[RES ? MMAX * MMAX + 1 : 1];
+    __shared__ double2 part[NW][MMAX];
+    __shared__ double2 su[MMAX], szt[MMAX];   // zero past row m
+    __shared__ double2 sv[MMAX], srow[MMAX], scol[MMAX];
+    __shared__ double sd2[MMAX], se2[MMAX];
+    __shared__ double2 stau;
+    __shared__ int sbest;
+
+    const SvdTile t = tiles[blockIdx.x];
+    const int m = t.m, n = t.n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = tid & 31, grp = tid >> 5;
+    // the tile, column-major, ld m
+    const auto mem = [&] {
+        if constexpr (RES) return TileLds{sA, (uint32_t)(m * n)};
+        else return TileMem{__builtin_amdgcn_make_buffer_rsrc((void *)(W + t.offW), (short)0, m * n * 16, 0x00020000)};
+    }();
+    if (RES) {
+        bool ok = true;
+        for (int e = tid; e < m * n; e += NT) {   // read along the rows of X
+            const int i = t.trans ? e / m : e / n, j = t.trans ? e % m : e % n;
+            const float2 x = X[(t.row0 + i) * ldx + t.col0 + j];
+            ok = ok && isfinite(x.x) && isfinite(x.y);
+            sA[t.trans ? i * m + j : j * m + i] = make_double2(x.x, x.y);
+        }
+        if (tid == 0) sA[m * n] = make_double2(0.0, 0.0);
+        if (!ok) *nonfinite = 1;
+    }
+    for (int r = tid; r < MMAX; r += NT) {
+        su[r] = szt[r] = sv[r] = make_double2(0.0, 0.0);
+        se2[r] = 0.0;
+    }
+    __syncthreads();
+    for (int r = tid; r < m; r += NT) scol[r] = mem.get(16 * r);
+    __syncthreads();
+
+    for (int k = 0; k < n; ++k) {
+        // column k (scol: after the left reflections so far, without the last right one)
+        if (wave == 0) {
+            const double2 cv = conj_c(sv[k]);
+            double2 x[ML];
+            double nn = 0.0;
+#pragma unroll
+            for (int i = 0; i < ML; ++i) {
+                const int r = lane + 64 * i;
+                x[i] = make_double2(0.0, 0.0);
+                if (r >= k && r < m) {
+                    x[i] = fma_c(neg_c(szt[r]), cv, scol[r]);
+                    if (r > k) nn = fma(x[i].x, x[i].x, fma(x[i].y, x[i].y, nn));
+                }
+            }
+            nn = sum64(nn);
+            double2 alpha = make_double2(0.0, 0.0);
+#pragma unroll
+            for (int i = 0; i < ML; ++i)
+                if (k >> 6 == i) alpha = make_double2(__shfl(x[i].x, k & 63, 64), __shfl(x[i].y, k & 63, 64));
+            const Reflect h = reflect(alpha, nn);
+#pragma unroll
+            for (int i = 0; i < ML; ++i) {
+                const int r = lane + 64 * i;
+                // zero above the diagonal: the passes below need no test of their rows against k
+                if (r < m) su[r] = r < k ? make_double2(0.0, 0.0) : r == k ? make_double2(1.0, 0.0) : cmul(x[i], h.scale);
+            }
+            if (lane == 0) {
+                sd2[k] = h.beta * h.beta;
+                stau = conj_c(h.tau);
+            }
+        }
+        if (k == n - 1) break;
+        __syncthreads();
+        // columns c > k: the right reflection of step k - 1 and the left one of step k
+        {
+            const double2 tau = stau;
+            double2 u[MR], zt[MR];   // of this lane's rows, the same for all columns
+#pragma unroll
+            for (int j = 0; j < MR; ++j) {
+                u[j] = su[l32 + 32 * j];
+                zt[j] = neg_c(szt[l32 + 32 * j]);
+            }
+            for (int c = k + 1 + grp; c < n; c += NG) {
+                const uint32_t base = 16u * (uint32_t)(c * m + l32);
+                const double2 cv = conj_c(sv[c]);
+                double2 a[MR];
+                double yr = 0.0, yi = 0.0;
+                // rows of 32 that lie above row k, and rows past m, are left out
+                auto off = [&](int j) { return 32 * j + 31 >= k && l32 + 32 * j < m ? base + 512u * j : OUTSIDE; };
+#pragma unroll
+                for (int j = 0; j < MR; ++j) a[j] = mem.get(off(j));
+#pragma unroll
+                for (int j = 0; j < MR; ++j)
+                    if (32 * j + 31 >= k) {   // uniform
+                        a[j] = fma_c(zt[j], cv, a[j]);
+                        yr = fma(u[j].x, a[j].x, fma(u[j].y, a[j].y, yr));   // conj(u) a
+                        yi = fma(u[j].x, a[j].y, fma(-u[j].y, a[j].x, yi));
+                    }
+                const double2 y = neg_c(cmul(tau, make_double2(sum32(yr), sum32(yi))));
+#pragma unroll
+                for (int j = 0; j < MR; ++j) {
+                    a[j] = fma_c(u[j], y, a[j]);
+                    mem.put(off(j), a[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < MR; ++j) {
+                    const int r = l32 + 32 * j;
+                    if (r == k) srow[c] = a[j];
+                    if (c == k + 1 && r < m) scol[r] = a[j];
+                }
+            }
+        }
+        __syncthreads();
+        // row k, columns > k: its reflection from the right
+        if (wave == 0) {
+            double2 x[ML];
+            double nn = 0.0;
+#pragma unroll
+            for (int i = 0; i < ML; ++i) {
+                const int c = lane + 64 * i;
+                x[i] = make_double2(0.0, 0.0);
+                if (c > k && c < n) {
+                    x[i] = conj_c(srow[c]);
+                    if (c > k + 1) nn = fma(x[i].x, x[i].x, fma(x[i].y, x[i].y, nn));
+                }
+            }
+            nn = sum64(nn);
+            const int k1 = k + 1;
+            double2 alpha = make_double2(0.0, 0.0);
+#pragma unroll
+            for (int i = 0; i < ML; ++i)
+                if (k1 >> 6 == i) alpha = make_double2(__shfl(x[i].x, k1 & 63, 64), __shfl(x[i].y, k1 & 63, 64));
+            const Reflect h = reflect(alpha, nn);
+#pragma unroll
+            for (int i = 0; i < ML; ++i) {
+                const int c = lane + 64 * i;
+                if (c > k && c < n) sv[c] = c == k1 ? make_double2(1.0, 0.0) : cmul(x[i], h.scale);
+            }
+            if (lane == 0) {
+                se2[k] = h.beta * h.beta;
+                stau = h.tau;
+            }
+        }
+        __syncthreads();
+        // zt = tau A v over the rows > k
+        {
+            double2 z[ML];
+#pragma unroll
+            for (int i = 0; i < ML; ++i) z[i] = make_double2(0.0, 0.0);
+            constexpr int CC = ML <= 4 ? 2 : 1;   // columns in flight
+            for (int c0 = k + 1 + wave; c0 < n; c0 += CC * NW) {
+                double2 a[CC][ML];
+#pragma unroll
+                for (int q = 0; q < CC; ++q) {
+                    const int c = c0 + q * NW;
+#pragma unroll
+                    for (int i = 0; i < ML; ++i) {
+                        const int r = lane + 64 * i;
+                        a[q][i] = mem.get(64 * i + 63 > k && r < m && c < n ? 16u * (uint32_t)(c * m + r) : OUTSIDE);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < CC; ++q) {
+                    const double2 v = sv[min(c0 + q * NW, n - 1)];
+#pragma unroll
+                    for (int i = 0; i < ML; ++i) z[i] = fma_c(a[q][i], v, z[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < ML; ++i) {
+                const int r = lane + 64 * i;
+                if (r < m) part[wave][r] = z[i];
+            }
+        }
+        __syncthreads();
+        for (int r = tid; r < m; r += NT) {
+            double2 z = part[0][r];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) {
+                z.x += part[w][r].x;
+                z.y += part[w][r].y;
+            }
+            szt[r] = r > k ? cmul(stau, z) : make_double2(0.0, 0.0);
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+
+    // the largest singular value: its interval cut in NS + 1 parts until it is a rounding wide
+    double lo = 0.0, hi = 0.0;
+    for (int i = tid; i < n; i += NT) {
+        const double d = sqrt(sd2[i]), e = sqrt(se2[i]), e0 = i ? sqrt(se2[i - 1]) : 0.0;
+        lo = fmax(lo, fmax(d, e));
+        hi = fmax(hi, d + fmax(e, e0));
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fmax(lo, __shfl_xor(lo, o, 64));
+        hi = fmax(hi, __shfl_xor(hi, o, 64));
+    }
+    if (lane == 0) part[wave][0] = make_double2(lo, hi);
+    __syncthreads();
+    for (int w = 0; w < NW; ++w) {
+        lo = fmax(lo, part[w][0].x);
+        hi = fmax(hi, part[w][0].y);
+    }
+    hi = fmax(hi * (1.0 + 1e-14), lo);
+    lo *= 1.0 - 1e-14;
+    const double sc = scale_of(hi);
+    // (the largest singular value lies between the largest entry and the largest row sum)
+    __syncthreads();
+    for (int i = tid; i < n; i += NT) {
+        sd2[i] *= sc * sc;
+        se2[i] *= sc * sc;
+    }
+    lo *= sc;
+    hi *= sc;
+    constexpr int NS = NT < 256 ? NT : 256;   // points per cut: one wave per SIMD, the recurrence is a serial chain
+    for (int it = 0; it < 9 && hi - lo > 1e-16 * hi; ++it) {
+        const double step = (hi - lo) / (NS + 1);
+        if (tid == 0) sbest = 0;
+        __syncthreads();
+        if (tid < NS && at_least(sd2, se2, n, fma(step, tid + 1, lo)) > 0) atomicMax(&sbest, tid + 1);
+        __syncthreads();
+        const int b = sbest;
+        __syncthreads();
+        const double nlo = fma(step, b, lo);
+        hi = b == NS ? hi : fma(step, b + 1, lo);
+        lo = nlo;
+    }
+    // the squares for the counts: d2 in the tile's sigma slots, e2 at the start of its W and the largest
+    // singular value behind them
+    double *e2out = reinterpret_cast<double *>(W + t.offW);
+    if (tid == 0) e2out[n] = 0.5 * (lo + hi) / sc;
+    for (int i = tid; i < n; i += NT) {
+        d2out[t.offS + i] = sd2[i] / (sc * sc);
+        e2out[i] = se2[i] / (sc * sc);
+    }
+}
+
+__global__ __launch_bounds__(256) void vmax_kernel(const SvdTile *__restrict__ tiles, int ntiles,
+                                                   const double2 *__restrict__ W, double *__restrict__ v0) {
+    __shared__ double red[256];
+    double x = 0.0;
+    for (int i = threadIdx.x; i < ntiles; i += 256)
+        x = fmax(x, reinterpret_cast<const double *>(W + tiles[i].offW)[tiles[i].n]);
+    red[threadIdx.x] = x;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (threadIdx.x < o) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + o]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *v0 = red[0];
+}
+
+// k of every tile (one workgroup each: the squares through LDS, the recurrence in one lane)
+__global__ __launch_bounds__(64) void count_kernel(const SvdTile *__restrict__ tiles, const double2 *__restrict__ W,
+                                                   const double *__restrict__ d2, const double *__restrict__ v0,
+                                                   double eps, int32_t *__restrict__ kout) {
+    __shared__ double sd2[BIDIAG_MAX_M], se2[BIDIAG_MAX_M];
+    const SvdTile t = tiles[blockIdx.x];
+    const double *e2 = reinterpret_cast<const double *>(W + t.offW);
+    const double sc = scale_of(*v0);
+    for (int i = threadIdx.x; i < t.n; i += 64) {
+        sd2[i] = d2[t.offS + i] * (sc * sc);
+        se2[i] = e2[i] * (sc * sc);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) kout[blockIdx.x] = at_least(sd2, se2, t.n, eps * *v0 * sc);
+}
+
+}  // namespace
+
+bool bidiag_in_lds(int mmax) { return mmax <= 64; }
+
+hipError_t launch_bidiag(const SvdTile *tiles, int ntiles, int mmax, const float2 *X, int64_t ldx, double2 *W,
+                         double *d2, int32_t *nonfinite, hipStream_t s) {
+    if (ntiles <= 0) return hipSuccess;
+    const dim3 g((unsigned)ntiles);
+    if (mmax <= 32)
+        hipLaunchKernelGGL((bidiag_kernel<32, 256, true>), g, dim3(256), 0, s, tiles, X, ldx, W, d2, nonfinite);
+    else if (mmax <= 64)
+        hipLaunchKernelGGL((bidiag_kernel<64, 1024, true>), g, dim3(1024), 0, s, tiles, X, ldx, W, d2, nonfinite);
+    else if (mmax <= 256)
+        hipLaunchKernelGGL((bidiag_kernel<256, 1024, false>), g, dim3(1024), 0, s, tiles, X, ldx, W, d2, nonfinite);
+    else if (mmax <= BIDIAG_MAX_M)
+        hipLaunchKernelGGL((bidiag_kernel<512, 512, false>), g, dim3(512), 0, s, tiles, X, ldx, W, d2, nonfinite);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_svd_counts(const SvdTile *tiles, int ntiles, const double2 *W, const double *d2, double eps,
+                             int32_t *kout, double *v0, hipStream_t s) {
+    if (ntiles <= 0) return hipSuccess;
+    hipLaunchKernelGGL(vmax_kernel, dim3(1), dim3(256), 0, s, tiles, ntiles, W, v0);
+    hipLaunchKernelGGL(count_kernel, dim3((unsigned)ntiles), dim3(64), 0, s, tiles, W, d2, v0, eps, kout);
+    return hipGetLastError();
+}
+
+}  // namespace tlr

@@ -1,5 +1,6 @@
-// Per-tile SVD in FP64 for the rank / tile-size estimate and the warm start
-// (Hyper-parameter selection and initialization; the examples' rank study).
+// Per-tile SVD in FP64 for the warm start, and for the rank / tile-size estimate where
+// bidiag.hip does not apply (Hyper-parameter selection and initialization; the
+// examples' rank study).
 //
 // Every tile X_ij (i >= j) of a reference solution is copied to FP64 and
 // decomposed by one-sided (Hestenes) Jacobi: column pairs of W = X_ij are
@@ -24,18 +25,22 @@ __device__ __forceinline__ double wsum(double v) { return __ockl_wfred_add_f64(v
 // X (complex64, row-major, ld ldx) -> W (complex128, column-major m x n per tile); V = I when wanted
 __global__ __launch_bounds__(256) void svd_gather_kernel(const SvdTile *__restrict__ tiles,
                                                          const float2 *__restrict__ X, int64_t ldx,
-                                                         double2 *__restrict__ W, double2 *__restrict__ V) {
+                                                         double2 *__restrict__ W, double2 *__restrict__ V,
+                                                         int32_t *__restrict__ nonfinite) {
     const SvdTile t = tiles[blockIdx.x];
+    bool ok = true;
     for (int c = blockIdx.y; c < t.n; c += gridDim.y) {
         for (int r = threadIdx.x; r < t.m; r += blockDim.x) {   // A[r][c] = X_ij[r][c] or X_ij[c][r]
             const float2 x = t.trans ? X[(int64_t)(t.row0 + c) * ldx + t.col0 + r]
                                      : X[(int64_t)(t.row0 + r) * ldx + t.col0 + c];
+            ok = ok && isfinite(x.x) && isfinite(x.y);
             W[t.offW + (int64_t)c * t.m + r] = make_double2(x.x, x.y);
         }
         if (V && t.offV >= 0)
             for (int r = threadIdx.x; r < t.n; r += blockDim.x)
                 V[t.offV + (int64_t)c * t.n + r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
     }
+    if (nonfinite && !ok) *nonfinite = 1;
 }
 
 // pair k of round r in the circle ordering of n' (even) columns: every pair once per n' - 1 rounds
@@ -252,9 +257,9 @@ __global__ __launch_bounds__(256) void svd_factors_kernel(const SvdTile *__restr
 }  // namespace
 
 hipError_t launch_svd_gather(const SvdTile *tiles, int ntiles, const float2 *X, int64_t ldx, double2 *W, double2 *V,
-                             hipStream_t s) {
+                             int32_t *nonfinite, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(svd_gather_kernel, dim3((unsigned)ntiles, 64), dim3(256), 0, s, tiles, X, ldx, W, V);
+    hipLaunchKernelGGL(svd_gather_kernel, dim3((unsigned)ntiles, 64), dim3(256), 0, s, tiles, X, ldx, W, V, nonfinite);
     return hipGetLastError();
 }
 

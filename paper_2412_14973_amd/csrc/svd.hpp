@@ -35,8 +35,9 @@ constexpr int SVD_MAX_N = 1024;     // tile columns handled by the per-tile sort
 constexpr int SVD_MAX_SWEEPS = 30;  // sweeps enqueued; converged sweeps return at once
 constexpr double SVD_TOL = 1e-13;   // rotate a pair while |w_p^H w_q| > tol ||w_p|| ||w_q||
 
+// nonfinite (may be NULL): set to 1 where a tile holds a value that is not finite
 hipError_t launch_svd_gather(const SvdTile *tiles, int ntiles, const float2 *X, int64_t ldx, double2 *W, double2 *V,
-                             hipStream_t s);
+                             int32_t *nonfinite, hipStream_t s);
 hipError_t launch_svd_round(const SvdTile *tiles, const int32_t *pair_tile, int npairs, int round, double2 *W,
                             double2 *V, const int32_t *flags, int32_t *busy, double tol, hipStream_t s);
 hipError_t launch_svd_sweep_end(int32_t *flags, int32_t *busy, hipStream_t s);
@@ -47,5 +48,16 @@ hipError_t launch_svd_order(const SvdTile *tiles, int ntiles, const double *sig,
 hipError_t launch_svd_factors(const SvdTile *tiles, const WarmItem *items, int nitems, const double2 *W,
                               const double2 *V, const double *sig, const int32_t *order, const float2 *X,
                               int64_t ldx, float2 *theta, hipStream_t s);
+
+// Counts without vectors (bidiag.hip), tiles of at most BIDIAG_MAX_M rows (mmax: the largest). Up to 64 rows the
+// tiles are read from X, else from W (gathered before). The squares of the bidiagonal go to d2 (sigma slots) and,
+// with the tile's largest singular value, to the start of its W.
+constexpr int BIDIAG_MAX_M = 512;
+bool bidiag_in_lds(int mmax);
+hipError_t launch_bidiag(const SvdTile *tiles, int ntiles, int mmax, const float2 *X, int64_t ldx, double2 *W,
+                         double *d2, int32_t *nonfinite, hipStream_t s);
+// v0 = the largest of them, k = #{sigma >= eps v0} per tile
+hipError_t launch_svd_counts(const SvdTile *tiles, int ntiles, const double2 *W, const double *d2, double eps,
+                             int32_t *kout, double *v0, hipStream_t s);
 
 }  // namespace tlr

@@ -1,0 +1,58 @@
+"""Rank counts from bidiagonals at the edges of their variants (tiles of 32, 64, 256 and 512 rows; ragged last tiles,
+tall and wide ones), against NumPy's singular values in FP64, and what they leave to the rotations: a tile that is not
+finite, tiles above 512 rows."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def _symmetric(nr, seed):
+    """Decaying singular values in every tile (a smooth kernel), some noise, exactly symmetric complex64."""
+    rng = np.random.default_rng(seed)
+    x = np.sort(rng.random(nr))
+    d = np.abs(x[:, None] - x[None, :])
+    a = np.exp(-1j * 40 * d) / (d + 0.02) + 0.5 * (rng.standard_normal((nr, nr)) + 1j * rng.standard_normal((nr, nr)))
+    return ((a + a.T) / 2).astype(np.complex64)
+
+
+def _reference(X, d, eps):
+    X = X.astype(np.complex128)
+    cut = list(range(0, X.shape[0], d)) + [X.shape[0]]
+    sv = {(i, j): np.linalg.svd(X[cut[i]:cut[i + 1], cut[j]:cut[j + 1]], compute_uv=False)
+          for i in range(len(cut) - 1) for j in range(i + 1)}
+    v0 = max(s[0] for s in sv.values())
+    t = eps * v0
+    assert min(np.min(np.abs(s - t)) for s in sv.values()) > 1e-10 * v0   # no singular value on the threshold
+    k = {ij: int(np.sum(s >= t)) for ij, s in sv.items()}
+    n = len(cut) - 1
+    return [k[i, j] for i in range(n) for j in range(i)], [k[i, i] for i in range(n)], v0
+
+
+@pytest.mark.parametrize("nr,d", [(1, 1), (5, 2), (33, 16), (64, 32), (97, 33), (150, 64), (140, 65), (300, 100), (520, 256),
+                                  (530, 257), (1024, 512), (600, 560)])
+@pytest.mark.parametrize("eps", [0.05, 1e-3])
+def test_rank_counts(nr, d, eps):
+    import paper_2412_14973_amd as tl
+    X = _symmetric(nr, 7 * nr + d)
+    ko, kd, v0 = tl.tile_ranks(torch.from_numpy(X).cuda(), d, eps)
+    ro, rd, v0r = _reference(X, d, eps)
+    assert ko.tolist() == ro and kd.tolist() == rd
+    # backward stable reduction: a few n u; the rotations (tiles above 512 rows) stop at 1e-13 per pair, and the
+    # rank tests hold them to 1e-12
+    assert abs(v0 - v0r) <= (1e-13 if d <= 512 else 1e-12) * v0r
+
+
+def test_rank_counts_zero_and_nonfinite():
+    import paper_2412_14973_amd as tl
+    ko, kd, v0 = tl.tile_ranks(torch.zeros(96, 96, dtype=torch.complex64, device="cuda"), 32, 0.01)
+    assert v0 == 0.0 and set(ko.tolist()) == set(kd.tolist()) == {32}   # sigma >= 0 holds for all
+    # one bad entry: its tile's other columns and all other tiles keep their counts
+    X = _symmetric(96, 3)
+    ref = _reference(X, 32, 0.05)
+    Y = X.copy()
+    Y[40, 2] = np.nan
+    ko, kd, v0 = tl.tile_ranks(torch.from_numpy(Y).cuda(), 32, 0.05)
+    assert kd.tolist() == ref[1] and ko.tolist()[1:] == ref[0][1:] and abs(v0 - ref[2]) <= 1e-12 * ref[2]
