@@ -1187,7 +1187,7 @@ struct Ctx {
     hipStream_t s;
     bool bf16 = false;          // BF16 hi+lo split products
     bool p3m = false;           // FP32 products in the three-real-product form
-    bool split = false;         // dense FP32 products with the contraction split over waves (gemm_split_k)
+    bool split = false;         // dense products with the contraction split over waves (gemm_split_k)
     int64_t xspace = 0;         // complex64 elements of X space per problem (1 or 2 ldk x ldk)
 
     int form() const { return bf16 ? F_BF16X3 : p3m ? F_3M : F_4M; }
@@ -1199,12 +1199,13 @@ struct Ctx {
     int64_t lo_words() const { return xspace; }
 };
 
-// The contraction of a dense FP32 product is split over the four waves of a workgroup where a wave for every
+// The contraction of a dense product is split over the four waves of a workgroup where a wave for every
 // 32 x 32 block would fill the chip's 1024 SIMDs fewer than eight times: below that the last round and the
 // few waves per SIMD cost more than the sums over the waves (one problem, three products, us for r = D X - U,
 // D^H r and [a | b], split against a wave per block: 512^2 16, 15, 24 against 38, 35, 63; 1024^2 59, 57, 107
 // against 70, 69, 121; 2304^2 560, 559, 1086 against 635, 637, 1228; 4096 x 2048 1518, 1579, 3050 against
-// 1503, 1537, 2957; where a batch fills the chip anyway the split is 2 to 4 % slower). The order of the sums
+// 1503, 1537, 2957; where a batch fills the chip anyway the split is 2 to 4 % slower; in BF16 2304^2 262, 246,
+// 469 against 296, 287, 471, and 3 to 7 % in full batches). The order of the sums
 // changes with it, so the choice looks at the problem's own sizes only: its results do not depend on its batch.
 constexpr int64_t SPLIT_MAX_BLOCKS = 8191;
 bool gemm_split_k(int64_t nr, int64_t ns) {
@@ -1222,14 +1223,13 @@ int fin(const Ctx &c, FinArgs f, const int32_t *counts, int ucount, int nsum) {
     f.pstride = c.pstride;
     f.counts = counts;
     f.ucount = ucount;
-    if (f.nfirst == 0) f.ucount2 = ucount;   // one count for all problems
     f.nsum = nsum;
     HIP_TRY(launch_finalize(f, c.nprob, c.s));
     return TLRMDD_OK;
 }
 
 // The dense products contract over the true length rounded up to the kernel's k step (16 complex,
-// 32 for the BF16 ring), not over the padded one: the padding is zero and would only add stages.
+// 32 in BF16), not over the padded one: the padding is zero and would only add stages.
 int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64_t ldu, int64_t sU, float2 *r) {
     const double np = c.nprob, ns = (double)c.ns, nr = (double)c.nr;
     const Work wk = gemm_work(c.form(), 8.0 * ns * nr * nr * np, 8.0 * np * (3.0 * ns * nr + nr * nr));
@@ -1238,18 +1238,22 @@ int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64
         const uint32_t *xh = reinterpret_cast<const uint32_t *>(X);
         GemmArgsB g;
         std::memset(&g, 0, sizeof(g));
-        g.Ahi = reinterpret_cast<const uint16_t *>(c.dsw());
-        g.Alo = reinterpret_cast<const uint16_t *>(c.dsw() + c.lds * c.ldk);
+        g.Ahi = c.dsw();
+        g.Alo = c.dsw() + c.lds * c.ldk;
         g.lda = c.ldk; g.sA = 2 * c.lds * c.ldk;
-        g.Bhi = reinterpret_cast<const uint16_t *>(xh);
-        g.Blo = reinterpret_cast<const uint16_t *>(xh + c.lo_words());
+        g.Bhi = xh;
+        g.Blo = xh + c.lo_words();
         g.ldb = c.ldk; g.sB = 2 * sX;
         g.C = r; g.ldc = c.ldk; g.sC = c.lds * c.ldk;
         g.E = U; g.lde = ldu; g.sE = sU;
+        if (c.w.rT) {   // the adjoint product's operand
+            g.Thi = c.w.rT; g.Tlo = c.w.rT + c.ldk * c.lds;
+            g.ldt = c.lds; g.sT = 2 * c.ldk * c.lds;
+        }
         g.partials = c.w.partials; g.sP = (int64_t)c.pstride;
         g.M = (int)c.lds; g.N = (int)c.ldk; g.K = (int)round_up(c.nr, 32);
-        g.Me = (int)c.ns; g.Ne = (int)c.nr;
-        HIP_TRY(timed(TLRMDD_K_GEMM_RESID, c.s, wk, [&] { return launch_cgemm_bf16(GM_RESID, g, c.nprob, c.s); }));
+        g.Me = g.Mt = (int)c.ns; g.Ne = g.Nt = (int)c.nr;
+        HIP_TRY(timed(TLRMDD_K_GEMM_RESID, c.s, wk, [&] { return launch_cgemm_bf16(GM_RESID, g, c.nprob, c.s, c.split); }));
         return TLRMDD_OK;
     }
     GemmArgs g = gemm_args();
@@ -1270,18 +1274,19 @@ int gemm_adjoint(const Ctx &c, const float2 *r, float2 *W, int64_t sW) {
     const double np = c.nprob, ns = (double)c.ns, nr = (double)c.nr;
     const Work wk = gemm_work(c.form(), 8.0 * nr * ns * nr * np, 8.0 * np * (2.0 * ns * nr + nr * nr));
     if (c.bf16) {
-        // r^T split planes (written by split_r_transpose) are the transposed B operand
+        // r^T split planes (written with r, or by split_r_transpose) are the transposed B operand
         GemmArgsB g;
         std::memset(&g, 0, sizeof(g));
-        g.Ahi = reinterpret_cast<const uint16_t *>(c.dhw());
-        g.Alo = reinterpret_cast<const uint16_t *>(c.dhw() + c.ldk * c.lds);
+        g.Ahi = c.dhw();
+        g.Alo = c.dhw() + c.ldk * c.lds;
         g.lda = c.lds; g.sA = 2 * c.ldk * c.lds;
-        g.Bhi = reinterpret_cast<const uint16_t *>(c.w.rT);
-        g.Blo = reinterpret_cast<const uint16_t *>(c.w.rT + c.ldk * c.lds);
+        g.Bhi = c.w.rT;
+        g.Blo = c.w.rT + c.ldk * c.lds;
         g.ldb = c.lds; g.sB = 2 * c.ldk * c.lds;
         g.C = W; g.ldc = c.ldk; g.sC = sW;
         g.M = (int)c.ldk; g.N = (int)c.ldk; g.K = (int)round_up(c.ns, 32);
-        HIP_TRY(timed(TLRMDD_K_GEMM_ADJOINT, c.s, wk, [&] { return launch_cgemm_bf16(GM_STORE, g, c.nprob, c.s); }));
+        g.Mt = g.Nt = (int)c.nr;
+        HIP_TRY(timed(TLRMDD_K_GEMM_ADJOINT, c.s, wk, [&] { return launch_cgemm_bf16(GM_STORE, g, c.nprob, c.s, c.split); }));
         return TLRMDD_OK;
     }
     GemmArgs g = gemm_args();
@@ -1303,17 +1308,18 @@ int gemm_line(const Ctx &c, const float2 *X1, const float2 *X2, int64_t sX) {
         const uint32_t *xh = reinterpret_cast<const uint32_t *>(X1);
         GemmArgsB g;
         std::memset(&g, 0, sizeof(g));
-        g.Ahi = reinterpret_cast<const uint16_t *>(c.dsw());
-        g.Alo = reinterpret_cast<const uint16_t *>(c.dsw() + c.lds * c.ldk);
+        g.Ahi = c.dsw();
+        g.Alo = c.dsw() + c.lds * c.ldk;
         g.lda = c.ldk; g.sA = 2 * c.lds * c.ldk;
-        g.Bhi = reinterpret_cast<const uint16_t *>(xh);
-        g.Blo = reinterpret_cast<const uint16_t *>(xh + c.lo_words());
+        g.Bhi = xh;
+        g.Blo = xh + c.lo_words();
         g.ldb = c.ldk; g.sB = 2 * sX; g.b2_rows = c.ldk;   // X2 planes follow X1's ldk rows
         g.C = c.w.a; g.C2 = c.w.b; g.ldc = c.ldk; g.sC = c.lds * c.ldk;
         g.E = c.w.r; g.lde = c.ldk; g.sE = c.lds * c.ldk;
         g.partials = c.w.partials; g.sP = (int64_t)c.pstride * 5;
         g.M = (int)c.lds; g.N = (int)c.ldk; g.K = (int)round_up(c.nr, 32);
-        HIP_TRY(timed(TLRMDD_K_GEMM_LINE, c.s, wk, [&] { return launch_cgemm_bf16(GM_LINE, g, c.nprob, c.s); }));
+        g.Mt = (int)c.ns; g.Nt = (int)c.nr;
+        HIP_TRY(timed(TLRMDD_K_GEMM_LINE, c.s, wk, [&] { return launch_cgemm_bf16(GM_LINE, g, c.nprob, c.s, c.split); }));
         return TLRMDD_OK;
     }
     GemmArgs g = gemm_args();
@@ -1330,7 +1336,7 @@ int gemm_line(const Ctx &c, const float2 *X1, const float2 *X2, int64_t sX) {
     return TLRMDD_OK;
 }
 
-// r^T split planes for the BF16 adjoint product
+// r^T split planes for the BF16 adjoint product, of an r that no product has just written
 int split_r_transpose(const Ctx &c) {
     if (!c.bf16) return TLRMDD_OK;
     HIP_TRY(launch_split_transpose(c.w.r, c.ldk, c.lds, c.ldk, c.w.rT, c.w.rT + c.ldk * c.lds, c.lds, c.nprob,
@@ -1358,13 +1364,8 @@ int stage(const Ctx &c, int p, const float2 *D, bool with_dh) {
     return TLRMDD_OK;
 }
 
-// partial-sum slots that the products of `mode` fill per problem: those of the FP32 kernel, or (dense
-// products in BF16 mode) one per 128 x 128 (GM_LINE: 128 x 64) tile
-int partial_slots(const Ctx &c, int mode, bool tile_form = false) {
-    if (c.bf16 && !tile_form)
-        return (int)(c.lds / GEMM_BM) * (int)(c.ldk / (mode == GM_LINE ? GEMM_BN / 2 : GEMM_BN));
-    return gemm_partial_slots((int)c.lds, (int)c.ldk);
-}
+// partial-sum slots that the products fill per problem
+int partial_slots(const Ctx &c) { return gemm_partial_slots((int)c.lds, (int)c.ldk); }
 
 // The whole solve, for one problem or a batch of equal-shape problems.
 // One run of the solver over `nprob` problems of one shape: tables, workspace views, staged operands
@@ -1565,18 +1566,15 @@ int clear_plane_padding(Run &R) {
 }
 
 // record < 0: no f-history entry
-// nfirst, first_parts: another number of partial sums for the problems before nfirst
-int fin_f(Run &R, int record, double lam, int nsum_parts, int nfirst = 0, int first_parts = 0) {
+int fin_f(Run &R, int record, double lam, int nsum_parts) {
     FinArgs f = fin_args(FIN_F, R.c.w.sc);
-    f.nfirst = nfirst;
-    f.ucount2 = nsum_parts;
     if (record >= 0) {
         f.fhist = R.single ? nullptr : R.c.D.fhist;
         f.fhist0 = R.fhist0;
         f.t = record;
     }
     f.lam = lam;
-    return fin(R.c, f, nullptr, nfirst ? first_parts : nsum_parts, 1);
+    return fin(R.c, f, nullptr, nsum_parts, 1);
 }
 
 // r = D C(theta) - U afresh: assembly and the dense product for the problems before the tile-form
@@ -1600,8 +1598,7 @@ int objective_fresh(Run &R, int record, double lam) {
     for (const LineSeg &sg : R.segs)
         if (sg.tile && sg.lt.lc.grad)
             if ((e = tile_resid(R, sg))) return e;
-    if ((e = split_r_transpose(c))) return e;
-    return fin_f(R, record, lam, partial_slots(c, GM_RESID, true), R.n_adj, partial_slots(c, GM_RESID));
+    return fin_f(R, record, lam, partial_slots(c));
 }
 
 int run_setup(Run &R, int op, int nprob, const tlrmdd_plan *plans, const void *const *D, const void *const *U,
@@ -1822,14 +1819,9 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
             if (st) return st;
         }
         {
-            // the dense-form problems come before the tile ranges
             FinArgs f = fin_args(FIN_LINE, c.w.sc);
             f.lam = lam;
-            f.nfirst = 0;
-            for (const LineSeg &sg : R.segs)
-                if (!sg.tile) f.nfirst = std::max(f.nfirst, sg.p0 + sg.np);
-            f.ucount2 = partial_slots(c, GM_LINE, true);
-            if ((st = fin(c, f, nullptr, f.nfirst ? partial_slots(c, GM_LINE) : f.ucount2, 5))) return st;
+            if ((st = fin(c, f, nullptr, partial_slots(c), 5))) return st;
         }
         // updates
         HIP_TRY(timed(TLRMDD_K_THETA_UPDATE, s,
@@ -1851,7 +1843,9 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
                 return launch_resid_update(c.D.rsegs, R.nrs, (float *)c.w.r, (const float *)c.w.a,
                                            (const float *)c.w.b, c.w.sc, c.w.partials, s);
             }));
-            if ((st = split_r_transpose(c))) return st;
+            Ctx ca = c;   // the problems whose gradient is the dense adjoint product
+            ca.nprob = R.n_adj;
+            if (ca.nprob > 0 && (st = split_r_transpose(ca))) return st;
             if ((st = fin_f(R, record_base >= 0 ? record_base + t + 1 : -1, lam, R.T.rseg_per_prob))) return st;
         }
         std::swap(R.gcur, R.gprev);
@@ -1959,7 +1953,7 @@ int tlrmdd_forward(tlrmdd_plan plan, const void *D, const void *U, const void *t
     if ((st = gemm_resid(c, c.w.XW, 0, (const float2 *)U, c.nr, 0, c.w.r))) return st;
     FinArgs f = fin_args(FIN_F_OUT, c.w.sc);
     f.fout = f_dev;
-    if ((st = fin(c, f, nullptr, partial_slots(c, GM_RESID), 1))) return st;
+    if ((st = fin(c, f, nullptr, partial_slots(c), 1))) return st;
     if (r_out) HIP_TRY(launch_copy2d(c.w.r, c.ldk, (float2 *)r_out, c.nr, c.ns, c.nr, stream));
     if (X_out) {
         if (c.bf16)   // the X space holds split planes: re-assemble X in complex64 for the caller
@@ -1996,11 +1990,10 @@ int tlrmdd_grad(tlrmdd_plan plan, const void *D, const void *U, const void *thet
     HIP_TRY(timed(TLRMDD_K_ASSEMBLE, stream, gemm_work(F_4M, plan->H.asm_cflops, 8.0 * (nr2 + thn)), [&] { return launch_assemble(false, c.D.tiles, c.D.asm_items, c.D.n_asm, c.D.probs, (const float2 *)theta, nullptr,
                             c.w.XW, nullptr, stream, c.bf16, 0, c.lo_words()); }));
     if ((st = gemm_resid(c, c.w.XW, 0, (const float2 *)U, c.nr, 0, c.w.r))) return st;
-    if ((st = split_r_transpose(c))) return st;
     if (f_dev) {
         FinArgs f = fin_args(FIN_F_OUT, c.w.sc);
         f.fout = f_dev;
-        if ((st = fin(c, f, nullptr, partial_slots(c, GM_RESID), 1))) return st;
+        if ((st = fin(c, f, nullptr, partial_slots(c), 1))) return st;
     }
     // the assembled X is dead once r exists: W = D^H r reuses its storage
     if ((st = gemm_adjoint(c, c.w.r, c.w.XW, 0))) return st;
@@ -2776,7 +2769,7 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
     f.partials = w.partials;
     f.pstride = N * tiles2;
     f.counts = nullptr;
-    f.ucount = f.ucount2 = (int32_t)(N * tiles2);
+    f.ucount = (int32_t)(N * tiles2);
     f.nsum = 1;
     f.fout = f_dev;
     HIP_TRY(launch_finalize(f, 1, s));

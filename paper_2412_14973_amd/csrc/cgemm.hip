@@ -41,15 +41,6 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 namespace {
 
-// the five products of the line-search sums: Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2
-__device__ __forceinline__ void line_terms(float (&blk)[5], float2 r, float2 a, float2 b) {
-    blk[0] = fmaf(r.x, a.x, fmaf(r.y, a.y, blk[0]));
-    blk[1] = fmaf(a.x, a.x, fmaf(a.y, a.y, blk[1]));
-    blk[2] = fmaf(r.x, b.x, fmaf(r.y, b.y, blk[2]));
-    blk[3] = fmaf(a.x, b.x, fmaf(a.y, b.y, blk[3]));
-    blk[4] = fmaf(b.x, b.x, fmaf(b.y, b.y, blk[4]));
-}
-
 __device__ __forceinline__ float flip(float v, uint32_t sign) { return __uint_as_float(__float_as_uint(v) ^ sign); }
 
 // The operands of one chunk of CH complex k as loaded. Every step multiplies two k, one per lane half h. A
@@ -236,109 +227,28 @@ __global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
     chunks(first, nc2, std::integral_constant<int, NB>{});
     if constexpr (SPLIT_K2) chunks(nc2, nc, std::integral_constant<int, 1>{});
 
-    // ---- epilogue ----
-    float2 *C = g.C + z * g.sC + z2 * g.sC2 + z3 * g.sC3 + z4 * g.sC4;
-    const int64_t ldc = g.ldc;
-    const int col = n0 + j32;
-    auto cval = [&](int h, int n, int r) {
-        const floatx16 *d = acc[h][n];
-        if constexpr (M3) return make_float2(d[0][r] - d[1][r], d[NT - 1][r] - d[0][r] - d[1][r]);
-        else return make_float2(d[0][r], d[1][r]);
-    };
-    constexpr int NR = KS == 1 ? 16 : 16 / KS;   // rows of a block that this wave finishes
-    constexpr int NS = MODE == GM_RESID ? 1 : 5;
-    auto row_of = [&](int h, int r) { return m0 + 32 * h + acc_row(KS == 1 ? r : wave * NR + r, lane); };
-    const float2 *E = MODE == GM_STORE ? nullptr : g.E + z * g.sE + z2 * g.sE2;
-    double *partials = MODE == GM_STORE ? nullptr : g.partials + z * g.sP + z2 * g.sP2;
-    __shared__ float2 part[KS][KS == 1 ? 1 : 16][KS == 1 ? 1 : 64];   // a, then b: less LDS, more waves per CU
-    __shared__ double red[KS][NS];
-#pragma unroll
-    for (int h = 0; h < HB; ++h)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            const int cc = col + 32 * cb;
-            // the entries of E: their loads are in flight together, and during the sums over the waves (an
-            // entry outside E reads E[0] and is dropped)
-            float2 e[NR];
-            if constexpr (MODE != GM_STORE) {
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const int row = row_of(h, r);
-                    const bool in = MODE == GM_LINE || (row < g.Me && cc < g.Ne);
-                    e[r] = E[in ? (int64_t)row * g.lde + cc : 0];
-                    if (!in) e[r] = make_float2(0.f, 0.f);
-                }
-            }
-            constexpr int NV = MODE == GM_LINE ? 2 : 1;   // a and b, or one block of C
-            float2 v[NV][NR];
-#pragma unroll
-            for (int n = 0; n < NV; ++n) {
-                if constexpr (KS == 1) {
-#pragma unroll
-                    for (int r = 0; r < NR; ++r) v[n][r] = cval(h, MODE == GM_LINE ? n : cb, r);
-                } else {
-                    if (n) __syncthreads();
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) part[wave][r][lane] = cval(h, n, r);
-                    __syncthreads();
-#pragma unroll
-                    for (int r = 0; r < NR; ++r) {
-                        float2 s = part[0][wave * NR + r][lane];
-#pragma unroll
-                        for (int w = 1; w < KS; ++w) {
-                            const float2 x = part[w][wave * NR + r][lane];
-                            s.x += x.x;
-                            s.y += x.y;
-                        }
-                        v[n][r] = s;
-                    }
-                }
-            }
-            float blk[NS];
-#pragma unroll
-            for (int q = 0; q < NS; ++q) blk[q] = 0.f;
-            if constexpr (MODE == GM_STORE) {
-                int64_t ccol = cc;
-                if (STAGE && g.scat_kp > 0) {
-                    if (cc >= g.scat_lim) continue;
-                    ccol += (int64_t)((cc % g.scat_w) / g.scat_kp) * g.scat_js;
-                }
-#pragma unroll
-                for (int r = 0; r < NR; ++r) C[(int64_t)row_of(h, r) * ldc + ccol] = v[0][r];
-            } else if constexpr (MODE == GM_RESID) {
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const float2 d = make_float2(v[0][r].x - e[r].x, v[0][r].y - e[r].y);
-                    C[(int64_t)row_of(h, r) * ldc + cc] = d;
-                    blk[0] = fmaf(d.x, d.x, fmaf(d.y, d.y, blk[0]));
-                }
-            } else {
-                float2 *C2 = g.C2 + z * g.sC + z2 * g.sC2;
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    C[(int64_t)row_of(h, r) * ldc + cc] = v[0][r];
-                    C2[(int64_t)row_of(h, r) * ldc + cc] = v[NV - 1][r];
-                    line_terms(blk, e[r], v[0][r], v[NV - 1][r]);
-                }
-            }
-            // a block's sums: its lanes' FP32 sums over the rows, added in FP64; one slot per 32 x 32 block,
-            // numbered by block row and column whatever the tile
-            if constexpr (MODE != GM_STORE) {
-                const int64_t slot = (int64_t)((m0 >> 5) + h) * (g.N >> 5) + (cc >> 5);
-#pragma unroll
-                for (int q = 0; q < NS; ++q) {
-                    const double s = wave_sum((double)blk[q]);
-                    if (lane == 0) {
-                        if constexpr (KS == 1) partials[slot * NS + q] = s;
-                        else red[wave][q] = s;
-                    }
-                }
-                if constexpr (KS > 1) {
-                    __syncthreads();
-                    if (t < NS) partials[slot * NS + t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
-                }
-            }
-        }
+    EpiArgs ea;
+    ea.C = g.C + z * g.sC + z2 * g.sC2 + z3 * g.sC3 + z4 * g.sC4;
+    ea.C2 = MODE == GM_LINE ? g.C2 + z * g.sC + z2 * g.sC2 : nullptr;
+    ea.ldc = g.ldc;
+    ea.E = MODE == GM_STORE ? nullptr : g.E + z * g.sE + z2 * g.sE2;
+    ea.lde = g.lde;
+    ea.Me = g.Me;
+    ea.Ne = g.Ne;
+    ea.partials = MODE == GM_STORE ? nullptr : g.partials + z * g.sP + z2 * g.sP2;
+    ea.nblk = g.N >> 5;
+    ea.scat_kp = g.scat_kp;
+    ea.scat_w = g.scat_w;
+    ea.scat_lim = g.scat_lim;
+    ea.scat_js = g.scat_js;
+    block_epilogue<MODE, STAGE, KS, HB, CB>(
+        ea,
+        [&](int h, int n, int r) {
+            const floatx16 *d = acc[h][n];
+            if constexpr (M3) return make_float2(d[0][r] - d[1][r], d[NT - 1][r] - d[0][r] - d[1][r]);
+            else return make_float2(d[0][r], d[1][r]);
+        },
+        m0, n0);
 }
 
 template <int MODE, bool M3, int ROLE, int KS, bool BIG = false>

@@ -1,34 +1,34 @@
 // Complex64 GEMM on CDNA4 BF16 matrix cores with a hi+lo split.
 //
 // Every FP32 operand x is carried as two BF16 numbers, hi = bf16(x) and
-// lo = bf16(x - hi); a product is evaluated as hi*hi + hi*lo + lo*hi with FP32
+// lo = bf16(x - hi); a product is evaluated as lo*hi + hi*lo + hi*hi with FP32
 // accumulation (the lo*lo term, about 2^-16 of the product, is dropped).
-// The complex product is the same realified real GEMM as in the FP32 kernel
-// (M x 2N x 2K, B expanded to [[Re b, Im b], [-Im b, Re b]] blocks), here on
-// v_mfma_f32_32x32x16_bf16: one instruction consumes 8 complex k.
+// A is M x K complex, B is given TRANSPOSED, N x K complex ("NT" form); for the
+// products of the method this is free: X, X1 and X2 are symmetric, and r^T is
+// written by the kernel that updates r. Operands are pre-split into separate hi
+// and lo planes of interleaved complex BF16 (4 bytes per complex). A row of A is
+// then a real row (Re, Im, Re, Im, ...); the real part of C takes the B row with
+// its imaginary parts negated (one XOR per word), the imaginary part the row with
+// (Re, Im) swapped (one rotation per word). One v_mfma_f32_32x32x16_bf16
+// multiplies 8 complex k of one of these products.
 //
-// Both operands are K-contiguous in memory ("NT" form): A is M x K complex
-// (row-major), B is given TRANSPOSED, N x K complex. For the products of the
-// method this is free: X, X1 and X2 are symmetric, and the adjoint operand
-// r^T is written by the kernel that updates r. Operands are pre-split into
-// separate hi and lo planes of interleaved complex BF16 (4 bytes per complex).
-//
-// Tiling: 512 threads = 8 waves (4 x 2), workgroup tile 256 rows x 128
-// complex columns, one workgroup per CU, 8 complex k per stage. At the BF16
-// rate a 128 x 128 tile needs about 13 TB/s of operand bandwidth from L2 and
-// the memory-side cache; the 256-row tile shares each B panel between twice
-// the rows and cuts that by a quarter. Operands go straight from global
-// memory to LDS (buffer_load ... lds, no staging registers) into a 4-stage
-// ring (four planes per stage: A hi/lo of 256 rows, B hi/lo of 128 rows,
-// 16-byte chunks XOR-swizzled so operand reads are bank-conflict free; 96 KiB);
-// loads run three stages ahead of the matrix cores. A stage's twelve fragment reads are one inline-asm group
-// with its own LDS wait: as plain loads the compiler, unable to tell the ring
-// buffers apart from the one the DMA just targeted, would wait for that DMA
-// too and undo the prefetch. Per stage each wave issues 2 x 4 x 3 MFMAs,
-// ordered so consecutive MFMAs accumulate into different tiles. Each
-// lane's B fragment (4 complex b of one column) is turned into the realified
-// row pair by one XOR (column parity 0: [Re, -Im]) or a 16-bit rotate
-// (parity 1: [Im, Re]) per 32-bit word.
+// As in cgemm.hip, every wave feeds its matrix instructions from global memory
+// through registers, without LDS and without a barrier in the k loop, here with
+// 2 x 2 blocks of 32 x 32 complex entries per wave (GM_LINE: two row blocks of a
+// and b): one block per wave asks L1 for 85 bytes per cycle and CU at the matrix
+// cores' rate, which is more than its 64; four ask for 43. The planes hold the
+// operands in the order of these loads (plane_word), which is what makes this work:
+// from row-major planes the same kernel reads 32 bytes of each cache line at a time
+// and reaches 235 of 424 Tflop/s (64 problems of 1024^2).
+// What bounds it: at 4096^2 463 to 476 Tflop/s of complex products (8 m n k), that is 1.4 Pflop/s of
+// BF16 products, above what a library product of 8192^3 reaches (1.04). Before, with 256 x 128 tiles
+// fed through LDS: 367 to 403, and at 1024^2 32 tiles for 256 CUs.
+// us for r = D X - U, D^H r and [a | b] (the first writes r^T's planes too, which took a pass of its own before):
+//   nr = ns     64 x 8 problems   448            1024            2304            1024 x 64 problems
+//   before      33, 15, 19        95, 60, 64     162, 127, 133   346, 295, 656   1953, 1446, 2948
+//   now         7, 7, 9           12, 10, 14     35, 29, 51      262, 246, 469   1581, 1316, 2713
+#include <algorithm>
+
 #include "gemm_common.hpp"
 
 namespace tlr {
@@ -38,230 +38,178 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
-constexpr int BM = 2 * GEMM_BM, BN = GEMM_BN;   // 256 x 128 (complex) workgroup tile
-constexpr int BKC = 8;                    // complex k per stage (= 16 real k = one MFMA)
-constexpr int ROWB = 32;                  // bytes per LDS row of a plane (8 complex BF16)
-constexpr int PLANE_A = BM * ROWB;        // 8 KiB per A plane
-constexpr int PLANE_B = BN * ROWB;        // 4 KiB per B plane
-constexpr int OFF_AL = PLANE_A, OFF_BH = 2 * PLANE_A, OFF_BL = 2 * PLANE_A + PLANE_B;
-constexpr int STAGE = 2 * PLANE_A + 2 * PLANE_B;   // A hi, A lo, B hi, B lo: 24 KiB
-constexpr int NSTAGE = 4;                 // LDS ring depth (96 KiB per workgroup)
-constexpr int NTHREADS = 512;
 
-__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+template <int HB, int NB>
+struct Chunk {
+    u32x4 a[HB][2], b[NB][2];   // [block][hi, lo]: 4 complex k per lane, lane half h holding 4 h .. 4 h + 3
+};
 
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding)
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | (((N >> 4) & 3) << 14));
-}
-
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-
-template <int MODE>
-__global__ __launch_bounds__(NTHREADS, 1) void cgemm_bf16x3_kernel(GemmArgsB g) {
-    // four distinct LDS objects (one per ring stage): reads of one stage and DMA into another are
-    // then provably disjoint, so no conservative vmcnt wait is needed before the operand reads
-    __shared__ __attribute__((aligned(1024))) unsigned char sm0[STAGE];
-    __shared__ __attribute__((aligned(1024))) unsigned char sm1[STAGE];
-    __shared__ __attribute__((aligned(1024))) unsigned char sm2[STAGE];
-    __shared__ __attribute__((aligned(1024))) unsigned char sm3[STAGE];
-
+template <int MODE, int HB, int CB, int KS>
+__global__ __launch_bounds__(256, 2) void cgemm_bf16x3_kernel(GemmArgsB g) {
+    constexpr int NB = MODE == GM_LINE ? 2 : CB;   // column blocks of B (GM_LINE: of X1 and of X2)
+    constexpr int WV = KS == 1 ? 2 : 1;            // waves per workgroup tile row and column
     const int z = blockIdx.y;
-    const int nb = gridDim.x;
+    // contiguous tile ranges per XCD, grouped by 8 tile rows
+    const int nwg = gridDim.x;
     int pid = blockIdx.x;
-    // contiguous tile ranges per XCD, grouped by 2 tile rows: an XCD's 8 tiles of a 1024-row problem
-    // (4 row tiles of 256) are 2 rows x 4 columns, so it fetches half of A instead of all of it
-    if ((nb & 7) == 0) pid = (pid & 7) * (nb >> 3) + (pid >> 3);
-    const int group_rows = 2;
-    const int per_group = group_rows * g.tiles_n;
+    if ((nwg & 7) == 0) pid = (pid & 7) * (nwg >> 3) + (pid >> 3);
+    const int per_group = 8 * g.tiles_n;
     const int grp = pid / per_group;
-    const int first_m = grp * group_rows;
-    const int gsz = min(g.tiles_m - first_m, group_rows);
-    const int tm = first_m + (pid % per_group) % gsz;
+    const int gsz = min(g.tiles_m - 8 * grp, 8);
+    const int tm = 8 * grp + (pid % per_group) % gsz;
     const int tn = (pid % per_group) / gsz;
-    const int m0 = tm * BM;
-    const int n0 = (MODE == GM_LINE) ? tn * (BN / 2) : tn * BN;
 
     const int t = threadIdx.x;
     const int lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform (LDS DMA base in M0)
-    const int wm = wave >> 1, wn = wave & 1;                   // wave rows 0..3, wave columns 0..1
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int m0 = 32 * HB * (tm * WV + (KS == 1 ? wave >> 1 : 0));
+    const int n0 = 32 * CB * (tn * WV + (KS == 1 ? wave & 1 : 0));
 
-    const __amdgpu_buffer_rsrc_t rAh = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(g.Ahi + z * g.sA * 2), (short)0, (int)g.bytesA, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rAl = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(g.Alo + z * g.sA * 2), (short)0, (int)g.bytesA, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rBh = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(g.Bhi + z * g.sB * 2), (short)0, (int)g.bytesB, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rBl = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(g.Blo + z * g.sB * 2), (short)0, (int)g.bytesB, 0x00020000);
+    __amdgpu_buffer_rsrc_t rsA[2], rsB[2];
+    rsA[0] = __builtin_amdgcn_make_buffer_rsrc((void *)(g.Ahi + z * g.sA), (short)0, (int)g.bytesA, 0x00020000);
+    rsA[1] = __builtin_amdgcn_make_buffer_rsrc((void *)(g.Alo + z * g.sA), (short)0, (int)g.bytesA, 0x00020000);
+    rsB[0] = __builtin_amdgcn_make_buffer_rsrc((void *)(g.Bhi + z * g.sB), (short)0, (int)g.bytesB, 0x00020000);
+    rsB[1] = __builtin_amdgcn_make_buffer_rsrc((void *)(g.Blo + z * g.sB), (short)0, (int)g.bytesB, 0x00020000);
+    uint32_t offA[HB], offB[NB];
+#pragma unroll
+    for (int h = 0; h < HB; ++h) offA[h] = (uint32_t)((m0 + 32 * h) * (g.lda * 4)) + lane * 16;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+        offB[n] = (uint32_t)((n0 + n * (MODE == GM_LINE ? g.b2_rows : 32)) * (g.ldb * 4)) + lane * 16;
 
-    // Direct global -> LDS loads: lane l of wave w fills the 16 bytes at (w * 64 + l) * 16 of a
-    // plane, i.e. row w*32 + l/2, stored chunk l&1. Chunks are XOR-swizzled by bit 3 of the row
-    // (stored = actual ^ ((row >> 3) & 1)) so the 16-byte operand reads hit distinct banks. Every
-    // wave loads its 32 rows of both A planes; waves 0-3 load the B hi plane, waves 4-7 the B lo
-    // plane (32 rows each): three loads per wave and stage. Rows of A past M read as zero (buffer
-    // range), so a 256-row tile may overhang a matrix of 128 * odd rows.
-    const int lrow = wave * 32 + (lane >> 1);
-    const int lchunk = (lane & 1) ^ ((lrow >> 3) & 1);
-    const uint32_t offA = (uint32_t)(((int64_t)(m0 + lrow) * g.lda) * 4 + lchunk * 16);
-    const int brow = (wave & 3) * 32 + (lane >> 1);
-    const bool b_lo = wave >= 4;
-    uint32_t offB;
-    {
-        int64_t row = n0 + brow;
-        if (MODE == GM_LINE) {
-            const int grp2 = brow >> 5;
-            row = n0 + (grp2 >> 1) * 32 + (brow & 31) + ((grp2 & 1) ? g.b2_rows : 0);
+    auto load = [&](Chunk<HB, NB> &c, int kt) {
+        const int so = kt * 1024;   // one block of a plane
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+#pragma unroll
+            for (int h = 0; h < HB; ++h) c.a[h][p] = __builtin_amdgcn_raw_buffer_load_b128(rsA[p], (int)offA[h], so, 0);
+#pragma unroll
+            for (int n = 0; n < NB; ++n) c.b[n][p] = __builtin_amdgcn_raw_buffer_load_b128(rsB[p], (int)offB[n], so, 0);
         }
-        offB = (uint32_t)(row * g.ldb * 4 + ((lane & 1) ^ ((brow >> 3) & 1)) * 16);
+    };
+
+    floatx16 acc[HB][NB][2];   // real and imaginary part
+#pragma unroll
+    for (int h = 0; h < HB; ++h)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[h][n][p][r] = 0.f;
+
+    auto mfma = [](u32x4 a, u32x4 b, floatx16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    };
+    auto compute = [&](const Chunk<HB, NB> &c) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            u32x4 b[2][2];   // [hi, lo][for the real, for the imaginary part]
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    b[p][0][w] = c.b[n][p][w] ^ 0x80000000u;
+                    b[p][1][w] = __builtin_amdgcn_alignbit(c.b[n][p][w], c.b[n][p][w], 16);
+                }
+#pragma unroll
+            for (int q = 0; q < 3; ++q)   // lo hi, hi lo, hi hi
+#pragma unroll
+                for (int h = 0; h < HB; ++h)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) acc[h][n][p] = mfma(c.a[h][q == 0 ? 1 : 0], b[q == 1 ? 1 : 0][p], acc[h][n][p]);
+        }
+    };
+
+    const int nk = m0 < g.Mt && n0 < g.Nt ? g.K / PLANE_KB : 0;
+    int kt = KS == 1 ? 0 : wave;
+    Chunk<HB, NB> r0, r1;
+    if (kt < nk) load(r0, kt);
+    for (; kt < nk; kt += 2 * KS) {
+        if (kt + KS < nk) load(r1, kt + KS);
+        compute(r0);
+        if (kt + KS < nk) {
+            if (kt + 2 * KS < nk) load(r0, kt + 2 * KS);
+            compute(r1);
+        }
     }
-    const __amdgpu_buffer_rsrc_t rB = b_lo ? rBl : rBh;
-    const int dstB = (b_lo ? OFF_BL : OFF_BH) + (wave & 3) * 1024;
-    auto issue = [&](unsigned char *buf, int kt) {
-        const int so = kt * BKC * 4;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rAh, (lds_ptr_t)(buf + wave * 1024), 16, (int)offA, so, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rAl, (lds_ptr_t)(buf + OFF_AL + wave * 1024), 16, (int)offA, so, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, (lds_ptr_t)(buf + dstB), 16, (int)offB, so, 0, 0);
-    };
-
-    floatx16 acc[2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    const int j32 = lane & 31;
-    const int half = lane >> 5;
-    const bool odd = (j32 & 1) != 0;
-    // fragment reads (swizzled chunk): A rows wm*64 + bm*32 + j32, B rows wn*64 + bn*16 + j32/2
-    const int a_off = (wm * 64 + j32) * ROWB + ((half ^ ((j32 >> 3) & 1)) * 16);
-    const int b_off = (wn * 64 + (j32 >> 1)) * ROWB + ((half ^ ((j32 >> 4) & 1)) * 16);
-
-    // realified B row pair from 4 complex b: even column -> [Re, -Im] (flip the sign bit of the
-    // high half), odd column -> [Im, Re] (rotate by 16); branch-free: rotr(x, sh) ^ msk
-    const unsigned sh = odd ? 16u : 0u;
-    const unsigned msk = odd ? 0u : 0x80000000u;
-    auto xform = [&](u32x4 v) {
-        u32x4 o;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) o[w] = __builtin_amdgcn_alignbit(v[w], v[w], sh) ^ msk;
-        return o;
-    };
-
-    // LDS addresses (32-bit) of this lane's fragments in each ring buffer
-    auto lds_addr = [](const unsigned char *p) { return (uint32_t)(uintptr_t)(lds_ptr_t)p; };
-    auto compute = [&](const unsigned char *st) {
-        const uint32_t va = lds_addr(st) + a_off, vb = lds_addr(st) + b_off;
-        u32x4 ah0, ah1, al0, al1, bh0, bh1, bh2, bh3, bl0, bl1, bl2, bl3;
-        // all twelve fragment reads of the stage in flight together, waited in the same block
-        // A hi rows +0 / +32 at 0 / 1024, A lo at 8192 / 9216; B hi (16 rows per block) at 16384 + 512 bn,
-        // B lo at 20480 + 512 bn
-        asm volatile(
-            "ds_read_b128 %0, %12\n\t"
-            "ds_read_b128 %1, %12 offset:1024\n\t"
-            "ds_read_b128 %2, %12 offset:8192\n\t"
-            "ds_read_b128 %3, %12 offset:9216\n\t"
-            "ds_read_b128 %4, %13 offset:16384\n\t"
-            "ds_read_b128 %5, %13 offset:16896\n\t"
-            "ds_read_b128 %6, %13 offset:17408\n\t"
-            "ds_read_b128 %7, %13 offset:17920\n\t"
-            "ds_read_b128 %8, %13 offset:20480\n\t"
-            "ds_read_b128 %9, %13 offset:20992\n\t"
-            "ds_read_b128 %10, %13 offset:21504\n\t"
-            "ds_read_b128 %11, %13 offset:22016\n\t"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(ah0), "=&v"(ah1), "=&v"(al0), "=&v"(al1), "=&v"(bh0), "=&v"(bh1), "=&v"(bh2), "=&v"(bh3),
-              "=&v"(bl0), "=&v"(bl1), "=&v"(bl2), "=&v"(bl3)
-            : "v"(va), "v"(vb));
-        const bf16x8 ah[2] = {as_bf16x8(ah0), as_bf16x8(ah1)};
-        const bf16x8 al[2] = {as_bf16x8(al0), as_bf16x8(al1)};
-        const bf16x8 bh[4] = {as_bf16x8(xform(bh0)), as_bf16x8(xform(bh1)), as_bf16x8(xform(bh2)), as_bf16x8(xform(bh3))};
-        const bf16x8 bl[4] = {as_bf16x8(xform(bl0)), as_bf16x8(xform(bl1)), as_bf16x8(xform(bl2)), as_bf16x8(xform(bl3))};
-        // consecutive MFMAs accumulate into different tiles
-#pragma unroll
-        for (int bn = 0; bn < 4; ++bn)
-#pragma unroll
-            for (int bm = 0; bm < 2; ++bm)
-                acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[bm], bh[bn], acc[bm][bn], 0, 0, 0);
-#pragma unroll
-        for (int bn = 0; bn < 4; ++bn)
-#pragma unroll
-            for (int bm = 0; bm < 2; ++bm)
-                acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[bm], bl[bn], acc[bm][bn], 0, 0, 0);
-#pragma unroll
-        for (int bn = 0; bn < 4; ++bn)
-#pragma unroll
-            for (int bm = 0; bm < 2; ++bm)
-                acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[bm], bh[bn], acc[bm][bn], 0, 0, 0);
-    };
-    // one ring step: stage kt (in `cur`) has landed once at most the loads of the two stages
-    // issued after it are outstanding; then the buffer of stage kt-1 (`nxt`) takes stage kt+3
-    auto step = [&](int kt, int nk, const unsigned char *cur, unsigned char *nxt) {
-        const int ahead = min(NSTAGE - 2, nk - 1 - kt);   // stages issued after kt (3 loads each)
-        if (ahead >= 2) wait_vm<6>();
-        else if (ahead == 1) wait_vm<3>();
-        else wait_vm<0>();
-        // Bare barrier: each wave has waited for its own DMA of stage kt above, so after the
-        // barrier the whole stage is in LDS, and every wave has finished reading stage kt-1.
-        // (A fenced barrier would drain all outstanding DMA and serialise the ring.)
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (kt + NSTAGE - 1 < nk) issue(nxt, kt + NSTAGE - 1);
-        compute(cur);
-    };
-
-    const int nk = g.K / BKC;   // a multiple of 16: K is padded to whole 128-tiles
-    issue(sm0, 0);
-    issue(sm1, 1);
-    issue(sm2, 2);
-    for (int kt = 0; kt < nk; kt += NSTAGE) {
-        step(kt + 0, nk, sm0, sm3);
-        step(kt + 1, nk, sm1, sm0);
-        step(kt + 2, nk, sm2, sm1);
-        step(kt + 3, nk, sm3, sm2);
-    }
-    __syncthreads();   // the LDS ring is reused by the epilogue's reduction scratch only after all reads
 
     EpiArgs ea;
     ea.C = g.C + z * g.sC;
-    ea.C2 = (MODE == GM_LINE) ? g.C2 + z * g.sC : nullptr;
+    ea.C2 = MODE == GM_LINE ? g.C2 + z * g.sC : nullptr;
     ea.ldc = g.ldc;
-    ea.E = (MODE == GM_STORE) ? nullptr : g.E + z * g.sE;
+    ea.E = MODE == GM_STORE ? nullptr : g.E + z * g.sE;
     ea.lde = g.lde;
     ea.Me = g.Me;
     ea.Ne = g.Ne;
     ea.partials = g.partials ? g.partials + z * g.sP : nullptr;
-    ea.Mrows = g.M;
-    ea.slot_step = g.tiles_n;
-    // partial slots in the numbering of 128-row tiles (the finalisation sums M/128 x tiles_n slots)
-    gemm_epilogue<MODE, 4>(acc, ea, m0, n0, 2 * tm * g.tiles_n + tn);
+    ea.nblk = g.N >> 5;
+    ea.scat_kp = 0;
+    // four registers of a lane are 16 bytes of C^T's split planes, at this lane's place in a block
+    uint32_t *const Thi = MODE == GM_RESID && g.Thi ? g.Thi + z * g.sT : nullptr;
+    uint32_t *const Tlo = Thi ? g.Tlo + z * g.sT : nullptr;
+    auto put_t = [&](int h, int cb, const float2 (&v)[16 / KS]) {
+        if (!Thi) return;
+        const int64_t w0 = plane_word(n0 + 32 * cb, m0 + 32 * h, g.ldt) + (KS > 1 ? wave * 256 : 0) + lane * 4;
+#pragma unroll
+        for (int q = 0; q < 4 / KS; ++q) {
+            uint4 hi, lo;
+            split_c(v[4 * q], hi.x, lo.x);
+            split_c(v[4 * q + 1], hi.y, lo.y);
+            split_c(v[4 * q + 2], hi.z, lo.z);
+            split_c(v[4 * q + 3], hi.w, lo.w);
+            *reinterpret_cast<uint4 *>(Thi + w0 + 256 * q) = hi;
+            *reinterpret_cast<uint4 *>(Tlo + w0 + 256 * q) = lo;
+        }
+    };
+    block_epilogue<MODE, false, KS, HB, CB>(
+        ea, [&](int h, int n, int r) { return make_float2(acc[h][n][0][r], acc[h][n][1][r]); }, m0, n0, put_t);
+}
+
+template <int MODE, int HB, int CB, int KS>
+hipError_t go(GemmArgsB a, int batch, hipStream_t s) {
+    constexpr int WV = KS == 1 ? 2 : 1;
+    if (a.M % (32 * HB * WV) || a.N % (32 * CB * WV)) return hipErrorInvalidValue;
+    a.tiles_m = a.M / (32 * HB * WV);
+    a.tiles_n = a.N / (32 * CB * WV);
+    hipLaunchKernelGGL((cgemm_bf16x3_kernel<MODE, HB, CB, KS>), dim3(a.tiles_m * a.tiles_n, batch), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+// A wave takes two by two blocks where every CU gets a workgroup of such tiles: 4 problems of 448^2 (196 tiles)
+// 24, 17, 28 us against 20, 17, 29 with one block per wave, one of 1024^2 (256) 35, 29, 51 against 34, 31, 54,
+// of 2304 x 576 (324) 85, 71, 134 against 87, 77, 147, of 2304^2 (1296) 262, 246, 469 against 298, 292, 506.
+constexpr int64_t BIG_TILES = 256;
+
+template <int MODE>
+hipError_t pick(const GemmArgsB &a, int batch, hipStream_t s, bool split) {
+    constexpr int CB = MODE == GM_LINE ? 1 : 2;
+    if (!split) return go<MODE, 2, CB, 1>(a, batch, s);
+    const int64_t tiles = (int64_t)((a.Mt + 63) / 64) * ((a.Nt + 63) / 64) * batch;
+    return tiles >= BIG_TILES ? go<MODE, 2, CB, 4>(a, batch, s) : go<MODE, 1, 1, 4>(a, batch, s);
 }
 
 }  // namespace
 
-hipError_t launch_cgemm_bf16(int mode, const GemmArgsB &a0, int batch, hipStream_t s) {
+hipError_t launch_cgemm_bf16(int mode, const GemmArgsB &a0, int batch, hipStream_t s, bool split) {
     GemmArgsB a = a0;
-    a.tiles_m = (a.M + BM - 1) / BM;
-    a.tiles_n = (mode == GM_LINE) ? a.N / (BN / 2) : a.N / BN;
     if (a.M <= 0 || a.N <= 0 || batch <= 0) return hipSuccess;
-    if (a.M % GEMM_BM || a.N % BN || a.K % (BKC * NSTAGE) || a.K <= 0) return hipErrorInvalidValue;
+    if (a.M % GEMM_PAD || a.N % GEMM_PAD || a.K % 32 || a.K <= 0 || a.lda % PLANE_KB ||
+        a.ldb % PLANE_KB || (mode == GM_LINE && a.b2_rows % 32)) return hipErrorInvalidValue;   // padded operands only
+    a.Mt = a.Mt > 0 ? std::min(a.Mt, a.M) : a.M;
+    a.Nt = a.Nt > 0 ? std::min(a.Nt, a.N) : a.N;
     const int64_t bytesA = (int64_t)a.M * a.lda * 4;
     const int64_t rowsB = (mode == GM_LINE) ? a.b2_rows + a.N : a.N;
     const int64_t bytesB = rowsB * a.ldb * 4;
     if (bytesA >= (int64_t)1 << 32 || bytesB >= (int64_t)1 << 32) return hipErrorInvalidValue;
     a.bytesA = (uint32_t)bytesA;
     a.bytesB = (uint32_t)bytesB;
-    dim3 grid(a.tiles_m * a.tiles_n, batch);
     switch (mode) {
-        case GM_STORE: hipLaunchKernelGGL(cgemm_bf16x3_kernel<GM_STORE>, grid, dim3(NTHREADS), 0, s, a); break;
-        case GM_RESID: hipLaunchKernelGGL(cgemm_bf16x3_kernel<GM_RESID>, grid, dim3(NTHREADS), 0, s, a); break;
-        case GM_LINE:  hipLaunchKernelGGL(cgemm_bf16x3_kernel<GM_LINE>, grid, dim3(NTHREADS), 0, s, a); break;
+        case GM_STORE: return pick<GM_STORE>(a, batch, s, split);
+        case GM_RESID: return pick<GM_RESID>(a, batch, s, split);
+        case GM_LINE: return pick<GM_LINE>(a, batch, s, split);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace tlr

@@ -98,9 +98,8 @@ struct GemmArgs {
 // transposed (K x M source, row pitch lda) and B conjugated; the adjoint product, whose A is given transposed
 // and conjugated (D itself for D^H)
 enum GemmRole : int32_t { GR_DENSE = 0, GR_TILE = 1, GR_TILE_TA_CB = 2, GR_ADJOINT = 3 };
-constexpr int GEMM_BM = 128;
-constexpr int GEMM_BN = 128;   // complex columns per workgroup (64 of a + 64 of b in GM_LINE)
-constexpr int GEMM_BK = 16;    // complex k per stage
+constexpr int GEMM_BN = 128;   // tile forms: tile sizes and gradient widths are multiples of this or of half of it
+constexpr int GEMM_BK = 16;    // complex k: a contraction length is a multiple of this
 constexpr int GEMM_PAD = 128;  // internal matrices are padded to multiples of this
 
 // BF16 hi+lo split: hi = bf16(x) (round to nearest even), lo = bf16(x - hi)
@@ -117,21 +116,33 @@ __device__ __forceinline__ void split_c(float2 v, uint32_t &hi, uint32_t &lo) {
     lo = lr | (li << 16);
 }
 
-// BF16 hi+lo split operands: planes of interleaved complex BF16 (one uint32 per complex).
+// Split planes hold one uint32 per complex (interleaved BF16), in the order in which the matrix instructions take
+// their operands: blocks of 32 rows x 8 k, in each the 64 lanes' 16 bytes, lane 32 h + j holding k = 4 h .. 4 h + 3
+// of row j. A wave's operand load is then 1 KB in a row, where rows of a plain row-major plane give 32 bytes of 32
+// cache lines, four times over.
+constexpr int PLANE_KB = 8;   // k per block
+__host__ __device__ __forceinline__ int64_t plane_word(int64_t row, int64_t k, int64_t ld) {
+    return ((row >> 5) * (ld >> 3) + (k >> 3)) * 256 + ((k & 4) << 5) + ((row & 31) << 2) + (k & 3);
+}
+
+// BF16 hi+lo split operands, as split planes
 struct GemmArgsB {
-    const uint16_t *Ahi, *Alo;  int64_t lda;   // M x K complex (row-major planes)
-    const uint16_t *Bhi, *Blo;  int64_t ldb;   // B TRANSPOSED: N x K complex planes
-    int64_t b2_rows;                           // GM_LINE: B2's rows start this many rows after B's
+    const uint32_t *Ahi, *Alo;  int64_t lda;   // M x K complex
+    const uint32_t *Bhi, *Blo;  int64_t ldb;   // B TRANSPOSED: N x K complex
+    int64_t b2_rows;                           // GM_LINE: B2's rows start this many rows after B's (a multiple of 32)
+    uint32_t *Thi, *Tlo;  int64_t ldt, sT;     // GM_RESID: split planes of C^T (N x M), or null
     float2 *C;        int64_t ldc;
     float2 *C2;
     const float2 *E;  int64_t lde;
     double *partials;
     int32_t M, N, K, Me, Ne;
+    int32_t Mt, Nt;                            // true shape of C (blocks outside are zero; 0: M, N)
     int32_t tiles_m, tiles_n;
     int64_t sA, sB, sC, sE, sP;                // batch strides (complex elements / doubles)
     uint32_t bytesA, bytesB;                   // set by the launcher
 };
-hipError_t launch_cgemm_bf16(int mode, const GemmArgsB &a, int batch, hipStream_t s);
+// split: as for launch_cgemm; its results do not depend on the tile that the launcher picks
+hipError_t launch_cgemm_bf16(int mode, const GemmArgsB &a, int batch, hipStream_t s, bool split);
 
 // ---- vector / scalar kernels ----
 constexpr int RED_THREADS = 256;
@@ -171,13 +182,13 @@ hipError_t launch_grad(const TileDesc *tiles, const GradItem *items, int nitems,
 
 hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, int64_t ldk,
                           float2 *DHs, int64_t lds, hipStream_t s);
-// split staging: Dhi/Dlo (lds x ldk planes) and DHhi/DHlo (ldk x lds planes, conjugate transpose)
+// split staging: Dhi/Dlo (lds x ldk split planes) and DHhi/DHlo (ldk x lds, conjugate transpose)
 hipError_t launch_stage_d_split(const float2 *D, int64_t ns, int64_t nr, uint32_t *Dh, uint32_t *Dl, int64_t ldk,
                                 uint32_t *DHh, uint32_t *DHl, int64_t lds, hipStream_t s);
-// rT = r^T split into planes: r is rows x cols (ld ldr), rT planes are cols x rows (ld ldt)
+// rT = r^T as split planes: r is rows x cols (ld ldr, multiples of 32), rT planes are cols x rows (ld ldt)
 hipError_t launch_split_transpose(const float2 *r, int64_t ldr, int64_t rows, int64_t cols, uint32_t *th,
                                   uint32_t *tl, int64_t ldt, int batch, int64_t s_r, int64_t s_t, hipStream_t s);
-// zero the padding of nplanes ld x ld uint32 planes (true size n x n), per problem of a batch
+// zero the padding of nplanes ld x ld split planes (true size n x n), per problem of a batch
 hipError_t launch_zero_pad(uint32_t *base, int64_t ld, int64_t n, int nplanes, int64_t plane_stride, int batch,
                            int64_t batch_stride, hipStream_t s);
 hipError_t launch_copy2d(const float2 *src, int64_t lds, float2 *dst, int64_t ldd,

@@ -1,5 +1,5 @@
 // Shared pieces of the complex GEMM kernels (FP32 and BF16 hi+lo split):
-// the accumulator layout of the 32 x 32 MFMA blocks and the epilogues.
+// the accumulator layout of the 32 x 32 MFMA blocks and the epilogue.
 #pragma once
 #include "common.hpp"
 
@@ -20,134 +20,136 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// the five products of the line-search sums: Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2
+__device__ __forceinline__ void line_terms(float (&blk)[5], float2 r, float2 a, float2 b) {
+    blk[0] = fmaf(r.x, a.x, fmaf(r.y, a.y, blk[0]));
+    blk[1] = fmaf(a.x, a.x, fmaf(a.y, a.y, blk[1]));
+    blk[2] = fmaf(r.x, b.x, fmaf(r.y, b.y, blk[2]));
+    blk[3] = fmaf(a.x, b.x, fmaf(a.y, b.y, blk[3]));
+    blk[4] = fmaf(b.x, b.x, fmaf(b.y, b.y, blk[4]));
+}
+
+// One batch entry's epilogue operands.
 struct EpiArgs {
-    float2 *C;         // output (GM_LINE: a)
-    float2 *C2;        // GM_LINE: b
+    float2 *C, *C2;    // output; GM_LINE: a and b
     int64_t ldc;
     const float2 *E;   // GM_RESID: U (true shape Me x Ne); GM_LINE: r
     int64_t lde;
     int32_t Me, Ne;
-    double *partials;  // this problem's partial sums
-    int32_t Mrows;     // rows of C (a 256-row tile may overhang it by 128; WROWS = 4 only)
-    int32_t slot_step; // WROWS = 4: partial slot of the second 128-row half = first + slot_step
+    double *partials;
+    int32_t nblk;      // 32-column blocks of C per row of blocks (partial slots are numbered by block)
+    int32_t scat_kp, scat_w, scat_lim;   // GM_STORE with STAGE: column scatter of the tile stages (see GemmArgs)
+    int64_t scat_js;
 };
 
-// Epilogue of a workgroup tile of WROWS x 64 rows and 128 complex columns held as 2 WROWS waves
-// (wave w: rows 64 (w / 2), columns 64 (w % 2)) of 2 x 4 accumulator blocks. GM_STORE: C = acc.
-// GM_RESID: C = acc - E, partial sum |C|^2. GM_LINE: blocks bn = 0,1 are a and bn = 2,3 are b at the
-// same columns; partial sums Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2. Partial sums of 16 products are
-// formed in FP32 registers and folded into FP64; each 128-row half's four waves are reduced in a
-// fixed order into one partial slot (WROWS = 2: slot pid; WROWS = 4: slots pid and pid + slot_step,
-// the second only when that half lies inside C).
-template <int MODE, int WROWS = 2>
-__device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[2][4], const EpiArgs &ea, int m0, int n0, int pid) {
-    constexpr int NWAVE = 2 * WROWS;
-    __shared__ double red[NWAVE][5];
-    const int t = threadIdx.x;
-    const int lane = t & 63;
-    const int wave = t >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int j32 = lane & 31;
-    // WROWS = 4: the waves of a 128-row half past the end of C write nothing
-    if (WROWS == 4 && m0 + wm * 64 >= ea.Mrows) {
-        if (MODE != GM_STORE) {
-            if (lane == 0)
+// Epilogue of a wave's HB x CB blocks of 32 x 32 complex entries from row m0 and column n0 on, each lane holding
+// whole entries of column lane % 32: cval(h, n, r) is accumulator row r of row block h and block n (GM_LINE: n = 0
+// is a and n = 1 is b at the same columns). GM_STORE: C = AB. GM_RESID: C = AB - E and the sum of |C|^2. GM_LINE:
+// the five line sums. KS > 1: the workgroup's KS waves hold shares of the same blocks; they are added in LDS in a
+// fixed order, each wave finishing 16 / KS rows of every lane. A block's sums are its lanes' FP32 sums over the
+// rows, added in FP64, one partial slot per 32 x 32 block, numbered by block row and column whatever the tile.
+// GM_RESID: also(h, cb, v) gets the finished rows of a lane (KS > 1: rows wave * 16 / KS and on of its registers).
+struct Nothing {
+    template <class V>
+    __device__ __forceinline__ void operator()(int, int, const V &) const {}
+};
+template <int MODE, bool STAGE, int KS, int HB, int CB, class F, class G = Nothing>
+__device__ __forceinline__ void block_epilogue(const EpiArgs &ea, F &&cval, int m0, int n0, G &&also = G()) {
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int col = n0 + (lane & 31);
+    constexpr int NR = 16 / KS;                   // rows of a block that this wave finishes
+    constexpr int NS = MODE == GM_RESID ? 1 : 5;
+    constexpr int NV = MODE == GM_LINE ? 2 : 1;   // a and b, or one block of C
+    auto row_of = [&](int h, int r) { return m0 + 32 * h + acc_row(KS == 1 ? r : wave * NR + r, lane); };
+    __shared__ float2 part[KS][KS == 1 ? 1 : 16][KS == 1 ? 1 : 64];   // one block at a time: less LDS, more waves
+    __shared__ double red[KS][NS];
 #pragma unroll
-                for (int s = 0; s < 5; ++s) red[wave][s] = 0.0;
-            __syncthreads();
-        }
-        return;
-    }
-    // ---- epilogues ----
-    float *C = reinterpret_cast<float *>(ea.C);
-    const int64_t ldc2 = 2 * (int64_t)ea.ldc;
-    if (MODE == GM_STORE) {
+    for (int h = 0; h < HB; ++h)
 #pragma unroll
-        for (int bm = 0; bm < 2; ++bm)
+        for (int cb = 0; cb < CB; ++cb) {
+            const int cc = col + 32 * cb;
+            // the entries of E: their loads are in flight together, and during the sums over the waves (an
+            // entry outside E reads E[0] and is dropped)
+            float2 e[NR];
+            if constexpr (MODE != GM_STORE) {
 #pragma unroll
-            for (int bn = 0; bn < 4; ++bn) {
-                const int64_t fcol = 2 * (int64_t)(n0 + wn * 64 + bn * 16) + j32;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = m0 + wm * 64 + bm * 32 + acc_row(r, lane);
-                    C[row * ldc2 + fcol] = acc[bm][bn][r];
+                for (int r = 0; r < NR; ++r) {
+                    const int row = row_of(h, r);
+                    const bool in = MODE == GM_LINE || (row < ea.Me && cc < ea.Ne);
+                    e[r] = ea.E[in ? (int64_t)row * ea.lde + cc : 0];
+                    if (!in) e[r] = make_float2(0.f, 0.f);
                 }
-                __builtin_amdgcn_sched_barrier(0);
             }
-        return;
-    }
-
-    const float *E = reinterpret_cast<const float *>(ea.E);
-    const int64_t lde2 = 2 * (int64_t)ea.lde;
-    double sums[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (MODE == GM_RESID) {
+            float2 v[NV][NR];
 #pragma unroll
-        for (int bm = 0; bm < 2; ++bm)
+            for (int n = 0; n < NV; ++n) {
+                if constexpr (KS == 1) {
 #pragma unroll
-            for (int bn = 0; bn < 4; ++bn) {
-                const int col = n0 + wn * 64 + bn * 16 + (j32 >> 1);
-                const int64_t fcol = 2 * (int64_t)(n0 + wn * 64 + bn * 16) + j32;
-                float blk = 0.f;
+                    for (int r = 0; r < NR; ++r) v[n][r] = cval(h, MODE == GM_LINE ? n : cb, r);
+                } else {
+                    if (h + cb + n) __syncthreads();   // the block before is finished
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = m0 + wm * 64 + bm * 32 + acc_row(r, lane);
-                    const bool in = row < ea.Me && col < ea.Ne;   // U has the true (unpadded) shape
-                    const float v = acc[bm][bn][r] - (in ? E[row * lde2 + fcol] : 0.f);
-                    C[row * ldc2 + fcol] = v;
-                    blk = fmaf(v, v, blk);
+                    for (int r = 0; r < 16; ++r) part[wave][r][lane] = cval(h, MODE == GM_LINE ? n : cb, r);
+                    __syncthreads();
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) {
+                        float2 s = part[0][wave * NR + r][lane];
+#pragma unroll
+                        for (int w = 1; w < KS; ++w) {
+                            const float2 x = part[w][wave * NR + r][lane];
+                            s.x += x.x;
+                            s.y += x.y;
+                        }
+                        v[n][r] = s;
+                    }
                 }
-                sums[0] += (double)blk;
-                // one accumulator block at a time: keeps the epilogue's loads from being
-                // hoisted together (register pressure)
-                __builtin_amdgcn_sched_barrier(0);
             }
-    } else {  // GM_LINE
-        float *C2 = reinterpret_cast<float *>(ea.C2);
+            float blk[NS];
 #pragma unroll
-        for (int bm = 0; bm < 2; ++bm)
-#pragma unroll
-            for (int bn = 0; bn < 2; ++bn) {
-                const int64_t fcol = 2 * (int64_t)(n0 + wn * 32 + bn * 16) + j32;
-                // 16 products per sum in FP32 registers, then folded into the FP64 sums
-                float blk[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = m0 + wm * 64 + bm * 32 + acc_row(r, lane);
-                    const float av = acc[bm][bn][r];
-                    const float bv = acc[bm][bn + 2][r];
-                    const float rv = E[row * lde2 + fcol];
-                    C[row * ldc2 + fcol] = av;
-                    C2[row * ldc2 + fcol] = bv;
-                    blk[0] = fmaf(rv, av, blk[0]);
-                    blk[1] = fmaf(av, av, blk[1]);
-                    blk[2] = fmaf(rv, bv, blk[2]);
-                    blk[3] = fmaf(av, bv, blk[3]);
-                    blk[4] = fmaf(bv, bv, blk[4]);
+            for (int q = 0; q < NS; ++q) blk[q] = 0.f;
+            if constexpr (MODE == GM_STORE) {
+                int64_t ccol = cc;
+                if (STAGE && ea.scat_kp > 0) {
+                    if (cc >= ea.scat_lim) continue;
+                    ccol += (int64_t)((cc % ea.scat_w) / ea.scat_kp) * ea.scat_js;
                 }
 #pragma unroll
-                for (int q = 0; q < 5; ++q) sums[q] += (double)blk[q];
-                __builtin_amdgcn_sched_barrier(0);
-            }
-    }
-    constexpr int NS = (MODE == GM_RESID) ? 1 : 5;
+                for (int r = 0; r < NR; ++r) ea.C[(int64_t)row_of(h, r) * ea.ldc + ccol] = v[0][r];
+            } else if constexpr (MODE == GM_RESID) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const double v = wave_sum(sums[s]);
-        if (lane == 0) red[wave][s] = v;
-    }
-    __syncthreads();
-    if (WROWS == 2) {
-        if (t < NS) {
-            const double v = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
-            ea.partials[(int64_t)pid * NS + t] = v;
+                for (int r = 0; r < NR; ++r) {
+                    const float2 d = make_float2(v[0][r].x - e[r].x, v[0][r].y - e[r].y);
+                    ea.C[(int64_t)row_of(h, r) * ea.ldc + cc] = d;
+                    blk[0] = fmaf(d.x, d.x, fmaf(d.y, d.y, blk[0]));
+                    v[0][r] = d;
+                }
+                also(h, cb, v[0]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    ea.C[(int64_t)row_of(h, r) * ea.ldc + cc] = v[0][r];
+                    ea.C2[(int64_t)row_of(h, r) * ea.ldc + cc] = v[NV - 1][r];
+                    line_terms(blk, e[r], v[0][r], v[NV - 1][r]);
+                }
+            }
+            if constexpr (MODE != GM_STORE) {
+                const int64_t slot = (int64_t)((m0 >> 5) + h) * ea.nblk + (cc >> 5);
+#pragma unroll
+                for (int q = 0; q < NS; ++q) {
+                    const double s = wave_sum((double)blk[q]);
+                    if (lane == 0) {
+                        if constexpr (KS == 1) ea.partials[slot * NS + q] = s;
+                        else red[wave][q] = s;
+                    }
+                }
+                if constexpr (KS > 1) {
+                    static_assert(KS == 4, "the fixed order of the waves' sums");
+                    __syncthreads();
+                    if (t < NS) ea.partials[slot * NS + t] = (red[0][t] + red[1][t]) + (red[KS - 2][t] + red[KS - 1][t]);
+                }
+            }
         }
-    } else if (t < 2 * NS) {
-        const int h = t / NS, q = t % NS;
-        if (m0 + 128 * h < ea.Mrows) {
-            const double v = ((red[4 * h][q] + red[4 * h + 1][q]) + red[4 * h + 2][q]) + red[4 * h + 3][q];
-            ea.partials[(int64_t)(pid + h * ea.slot_step) * NS + q] = v;
-        }
-    }
 }
 
 }  // namespace tlr

@@ -31,16 +31,22 @@ __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(
 
 // Output: complex64 (OUTB = false) or split BF16 planes (OUTB = true, see launch_assemble).
 template <bool OUTB>
-__device__ __forceinline__ void put(float2 *X, int64_t o, int64_t low, float2 v) {
+__device__ __forceinline__ void put(float2 *X, int64_t row, int64_t col, int64_t ldx, int64_t low, float2 v) {
     if (OUTB) {
         uint32_t h, l;
         split_c(v, h, l);
-        uint32_t *w = reinterpret_cast<uint32_t *>(X);
-        w[o] = h;
-        w[o + low] = l;
+        uint32_t *w = reinterpret_cast<uint32_t *>(X) + plane_word(row, col, ldx);
+        w[0] = h;
+        w[low] = l;
     } else {
-        X[o] = v;
+        X[row * ldx + col] = v;
     }
+}
+// entry e of a 64 x 64 block in the order of the output: along its rows, or four entries of each row in turn
+template <bool OUTB>
+__device__ __forceinline__ void out_entry(int e, int &row, int &col) {
+    row = OUTB ? (e >> 2) & 63 : e >> 6;
+    col = OUTB ? ((e >> 8) << 2) + (e & 3) : e & 63;
 }
 
 constexpr int AB = ASM_B;            // block edge (rows and columns)
@@ -109,13 +115,14 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
         }
         __syncthreads();
         for (int e = t; e < AB * AB; e += 256) {
-            const int rr = e >> 6, cc = e & 63;
+            int rr, cc;
+            out_entry<OUTB>(e, rr, cc);
             if (rr < nrow && cc < ncol) {
                 const float2 zd = Z[(int64_t)(r0 + rr) * d + c0 + cc];
                 const float2 zt = sT[cc * ST_P + rr];
-                const int64_t o = (td.row0 + r0 + rr) * ldx + td.col0 + c0 + cc;
-                put<OUTB>(X, o, low, make_float2(0.5f * (zd.x + zt.x), 0.5f * (zd.y + zt.y)));
-                if (DIR) put<OUTB>(X2, o, low, make_float2(0.f, 0.f));
+                const int64_t row = td.row0 + r0 + rr, col = td.col0 + c0 + cc;
+                put<OUTB>(X, row, col, ldx, low, make_float2(0.5f * (zd.x + zt.x), 0.5f * (zd.y + zt.y)));
+                if (DIR) put<OUTB>(X2, row, col, ldx, low, make_float2(0.f, 0.f));
             }
         }
         return;
@@ -215,14 +222,16 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
         __syncthreads();
         float2 *dst = f ? X2 : X;
         for (int e = t; e < AB * AB; e += 256) {
-            const int rr = e >> 6, cc = e & 63;
+            int rr, cc;
+            out_entry<OUTB>(e, rr, cc);
             if (rr < nrow && cc < ncol && (!qq || r0 + rr >= c0 + cc))
-                put<OUTB>(dst, (td.row0 + r0 + rr) * ldx + td.col0 + c0 + cc, low, sT[rr * ST_P + cc]);
+                put<OUTB>(dst, td.row0 + r0 + rr, td.col0 + c0 + cc, ldx, low, sT[rr * ST_P + cc]);
         }
         for (int e = t; e < AB * AB; e += 256) {
-            const int cc = e >> 6, rr = e & 63;
+            int rr, cc;
+            out_entry<OUTB>(e, cc, rr);
             if (cc < ncol && rr < nrow && (!qq || r0 + rr > c0 + cc))
-                put<OUTB>(dst, (td.col0 + c0 + cc) * ldx + td.row0 + r0 + rr, low, sT[rr * ST_P + cc]);
+                put<OUTB>(dst, td.col0 + c0 + cc, td.row0 + r0 + rr, ldx, low, sT[rr * ST_P + cc]);
         }
     }
 }

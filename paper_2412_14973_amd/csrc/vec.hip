@@ -38,6 +38,20 @@ __global__ __launch_bounds__(256) void stage_d_kernel(const float2 *__restrict__
     }
 }
 
+// a 32 x 32 block of split planes: 4 KB in a row, 16 bytes per thread
+template <class F>
+__device__ __forceinline__ void put_plane_block(uint32_t *hi, uint32_t *lo, int64_t base, F &&at) {
+    const int t = threadIdx.x;
+    const int row = t & 31, k = PLANE_KB * (t >> 6) + ((t & 32) >> 3);
+    uint4 h, l;
+    split_c(at(row, k), h.x, l.x);
+    split_c(at(row, k + 1), h.y, l.y);
+    split_c(at(row, k + 2), h.z, l.z);
+    split_c(at(row, k + 3), h.w, l.w);
+    reinterpret_cast<uint4 *>(hi + base)[t] = h;
+    reinterpret_cast<uint4 *>(lo + base)[t] = l;
+}
+
 __global__ __launch_bounds__(256) void stage_d_split_kernel(const float2 *__restrict__ D, int64_t ns, int64_t nr,
                                                             uint32_t *__restrict__ Dh, uint32_t *__restrict__ Dl,
                                                             int64_t ldk, uint32_t *__restrict__ DHh,
@@ -49,32 +63,18 @@ __global__ __launch_bounds__(256) void stage_d_split_kernel(const float2 *__rest
         const int64_t s = s0 + r, c = c0 + tx;
         float2 v = make_float2(0.f, 0.f);
         if (s < ns && c < nr) v = D[s * nr + c];
-        if (s < lds && c < ldk) {
-            uint32_t h, l;
-            split_c(v, h, l);
-            Dh[s * ldk + c] = h;
-            Dl[s * ldk + c] = l;
-        }
         tile[r][tx] = v;
     }
-    if (!DHh) return;
     __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int64_t c = c0 + r, s = s0 + tx;
-        if (s < lds && c < ldk) {
-            const float2 v = tile[tx][r];
-            uint32_t h, l;
-            split_c(make_float2(v.x, -v.y), h, l);
-            DHh[c * lds + s] = h;
-            DHl[c * lds + s] = l;
-        }
-    }
+    put_plane_block(Dh, Dl, plane_word(s0, c0, ldk), [&](int row, int k) { return tile[row][k]; });
+    if (DHh)
+        put_plane_block(DHh, DHl, plane_word(c0, s0, lds),
+                        [&](int row, int k) { return make_float2(tile[k][row].x, -tile[k][row].y); });
 }
 
-__global__ __launch_bounds__(256) void split_transpose_kernel(const float2 *__restrict__ r, int64_t ldr, int64_t rows,
-                                                              int64_t cols, uint32_t *__restrict__ th,
-                                                              uint32_t *__restrict__ tl, int64_t ldt, int64_t s_r,
-                                                              int64_t s_t) {
+__global__ __launch_bounds__(256) void split_transpose_kernel(const float2 *__restrict__ r, int64_t ldr,
+                                                              uint32_t *__restrict__ th, uint32_t *__restrict__ tl,
+                                                              int64_t ldt, int64_t s_r, int64_t s_t) {
     __shared__ float2 tile[32][33];
     const int z = blockIdx.z;
     r += z * s_r;
@@ -82,29 +82,18 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(const float2 *__re
     tl += z * s_t;
     const int64_t r0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int q = ty; q < 32; q += 8) {
-        const int64_t i = r0 + q, j = c0 + tx;
-        tile[q][tx] = (i < rows && j < cols) ? r[i * ldr + j] : make_float2(0.f, 0.f);
-    }
+    for (int q = ty; q < 32; q += 8) tile[q][tx] = r[(r0 + q) * ldr + c0 + tx];
     __syncthreads();
-    for (int q = ty; q < 32; q += 8) {
-        const int64_t j = c0 + q, i = r0 + tx;
-        if (i < rows && j < cols) {
-            uint32_t h, l;
-            split_c(tile[tx][q], h, l);
-            th[j * ldt + i] = h;
-            tl[j * ldt + i] = l;
-        }
-    }
+    put_plane_block(th, tl, plane_word(c0, r0, ldt), [&](int row, int k) { return tile[k][row]; });
 }
 
-// zero the padding (rows >= n, and columns >= n of rows < n) of ld x ld word planes
+// zero the padding (rows >= n, and columns >= n of rows < n) of ld x ld split planes
 __global__ void zero_pad_kernel(uint32_t *__restrict__ base, int64_t ld, int64_t n, int64_t plane_stride,
                                 int64_t batch_stride) {
     const int64_t row = blockIdx.x;
-    uint32_t *p = base + (int64_t)blockIdx.z * batch_stride + (int64_t)blockIdx.y * plane_stride + row * ld;
+    uint32_t *p = base + (int64_t)blockIdx.z * batch_stride + (int64_t)blockIdx.y * plane_stride;
     const int64_t c0 = row < n ? n : 0;
-    for (int64_t c = c0 + threadIdx.x; c < ld; c += blockDim.x) p[c] = 0u;
+    for (int64_t c = c0 + threadIdx.x; c < ld; c += blockDim.x) p[plane_word(row, c, ld)] = 0u;
 }
 
 __global__ void copy2d_kernel(const float2 *__restrict__ src, int64_t lds, float2 *__restrict__ dst,
@@ -604,7 +593,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs fa) {
     __shared__ double sG[FIN_NB * FIN_NB + FIN_NB];
     __shared__ double few[4][FIN_FEW];
     const int prob = blockIdx.x;
-    const int count = fa.counts ? fa.counts[prob] : prob < fa.nfirst ? fa.ucount : fa.ucount2;
+    const int count = fa.counts ? fa.counts[prob] : fa.ucount;
     const double *base = fa.partials + (int64_t)prob * fa.pstride * fa.nsum;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (fa.nsum <= FIN_FEW) {
@@ -662,7 +651,8 @@ hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, i
 
 hipError_t launch_stage_d_split(const float2 *D, int64_t ns, int64_t nr, uint32_t *Dh, uint32_t *Dl, int64_t ldk,
                                 uint32_t *DHh, uint32_t *DHl, int64_t lds, hipStream_t s) {
-    dim3 grid((unsigned)((ldk + 31) / 32), (unsigned)((lds + 31) / 32));
+    if (ldk % 32 || lds % 32) return hipErrorInvalidValue;   // whole blocks
+    dim3 grid((unsigned)(ldk / 32), (unsigned)(lds / 32));
     hipLaunchKernelGGL(stage_d_split_kernel, grid, dim3(256), 0, s, D, ns, nr, Dh, Dl, ldk, DHh, DHl, lds);
     return hipGetLastError();
 }
@@ -670,8 +660,9 @@ hipError_t launch_stage_d_split(const float2 *D, int64_t ns, int64_t nr, uint32_
 hipError_t launch_split_transpose(const float2 *r, int64_t ldr, int64_t rows, int64_t cols, uint32_t *th,
                                   uint32_t *tl, int64_t ldt, int batch, int64_t s_r, int64_t s_t, hipStream_t s) {
     if (rows <= 0 || cols <= 0 || batch <= 0) return hipSuccess;
-    dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32), (unsigned)batch);
-    hipLaunchKernelGGL(split_transpose_kernel, grid, dim3(256), 0, s, r, ldr, rows, cols, th, tl, ldt, s_r, s_t);
+    if (rows % 32 || cols % 32 || ldt % 32) return hipErrorInvalidValue;   // whole blocks
+    dim3 grid((unsigned)(cols / 32), (unsigned)(rows / 32), (unsigned)batch);
+    hipLaunchKernelGGL(split_transpose_kernel, grid, dim3(256), 0, s, r, ldr, th, tl, ldt, s_r, s_t);
     return hipGetLastError();
 }
 

@@ -25,7 +25,6 @@ struct FinArgs {
     int64_t pstride;       // entries per problem
     const int32_t *counts; // entries used per problem (NULL -> ucount)
     int32_t ucount;
-    int32_t nfirst, ucount2;   // without counts: ucount for the problems before nfirst, ucount2 for the others
     int32_t m1;            // ring slots (lbfgs_m + 1)
     int32_t t;             // f-history index (FIN_F)
     SolveScalars *sc;

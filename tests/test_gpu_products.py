@@ -48,3 +48,79 @@ def test_products_entry_by_entry(nr, ns, form):
     bound = c * (2 * ns + 4) * U32 * (D2.abs().T.contiguous() @ U2.abs())
     err = (W.to(torch.complex128) - ref).abs()
     assert bool((err <= bound).all()), float((err / bound).max())
+
+
+# BF16 hi+lo split: hi is within 2^-9 |x| of x and lo within 2^-18 |x| of the rest, so a product misses at most
+# 3 * 2^-18 |a||b| (lo lo dropped, two roundings of lo), rounded up to 2^-16; the 6 K products of an entry are added
+# in FP32, at most one unit in the last place (2 u) each. sqrt(2) from the parts to the complex entry.
+def _bf16_bound(K):
+    return 2 ** 0.5 * (2.0 ** -16 + (6 * K + 8) * 2 * U32)
+
+
+@pytest.mark.parametrize("nr,ns", [(1, 1), (7, 40), (31, 33), (33, 31), (64, 63), (65, 129), (130, 16), (257, 95),
+                                   (1000, 999), (2912, 40)])
+def test_bf16_products_entry_by_entry(nr, ns):
+    """One X = Q Q^T: r, W = D^H U and the gradient (W + W^T) conj(Q) with W = D^H r, whose r^T is written with r."""
+    import paper_2412_14973_amd as tl
+    plan = tl.Plan(np.array([nr]), np.zeros(0, dtype=np.int32), np.ones(1, dtype=np.int32), ns)
+    gen = torch.Generator(device="cuda").manual_seed(100 * nr + ns)
+
+    def rand(*shape):
+        return torch.complex(torch.randn(shape, generator=gen, device="cuda"), torch.randn(shape, generator=gen, device="cuda"))
+    D, U, theta = rand(ns, nr), rand(ns, nr), rand(plan.theta_size)
+    f, r, X = tl.forward(plan, D, U, theta, tl.BF16X3, want_r=True, want_X=True)
+    D2, U2, X2, r2 = (t.to(torch.complex128) for t in (D, U, X, r))
+    aDH = D2.abs().T.contiguous()
+    ref = D2 @ X2 - U2
+    bound = (_bf16_bound(nr) + 4 * U32) * (D2.abs() @ X2.abs()) + 2 * U32 * (U2.abs() + ref.abs())
+    err = (r2 - ref).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+    W = tl.adjoint(plan, D, U, tl.BF16X3)
+    err = (W.to(torch.complex128) - D2.mH.contiguous() @ U2).abs()
+    bound = _bf16_bound(ns) * (aDH @ U2.abs())
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+    fg, g = tl.grad(plan, D, U, theta, tl.BF16X3)
+    assert float(fg) == float(f)
+    Q = theta.to(torch.complex128).reshape(nr, -1)
+    W2 = D2.mH.contiguous() @ r2
+    G = (W2 + W2.T) @ Q.conj()
+    bW = _bf16_bound(ns) * (aDH @ r2.abs())
+    bound = (bW + bW.T) @ Q.abs() + (2 * nr + 8) * 2 * U32 * ((W2.abs() + W2.abs().T) @ Q.abs())
+    err = (g.to(torch.complex128).reshape(nr, -1) - G).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+
+def test_bf16_tiles_agree_bit_for_bit():
+    """A wave's tile (one block of 32 x 32, or two by two) follows the launch; the sums do not."""
+    import paper_2412_14973_amd as tl
+    nr, ns, count = 450, 420, 8   # 49 tiles of 64 x 64 a problem: one block per wave alone, two by two in the batch
+    plans = [tl.Plan(np.array([150, 150, 150]), np.full(3, 4, dtype=np.int32), np.full(3, 5, dtype=np.int32), ns)
+             for _ in range(count)]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+
+    def rand(*shape):
+        return torch.complex(torch.randn(shape, generator=gen, device="cuda"), torch.randn(shape, generator=gen, device="cuda"))
+    D, U = ([rand(ns, nr) for _ in range(count)] for _ in range(2))
+    th = [0.1 * rand(plans[0].theta_size) for _ in range(count)]
+    alone = [tl.solve(p, d, u, t, iters=4, precision=tl.BF16X3) for p, d, u, t in zip(plans, D, U, th)]
+    thb, fb = tl.solve_batched(plans, D, U, th, iters=4, precision=tl.BF16X3)
+    for i in range(count):
+        assert torch.equal(alone[i][0], thb[i]) and torch.equal(alone[i][1], fb[i])
+
+
+def test_bf16_unsplit_solve():
+    """Above 8191 blocks a wave contracts alone: the line products against the FP32 solve (tolerance of the mode)."""
+    import paper_2412_14973_amd as tl
+    nr, ns = 2912, 40
+    plan = tl.Plan(np.array([1456, 1456]), np.full(1, 3, dtype=np.int32), np.full(2, 3, dtype=np.int32), ns)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+
+    def rand(*shape):
+        return torch.complex(torch.randn(shape, generator=gen, device="cuda"), torch.randn(shape, generator=gen, device="cuda"))
+    D, U, th = rand(ns, nr) / ns, rand(ns, nr), rand(plan.theta_size)
+    out = [tl.solve(plan, D, U, th, iters=3, precision=p) for p in (tl.FP32, tl.BF16X3)]
+    (t0, f0), (t1, f1) = out
+    assert float(((f0 - f1).abs() / f0).max()) <= 5e-3
+    assert float((t0 - t1).norm() / t0.norm()) <= 5e-3
