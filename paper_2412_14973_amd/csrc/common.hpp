@@ -52,9 +52,8 @@ struct GradItem {
     int32_t prob;
     int32_t kq;     // G_L/G_Q/G_R: rank entries in the item, in units of 16 (1..4)
 };
-constexpr int GR_ROWS = 64;   // rows (G_L/G_Q) or cols (G_R) per item
+constexpr int GR_ROWS = 32;   // rows (G_L/G_Q) or cols (G_R) per item
 constexpr int GR_KK = 64;     // rank entries per item (at most)
-constexpr int GR_CH = 4;      // contraction chunk (small: many workgroups per CU hide the W loads)
 constexpr int GZ_BR = 32, GZ_BC = 64;
 
 // ---- complex GEMM on MFMA ----

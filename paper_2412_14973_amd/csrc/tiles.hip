@@ -14,8 +14,9 @@
 //
 // Gradient (ADMM solver section, eqs. DXLR): with W = D^H r and W' = W + W^T,
 // grad L = W' R^H, grad R = L^H W', grad Q = W' conj(Q), grad Z = W'/2.
-// W' is never formed: each block of W'_ij is built in LDS from a block of
-// W_ij plus the transposed block of W_ji, both read coalesced.
+// W' is never formed: its entries are added in registers from W_ij and W_ji.
+#include <type_traits>
+
 #include "gemm_common.hpp"
 
 namespace tlr {
@@ -236,154 +237,152 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
     }
 }
 
-constexpr int GW_P = GR_ROWS + 1;      // W' planes [GR_CH][GW_P] floats (contraction index major)
-constexpr int GF_P = GR_KK + 1;        // factor stage [GR_CH][GF_P] complex
-constexpr int GW_PL = GR_CH * GW_P;    // floats per W' plane
-constexpr int GO_P = GR_ROWS + 1;      // output stage of G_R [GR_KK][GO_P] complex
-
-// One gradient item: a 64 x kn block (kn <= 64 rank entries from b0) of G = W' conj(F), where
+// One gradient item: a 32 x kn block (kn <= 64 rank entries from b0) of G = W' conj(F), where
 //   G_L: rows of the tile, F[c][kk] = R[kk][c]    (G_L = W' R^H, contraction over tile columns)
 //   G_Q: rows of the tile, F[c][kk] = Q[c][kk]    (G_Q = (W + W^T) conj(Q))
 //   G_R: cols of the tile, F[r][kk] = L[r][kk]    (G_R^T = W'^T conj(L), contraction over tile rows)
-// with W' = W_ij + W_ji^T built in LDS chunk by chunk (both parts' loads issued together, each read
-// along its own rows). Chunks are only 4 contraction steps wide: that keeps a workgroup at 72 VGPRs
-// and 17 KB of LDS, and the seven workgroups per CU that this allows hide the W loads far better
-// than fewer, wider ones (32-wide chunks: 3 workgroups per CU, 1.3x the time). The contraction runs on the FP32 matrix cores in realified form (one
-// v_mfma_f32_32x32x2_f32 per complex contraction step: (Re, Im) of W'[m][c] as the two A entries,
-// the real 2 x 2 block of conj(F[c][n]) as B). Wave w owns rank entries 16 w .. 16 w + 15 and both
-// 32-row halves; waves past the item's rank only stage data. W' sits in LDS as re / im planes with
-// the contraction index major (one conflict-free float per A entry); G_R is transposed through LDS
-// so its rows are written whole.
+// with W' = W_ij + W_ji^T formed in registers: both parts are read where they lie, one along the lanes' own rows
+// (16 bytes at a time), one across them (a row of 32 entries at a time). The contraction runs on the FP32 matrix
+// cores: a v_mfma_f32_32x32x2_f32 takes the real parts of W'[m][c] for two c, another one their imaginary parts, against
+// (Re, -Im) and (Im, Re) of F[c][n] as two real columns each, so a lane holds one component of 16 rows of a rank entry.
+// The item's four waves take chunks of 8 c in turn and their sums are added in LDS at the end; until then a wave waits
+// for nobody.
+//
+// What bounds it: the matrix cores in full launches, where a rank is padded to 16 (4096^2 of tiles 256, rank 32: 66 us,
+// 130 TFLOP/s of 8 d d k a product), else the chain of chunks. Before, a workgroup of 64 rows staged W' and F in LDS,
+// 4 c and three barriers at a time: 113 us; nr 1024 (tiles 128, rank 20) 43 us, now 8.2; nr 2304 (tiles 512,
+// rank 40) 166, now 49.
+constexpr int GR_CH = 8;               // contraction entries per chunk: four per half of a wave
+constexpr int GP_P = 66;               // partial blocks [4 waves][16][GP_P] floats
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+template <int KQ>
+struct GradChunk {
+    float2 w1[4], w2[4], f[KQ][4];
+};
+
+template <int KQ, bool FROW>
 __device__ __forceinline__ void grad_block(const GradItem &it, const TileDesc &td, const float2 *__restrict__ W,
                                            int64_t ldw, const float2 *__restrict__ theta, float2 *__restrict__ g,
                                            float *smem) {
-    float *sW = smem;                                              // [re, im][GR_CH][GW_P]
-    float2 *sF = reinterpret_cast<float2 *>(smem + 2 * GW_PL);     // [GR_CH][GF_P]
     const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6;
+    const int lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int j32 = lane & 31, half = lane >> 5;
-    const int k = td.k;
-    const int a0 = it.a0, b0 = it.b0;
+    const int k = td.k, a0 = it.a0, b0 = it.b0;
     const int kn = min(GR_KK, k - b0);
     const bool colside = it.kind == G_R;
     const int nout = min(GR_ROWS, (colside ? td.dj : td.di) - a0);   // out-rows in this item
     const int ncon = colside ? td.di : td.dj;                        // contraction length
-    const float2 *F = it.kind == G_L ? theta + td.offB : theta + td.offA;
-    const bool active = 16 * wave < kn;
-    const int fidx = 2 * 16 * wave + (j32 ^ half);                   // float of the realified B entry
-    const uint32_t fsign = (!half && (j32 & 1)) ? 0x80000000u : 0u;  // conj: -Im f in the first k row
+    // W'[m][c] = w1[m ldw + c] + w2[c ldw + m]. Buffer loads: an offset past the end gives zero, so the chunks at
+    // the end of the contraction need no branch (a branch would make each load wait for the ones before it).
+    const uint32_t ld8 = (uint32_t)ldw * 8;
+    const auto rsW = __builtin_amdgcn_make_buffer_rsrc((void *)W, (short)0, (int)(uint32_t)min(ldw * ldw * 8, (int64_t)0xfffffff0), 0x00020000);
+    const auto rsF = __builtin_amdgcn_make_buffer_rsrc((void *)(theta + (FROW ? td.offB : td.offA)), (short)0,
+                                                       (int)(8 * k * (FROW ? td.dj : td.di)), 0x00020000);
+    const uint32_t row1 = (uint32_t)(colside ? td.col0 : td.row0) + a0, col1 = (uint32_t)(colside ? td.row0 : td.col0);
+    const uint32_t row2 = (uint32_t)(colside ? td.row0 : td.col0), col2 = (uint32_t)(colside ? td.col0 : td.row0) + a0;
+    const uint32_t m = min(j32, nout - 1);   // rows and rank entries past the item repeat its last one and are dropped
+    const uint32_t o1 = (row1 + m) * ld8 + (col1 + 4 * half) * 8, o2 = (row2 + 4 * half) * ld8 + (col2 + m) * 8;
+    const int comp = j32 & 1;
+    const uint32_t fs = FROW ? 8 : 8 * k;
+    uint32_t of[KQ];
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+        const uint32_t n = b0 + min(16 * q + (j32 >> 1), kn - 1);
+        of[q] = (FROW ? n * td.dj * 8 : n * 8) + 4 * half * fs;
+    }
 
-    floatx16 acc[2];
+    auto load = [&](GradChunk<KQ> &x, int ch) {
+        const uint32_t c = ch * GR_CH;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-
-    for (int c0 = 0; c0 < ncon; c0 += GR_CH) {
-        const int cn = min(GR_CH, ncon - c0);
-        // W' = W_ij part + W_ji part: both parts' loads are issued before either is stored
-        //   part 0: W'[m][c] = W_ij[a0+m][c0+c] (G_L, G_Q) or W_ij[c0+c][a0+m] (G_R)
-        //   part 1: + W_ji[c0+c][a0+m] (G_L, G_Q) or + W_ji[a0+m][c0+c] (G_R)
-        float2 v0[GR_ROWS * GR_CH / 256], v1[GR_ROWS * GR_CH / 256];
-#pragma unroll
-        for (int u = 0; u < GR_ROWS * GR_CH / 256; ++u) {
-            const int e = t + 256 * u;
-            int m, c;
-            int64_t o;
-            if (!colside) { m = e / GR_CH; c = e % GR_CH; o = (td.row0 + a0 + m) * ldw + td.col0 + c0 + c; }
-            else { c = e / GR_ROWS; m = e % GR_ROWS; o = (td.row0 + c0 + c) * ldw + td.col0 + a0 + m; }
-            v0[u] = (m < nout && c < cn) ? W[o] : make_float2(0.f, 0.f);
-            if (!colside) { c = e / GR_ROWS; m = e % GR_ROWS; o = (td.col0 + c0 + c) * ldw + td.row0 + a0 + m; }
-            else { m = e / GR_CH; c = e % GR_CH; o = (td.col0 + a0 + m) * ldw + td.row0 + c0 + c; }
-            v1[u] = (m < nout && c < cn) ? W[o] : make_float2(0.f, 0.f);
+        for (int i = 0; i < 4; i += 2) {   // the second entry may lie past the tile: dropped in compute()
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsW, (int)(o1 + 8 * i), (int)(8 * c), 0);
+            x.w1[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+            x.w1[i + 1] = make_float2(__uint_as_float(v[2]), __uint_as_float(v[3]));
         }
 #pragma unroll
-        for (int u = 0; u < GR_ROWS * GR_CH / 256; ++u) {
-            const int e = t + 256 * u;
-            int m, c;
-            if (!colside) { m = e / GR_CH; c = e % GR_CH; } else { c = e / GR_ROWS; m = e % GR_ROWS; }
-            sW[c * GW_P + m] = v0[u].x;
-            sW[GW_PL + c * GW_P + m] = v0[u].y;
-        }
-        for (int e = t; e < GR_CH * GR_KK; e += 256) {
-            int c, kk;
-            int64_t o;
-            if (it.kind == G_L) { kk = e / GR_CH; c = e % GR_CH; o = (int64_t)(b0 + kk) * td.dj + c0 + c; }
-            else { c = e / GR_KK; kk = e % GR_KK; o = (int64_t)(c0 + c) * k + b0 + kk; }
-            sF[c * GF_P + kk] = (c < cn && kk < kn) ? F[o] : make_float2(0.f, 0.f);
-        }
-        __syncthreads();
+        for (int i = 0; i < 4; ++i) {
+            const bool in = (int)c + 4 * half + i < ncon;
+            u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsW, in ? (int)(o2 + (c + i) * ld8) : -1, 0, 0);
+            x.w2[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
 #pragma unroll
-        for (int u = 0; u < GR_ROWS * GR_CH / 256; ++u) {
-            const int e = t + 256 * u;
-            int m, c;
-            if (!colside) { c = e / GR_ROWS; m = e % GR_ROWS; } else { m = e / GR_CH; c = e % GR_CH; }
-            sW[c * GW_P + m] += v1[u].x;
-            sW[GW_PL + c * GW_P + m] += v1[u].y;
-        }
-        __syncthreads();
-        if (active) {
-            const float *fw = reinterpret_cast<const float *>(sF);
-#pragma unroll 4
-            for (int c = 0; c < cn; ++c) {
-                const float b = __uint_as_float(__float_as_uint(fw[2 * c * GF_P + fidx]) ^ fsign);
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(sW[half * GW_PL + c * GW_P + 32 * i + j32], b,
-                                                                   acc[i], 0, 0, 0);
+            for (int q = 0; q < KQ; ++q) {
+                v = __builtin_amdgcn_raw_buffer_load_b64(rsF, in ? (int)(of[q] + (c + i) * fs) : -1, 0, 0);
+                x.f[q][i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
             }
         }
-        __syncthreads();
-    }
-    // lane (j32, half) holds component j32 & 1 of rank entry 16 wave + j32 / 2 for out-rows
-    // 32 i + acc_row(r, lane)
-    const int kk = 16 * wave + (j32 >> 1), comp = j32 & 1;
-    if (!colside) {
-        // grad L / grad Q at the factor's own offset, rows of k entries
-        if (active)
+    };
+    floatx16 acc[KQ];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+    for (int q = 0; q < KQ; ++q)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int m = 32 * i + acc_row(r, lane);
-                    if (m < nout && kk < kn)
-                        reinterpret_cast<float *>(g)[2 * (td.offA + (int64_t)(a0 + m) * k + b0 + kk) + comp] = acc[i][r];
-                }
-        return;
-    }
-    // grad R = L^H W' has the entries of G_R^T: stage [kk][m] (32 rank entries at a time: the
-    // waves that own them) and write rows of R's gradient
-    float *sO = smem;   // [GR_KK / 2][GO_P] complex
-    const float2 *sO2 = reinterpret_cast<const float2 *>(sO);
+        for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
+    auto compute = [&](const GradChunk<KQ> &x, int ch) {
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-        if (active && (wave >> 1) == hh)
+        for (int i = 0; i < 4; ++i) {
+            const bool in = ch * GR_CH + 4 * half + i < ncon;
+            const float wx = in ? x.w1[i].x + x.w2[i].x : 0.f, wy = in ? x.w1[i].y + x.w2[i].y : 0.f;
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int q = 0; q < KQ; ++q)
+                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(wx, comp ? -x.f[q][i].y : x.f[q][i].x, acc[q], 0, 0, 0);
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    sO[2 * ((kk - 32 * hh) * GO_P + 32 * i + acc_row(r, lane)) + comp] = acc[i][r];
-        __syncthreads();
-        for (int e = t; e < (GR_KK / 2) * GR_ROWS; e += 256) {
-            const int q = e >> 6, m = e & 63;
-            const int qq = 32 * hh + q;
-            if (qq < kn && m < nout) g[td.offB + (int64_t)(b0 + qq) * td.dj + a0 + m] = sO2[q * GO_P + m];
+            for (int q = 0; q < KQ; ++q)
+                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(wy, comp ? x.f[q][i].x : x.f[q][i].y, acc[q], 0, 0, 0);
         }
+    };
+    const int nch = (ncon + GR_CH - 1) / GR_CH;
+    GradChunk<KQ> x0, x1;
+    int ch = wave;
+    if (ch < nch) {
+        load(x0, ch);
+        for (; ch + 4 < nch; ch += 8) {
+            load(x1, ch + 4);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(x0, ch);
+            load(x0, ch + 8);   // past the end: reads nothing (see rsW) or is not used
+            __builtin_amdgcn_sched_barrier(0);
+            compute(x1, ch + 4);
+        }
+        if (ch < nch) compute(x0, ch);
+    }
+
+    // lane (j32, half) holds component comp of rank entry 16 q + j32 / 2 for out-rows acc_row(r, lane)
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+        if (q) __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) smem[(wave * 16 + r) * GP_P + lane] = acc[q][r];
         __syncthreads();
+#pragma unroll
+        for (int e = t; e < 512; e += 256) {   // entries of the block, in the order of the output
+            const int row = colside ? e & 31 : e >> 4, n = colside ? e >> 5 : e & 15;
+            const int o = ((row & 3) + 4 * (row >> 3)) * GP_P + 32 * ((row >> 2) & 1) + 2 * n;
+            float2 s = *reinterpret_cast<const float2 *>(smem + o);
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+                const float2 v = *reinterpret_cast<const float2 *>(smem + w * 16 * GP_P + o);
+                s.x += v.x;
+                s.y += v.y;
+            }
+            if (row < nout && 16 * q + n < kn) {
+                if (colside) g[td.offB + (int64_t)(b0 + 16 * q + n) * td.dj + a0 + row] = s;   // G_R^T
+                else g[td.offA + (int64_t)(a0 + row) * k + b0 + 16 * q + n] = s;
+            }
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void grad_kernel(const TileDesc *__restrict__ tiles,
+__global__ __launch_bounds__(256, 2) void grad_kernel(const TileDesc *__restrict__ tiles,
                                                    const GradItem *__restrict__ items,
                                                    const ProbOff *__restrict__ probs,
                                                    const float2 *__restrict__ W_base,
                                                    const float2 *__restrict__ theta_base,
                                                    float2 *__restrict__ g_base) {
-    constexpr int SM_G = 2 * GW_PL + 2 * GR_CH * GF_P;
-    constexpr int SM_O = 2 * (GR_KK / 2) * GO_P;
+    constexpr int SM_G = 4 * 16 * GP_P;
     constexpr int SM_Z = 2 * GZ_BC * (GZ_BR + 1);
-    constexpr int SM_F = SM_G > SM_O ? (SM_G > SM_Z ? SM_G : SM_Z) : (SM_O > SM_Z ? SM_O : SM_Z);
-    __shared__ float smem[SM_F];
+    __shared__ __attribute__((aligned(8))) float smem[SM_G > SM_Z ? SM_G : SM_Z];
     const GradItem it = items[blockIdx.x];
     const TileDesc td = tiles[it.tile];
     const ProbOff po = probs[it.prob];
@@ -417,7 +416,16 @@ __global__ __launch_bounds__(256) void grad_kernel(const TileDesc *__restrict__ 
         }
         return;
     }
-    grad_block(it, td, W, ldw, theta, g, smem);
+    auto go = [&](auto kq) {
+        if (it.kind == G_L) grad_block<decltype(kq)::value, true>(it, td, W, ldw, theta, g, smem);
+        else grad_block<decltype(kq)::value, false>(it, td, W, ldw, theta, g, smem);
+    };
+    switch (it.kq) {
+        case 1: go(std::integral_constant<int, 1>()); break;
+        case 2: go(std::integral_constant<int, 2>()); break;
+        case 3: go(std::integral_constant<int, 3>()); break;
+        default: go(std::integral_constant<int, 4>()); break;
+    }
 }
 
 }  // namespace
