@@ -5,9 +5,9 @@
 // Every wave owns one 32 x 32 block of C (GM_LINE: the same block of a and b) and feeds its MFMAs from
 // global memory through registers, without LDS and without a barrier in the k loop. An FP32 MFMA takes 64
 // cycles, so the 8 KiB of operands that a wave needs per 16 complex k (1536 cycles of products in the
-// three-product form) come to 21 bytes per cycle and CU, a third of what L1 delivers; the loads of the next
-// 16 k are in flight during the products of the present 16, and the other waves of the SIMD (3 to 4, 2 or 3
-// in GM_LINE) cover the rest. The matrix core rate is what bounds it. Measured, TFLOP/s counted 8mnk with
+// three-product form) come to 21 bytes per cycle and CU, a third of what L1 delivers; the other waves of the
+// SIMD (3 to 4, 2 or 3 in GM_LINE) cover the loads, and in small launches the products of the chunk before
+// (AHEAD). The matrix core rate is what bounds it. Measured, TFLOP/s counted 8mnk with
 // the 128 x 128 tiles staged through LDS that this replaces in brackets: one problem of 1024^2, three
 // products: r = D X - U 58 us (252), D^H r 56 (223), [a | b] 107 (234); one of 4096 x 2048: 1500 us (1678),
 // 1537 (1547), 2957 (3077); 34 of 1024^2, four-product form 144 (144), three-product form 132 (125).
@@ -56,7 +56,11 @@ struct Chunk {
     float2 b[NB][CH / 2];
 };
 
-template <int MODE, bool M3, int ROLE, int KS, bool BIG = false>
+constexpr int SCHED_ALU = 0x6;   // only ALU instructions may be moved across the barrier
+
+// AHEAD: a chunk's loads stay in flight during the products of the one before. Without it they do not: a branch
+// around the next chunk's loads makes the wait for the chunk at hand a wait for all, and the other waves cover that.
+template <int MODE, bool M3, int ROLE, int KS, bool BIG, bool AHEAD>
 __global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
     constexpr bool TA = ROLE == GR_TILE_TA_CB || ROLE == GR_ADJOINT;
     constexpr bool STAGE = ROLE == GR_TILE || ROLE == GR_TILE_TA_CB;
@@ -215,12 +219,24 @@ __global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
         Chunk<TA, HB, NB, CH> r0, r1;
         constexpr bool B2 = decltype(nb_tag)::value > 1;
         if (c < end) load(r0, c * CH, B2);
-        for (; c < end; c += 2 * KS) {
-            if (c + KS < end) load(r1, (c + KS) * CH, B2);
-            compute(r0, nb_tag);
-            if (c + KS < end) {
-                if (c + 2 * KS < end) load(r0, (c + 2 * KS) * CH, B2);
+        if constexpr (AHEAD) {
+            for (; c + KS < end; c += 2 * KS) {
+                load(r1, (c + KS) * CH, B2);
+                __builtin_amdgcn_sched_barrier(SCHED_ALU);
+                compute(r0, nb_tag);
+                load(r0, min(c + 2 * KS, end - 1) * CH, B2);
+                __builtin_amdgcn_sched_barrier(SCHED_ALU);
                 compute(r1, nb_tag);
+            }
+            if (c < end) compute(r0, nb_tag);
+        } else {
+            for (; c < end; c += 2 * KS) {
+                if (c + KS < end) load(r1, (c + KS) * CH, B2);
+                compute(r0, nb_tag);
+                if (c + KS < end) {
+                    if (c + 2 * KS < end) load(r0, (c + 2 * KS) * CH, B2);
+                    compute(r1, nb_tag);
+                }
             }
         }
     };
@@ -251,9 +267,24 @@ __global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
         m0, n0);
 }
 
+// Three products in full launches do better without AHEAD (the results are the same): their SIMDs are full, and a
+// sum of the operands per product lets the scheduler fill the waits. us, without and with it:
+//   r = D X - U, D^H r, [a | b] of 448^2 15, 14, 23 and 14, 13, 21; of 1024^2 (1024 workgroups) 64, 62, 118 and 65, 62,
+//   135; 16 of 1024^2 806, 785, 1550 and 828, 794, 1557; the line stages of one problem of tiles 128 (256 to 1024
+//   workgroups) 102 and 95, of 8 problems 580 and 590.
+// Four products and the 2 x 2 wave tiles always take it: 448^2 15, 14, 23 us without, 14, 14, 21 with it; D^H r of
+// 4096 x 2048 1482 and 1436.
+constexpr int64_t AHEAD_MAX_WG = 1023;
 template <int MODE, bool M3, int ROLE, int KS, bool BIG = false>
 hipError_t go(const GemmArgs &a, int batch, hipStream_t s) {
-    hipLaunchKernelGGL((cgemm_kernel<MODE, M3, ROLE, KS, BIG>), dim3(a.tiles_m * a.tiles_n, batch), dim3(256), 0, s, a);
+    const dim3 grid(a.tiles_m * a.tiles_n, batch);
+    if constexpr (M3 && !BIG) {
+        if ((int64_t)grid.x * batch > AHEAD_MAX_WG) {
+            hipLaunchKernelGGL((cgemm_kernel<MODE, M3, ROLE, KS, BIG, false>), grid, dim3(256), 0, s, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((cgemm_kernel<MODE, M3, ROLE, KS, BIG, true>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

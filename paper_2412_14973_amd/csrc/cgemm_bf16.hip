@@ -19,14 +19,14 @@
 // cores' rate, which is more than its 64; four ask for 43. The planes hold the
 // operands in the order of these loads (plane_word), which is what makes this work:
 // from row-major planes the same kernel reads 32 bytes of each cache line at a time
-// and reaches 235 of 424 Tflop/s (64 problems of 1024^2).
+// and reaches 235 of 424 Tflop/s (64 problems of 1024^2). The next chunk's loads are in flight during a chunk's products: 5 to 10 %.
 // What bounds it: at 4096^2 463 to 476 Tflop/s of complex products (8 m n k), that is 1.4 Pflop/s of
 // BF16 products, above what a library product of 8192^3 reaches (1.04). Before, with 256 x 128 tiles
 // fed through LDS: 367 to 403, and at 1024^2 32 tiles for 256 CUs.
 // us for r = D X - U, D^H r and [a | b] (the first writes r^T's planes too, which took a pass of its own before):
 //   nr = ns     64 x 8 problems   448            1024            2304            1024 x 64 problems
 //   before      33, 15, 19        95, 60, 64     162, 127, 133   346, 295, 656   1953, 1446, 2948
-//   now         7, 7, 9           12, 10, 14     35, 29, 51      262, 246, 469   1581, 1316, 2713
+//   now         7, 7, 8           10, 9, 12      32, 26, 49      251, 237, 450   1403, 1206, 2468
 #include <algorithm>
 
 #include "gemm_common.hpp"
@@ -37,7 +37,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
-
 
 template <int HB, int NB>
 struct Chunk {
@@ -124,14 +123,19 @@ __global__ __launch_bounds__(256, 2) void cgemm_bf16x3_kernel(GemmArgsB g) {
     const int nk = m0 < g.Mt && n0 < g.Nt ? g.K / PLANE_KB : 0;
     int kt = KS == 1 ? 0 : wave;
     Chunk<HB, NB> r0, r1;
-    if (kt < nk) load(r0, kt);
-    for (; kt < nk; kt += 2 * KS) {
-        if (kt + KS < nk) load(r1, kt + KS);
-        compute(r0);
-        if (kt + KS < nk) {
-            if (kt + 2 * KS < nk) load(r0, kt + 2 * KS);
+    if (kt < nk) {
+        // the next chunk's loads without a branch around them (the last one's again at the end): behind a branch
+        // that may have skipped them, the wait for the chunk at hand would be a wait for all
+        load(r0, kt);
+        for (; kt + KS < nk; kt += 2 * KS) {
+            load(r1, kt + KS);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(r0);
+            load(r0, min(kt + 2 * KS, nk - 1));
+            __builtin_amdgcn_sched_barrier(0);
             compute(r1);
         }
+        if (kt < nk) compute(r0);
     }
 
     EpiArgs ea;
@@ -178,7 +182,8 @@ hipError_t go(GemmArgsB a, int batch, hipStream_t s) {
 
 // A wave takes two by two blocks where every CU gets a workgroup of such tiles: 4 problems of 448^2 (196 tiles)
 // 24, 17, 28 us against 20, 17, 29 with one block per wave, one of 1024^2 (256) 35, 29, 51 against 34, 31, 54,
-// of 2304 x 576 (324) 85, 71, 134 against 87, 77, 147, of 2304^2 (1296) 262, 246, 469 against 298, 292, 506.
+// of 2304 x 576 (324) 85, 71, 134 against 87, 77, 147, of 2304^2 (1296) 262, 246, 469 against 298, 292, 506 (all
+// before the loads of a chunk were moved ahead of the products of the last).
 constexpr int64_t BIG_TILES = 256;
 
 template <int MODE>
