@@ -1063,6 +1063,14 @@ int check_precision(int precision) {
 GemmArgs gemm_args() {
     GemmArgs g;
     std::memset(&g, 0, sizeof(g));
+    g.Mc = g.Nc = INT32_MAX;
+    return g;
+}
+
+GemmArgsB gemm_args_bf16() {
+    GemmArgsB g;
+    std::memset(&g, 0, sizeof(g));
+    g.Mc = g.Nc = INT32_MAX;
     return g;
 }
 
@@ -1189,6 +1197,9 @@ struct Ctx {
     bool p3m = false;           // FP32 products in the three-real-product form
     bool split = false;         // dense products with the contraction split over waves (gemm_split_k)
     int64_t xspace = 0;         // complex64 elements of X space per problem (1 or 2 ldk x ldk)
+    const float2 *Dx = nullptr; // the caller's D where it is read in place (see read_in_place), else null: w.Ds
+    const float2 *dmat() const { return Dx ? Dx : w.Ds; }
+    int64_t ldd() const { return Dx ? nr : ldk; }
 
     int form() const { return bf16 ? F_BF16X3 : p3m ? F_3M : F_4M; }
     // split planes (uint32 words, one per complex): per problem [hi | lo]
@@ -1230,21 +1241,25 @@ int fin(const Ctx &c, FinArgs f, const int32_t *counts, int ucount, int nsum) {
 
 // The dense products contract over the true length rounded up to the kernel's k step (16 complex,
 // 32 in BF16), not over the padded one: the padding is zero and would only add stages.
-int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64_t ldu, int64_t sU, float2 *r) {
+// r_true: r is ns x nr (or null: not wanted), else padded
+int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64_t ldu, int64_t sU, float2 *r,
+               bool r_true = false) {
+    const int64_t ldr = r_true ? c.nr : c.ldk;
+    const int Mc = !r_true ? INT32_MAX : r ? (int)c.ns : 0, Nc = !r_true ? INT32_MAX : r ? (int)c.nr : 0;
     const double np = c.nprob, ns = (double)c.ns, nr = (double)c.nr;
     const Work wk = gemm_work(c.form(), 8.0 * ns * nr * nr * np, 8.0 * np * (3.0 * ns * nr + nr * nr));
     if (c.bf16) {
         // X given as the split planes that start at the same place (word 2 * offset of X)
         const uint32_t *xh = reinterpret_cast<const uint32_t *>(X);
-        GemmArgsB g;
-        std::memset(&g, 0, sizeof(g));
+        GemmArgsB g = gemm_args_bf16();
         g.Ahi = c.dsw();
         g.Alo = c.dsw() + c.lds * c.ldk;
         g.lda = c.ldk; g.sA = 2 * c.lds * c.ldk;
         g.Bhi = xh;
         g.Blo = xh + c.lo_words();
         g.ldb = c.ldk; g.sB = 2 * sX;
-        g.C = r; g.ldc = c.ldk; g.sC = c.lds * c.ldk;
+        g.C = r; g.ldc = ldr; g.sC = c.lds * c.ldk;
+        g.Mc = Mc; g.Nc = Nc;
         g.E = U; g.lde = ldu; g.sE = sU;
         if (c.w.rT) {   // the adjoint product's operand
             g.Thi = c.w.rT; g.Tlo = c.w.rT + c.ldk * c.lds;
@@ -1257,9 +1272,10 @@ int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64
         return TLRMDD_OK;
     }
     GemmArgs g = gemm_args();
-    g.A = c.w.Ds; g.lda = c.ldk; g.sA = c.lds * c.ldk;
+    g.A = c.dmat(); g.lda = c.ldd(); g.sA = c.lds * c.ldk;
     g.B = X; g.ldb = c.ldk; g.sB = sX;
-    g.C = r; g.ldc = c.ldk; g.sC = c.lds * c.ldk;
+    g.C = r; g.ldc = ldr; g.sC = c.lds * c.ldk;
+    g.Mc = Mc; g.Nc = Nc;
     g.E = U; g.lde = ldu; g.sE = sU;
     g.partials = c.w.partials; g.sP = (int64_t)c.pstride;   // one sum per workgroup
     g.M = (int)c.lds; g.N = (int)c.ldk; g.K = (int)round_up(c.nr, GEMM_BK);
@@ -1270,31 +1286,35 @@ int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64
     return TLRMDD_OK;
 }
 
-int gemm_adjoint(const Ctx &c, const float2 *r, float2 *W, int64_t sW) {
+// W = D^H r. ldr = nr: r is ns x nr, else padded (BF16 products read its planes instead); ldw = nr: W is nr x nr
+int gemm_adjoint(const Ctx &c, const float2 *r, int64_t ldr, float2 *W, int64_t ldw, int64_t sW) {
+    const int Wc = ldw == c.nr ? (int)c.nr : INT32_MAX;
     const double np = c.nprob, ns = (double)c.ns, nr = (double)c.nr;
     const Work wk = gemm_work(c.form(), 8.0 * nr * ns * nr * np, 8.0 * np * (2.0 * ns * nr + nr * nr));
     if (c.bf16) {
         // r^T split planes (written with r, or by split_r_transpose) are the transposed B operand
-        GemmArgsB g;
-        std::memset(&g, 0, sizeof(g));
+        GemmArgsB g = gemm_args_bf16();
         g.Ahi = c.dhw();
         g.Alo = c.dhw() + c.ldk * c.lds;
         g.lda = c.lds; g.sA = 2 * c.ldk * c.lds;
         g.Bhi = c.w.rT;
         g.Blo = c.w.rT + c.ldk * c.lds;
         g.ldb = c.lds; g.sB = 2 * c.ldk * c.lds;
-        g.C = W; g.ldc = c.ldk; g.sC = sW;
+        g.C = W; g.ldc = ldw; g.sC = sW;
+        g.Mc = g.Nc = Wc;
         g.M = (int)c.ldk; g.N = (int)c.ldk; g.K = (int)round_up(c.ns, 32);
         g.Mt = g.Nt = (int)c.nr;
         HIP_TRY(timed(TLRMDD_K_GEMM_ADJOINT, c.s, wk, [&] { return launch_cgemm_bf16(GM_STORE, g, c.nprob, c.s, c.split); }));
         return TLRMDD_OK;
     }
     GemmArgs g = gemm_args();
-    g.A = c.w.Ds; g.lda = c.ldk; g.sA = c.lds * c.ldk;   // read transposed and conjugated
-    g.B = r; g.ldb = c.ldk; g.sB = c.lds * c.ldk;
-    g.C = W; g.ldc = c.ldk; g.sC = sW;
+    g.A = c.dmat(); g.lda = c.ldd(); g.sA = c.lds * c.ldk;   // read transposed and conjugated
+    g.B = r; g.ldb = ldr; g.sB = c.lds * c.ldk;
+    g.C = W; g.ldc = ldw; g.sC = sW;
+    g.Mc = g.Nc = Wc;
     g.M = (int)c.ldk; g.N = (int)c.ldk; g.K = (int)round_up(c.ns, GEMM_BK);
     g.Mt = g.Nt = (int)c.nr;
+    g.Kt = (int)c.ns;
     HIP_TRY(timed(TLRMDD_K_GEMM_ADJOINT, c.s, wk, [&] {
         return launch_cgemm(GM_STORE, g, c.nprob, c.s, GR_ADJOINT, c.p3m, c.split);
     }));
@@ -1306,8 +1326,7 @@ int gemm_line(const Ctx &c, const float2 *X1, const float2 *X2, int64_t sX) {
     const Work wk = gemm_work(c.form(), 16.0 * ns * nr * nr * np, 8.0 * np * (4.0 * ns * nr + 2.0 * nr * nr));
     if (c.bf16) {
         const uint32_t *xh = reinterpret_cast<const uint32_t *>(X1);
-        GemmArgsB g;
-        std::memset(&g, 0, sizeof(g));
+        GemmArgsB g = gemm_args_bf16();
         g.Ahi = c.dsw();
         g.Alo = c.dsw() + c.lds * c.ldk;
         g.lda = c.ldk; g.sA = 2 * c.lds * c.ldk;
@@ -1339,8 +1358,29 @@ int gemm_line(const Ctx &c, const float2 *X1, const float2 *X2, int64_t sX) {
 // r^T split planes for the BF16 adjoint product, of an r that no product has just written
 int split_r_transpose(const Ctx &c) {
     if (!c.bf16) return TLRMDD_OK;
-    HIP_TRY(launch_split_transpose(c.w.r, c.ldk, c.lds, c.ldk, c.w.rT, c.w.rT + c.ldk * c.lds, c.lds, c.nprob,
+    HIP_TRY(launch_split_transpose(c.w.r, c.ldk, c.lds, c.ldk, c.w.rT, c.w.rT + c.ldk * c.lds, c.lds, c.ldk, c.nprob,
                                    c.lds * c.ldk, 2 * c.ldk * c.lds, c.s));
+    return TLRMDD_OK;
+}
+
+// whether two arrays of complex64 share memory
+bool overlap(const void *a, int64_t na, const void *b, int64_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + (uintptr_t)nb * sizeof(float2) && y < x + (uintptr_t)na * sizeof(float2);
+}
+
+// Whether the FP32 products of one call can read D where the caller has it (ns x nr) instead of a padded copy: r = D X
+// loads 16 bytes of a row at a time over K rounded up to 16, so rows have to begin at 16 bytes and end with a whole
+// step. Saves reading and writing D once: nr 1024 6 us of 139, nr 4096 x 2048 25 us of 3100.
+bool read_in_place(const Ctx &c, const void *D) {
+    return !c.bf16 && c.nr % GEMM_BK == 0 && (reinterpret_cast<uintptr_t>(D) & 15) == 0;
+}
+
+// Zeros in the padding of X for one call. The products only multiply by them where nr is no whole number of k steps:
+// what columns past nr hold stays in the columns of r past nr, which are written as zeros.
+int clear_x_padding(const Ctx &c) {
+    if (c.nr % (c.bf16 ? 32 : GEMM_BK) == 0) return TLRMDD_OK;
+    HIP_TRY(launch_fill_zero(c.w.XW, (size_t)c.ldk * c.ldk * sizeof(float2), c.s));
     return TLRMDD_OK;
 }
 
@@ -1755,7 +1795,7 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
                 if ((st = tile_gradient(R, sg, R.gcur))) return st;
         if (R.n_adj > 0) {
             const Ctx ca = R.n_adj == c.nprob ? c : line_ctx(c, 0, R.n_adj);
-            if ((st = gemm_adjoint(ca, c.w.r, R.X1, R.xstride))) return st;
+            if ((st = gemm_adjoint(ca, c.w.r, c.ldk, R.X1, c.ldk, R.xstride))) return st;
             const int ng = (R.single || R.n_adj == c.nprob) ? c.D.n_grad : R.grad_first[R.n_adj];
             const double nr = (double)c.nr;
             const Work wk = gemm_work(F_4M, R.grad_pre[R.n_adj], 8.0 * (nr * nr * R.n_adj + 2.0 * R.theta_pre[R.n_adj]));
@@ -1945,16 +1985,20 @@ int tlrmdd_forward(tlrmdd_plan plan, const void *D, const void *U, const void *t
     c.D = plan->D;
     set_precision(c, precision);
     c.xspace = c.ldk * c.ldk;
-    if (c.ldk != c.nr) HIP_TRY(launch_fill_zero(c.w.XW, (size_t)c.ldk * c.ldk * sizeof(float2), stream));
-    if ((st = stage(c, 0, (const float2 *)D, false))) return st;
+    if ((st = clear_x_padding(c))) return st;
+    // r is written where the caller wants it, unless another workgroup may still read there
+    const bool r_apart = !r_out || !overlap(r_out, c.ns * c.nr, D, c.ns * c.nr);
+    const bool r_direct = !r_out || r_out == U || !overlap(r_out, c.ns * c.nr, U, c.ns * c.nr);
+    if (r_apart && read_in_place(c, D)) c.Dx = (const float2 *)D;
+    else if ((st = stage(c, 0, (const float2 *)D, false))) return st;
     const double nr2 = (double)c.nr * (double)c.nr, thn = (double)plan->H.theta_size;
     HIP_TRY(timed(TLRMDD_K_ASSEMBLE, stream, gemm_work(F_4M, plan->H.asm_cflops, 8.0 * (nr2 + thn)), [&] { return launch_assemble(false, c.D.tiles, c.D.asm_items, c.D.n_asm, c.D.probs, (const float2 *)theta, nullptr,
                             c.w.XW, nullptr, stream, c.bf16, 0, c.lo_words()); }));
-    if ((st = gemm_resid(c, c.w.XW, 0, (const float2 *)U, c.nr, 0, c.w.r))) return st;
+    if ((st = gemm_resid(c, c.w.XW, 0, (const float2 *)U, c.nr, 0, r_direct ? (float2 *)r_out : c.w.r, r_direct))) return st;
     FinArgs f = fin_args(FIN_F_OUT, c.w.sc);
     f.fout = f_dev;
     if ((st = fin(c, f, nullptr, partial_slots(c), 1))) return st;
-    if (r_out) HIP_TRY(launch_copy2d(c.w.r, c.ldk, (float2 *)r_out, c.nr, c.ns, c.nr, stream));
+    if (!r_direct) HIP_TRY(launch_copy2d(c.w.r, c.ldk, (float2 *)r_out, c.nr, c.ns, c.nr, stream));
     if (X_out) {
         if (c.bf16)   // the X space holds split planes: re-assemble X in complex64 for the caller
             HIP_TRY(launch_assemble(false, c.D.tiles, c.D.asm_items, c.D.n_asm, c.D.probs, (const float2 *)theta,
@@ -1984,19 +2028,21 @@ int tlrmdd_grad(tlrmdd_plan plan, const void *D, const void *U, const void *thet
     c.D = plan->D;
     set_precision(c, precision);
     c.xspace = c.ldk * c.ldk;
-    if (c.ldk != c.nr) HIP_TRY(launch_fill_zero(c.w.XW, (size_t)c.ldk * c.ldk * sizeof(float2), stream));
-    if ((st = stage(c, 0, (const float2 *)D, true))) return st;
+    if ((st = clear_x_padding(c))) return st;
+    if (read_in_place(c, D)) c.Dx = (const float2 *)D;
+    else if ((st = stage(c, 0, (const float2 *)D, true))) return st;
     const double nr2 = (double)c.nr * (double)c.nr, thn = (double)plan->H.theta_size;
     HIP_TRY(timed(TLRMDD_K_ASSEMBLE, stream, gemm_work(F_4M, plan->H.asm_cflops, 8.0 * (nr2 + thn)), [&] { return launch_assemble(false, c.D.tiles, c.D.asm_items, c.D.n_asm, c.D.probs, (const float2 *)theta, nullptr,
                             c.w.XW, nullptr, stream, c.bf16, 0, c.lo_words()); }));
-    if ((st = gemm_resid(c, c.w.XW, 0, (const float2 *)U, c.nr, 0, c.w.r))) return st;
+    // (in BF16 only the planes of r^T are read again)
+    if ((st = gemm_resid(c, c.w.XW, 0, (const float2 *)U, c.nr, 0, c.bf16 ? nullptr : c.w.r, c.bf16))) return st;
     if (f_dev) {
         FinArgs f = fin_args(FIN_F_OUT, c.w.sc);
         f.fout = f_dev;
         if ((st = fin(c, f, nullptr, partial_slots(c), 1))) return st;
     }
     // the assembled X is dead once r exists: W = D^H r reuses its storage
-    if ((st = gemm_adjoint(c, c.w.r, c.w.XW, 0))) return st;
+    if ((st = gemm_adjoint(c, c.w.r, c.ldk, c.w.XW, c.ldk, 0))) return st;
     HIP_TRY(timed(TLRMDD_K_GRAD, stream, gemm_work(F_4M, plan->H.grad_cflops, 8.0 * (nr2 + 2.0 * thn)), [&] { return launch_grad(c.D.tiles, c.D.grad_items, c.D.n_grad, c.D.probs, c.w.XW, (const float2 *)theta,
                         (float2 *)grad_out, stream); }));
     return TLRMDD_OK;
@@ -2021,12 +2067,23 @@ int tlrmdd_adjoint(tlrmdd_plan plan, const void *D, const void *U, void *X_out, 
     c.D = plan->D;
     set_precision(c, precision);
     c.xspace = c.ldk * c.ldk;
-    if ((st = stage(c, 0, (const float2 *)D, true))) return st;
-    // U takes the place of the residual: padded copy with zero padding, then W = D^H U
-    HIP_TRY(launch_stage_d((const float2 *)U, c.ns, c.nr, c.w.r, c.ldk, nullptr, c.lds, stream));
-    if ((st = split_r_transpose(c))) return st;
-    if ((st = gemm_adjoint(c, c.w.r, c.w.XW, 0))) return st;
-    HIP_TRY(launch_copy2d(c.w.XW, c.ldk, (float2 *)X_out, c.nr, c.nr, c.nr, stream));
+    if (c.bf16) {
+        uint32_t *hh = c.dhw(), *rt = c.w.rT;
+        HIP_TRY(timed(TLRMDD_K_STAGE, stream, bytes_work(16.0 * (double)c.ns * (double)c.nr), [&] {
+            return launch_stage_d_split((const float2 *)D, c.ns, c.nr, nullptr, nullptr, c.ldk, hh, hh + c.ldk * c.lds,
+                                        c.lds, stream);
+        }));
+        HIP_TRY(launch_split_transpose((const float2 *)U, c.nr, c.ns, c.nr, rt, rt + c.ldk * c.lds, c.lds, c.ldk, 1, 0,
+                                       0, stream));
+    } else {
+        c.Dx = (const float2 *)D;   // this product reads 8 bytes at a time: any D will do
+    }
+    if (overlap(X_out, c.nr * c.nr, D, c.ns * c.nr) || overlap(X_out, c.nr * c.nr, U, c.ns * c.nr)) {
+        if ((st = gemm_adjoint(c, (const float2 *)U, c.nr, c.w.XW, c.ldk, 0))) return st;
+        HIP_TRY(launch_copy2d(c.w.XW, c.ldk, (float2 *)X_out, c.nr, c.nr, c.nr, stream));
+        return TLRMDD_OK;
+    }
+    if ((st = gemm_adjoint(c, (const float2 *)U, c.nr, (float2 *)X_out, c.nr, 0))) return st;
     return TLRMDD_OK;
 }
 
@@ -2596,17 +2653,17 @@ namespace {
 struct TlrHost {
     int N = 0;
     int64_t Kpmax = 0, K1p = 0, K2p = 0, dp = 0;   // padded operand shapes (uniform per tile)
-    std::vector<PackItem> packA, packB;
-    std::vector<GatherItem> gather;
+    std::vector<PackItem> packA, packB;             // with the padding, as zeros
+    std::vector<int64_t> cmap;                      // where stage 1 stores its columns in the stage 2 operands
     std::vector<std::pair<int, int>> runs;          // [first, last] tiles of equal size
 };
 
 struct TlrWs {
-    float2 *Ds, *A, *P, *B, *Pcol, *R;
+    float2 *Ds, *A, *B, *Pcol;
     double *partials;
     SolveScalars *sc;
-    PackItem *pa, *pb;
-    GatherItem *gi;
+    PackItem *pack;
+    int64_t *cmap;
     size_t bytes;
 };
 
@@ -2638,7 +2695,15 @@ TlrHost tlr_plan(const HostLayout &H, int64_t lds) {
     T.K1p = round_up(kmax, GEMM_PAD);
     T.K2p = round_up(kmax, GEMM_BK);   // sum over i of k(i, j) equals K1[j] (ranks are symmetric)
     T.dp = round_up(dmax, GEMM_PAD);
-    const int64_t sA = T.Kpmax * T.K1p, sP = lds * T.K1p, sB = T.K2p * T.dp, sPc = lds * T.K2p;
+    const int64_t sA = T.Kpmax * T.K1p, sB = T.K2p * T.dp, sPc = lds * T.K2p;
+    T.cmap.assign(N * T.K1p, -1);
+    auto zero = [](std::vector<PackItem> &to, int64_t dst, int64_t ldd, int64_t rows, int64_t cols) {
+        if (rows <= 0 || cols <= 0) return;
+        PackItem z{};
+        z.op = PACK_ZERO;
+        z.rows = (int32_t)rows; z.cols = (int32_t)cols; z.dst = dst; z.ldd = ldd;
+        to.push_back(z);
+    };
     std::vector<int64_t> roff(N, 0);   // running row offset inside B_j / column offset inside Pcol_j
     for (int i = 0; i < N; ++i) {
         int64_t coff = 0;
@@ -2663,14 +2728,17 @@ TlrHost tlr_plan(const HostLayout &H, int64_t lds) {
             }
             T.packA.push_back(a);
             T.packB.push_back(b);
-            GatherItem g{};
-            g.k = k;
-            g.src = i * sP + coff; g.lds = T.K1p;
-            g.dst = j * sPc + roff[j]; g.ldd = T.K2p;
-            T.gather.push_back(g);
+            for (int q = 0; q < k; ++q) T.cmap[i * T.K1p + coff + q] = j * sPc + roff[j] + q;
             coff += k;
             roff[j] += k;
         }
+        // Pcol_i has as many columns as P_i: its padding gets the zero columns that follow P_i's
+        for (int64_t q = K1[i]; q < T.K2p; ++q) T.cmap[i * T.K1p + q] = i * sPc + q;
+        const int64_t d = H.d[i];
+        zero(T.packA, i * sA + K1[i], T.K1p, d, T.K1p - K1[i]);
+        zero(T.packA, i * sA + d * T.K1p, T.K1p, T.Kpmax - d, T.K1p);
+        zero(T.packB, i * sB + d, T.dp, K1[i], T.dp - d);
+        zero(T.packB, i * sB + K1[i] * T.dp, T.dp, T.K2p - K1[i], T.dp);
     }
     for (int i = 0; i < N;) {   // runs of equal tile size share one batched launch per stage
         int e = i;
@@ -2693,15 +2761,12 @@ TlrWs tlr_carve(char *base, const TlrHost &T, int64_t lds, int64_t ldk) {
     const int64_t N = T.N;
     w.Ds = (float2 *)take((size_t)lds * ldk * c8);
     w.A = (float2 *)take((size_t)N * T.Kpmax * T.K1p * c8);
-    w.P = (float2 *)take((size_t)N * lds * T.K1p * c8);
     w.B = (float2 *)take((size_t)N * T.K2p * T.dp * c8);
     w.Pcol = (float2 *)take((size_t)N * lds * T.K2p * c8);
-    w.R = (float2 *)take((size_t)N * lds * T.dp * c8);
     w.partials = (double *)take((size_t)N * gemm_partial_slots((int)lds, (int)T.dp) * sizeof(double));
     w.sc = (SolveScalars *)take(sizeof(SolveScalars));
-    w.pa = (PackItem *)take(T.packA.size() * sizeof(PackItem));
-    w.pb = (PackItem *)take(T.packB.size() * sizeof(PackItem));
-    w.gi = (GatherItem *)take(T.gather.size() * sizeof(GatherItem));
+    w.pack = (PackItem *)take((T.packA.size() + T.packB.size()) * sizeof(PackItem));
+    w.cmap = (int64_t *)take(T.cmap.size() * sizeof(int64_t));
     w.bytes = o;
     return w;
 }
@@ -2724,58 +2789,68 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
     if (!plan || !D || !U || !theta || !f_dev || !workspace) return fail(TLRMDD_INVALID_ARGUMENT, "NULL argument");
     const HostLayout &H = plan->H;
     const int64_t ns = H.ns, nr = H.nr, lds = plan->lds, ldk = plan->ldk;
-    const TlrHost T = tlr_plan(H, lds);
+    TlrHost T = tlr_plan(H, lds);
     const TlrWs w = tlr_carve((char *)workspace, T, lds, ldk);
     if (w.bytes > ws_bytes) return fail(TLRMDD_WORKSPACE, "workspace too small");
     hipStream_t s = stream;
+    for (PackItem b : T.packB) {   // one list, relative to A
+        b.dst += w.B - w.A;
+        T.packA.push_back(b);
+    }
     Upload up;
-    up.add(w.pa, T.packA.data(), T.packA.size() * sizeof(PackItem));
-    up.add(w.pb, T.packB.data(), T.packB.size() * sizeof(PackItem));
-    up.add(w.gi, T.gather.data(), T.gather.size() * sizeof(GatherItem));
+    up.add(w.pack, T.packA.data(), T.packA.size() * sizeof(PackItem));
+    up.add(w.cmap, T.cmap.data(), T.cmap.size() * sizeof(int64_t));
     int st = up.commit(s);
     if (st) return st;
     const int64_t N = T.N;
-    // padding of the packed operands must read as zero
-    HIP_TRY(launch_fill_zero(w.A, (size_t)N * T.Kpmax * T.K1p * sizeof(float2), s));
-    HIP_TRY(launch_fill_zero(w.B, (size_t)N * T.K2p * T.dp * sizeof(float2), s));
-    HIP_TRY(launch_fill_zero(w.Pcol, (size_t)N * lds * T.K2p * sizeof(float2), s));
-    HIP_TRY(launch_stage_d((const float2 *)D, ns, nr, w.Ds, ldk, nullptr, lds, s));
-    HIP_TRY(launch_tlr_pack(w.pa, (int)T.packA.size(), (const float2 *)theta, w.A, s));
-    HIP_TRY(launch_tlr_pack(w.pb, (int)T.packB.size(), (const float2 *)theta, w.B, s));
-    const int64_t tiles2 = gemm_partial_slots((int)lds, (int)T.dp);
-    for (const auto &run : T.runs) {   // stage 1: P_i = D_:,i A_i
+    // D in place where every tile column begins at 16 bytes and ends with a whole k step; else a padded copy
+    bool in_place = (reinterpret_cast<uintptr_t>(D) & 15) == 0 && !(r_out && overlap(r_out, ns * nr, D, ns * nr));
+    for (int i = 0; i < T.N; ++i) in_place = in_place && H.d[i] % GEMM_BK == 0;
+    const float2 *Dm = in_place ? (const float2 *)D : w.Ds;
+    const int64_t ldd = in_place ? nr : ldk;
+    if (!in_place) HIP_TRY(launch_stage_d((const float2 *)D, ns, nr, w.Ds, ldk, nullptr, lds, s));
+    HIP_TRY(launch_tlr_pack(w.pack, (int)T.packA.size(), (const float2 *)theta, w.A, s));
+    for (const auto &run : T.runs) {   // stage 1: P_i = D_:,i A_i, stored as the column blocks of every Pcol_j
         const int i0 = run.first, cnt = run.second - run.first + 1, di = H.d[i0];
         GemmArgs g = gemm_args();
-        g.A = w.Ds + H.start[i0]; g.lda = ldk; g.sA = di;
+        g.A = Dm + H.start[i0]; g.lda = ldd; g.sA = di;
         g.B = w.A + i0 * T.Kpmax * T.K1p; g.ldb = T.K1p; g.sB = T.Kpmax * T.K1p;
-        g.C = w.P + i0 * lds * T.K1p; g.ldc = T.K1p; g.sC = lds * T.K1p;
+        g.C = w.Pcol; g.ldc = T.K2p;
+        g.cmap = w.cmap + i0 * T.K1p; g.s_cmap = T.K1p;
         g.M = (int)lds; g.N = (int)T.K1p; g.K = (int)round_up(di, GEMM_BK);
+        g.Mt = (int)ns;
         HIP_TRY(launch_cgemm(GM_STORE, g, cnt, s, GR_DENSE, false, false));
     }
-    HIP_TRY(launch_tlr_gather(w.gi, (int)T.gather.size(), w.P, w.Pcol, lds, s));
+    int64_t slots = 0;
+    // r goes where the caller wants it, unless another workgroup may still read U there: then over the copy of D
+    const bool direct = !r_out || r_out == U || !overlap(r_out, ns * nr, U, ns * nr);
+    float2 *r = direct ? (float2 *)r_out : w.Ds;
+    const int64_t ldr = direct ? nr : ldk;
     for (const auto &run : T.runs) {   // stage 2: r_:,j = Pcol_j B_j - U_:,j
         const int j0 = run.first, cnt = run.second - run.first + 1, dj = H.d[j0];
         GemmArgs g = gemm_args();
         g.A = w.Pcol + j0 * lds * T.K2p; g.lda = T.K2p; g.sA = lds * T.K2p;
         g.B = w.B + j0 * T.K2p * T.dp; g.ldb = T.dp; g.sB = T.K2p * T.dp;
-        g.C = w.R + j0 * lds * T.dp; g.ldc = T.dp; g.sC = lds * T.dp;
+        if (r) {
+            g.C = r + H.start[j0]; g.ldc = ldr; g.sC = dj;
+        }
+        g.Mc = r ? (int)ns : 0; g.Nc = r ? dj : 0;
         g.E = (const float2 *)U + H.start[j0]; g.lde = nr; g.sE = dj;
-        g.partials = w.partials + j0 * tiles2; g.sP = tiles2;
-        g.M = (int)lds; g.N = (int)T.dp; g.K = (int)T.K2p;
-        g.Me = (int)ns; g.Ne = dj;
+        g.M = (int)lds; g.N = (int)round_up(dj, 64); g.K = (int)T.K2p;
+        g.Me = g.Mt = (int)ns; g.Ne = g.Nt = dj;
+        g.partials = w.partials + slots; g.sP = gemm_partial_slots(g.M, g.N);
+        slots += cnt * g.sP;
         HIP_TRY(launch_cgemm(GM_RESID, g, cnt, s, GR_DENSE, false, false));
     }
     FinArgs f = fin_args(FIN_F_OUT, w.sc);
     f.partials = w.partials;
-    f.pstride = N * tiles2;
+    f.pstride = slots;
     f.counts = nullptr;
-    f.ucount = (int32_t)(N * tiles2);
+    f.ucount = (int32_t)slots;
     f.nsum = 1;
     f.fout = f_dev;
     HIP_TRY(launch_finalize(f, 1, s));
-    if (r_out)
-        for (int j = 0; j < N; ++j)
-            HIP_TRY(launch_copy2d(w.R + j * lds * T.dp, T.dp, (float2 *)r_out + H.start[j], nr, ns, H.d[j], s));
+    if (!direct) HIP_TRY(launch_copy2d(w.Ds, ldk, (float2 *)r_out, nr, ns, nr, s));
     return TLRMDD_OK;
 }
 

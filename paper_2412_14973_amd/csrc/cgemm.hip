@@ -26,9 +26,10 @@
 // Epilogues: GM_STORE (C = AB), GM_RESID (C = AB - U plus FP64 partial sums of |C|^2) and GM_LINE (a and b
 // plus FP64 partial sums of Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2 for the exact line search).
 //
-// Operands are padded to whole 64-tiles with zeros, so no load carries a bounds check (they are buffer
-// loads: anything past an operand's last row reads zero); blocks outside the true sizes (Mt x Nt) are
-// written as zeros without their products.
+// Operands are padded to whole 64-tiles with zeros, or read where the caller has them: no load carries a bounds
+// check (they are buffer loads: anything past an operand's last row reads zero), and what a row-major operand
+// holds past its last column only reaches columns or rows of C that are not stored (Mc x Nc), not summed
+// (Me x Ne) or never read. Blocks outside the true sizes (Mt x Nt) are written as zeros without their products.
 #include <algorithm>
 #include <type_traits>
 
@@ -118,9 +119,9 @@ __global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
     const int n0 = 32 * CB * (tn * WV + (KS == 1 ? wn : 0));
 
     const __amdgpu_buffer_rsrc_t rsA =
-        __builtin_amdgcn_make_buffer_rsrc((void *)A, (short)0, (int)g.bytesA, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(scalar(A), (short)0, (int)g.bytesA, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsB =
-        __builtin_amdgcn_make_buffer_rsrc((void *)B, (short)0, (int)g.bytesB, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(scalar(B), (short)0, (int)g.bytesB, 0x00020000);
     uint32_t offA[HB];
     offA[0] = TA ? (uint32_t)(((int64_t)HK * half * g.lda + m0 + j32) * 8)
                  : (uint32_t)(((int64_t)(m0 + j32) * g.lda + 2 * half) * 8);
@@ -251,13 +252,17 @@ __global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
     ea.lde = g.lde;
     ea.Me = g.Me;
     ea.Ne = g.Ne;
+    ea.Mc = g.Mc;
+    ea.Nc = g.Nc;
     ea.partials = MODE == GM_STORE ? nullptr : g.partials + z * g.sP + z2 * g.sP2;
     ea.nblk = g.N >> 5;
     ea.scat_kp = g.scat_kp;
     ea.scat_w = g.scat_w;
     ea.scat_lim = g.scat_lim;
     ea.scat_js = g.scat_js;
-    block_epilogue<MODE, STAGE, KS, HB, CB>(
+    constexpr int COLS = MODE != GM_STORE ? COL_PLAIN : STAGE ? COL_SCAT : ROLE == GR_DENSE ? COL_MAP : COL_PLAIN;
+    ea.cmap = COLS == COL_MAP ? g.cmap + z * g.s_cmap : nullptr;
+    block_epilogue<MODE, COLS, KS, HB, CB>(
         ea,
         [&](int h, int n, int r) {
             const floatx16 *d = acc[h][n];
@@ -331,6 +336,7 @@ hipError_t launch_cgemm(int mode, const GemmArgs &a0, int batch, hipStream_t s, 
     const bool ta = role == GR_TILE_TA_CB || role == GR_ADJOINT;
     if (a.M % 64 || a.N % 64 || a.K % GEMM_BK || a.K <= 0) return hipErrorInvalidValue;   // padded operands only
     if ((ta && mode != GM_STORE) || (stage && (split || !m3))) return hipErrorInvalidValue;
+    if (mode == GM_STORE && role == GR_DENSE && !a.cmap) return hipErrorInvalidValue;
     if (a.K2 < 0 || a.K2 > a.K || a.K2 % GEMM_BK || (a.K2 && !(mode == GM_LINE && stage))) return hipErrorInvalidValue;
     if (a.nz3 > 1 || a.nz4 > 1) {
         const int64_t inner = (int64_t)std::max(1, a.nz3) * std::max(1, a.nz4);
@@ -343,11 +349,12 @@ hipError_t launch_cgemm(int mode, const GemmArgs &a0, int batch, hipStream_t s, 
     a.tiles_n = a.N / wt;
     a.Mt = a.Mt > 0 ? std::min(a.Mt, a.M) : a.M;
     a.Nt = a.Nt > 0 ? std::min(a.Nt, a.N) : a.N;
-    // byte extents of the buffer resources (32-bit): A is Mt x lda (transposed source: K x lda), B is K x ldb
+    // byte extents of the buffer resources (32-bit): A is Mt x lda (transposed source: Kt x lda), B is Kt x ldb
     // (GM_LINE: B2 follows B)
     if (ta && a.lda < a.Mt) return hipErrorInvalidValue;
-    const int64_t bytesA = (int64_t)(ta ? a.K : a.Mt) * a.lda * 8;
-    int64_t bytesB = (int64_t)a.K * a.ldb * 8;
+    const int kt = a.Kt > 0 ? std::min(a.Kt, a.K) : a.K;
+    const int64_t bytesA = (int64_t)(ta ? kt : a.Mt) * a.lda * 8;
+    int64_t bytesB = (int64_t)kt * a.ldb * 8;
     a.b2_off = 0;
     if (mode == GM_LINE) {
         a.b2_off = a.B2 - a.B;

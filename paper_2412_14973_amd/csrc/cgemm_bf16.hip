@@ -65,10 +65,10 @@ __global__ __launch_bounds__(256, 2) void cgemm_bf16x3_kernel(GemmArgsB g) {
     const int n0 = 32 * CB * (tn * WV + (KS == 1 ? wave & 1 : 0));
 
     __amdgpu_buffer_rsrc_t rsA[2], rsB[2];
-    rsA[0] = __builtin_amdgcn_make_buffer_rsrc((void *)(g.Ahi + z * g.sA), (short)0, (int)g.bytesA, 0x00020000);
-    rsA[1] = __builtin_amdgcn_make_buffer_rsrc((void *)(g.Alo + z * g.sA), (short)0, (int)g.bytesA, 0x00020000);
-    rsB[0] = __builtin_amdgcn_make_buffer_rsrc((void *)(g.Bhi + z * g.sB), (short)0, (int)g.bytesB, 0x00020000);
-    rsB[1] = __builtin_amdgcn_make_buffer_rsrc((void *)(g.Blo + z * g.sB), (short)0, (int)g.bytesB, 0x00020000);
+    rsA[0] = __builtin_amdgcn_make_buffer_rsrc(scalar(g.Ahi + z * g.sA), (short)0, (int)g.bytesA, 0x00020000);
+    rsA[1] = __builtin_amdgcn_make_buffer_rsrc(scalar(g.Alo + z * g.sA), (short)0, (int)g.bytesA, 0x00020000);
+    rsB[0] = __builtin_amdgcn_make_buffer_rsrc(scalar(g.Bhi + z * g.sB), (short)0, (int)g.bytesB, 0x00020000);
+    rsB[1] = __builtin_amdgcn_make_buffer_rsrc(scalar(g.Blo + z * g.sB), (short)0, (int)g.bytesB, 0x00020000);
     uint32_t offA[HB], offB[NB];
 #pragma unroll
     for (int h = 0; h < HB; ++h) offA[h] = (uint32_t)((m0 + 32 * h) * (g.lda * 4)) + lane * 16;
@@ -146,9 +146,10 @@ __global__ __launch_bounds__(256, 2) void cgemm_bf16x3_kernel(GemmArgsB g) {
     ea.lde = g.lde;
     ea.Me = g.Me;
     ea.Ne = g.Ne;
+    ea.Mc = g.Mc;
+    ea.Nc = g.Nc;
     ea.partials = g.partials ? g.partials + z * g.sP : nullptr;
     ea.nblk = g.N >> 5;
-    ea.scat_kp = 0;
     // four registers of a lane are 16 bytes of C^T's split planes, at this lane's place in a block
     uint32_t *const Thi = MODE == GM_RESID && g.Thi ? g.Thi + z * g.sT : nullptr;
     uint32_t *const Tlo = Thi ? g.Tlo + z * g.sT : nullptr;
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(256, 2) void cgemm_bf16x3_kernel(GemmArgsB g) {
             *reinterpret_cast<uint4 *>(Tlo + w0 + 256 * q) = lo;
         }
     };
-    block_epilogue<MODE, false, KS, HB, CB>(
+    block_epilogue<MODE, COL_PLAIN, KS, HB, CB>(
         ea, [&](int h, int n, int r) { return make_float2(acc[h][n][0][r], acc[h][n][1][r]); }, m0, n0, put_t);
 }
 

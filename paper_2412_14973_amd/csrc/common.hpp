@@ -70,6 +70,11 @@ struct GemmArgs {
     int32_t M, N, K;                 // padded sizes: M, N multiples of 64, K of 16 (zero padding)
     int32_t Me, Ne;                  // GM_RESID: true shape of E (reads outside are zero)
     int32_t Mt, Nt;                  // true shape of C (blocks outside are zero; 0: M, N)
+    int32_t Kt;                      // true K: rows of B, and of a transposed A, from Kt on read zero (0: K)
+    int32_t Mc, Nc;                  // C is stored inside Mc x Nc only (0, 0: nowhere, GM_STORE and GM_RESID)
+    // GM_STORE of dense products: column n of entry z goes to C + row ldc + cmap[z s_cmap + n], or nowhere (negative)
+    const int64_t *cmap;
+    int64_t s_cmap;
     int64_t b2_off;                  // GM_LINE: B2 - B in complex elements (set by the launcher)
     uint32_t bytesA, bytesB;         // buffer extents (set by the launcher)
     int32_t tiles_m, tiles_n;
@@ -136,6 +141,7 @@ struct GemmArgsB {
     double *partials;
     int32_t M, N, K, Me, Ne;
     int32_t Mt, Nt;                            // true shape of C (blocks outside are zero; 0: M, N)
+    int32_t Mc, Nc;                            // C is stored inside Mc x Nc only
     int32_t tiles_m, tiles_n;
     int64_t sA, sB, sC, sE, sP;                // batch strides (complex elements / doubles)
     uint32_t bytesA, bytesB;                   // set by the launcher
@@ -181,12 +187,14 @@ hipError_t launch_grad(const TileDesc *tiles, const GradItem *items, int nitems,
 
 hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, int64_t ldk,
                           float2 *DHs, int64_t lds, hipStream_t s);
-// split staging: Dhi/Dlo (lds x ldk split planes) and DHhi/DHlo (ldk x lds, conjugate transpose)
+// split staging: Dhi/Dlo (lds x ldk split planes; or null) and DHhi/DHlo (ldk x lds, conjugate transpose)
 hipError_t launch_stage_d_split(const float2 *D, int64_t ns, int64_t nr, uint32_t *Dh, uint32_t *Dl, int64_t ldk,
                                 uint32_t *DHh, uint32_t *DHl, int64_t lds, hipStream_t s);
-// rT = r^T as split planes: r is rows x cols (ld ldr, multiples of 32), rT planes are cols x rows (ld ldt)
+// rT = r^T as split planes: r is rows x cols (ld ldr), the planes are colsp x rowsp (ld rowsp, multiples of 32) and
+// zero outside
 hipError_t launch_split_transpose(const float2 *r, int64_t ldr, int64_t rows, int64_t cols, uint32_t *th,
-                                  uint32_t *tl, int64_t ldt, int batch, int64_t s_r, int64_t s_t, hipStream_t s);
+                                  uint32_t *tl, int64_t rowsp, int64_t colsp, int batch, int64_t s_r, int64_t s_t,
+                                  hipStream_t s);
 // zero the padding of nplanes ld x ld split planes (true size n x n), per problem of a batch
 hipError_t launch_zero_pad(uint32_t *base, int64_t ld, int64_t n, int nplanes, int64_t plane_stride, int batch,
                            int64_t batch_stride, hipStream_t s);

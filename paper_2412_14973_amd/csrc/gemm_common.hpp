@@ -20,6 +20,15 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// a uniform pointer, in scalar registers: where the compiler has computed it in vector registers, every buffer load
+// from it would become a loop over the lanes' values
+__device__ __forceinline__ void *scalar(const void *p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return reinterpret_cast<void *>(lo | hi << 32);
+}
+
 // the five products of the line-search sums: Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2
 __device__ __forceinline__ void line_terms(float (&blk)[5], float2 r, float2 a, float2 b) {
     blk[0] = fmaf(r.x, a.x, fmaf(r.y, a.y, blk[0]));
@@ -36,11 +45,14 @@ struct EpiArgs {
     const float2 *E;   // GM_RESID: U (true shape Me x Ne); GM_LINE: r
     int64_t lde;
     int32_t Me, Ne;
+    int32_t Mc, Nc;    // C is stored inside Mc x Nc only (not GM_LINE)
     double *partials;
     int32_t nblk;      // 32-column blocks of C per row of blocks (partial slots are numbered by block)
-    int32_t scat_kp, scat_w, scat_lim;   // GM_STORE with STAGE: column scatter of the tile stages (see GemmArgs)
+    const int64_t *cmap;                 // GM_STORE with COL_MAP (see GemmArgs)
+    int32_t scat_kp, scat_w, scat_lim;   // GM_STORE with COL_SCAT: column scatter of the tile stages (see GemmArgs)
     int64_t scat_js;
 };
+enum ColumnsOfC { COL_PLAIN, COL_SCAT, COL_MAP };
 
 // Epilogue of a wave's HB x CB blocks of 32 x 32 complex entries from row m0 and column n0 on, each lane holding
 // whole entries of column lane % 32: cval(h, n, r) is accumulator row r of row block h and block n (GM_LINE: n = 0
@@ -53,7 +65,7 @@ struct Nothing {
     template <class V>
     __device__ __forceinline__ void operator()(int, int, const V &) const {}
 };
-template <int MODE, bool STAGE, int KS, int HB, int CB, class F, class G = Nothing>
+template <int MODE, int COLS, int KS, int HB, int CB, class F, class G = Nothing>
 __device__ __forceinline__ void block_epilogue(const EpiArgs &ea, F &&cval, int m0, int n0, G &&also = G()) {
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -69,6 +81,18 @@ __device__ __forceinline__ void block_epilogue(const EpiArgs &ea, F &&cval, int 
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             const int cc = col + 32 * cb;
+            // two loops: a condition on every store costs the full blocks a fifth of the whole product
+            const bool whole = m0 + 32 * h + 32 <= ea.Mc && n0 + 32 * cb + 32 <= ea.Nc;
+            auto put = [&](int64_t ccol, const float2 (&c)[NR]) {
+                if (whole) {
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) ea.C[(int64_t)row_of(h, r) * ea.ldc + ccol] = c[r];
+                } else if (cc < ea.Nc) {
+#pragma unroll
+                    for (int r = 0; r < NR; ++r)
+                        if (row_of(h, r) < ea.Mc) ea.C[(int64_t)row_of(h, r) * ea.ldc + ccol] = c[r];
+                }
+            };
             // the entries of E: their loads are in flight together, and during the sums over the waves (an
             // entry outside E reads E[0] and is dropped)
             float2 e[NR];
@@ -110,20 +134,25 @@ __device__ __forceinline__ void block_epilogue(const EpiArgs &ea, F &&cval, int 
             for (int q = 0; q < NS; ++q) blk[q] = 0.f;
             if constexpr (MODE == GM_STORE) {
                 int64_t ccol = cc;
-                if (STAGE && ea.scat_kp > 0) {
+                if (COLS == COL_SCAT && ea.scat_kp > 0) {
                     if (cc >= ea.scat_lim) continue;
                     ccol += (int64_t)((cc % ea.scat_w) / ea.scat_kp) * ea.scat_js;
                 }
-#pragma unroll
-                for (int r = 0; r < NR; ++r) ea.C[(int64_t)row_of(h, r) * ea.ldc + ccol] = v[0][r];
+                if (COLS == COL_MAP) {
+                    ccol = ea.cmap[cc];
+                    if (ccol < 0) continue;
+                }
+                put(ccol, v[0]);
             } else if constexpr (MODE == GM_RESID) {
 #pragma unroll
                 for (int r = 0; r < NR; ++r) {
-                    const float2 d = make_float2(v[0][r].x - e[r].x, v[0][r].y - e[r].y);
-                    ea.C[(int64_t)row_of(h, r) * ea.ldc + cc] = d;
+                    // zero outside E: an operand read in place has other entries there than zeros
+                    const bool in = row_of(h, r) < ea.Me && cc < ea.Ne;
+                    const float2 d = in ? make_float2(v[0][r].x - e[r].x, v[0][r].y - e[r].y) : make_float2(0.f, 0.f);
                     blk[0] = fmaf(d.x, d.x, fmaf(d.y, d.y, blk[0]));
                     v[0][r] = d;
                 }
+                put(cc, v[0]);
                 also(h, cb, v[0]);
             } else {
 #pragma unroll

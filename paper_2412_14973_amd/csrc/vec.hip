@@ -66,14 +66,14 @@ __global__ __launch_bounds__(256) void stage_d_split_kernel(const float2 *__rest
         tile[r][tx] = v;
     }
     __syncthreads();
-    put_plane_block(Dh, Dl, plane_word(s0, c0, ldk), [&](int row, int k) { return tile[row][k]; });
+    if (Dh) put_plane_block(Dh, Dl, plane_word(s0, c0, ldk), [&](int row, int k) { return tile[row][k]; });
     if (DHh)
         put_plane_block(DHh, DHl, plane_word(c0, s0, lds),
                         [&](int row, int k) { return make_float2(tile[k][row].x, -tile[k][row].y); });
 }
 
-__global__ __launch_bounds__(256) void split_transpose_kernel(const float2 *__restrict__ r, int64_t ldr,
-                                                              uint32_t *__restrict__ th, uint32_t *__restrict__ tl,
+__global__ __launch_bounds__(256) void split_transpose_kernel(const float2 *__restrict__ r, int64_t ldr, int64_t rows,
+                                                              int64_t cols, uint32_t *__restrict__ th, uint32_t *__restrict__ tl,
                                                               int64_t ldt, int64_t s_r, int64_t s_t) {
     __shared__ float2 tile[32][33];
     const int z = blockIdx.z;
@@ -82,7 +82,10 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(const float2 *__re
     tl += z * s_t;
     const int64_t r0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int q = ty; q < 32; q += 8) tile[q][tx] = r[(r0 + q) * ldr + c0 + tx];
+    for (int q = ty; q < 32; q += 8) {
+        const int64_t i = r0 + q, j = c0 + tx;
+        tile[q][tx] = (i < rows && j < cols) ? r[i * ldr + j] : make_float2(0.f, 0.f);
+    }
     __syncthreads();
     put_plane_block(th, tl, plane_word(c0, r0, ldt), [&](int row, int k) { return tile[k][row]; });
 }
@@ -658,11 +661,12 @@ hipError_t launch_stage_d_split(const float2 *D, int64_t ns, int64_t nr, uint32_
 }
 
 hipError_t launch_split_transpose(const float2 *r, int64_t ldr, int64_t rows, int64_t cols, uint32_t *th,
-                                  uint32_t *tl, int64_t ldt, int batch, int64_t s_r, int64_t s_t, hipStream_t s) {
+                                  uint32_t *tl, int64_t rowsp, int64_t colsp, int batch, int64_t s_r, int64_t s_t,
+                                  hipStream_t s) {
     if (rows <= 0 || cols <= 0 || batch <= 0) return hipSuccess;
-    if (rows % 32 || cols % 32 || ldt % 32) return hipErrorInvalidValue;   // whole blocks
-    dim3 grid((unsigned)(cols / 32), (unsigned)(rows / 32), (unsigned)batch);
-    hipLaunchKernelGGL(split_transpose_kernel, grid, dim3(256), 0, s, r, ldr, th, tl, ldt, s_r, s_t);
+    if (rowsp % 32 || colsp % 32 || rowsp < rows || colsp < cols) return hipErrorInvalidValue;   // whole blocks
+    dim3 grid((unsigned)(colsp / 32), (unsigned)(rowsp / 32), (unsigned)batch);
+    hipLaunchKernelGGL(split_transpose_kernel, grid, dim3(256), 0, s, r, ldr, rows, cols, th, tl, rowsp, s_r, s_t);
     return hipGetLastError();
 }
 
