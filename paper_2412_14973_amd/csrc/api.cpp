@@ -1384,23 +1384,38 @@ int clear_x_padding(const Ctx &c) {
     return TLRMDD_OK;
 }
 
-// staging of D for problem p (padded; split planes in BF16 mode): reads D, writes D and D^H
-int stage(const Ctx &c, int p, const float2 *D, bool with_dh) {
-    with_dh = with_dh && c.bf16;   // the FP32 adjoint product reads D itself
-    const Work wk = bytes_work((with_dh ? 24.0 : 16.0) * (double)c.ns * (double)c.nr);
-    if (c.bf16) {
-        uint32_t *dh = c.dsw() + (int64_t)p * 2 * c.lds * c.ldk;
-        uint32_t *hh = with_dh ? c.dhw() + (int64_t)p * 2 * c.ldk * c.lds : nullptr;
-        HIP_TRY(timed(TLRMDD_K_STAGE, c.s, wk, [&] {
-            return launch_stage_d_split(D, c.ns, c.nr, dh, dh + c.lds * c.ldk, c.ldk, hh,
-                                        hh ? hh + c.ldk * c.lds : nullptr, c.lds, c.s);
-        }));
-    } else {
-        HIP_TRY(timed(TLRMDD_K_STAGE, c.s, wk, [&] {
-            return launch_stage_d(D, c.ns, c.nr, c.w.Ds + (int64_t)p * c.lds * c.ldk, c.ldk,
-                                  with_dh ? c.w.DHs + (int64_t)p * c.ldk * c.lds : nullptr, c.lds, c.s);
-        }));
+// the arrays of problems p0 .. p0 + count - 1 for one launch
+Problems problems(int p0, int count, const tlrmdd_plan *plans, const void *const *D, const void *const *U,
+                  void *const *theta) {
+    Problems q;
+    std::memset(&q, 0, sizeof(q));
+    for (int i = 0; i < count; ++i) {
+        q.D[i] = D ? (const float2 *)D[p0 + i] : nullptr;
+        q.U[i] = U ? (const float2 *)U[p0 + i] : nullptr;
+        q.theta[i] = theta ? (float2 *)theta[p0 + i] : nullptr;
+        q.theta_n[i] = plans ? plans[p0 + i]->H.theta_size : 0;
     }
+    return q;
+}
+
+// BF16: split planes of D and, with_dh, D^H of problems p0 ..
+int stage_split(const Ctx &c, const Problems &in, int p0, int count, bool with_d, bool with_dh) {
+    const int64_t n = c.lds * c.ldk;
+    uint32_t *dh = with_d ? c.dsw() + 2 * p0 * n : nullptr, *hh = with_dh ? c.dhw() + 2 * p0 * n : nullptr;
+    const double b = (8.0 + (with_d ? 8.0 : 0.0) + (with_dh ? 8.0 : 0.0)) * (double)c.ns * (double)c.nr * count;
+    HIP_TRY(timed(TLRMDD_K_STAGE, c.s, bytes_work(b), [&] {
+        return launch_stage_d_split(in, count, c.ns, c.nr, dh, dh ? dh + n : nullptr, c.ldk, hh, hh ? hh + n : nullptr,
+                                    c.lds, 2 * n, c.s);
+    }));
+    return TLRMDD_OK;
+}
+
+// staging of D for a call on one problem (padded; split planes in BF16 mode, with_dh: of D^H too)
+int stage(const Ctx &c, const void *D, bool with_dh) {
+    if (c.bf16) return stage_split(c, problems(0, 1, nullptr, &D, nullptr, nullptr), 0, 1, true, with_dh);
+    HIP_TRY(timed(TLRMDD_K_STAGE, c.s, bytes_work(16.0 * (double)c.ns * (double)c.nr), [&] {
+        return launch_stage_d((const float2 *)D, c.ns, c.nr, c.w.Ds, c.ldk, nullptr, c.lds, c.s);
+    }));
     return TLRMDD_OK;
 }
 
@@ -1422,6 +1437,8 @@ struct Run {
     float *gcur = nullptr, *gprev = nullptr;
     double *fhist0 = nullptr;
     const tlrmdd_opts *opts = nullptr;
+    bool fresh = false;              // the scalars are as staged: no pairs to drop
+    bool fresh_p = false;            // the theta half of Pcol was formed from the present theta (objective_fresh)
     // ADMM state (op 3): split variable, scaled dual, penalty center
     float *z = nullptr, *u = nullptr, *cen = nullptr;
     std::vector<LineSeg> segs;       // line-search form of every problem range
@@ -1638,6 +1655,7 @@ int objective_fresh(Run &R, int record, double lam) {
     for (const LineSeg &sg : R.segs)
         if (sg.tile && sg.lt.lc.grad)
             if ((e = tile_resid(R, sg))) return e;
+    R.fresh_p = true;
     return fin_f(R, record, lam, partial_slots(c));
 }
 
@@ -1711,8 +1729,14 @@ int run_setup(Run &R, int op, int nprob, const tlrmdd_plan *plans, const void *c
         line_tile_tables(Hseg, toff, sg.lt.lc, c.lds, pack);
         if ((int)pack.size() != sg.lt.npack)
             return fail(TLRMDD_UNSUPPORTED, "tile-form line search tables");
-        up.add(sg.lt.pack, pack.data(), pack.size() * sizeof(PackItem));
-        HIP_TRY(launch_fill_zero(sg.lt.PA, sg.lt.zero_bytes, s));   // rank padding reads as zero
+        // what no pack writes reads as zero: the padding of ranks, the columns between nt kpad and Wg
+        bool padded = false;
+        for (const PackItem &it : pack) padded = padded || std::min(it.rows, it.cols) < sg.lt.lc.kpad;
+        if (padded) HIP_TRY(launch_fill_zero(sg.lt.PA, sg.lt.zero_bytes, s));
+        // the range's tables lie one after the other: one copy
+        char *t0 = (char *)(sg.lt.lc.grad ? (void *)sg.lt.gpack : (void *)sg.lt.pack);
+        std::vector<char> img((char *)(sg.lt.pack + sg.lt.npack) - t0);
+        std::memcpy(img.data() + ((char *)sg.lt.pack - t0), pack.data(), pack.size() * sizeof(PackItem));
         if (sg.lt.lc.grad) {
             std::vector<PackItem> gpack;
             std::vector<TGradItem> gitems;
@@ -1720,11 +1744,12 @@ int run_setup(Run &R, int op, int nprob, const tlrmdd_plan *plans, const void *c
             if ((int)gpack.size() != sg.lt.ngpack || (int)gitems.size() > sg.lt.ngitems)
                 return fail(TLRMDD_UNSUPPORTED, "tile-form gradient tables");
             sg.lt.ngitems = (int)gitems.size();
-            up.add(sg.lt.gpack, gpack.data(), gpack.size() * sizeof(PackItem));
-            up.add(sg.lt.gitems, gitems.data(), gitems.size() * sizeof(TGradItem));
-            // B^H padding and the unused columns of S read as zero
-            HIP_TRY(launch_fill_zero((char *)sg.lt.PA + sg.lt.gzero_off, sg.lt.gzero_bytes, s));
+            std::memcpy(img.data(), gpack.data(), gpack.size() * sizeof(PackItem));
+            std::memcpy(img.data() + ((char *)sg.lt.gitems - t0), gitems.data(), gitems.size() * sizeof(TGradItem));
+            if (padded || sg.lt.Wg != (int64_t)sg.lt.lc.nt * sg.lt.lc.kpad)
+                HIP_TRY(launch_fill_zero((char *)sg.lt.PA + sg.lt.gzero_off, sg.lt.gzero_bytes, s));
         }
+        up.add(t0, img.data(), img.size());
     }
     if (R.single) c.D = plans[0]->D;
     else upload_tables(R.T, nprob, c.w, c.D, fhist, up);
@@ -1748,22 +1773,30 @@ int run_setup(Run &R, int op, int nprob, const tlrmdd_plan *plans, const void *c
 
     // padding of the X space must read as zero (the assembly writes only the true nr x nr block)
     if (c.ldk != nr) HIP_TRY(launch_fill_zero(c.w.XW, (size_t)nprob * R.xstride * sizeof(float2), s));
-    const double snr = (double)ns * (double)nr;
-    for (int p = 0; p < nprob; ++p) {
-        if ((st = stage(c, p, (const float2 *)D[p], true))) return st;
-        if (c.w.Dc != c.w.Ds)   // BF16 mode with tile-form ranges: their complex64 D
-            HIP_TRY(timed(TLRMDD_K_STAGE, s, bytes_work(16.0 * snr), [&] {
-                return launch_stage_d((const float2 *)D[p], c.ns, c.nr, c.w.Dc + p * c.lds * c.ldk, c.ldk, nullptr,
-                                      c.lds, s);
-            }));
-        HIP_TRY(timed(TLRMDD_K_STAGE, s, bytes_work(16.0 * snr), [&] {
-            return launch_copy2d((const float2 *)U[p], nr, c.w.Us + p * R.rstride, c.ldk, ns, nr, s);
-        }));
-        HIP_TRY(hipMemcpyAsync(c.w.th + 2 * R.T.probs[p].theta, theta[p],
-                               plans[p]->H.theta_size * sizeof(float2), hipMemcpyDeviceToDevice, s));
+    // One problem whose shape is whole tiles is read where the caller has it; else padded copies of D (BF16: split planes,
+    // and a complex64 copy for tile-form ranges) and U, a launch for every PROBLEMS_MAX problems.
+    float2 *Ds = c.bf16 ? (c.w.Dc != c.w.Ds ? c.w.Dc : nullptr) : c.w.Ds, *Us = c.w.Us;
+    auto aligned = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+    if (R.single && !c.bf16 && c.ldk == nr && c.lds == ns && aligned(D[0]) && aligned(U[0])) {
+        c.w.Ds = c.w.Dc = (float2 *)const_cast<void *>(D[0]);
+        c.w.Us = (float2 *)const_cast<void *>(U[0]);
+        Ds = Us = nullptr;
     }
-    FinArgs f0 = fin_args(FIN_INIT, c.w.sc);
-    return fin(c, f0, nullptr, 0, 1);
+    const double snr = (double)ns * (double)nr;
+    for (int p0 = 0; p0 < nprob; p0 += PROBLEMS_MAX) {
+        const int n = std::min(PROBLEMS_MAX, nprob - p0);
+        const Problems in = problems(p0, n, plans, D, U, theta);
+        if (c.bf16 && (st = stage_split(c, in, p0, n, true, true))) return st;
+        double th = 0.0;
+        for (int i = 0; i < n; ++i) th += (double)in.theta_n[i];
+        HIP_TRY(timed(TLRMDD_K_STAGE, s, bytes_work(16.0 * (((Ds ? 1 : 0) + (Us ? 1 : 0)) * snr * n + th)), [&] {
+            return launch_stage_problems(in, n, ns, nr, c.lds, c.ldk, Ds ? Ds + p0 * R.rstride : nullptr,
+                                         Us ? Us + p0 * R.rstride : nullptr, c.D.probs + p0, (float2 *)c.w.th,
+                                         c.w.sc + p0, s);
+        }));
+    }
+    R.fresh = true;
+    return TLRMDD_OK;
 }
 
 // `iters` iterations of L-BFGS (or steepest descent) with exact line search on
@@ -1775,7 +1808,8 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
     hipStream_t s = c.s;
     const int m1 = R.m1, nt = R.nt;
     int st;
-    if ((st = fin(c, fin_args(FIN_RESET, c.w.sc), nullptr, 0, 1))) return st;
+    if (!R.fresh && (st = fin(c, fin_args(FIN_RESET, c.w.sc), nullptr, 0, 1))) return st;
+    R.fresh = false;
     if (lam != 0.0) {
         HIP_TRY(launch_pen(c.D.tsegs, nt, c.w.th, cen, nullptr, c.w.partials, s));
         if ((st = fin(c, fin_args(FIN_THNORM, c.w.sc), c.D.tcount, 0, 1))) return st;
@@ -1783,7 +1817,7 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
     // tile-form gradient ranges: the theta half of Pcol for the current theta (the direction half is
     // theta too here, and unused)
     for (const LineSeg &sg : R.segs)
-        if (sg.tile && sg.lt.lc.grad && iters > 0)
+        if (sg.tile && sg.lt.lc.grad && iters > 0 && !R.fresh_p)   // (just formed with the residual otherwise)
             if ((st = tile_stage1(R, sg, c.w.th))) return st;
     for (int t = 0; t < iters; ++t) {
         // gradient from the tracked residual (eqs. DXLR): W = D^H r and the tile blocks of W' for the
@@ -1890,13 +1924,17 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
         }
         std::swap(R.gcur, R.gprev);
     }
+    if (iters > 0) R.fresh_p = false;   // carried from here on, not fresh
     return TLRMDD_OK;
 }
 
 int run_finish(Run &R, const tlrmdd_plan *plans, void *const *theta) {
-    for (int p = 0; p < R.c.nprob; ++p)
-        HIP_TRY(hipMemcpyAsync(theta[p], R.c.w.th + 2 * R.T.probs[p].theta, plans[p]->H.theta_size * sizeof(float2),
-                               hipMemcpyDeviceToDevice, R.c.s));
+    const Ctx &c = R.c;
+    for (int p0 = 0; p0 < c.nprob; p0 += PROBLEMS_MAX) {
+        const int n = std::min(PROBLEMS_MAX, c.nprob - p0);
+        HIP_TRY(launch_collect_theta(problems(p0, n, plans, nullptr, nullptr, theta), n, c.D.probs + p0,
+                                     (const float2 *)c.w.th, c.s));
+    }
     return TLRMDD_OK;
 }
 
@@ -1990,7 +2028,7 @@ int tlrmdd_forward(tlrmdd_plan plan, const void *D, const void *U, const void *t
     const bool r_apart = !r_out || !overlap(r_out, c.ns * c.nr, D, c.ns * c.nr);
     const bool r_direct = !r_out || r_out == U || !overlap(r_out, c.ns * c.nr, U, c.ns * c.nr);
     if (r_apart && read_in_place(c, D)) c.Dx = (const float2 *)D;
-    else if ((st = stage(c, 0, (const float2 *)D, false))) return st;
+    else if ((st = stage(c, D, false))) return st;
     const double nr2 = (double)c.nr * (double)c.nr, thn = (double)plan->H.theta_size;
     HIP_TRY(timed(TLRMDD_K_ASSEMBLE, stream, gemm_work(F_4M, plan->H.asm_cflops, 8.0 * (nr2 + thn)), [&] { return launch_assemble(false, c.D.tiles, c.D.asm_items, c.D.n_asm, c.D.probs, (const float2 *)theta, nullptr,
                             c.w.XW, nullptr, stream, c.bf16, 0, c.lo_words()); }));
@@ -2030,7 +2068,7 @@ int tlrmdd_grad(tlrmdd_plan plan, const void *D, const void *U, const void *thet
     c.xspace = c.ldk * c.ldk;
     if ((st = clear_x_padding(c))) return st;
     if (read_in_place(c, D)) c.Dx = (const float2 *)D;
-    else if ((st = stage(c, 0, (const float2 *)D, true))) return st;
+    else if ((st = stage(c, D, true))) return st;
     const double nr2 = (double)c.nr * (double)c.nr, thn = (double)plan->H.theta_size;
     HIP_TRY(timed(TLRMDD_K_ASSEMBLE, stream, gemm_work(F_4M, plan->H.asm_cflops, 8.0 * (nr2 + thn)), [&] { return launch_assemble(false, c.D.tiles, c.D.asm_items, c.D.n_asm, c.D.probs, (const float2 *)theta, nullptr,
                             c.w.XW, nullptr, stream, c.bf16, 0, c.lo_words()); }));
@@ -2068,11 +2106,8 @@ int tlrmdd_adjoint(tlrmdd_plan plan, const void *D, const void *U, void *X_out, 
     set_precision(c, precision);
     c.xspace = c.ldk * c.ldk;
     if (c.bf16) {
-        uint32_t *hh = c.dhw(), *rt = c.w.rT;
-        HIP_TRY(timed(TLRMDD_K_STAGE, stream, bytes_work(16.0 * (double)c.ns * (double)c.nr), [&] {
-            return launch_stage_d_split((const float2 *)D, c.ns, c.nr, nullptr, nullptr, c.ldk, hh, hh + c.ldk * c.lds,
-                                        c.lds, stream);
-        }));
+        uint32_t *rt = c.w.rT;
+        if ((st = stage_split(c, problems(0, 1, nullptr, &D, nullptr, nullptr), 0, 1, false, true))) return st;
         HIP_TRY(launch_split_transpose((const float2 *)U, c.nr, c.ns, c.nr, rt, rt + c.ldk * c.lds, c.lds, c.ldk, 1, 0,
                                        0, stream));
     } else {

@@ -187,9 +187,23 @@ hipError_t launch_grad(const TileDesc *tiles, const GradItem *items, int nitems,
 
 hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, int64_t ldk,
                           float2 *DHs, int64_t lds, hipStream_t s);
-// split staging: Dhi/Dlo (lds x ldk split planes; or null) and DHhi/DHlo (ldk x lds, conjugate transpose)
-hipError_t launch_stage_d_split(const float2 *D, int64_t ns, int64_t nr, uint32_t *Dh, uint32_t *Dl, int64_t ldk,
-                                uint32_t *DHh, uint32_t *DHl, int64_t lds, hipStream_t s);
+// The callers' arrays of up to PROBLEMS_MAX problems of a launch, by value: nothing to upload, and a captured launch
+// keeps them.
+constexpr int PROBLEMS_MAX = 32;
+struct Problems {
+    const float2 *D[PROBLEMS_MAX], *U[PROBLEMS_MAX];
+    float2 *theta[PROBLEMS_MAX];
+    int64_t theta_n[PROBLEMS_MAX];
+};
+// a solve's inputs: padded D and U (lds x ldk per problem; null: not copied), theta at probs[p].theta, fresh scalars
+hipError_t launch_stage_problems(const Problems &in, int count, int64_t ns, int64_t nr, int64_t lds, int64_t ldk,
+                                 float2 *Ds, float2 *Us, const ProbOff *probs, float2 *th, SolveScalars *sc,
+                                 hipStream_t s);
+hipError_t launch_collect_theta(const Problems &out, int count, const ProbOff *probs, const float2 *th, hipStream_t s);
+// split staging: Dhi/Dlo (lds x ldk split planes; or null) and DHhi/DHlo (ldk x lds, conjugate transpose; or null),
+// stride words from problem to problem
+hipError_t launch_stage_d_split(const Problems &in, int count, int64_t ns, int64_t nr, uint32_t *Dh, uint32_t *Dl,
+                                int64_t ldk, uint32_t *DHh, uint32_t *DHl, int64_t lds, int64_t stride, hipStream_t s);
 // rT = r^T as split planes: r is rows x cols (ld ldr), the planes are colsp x rowsp (ld rowsp, multiples of 32) and
 // zero outside
 hipError_t launch_split_transpose(const float2 *r, int64_t ldr, int64_t rows, int64_t cols, uint32_t *th,

@@ -77,10 +77,12 @@ __global__ __launch_bounds__(256) void tlr_pack_kernel(const PackItem *__restric
 // Gradient blocks of the tile form from the partial planes of its two products (fixed summation
 // order: the H1 planes, then the H2 planes) in 32 x 32 tiles: every thread reads along the rows of H
 // (c fastest); transposed blocks pass through LDS so that they are written along the rows of g too.
+// NP planes of each: their loads are in flight together (12 us with a loop over the planes at nr 1024, tiles 128,
+// rank 24, now 5).
+template <int NP>
 __global__ __launch_bounds__(256) void tlr_grad_kernel(const TGradItem *__restrict__ items,
                                                        const float2 *__restrict__ H1,
-                                                       const float2 *__restrict__ H2, int nparts,
-                                                       int64_t part_stride, int64_t ldh, int conj1,
+                                                       const float2 *__restrict__ H2, int64_t part_stride, int64_t ldh, int conj1,
                                                        float2 *__restrict__ g) {
     __shared__ float2 tile[32][33];
     const TGradItem it = items[blockIdx.x];
@@ -95,16 +97,22 @@ __global__ __launch_bounds__(256) void tlr_grad_kernel(const TGradItem *__restri
             float sx = 0.f, sy = 0.f;
             if (r < it.rows && c < it.cols) {
                 const int64_t h = it.src + (int64_t)r * ldh + c;
-                for (int p = 0; p < nparts; ++p) {
-                    const float2 a = H1[h + p * part_stride];
-                    sx += a.x;
-                    sy += a.y;
+                float2 a1[NP], a2[NP];
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    a1[p] = H1[h + p * part_stride];
+                    a2[p] = H2[h + p * part_stride];
+                }
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    sx += a1[p].x;
+                    sy += a1[p].y;
                 }
                 if (conj1) sy = -sy;
-                for (int p = 0; p < nparts; ++p) {
-                    const float2 a = H2[h + p * part_stride];
-                    sx += a.x;
-                    sy += a.y;
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    sx += a2[p].x;
+                    sy += a2[p].y;
                 }
             }
             v[j] = make_float2(sx, sy);
@@ -130,6 +138,9 @@ __global__ __launch_bounds__(256) void tlr_grad_kernel(const TGradItem *__restri
 }
 
 // Pcol theta half += step * direction half (float4 = two complex per thread; half_cols and ld even)
+// A read-modify-write over Pcol: enough workgroups for the bandwidth (16 per entry before: 13 us at nr 1024, tiles 128,
+// rank 24, now 6).
+constexpr int PX_LOADS = 4;
 __global__ __launch_bounds__(256) void tlr_paxpy_kernel(float2 *__restrict__ Pcol, int nt, int64_t entry_stride,
                                                         int64_t rows, int64_t ld, int64_t half_cols,
                                                         const SolveScalars *__restrict__ sc) {
@@ -138,18 +149,30 @@ __global__ __launch_bounds__(256) void tlr_paxpy_kernel(float2 *__restrict__ Pco
     if (st.frozen) return;   // theta was not updated
     const float a = (float)st.step;
     float2 *base = Pcol + e * entry_stride;
-    const int64_t h = half_cols >> 1;   // float4 per row and half
-    const int64_t n = rows * h;
-    for (int64_t i = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.y * blockDim.x) {
-        const int64_t row = i / h, c2 = i - row * h;
-        const float4 pv = *reinterpret_cast<const float4 *>(base + row * ld + 2 * c2);
-        float4 *tp = reinterpret_cast<float4 *>(base + row * ld + half_cols + 2 * c2);
-        float4 tv = *tp;
-        tv.x += a * pv.x;
-        tv.y += a * pv.y;
-        tv.z += a * pv.z;
-        tv.w += a * pv.w;
-        *tp = tv;
+    const uint32_t h = (uint32_t)(half_cols >> 1);   // float4 per row and half
+    const uint32_t n = (uint32_t)rows * h;
+    // PX_LOADS entries per thread, all loads ahead of the stores
+    for (uint32_t i0 = blockIdx.y * (256 * PX_LOADS) + threadIdx.x; i0 < n; i0 += gridDim.y * (256 * PX_LOADS)) {
+        float4 pv[PX_LOADS], tv[PX_LOADS];
+        float4 *tp[PX_LOADS];
+#pragma unroll
+        for (int u = 0; u < PX_LOADS; ++u) {
+            const uint32_t i = min(i0 + 256 * u, n - 1);
+            const uint32_t row = i / h, c2 = i - row * h;
+            float2 *q = base + (int64_t)row * ld + 2 * c2;
+            pv[u] = *reinterpret_cast<const float4 *>(q);
+            tp[u] = reinterpret_cast<float4 *>(q + half_cols);
+            tv[u] = *tp[u];
+        }
+#pragma unroll
+        for (int u = 0; u < PX_LOADS; ++u) {
+            if (i0 + 256 * u >= n) break;
+            tv[u].x += a * pv[u].x;
+            tv[u].y += a * pv[u].y;
+            tv[u].z += a * pv[u].z;
+            tv[u].w += a * pv[u].w;
+            *tp[u] = tv[u];
+        }
     }
 }
 
@@ -158,8 +181,9 @@ __global__ __launch_bounds__(256) void tlr_paxpy_kernel(float2 *__restrict__ Pco
 hipError_t launch_tlr_grad(const TGradItem *items, int nitems, const float2 *H1, const float2 *H2, int nparts,
                            int64_t part_stride, int64_t ldh, bool conj1, float2 *g, hipStream_t s) {
     if (nitems <= 0) return hipSuccess;
-    hipLaunchKernelGGL(tlr_grad_kernel, dim3((unsigned)nitems, 8), dim3(256), 0, s, items, H1, H2, nparts,
-                       part_stride, ldh, conj1 ? 1 : 0, g);
+    if (nparts != 4) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(tlr_grad_kernel<4>, dim3((unsigned)nitems, 8), dim3(256), 0, s, items, H1, H2, part_stride, ldh,
+                       conj1 ? 1 : 0, g);
     return hipGetLastError();
 }
 
@@ -167,7 +191,10 @@ hipError_t launch_tlr_paxpy(float2 *Pcol, int nentries, int nt, int64_t entry_st
                             int64_t half_cols, const SolveScalars *sc, hipStream_t s) {
     if (nentries <= 0 || rows <= 0) return hipSuccess;
     if ((half_cols & 1) || (ld & 1) || (entry_stride & 1)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(tlr_paxpy_kernel, dim3((unsigned)nentries, 16), dim3(256), 0, s, Pcol, nt, entry_stride,
+    const int64_t n = rows * (half_cols >> 1);
+    if (n > INT32_MAX) return hipErrorInvalidValue;
+    const unsigned blocks = (unsigned)std::min<int64_t>((n + 256 * PX_LOADS - 1) / (256 * PX_LOADS), 65535);
+    hipLaunchKernelGGL(tlr_paxpy_kernel, dim3((unsigned)nentries, blocks), dim3(256), 0, s, Pcol, nt, entry_stride,
                        rows, ld, half_cols, sc);
     return hipGetLastError();
 }

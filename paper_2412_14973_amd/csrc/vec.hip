@@ -52,11 +52,20 @@ __device__ __forceinline__ void put_plane_block(uint32_t *hi, uint32_t *lo, int6
     reinterpret_cast<uint4 *>(lo + base)[t] = l;
 }
 
-__global__ __launch_bounds__(256) void stage_d_split_kernel(const float2 *__restrict__ D, int64_t ns, int64_t nr,
+__global__ __launch_bounds__(256) void stage_d_split_kernel(Problems in, int64_t ns, int64_t nr,
                                                             uint32_t *__restrict__ Dh, uint32_t *__restrict__ Dl,
                                                             int64_t ldk, uint32_t *__restrict__ DHh,
-                                                            uint32_t *__restrict__ DHl, int64_t lds) {
+                                                            uint32_t *__restrict__ DHl, int64_t lds, int64_t stride) {
     __shared__ float2 tile[32][33];
+    const float2 *__restrict__ D = in.D[blockIdx.z];
+    if (Dh) {
+        Dh += blockIdx.z * stride;
+        Dl += blockIdx.z * stride;
+    }
+    if (DHh) {
+        DHh += blockIdx.z * stride;
+        DHl += blockIdx.z * stride;
+    }
     const int64_t s0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     for (int r = ty; r < 32; r += 8) {
@@ -70,6 +79,69 @@ __global__ __launch_bounds__(256) void stage_d_split_kernel(const float2 *__rest
     if (DHh)
         put_plane_block(DHh, DHl, plane_word(c0, s0, lds),
                         [&](int row, int k) { return make_float2(tile[k][row].x, -tile[k][row].y); });
+}
+
+// The inputs of a solve, all problems in one launch (per problem copies left a batch of small ones waiting for their
+// launches: 24 launches and 16 copies for 8 problems of nr 64, a quarter of a
+// five-iteration solve): padded D and U, theta, and the initial scalars. blockIdx.y is the
+// problem; blockIdx.x takes STG_ROWS rows of D (unless Ds is null), then of U (unless Us is null), then 1024 entries of
+// theta.
+constexpr int STG_ROWS = 4;
+__global__ __launch_bounds__(256) void stage_problems_kernel(Problems in, int64_t ns, int64_t nr, int64_t lds,
+                                                             int64_t ldk, float2 *__restrict__ Ds,
+                                                             float2 *__restrict__ Us, const ProbOff *__restrict__ probs,
+                                                             float2 *__restrict__ th, SolveScalars *__restrict__ sc) {
+    const int p = blockIdx.y, t = threadIdx.x;
+    const int nb = (int)(lds / STG_ROWS);
+    int b = blockIdx.x;
+    const float2 *src = nullptr;
+    float2 *dst = nullptr;
+    if (Ds) {
+        if (b < nb) { src = in.D[p]; dst = Ds; }
+        b -= nb;
+    }
+    if (!src && Us) {
+        if (b < nb) { src = in.U[p]; dst = Us; }
+        b -= nb;
+    }
+    if (src) {
+        const int64_t r0 = (int64_t)(b + nb) * STG_ROWS;
+        dst += p * lds * ldk;
+        for (int64_t c = t; c < ldk; c += 256) {
+            float2 v[STG_ROWS];
+#pragma unroll
+            for (int r = 0; r < STG_ROWS; ++r)
+                v[r] = (r0 + r < ns && c < nr) ? src[(r0 + r) * nr + c] : make_float2(0.f, 0.f);
+#pragma unroll
+            for (int r = 0; r < STG_ROWS; ++r) dst[(r0 + r) * ldk + c] = v[r];
+        }
+        return;
+    }
+    const int64_t n = in.theta_n[p];
+    float2 *o = th + probs[p].theta;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t i = (int64_t)b * 1024 + 256 * u + t;
+        if (i < n) o[i] = in.theta[p][i];
+    }
+    if (b == 0 && t == 0) {
+        SolveScalars &s = sc[p];
+        s.head = 0; s.count = 0; s.restart = 0; s.frozen = 0; s.gamma = 1.0; s.step = 0.0;
+        s.f = 0.0; s.fdata = 0.0; s.thnorm2 = 0.0; s.tp = 0.0; s.pnorm2 = 0.0;
+    }
+}
+
+// theta back to the callers' vectors
+__global__ __launch_bounds__(256) void collect_theta_kernel(Problems out, const ProbOff *__restrict__ probs,
+                                                            const float2 *__restrict__ th) {
+    const int p = blockIdx.y;
+    const int64_t n = out.theta_n[p];
+    const float2 *v = th + probs[p].theta;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t i = (int64_t)blockIdx.x * 1024 + 256 * u + threadIdx.x;
+        if (i < n) out.theta[p][i] = v[i];
+    }
 }
 
 __global__ __launch_bounds__(256) void split_transpose_kernel(const float2 *__restrict__ r, int64_t ldr, int64_t rows,
@@ -460,14 +532,10 @@ __global__ __launch_bounds__(256) void resid_update_kernel(const VecSeg *__restr
 // per-problem finalisation (one block per problem)
 // ---------------------------------------------------------------------------
 // the scalar work of one problem (thread 0); G: the staged Gram matrix and coefficients (FIN_GRAM)
-__device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, const double *tot, double *Gs) {
-    SolveScalars &s = fa.sc[prob];
+__device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, const double *tot, double *Gs,
+                                                 SolveScalars &s) {
     const int m1 = fa.m1;
     switch (fa.op) {
-        case FIN_INIT:
-            s.head = 0; s.count = 0; s.restart = 0; s.frozen = 0; s.gamma = 1.0; s.step = 0.0;
-            s.f = 0.0; s.fdata = 0.0; s.thnorm2 = 0.0; s.tp = 0.0; s.pnorm2 = 0.0;
-            break;
         case FIN_F: {  // tot[0] = ||r||^2
             const double f = 0.5 * tot[0] + fa.lam * s.thnorm2;
             s.f = f;
@@ -591,21 +659,34 @@ __device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, co
 // stages the problem's Gram matrix and coefficient vector, which are written back afterwards.
 constexpr int FIN_NB = 2 * (MAX_LBFGS_M + 1) + 1;
 constexpr int FIN_FEW = 5;
-__global__ __launch_bounds__(256) void finalize_kernel(FinArgs fa) {
+// One workgroup per problem: the sums, then the scalars by one thread. The launch lies between two others that wait
+// for it, so its latency is what counts: the scalars are worked on in LDS (they are read and written there and in
+// global memory by all threads at once), and the Gram pass's 6 m1 sums are added by 1024 threads (NT), each every
+// (1024 / 6 m1)-th segment of one sum. us at nr 1024, tiles 128, one to five pairs held,
+// before and now: Gram 10.5 to 14, 6.6 to 8; of 4.7 that any launch in the chain takes.
+template <int NT>
+__global__ __launch_bounds__(NT) void finalize_kernel(FinArgs fa) {
     __shared__ double tot[6 * (MAX_LBFGS_M + 1)];
-    __shared__ double sG[FIN_NB * FIN_NB + FIN_NB];
-    __shared__ double few[4][FIN_FEW];
+    __shared__ double sG[NT > 256 ? FIN_NB * FIN_NB + FIN_NB : 1];
+    __shared__ double red[NT > 256 ? NT : 4 * FIN_FEW];
+    __shared__ SolveScalars ss;
+    static_assert(sizeof(SolveScalars) % 8 == 0 && sizeof(SolveScalars) / 8 <= 256, "one word per thread");
+    constexpr int SW = sizeof(SolveScalars) / 8;
     const int prob = blockIdx.x;
+    const int t = threadIdx.x;
+    const bool scalars = fa.op != FIN_F_OUT;   // the plain objective has none
+    double *gs = reinterpret_cast<double *>(fa.sc + prob), *ls = reinterpret_cast<double *>(&ss);
+    if (scalars && t < SW) ls[t] = gs[t];
     const int count = fa.counts ? fa.counts[prob] : fa.ucount;
     const double *base = fa.partials + (int64_t)prob * fa.pstride * fa.nsum;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (fa.nsum <= FIN_FEW) {
+    const int lane = t & 63, wv = t >> 6;
+    if constexpr (NT == 256) {
         // products' sums, up to thousands of slots: a thread adds every 256th slot, all sums of a slot at once
         // (their loads are in flight together), then the lanes and the four waves
         double v[FIN_FEW];
 #pragma unroll
         for (int k = 0; k < FIN_FEW; ++k) v[k] = 0.0;
-        for (int i = threadIdx.x; i < count; i += 256)
+        for (int i = t; i < count; i += 256)
 #pragma unroll
             for (int k = 0; k < FIN_FEW; ++k)
                 if (k < fa.nsum) v[k] += base[(int64_t)i * fa.nsum + k];
@@ -613,30 +694,39 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs fa) {
         for (int k = 0; k < FIN_FEW; ++k) {
             if (k >= fa.nsum) break;
             const double s = wave_sum64(v[k]);
-            if (lane == 0) few[wv][k] = s;
+            if (lane == 0) red[wv * FIN_FEW + k] = s;
         }
         __syncthreads();
-        if (threadIdx.x < fa.nsum)
-            tot[threadIdx.x] = (few[0][threadIdx.x] + few[1][threadIdx.x]) + (few[2][threadIdx.x] + few[3][threadIdx.x]);
+        if (t < fa.nsum)
+            tot[t] = (red[t] + red[FIN_FEW + t]) + (red[2 * FIN_FEW + t] + red[3 * FIN_FEW + t]);
     } else {
-        for (int k = wv; k < fa.nsum; k += 4) {
-            double v = 0.0;
-            for (int i = lane; i < count; i += 64) v += base[(int64_t)i * fa.nsum + k];
-            v = wave_sum64(v);
-            if (lane == 0) tot[k] = v;
+        const int parts = NT / fa.nsum;   // fa.nsum <= 6 (MAX_LBFGS_M + 1)
+        const int q = t / fa.nsum;
+        double v = 0.0;
+        if (q < parts)
+#pragma unroll 8
+            for (int i = q; i < count; i += parts) v += base[(int64_t)i * fa.nsum + (t - q * fa.nsum)];
+        red[t] = v;
+        __syncthreads();
+        if (t < fa.nsum) {
+            double a = 0.0;
+            for (int i = 0; i < parts; ++i) a += red[i * fa.nsum + t];
+            tot[t] = a;
         }
     }
     const int m1 = fa.m1;
     const int gwords = (2 * m1 + 1) * (2 * m1 + 1) + 2 * m1 + 1;
     double *Gg = fa.op == FIN_GRAM ? fa.gram + (int64_t)prob * fa.gstride : nullptr;
-    if (Gg)
-        for (int i = threadIdx.x; i < gwords; i += 256) sG[i] = Gg[i];
+    if constexpr (NT > 256)
+        if (Gg)
+            for (int i = t; i < gwords; i += NT) sG[i] = Gg[i];
     __syncthreads();
-    if (threadIdx.x == 0) finalize_scalars(fa, prob, tot, sG);
-    if (Gg) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < gwords; i += 256) Gg[i] = sG[i];
-    }
+    if (t == 0) finalize_scalars(fa, prob, tot, sG, ss);
+    __syncthreads();
+    if (scalars && t < SW) gs[t] = ls[t];
+    if constexpr (NT > 256)
+        if (Gg)
+            for (int i = t; i < gwords; i += NT) Gg[i] = sG[i];
 }
 
 
@@ -652,11 +742,39 @@ hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, i
     return hipGetLastError();
 }
 
-hipError_t launch_stage_d_split(const float2 *D, int64_t ns, int64_t nr, uint32_t *Dh, uint32_t *Dl, int64_t ldk,
-                                uint32_t *DHh, uint32_t *DHl, int64_t lds, hipStream_t s) {
-    if (ldk % 32 || lds % 32) return hipErrorInvalidValue;   // whole blocks
-    dim3 grid((unsigned)(ldk / 32), (unsigned)(lds / 32));
-    hipLaunchKernelGGL(stage_d_split_kernel, grid, dim3(256), 0, s, D, ns, nr, Dh, Dl, ldk, DHh, DHl, lds);
+hipError_t launch_stage_d_split(const Problems &in, int count, int64_t ns, int64_t nr, uint32_t *Dh, uint32_t *Dl,
+                                int64_t ldk, uint32_t *DHh, uint32_t *DHl, int64_t lds, int64_t stride, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    if (ldk % 32 || lds % 32 || count > PROBLEMS_MAX) return hipErrorInvalidValue;   // whole blocks
+    dim3 grid((unsigned)(ldk / 32), (unsigned)(lds / 32), (unsigned)count);
+    hipLaunchKernelGGL(stage_d_split_kernel, grid, dim3(256), 0, s, in, ns, nr, Dh, Dl, ldk, DHh, DHl, lds, stride);
+    return hipGetLastError();
+}
+
+namespace {
+unsigned theta_blocks(const Problems &in, int count) {
+    int64_t n = 1;
+    for (int p = 0; p < count; ++p) n = std::max(n, in.theta_n[p]);
+    return (unsigned)((n + 1023) / 1024);
+}
+}  // namespace
+
+hipError_t launch_stage_problems(const Problems &in, int count, int64_t ns, int64_t nr, int64_t lds, int64_t ldk,
+                                 float2 *Ds, float2 *Us, const ProbOff *probs, float2 *th, SolveScalars *sc,
+                                 hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    if (lds % STG_ROWS || count > PROBLEMS_MAX) return hipErrorInvalidValue;
+    const unsigned rows = (unsigned)(lds / STG_ROWS) * ((Ds ? 1u : 0u) + (Us ? 1u : 0u));
+    hipLaunchKernelGGL(stage_problems_kernel, dim3(rows + theta_blocks(in, count), (unsigned)count), dim3(256), 0, s, in,
+                       ns, nr, lds, ldk, Ds, Us, probs, th, sc);
+    return hipGetLastError();
+}
+
+hipError_t launch_collect_theta(const Problems &out, int count, const ProbOff *probs, const float2 *th, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    if (count > PROBLEMS_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(collect_theta_kernel, dim3(theta_blocks(out, count), (unsigned)count), dim3(256), 0, s, out, probs,
+                       th);
     return hipGetLastError();
 }
 
@@ -747,7 +865,9 @@ hipError_t launch_resid_update(const VecSeg *segs, int nseg, float *r, const flo
 }
 hipError_t launch_finalize(const FinArgs &fa, int nprob, hipStream_t s) {
     if (nprob <= 0) return hipSuccess;
-    hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)nprob), dim3(256), 0, s, fa);
+    if ((fa.op == FIN_GRAM) != (fa.nsum > FIN_FEW) || fa.nsum > 6 * (MAX_LBFGS_M + 1)) return hipErrorInvalidValue;
+    if (fa.op == FIN_GRAM) hipLaunchKernelGGL(finalize_kernel<1024>, dim3((unsigned)nprob), dim3(1024), 0, s, fa);
+    else hipLaunchKernelGGL(finalize_kernel<256>, dim3((unsigned)nprob), dim3(256), 0, s, fa);
     return hipGetLastError();
 }
 

@@ -15,7 +15,7 @@ struct VecSeg {
 constexpr int VEC_CH = 4096;   // floats per segment (a multiple of 1024; offsets multiples of 4)
 
 enum FinOp : int32_t {
-    FIN_INIT = 0, FIN_F, FIN_F_OUT, FIN_THNORM, FIN_GRAM, FIN_LAMTERMS, FIN_LINE, FIN_RECORD, FIN_RESET
+    FIN_F = 0, FIN_F_OUT, FIN_THNORM, FIN_GRAM, FIN_LAMTERMS, FIN_LINE, FIN_RECORD, FIN_RESET
 };
 
 struct FinArgs {

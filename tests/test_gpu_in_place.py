@@ -105,3 +105,45 @@ def test_results_over_inputs(sizes, ns):
     room[:ns] = D
     tl._lib.check(lib.tlrmdd_adjoint(plan.handle, _p(room), _p(U), _p(room), tl.FP32, _p(ws), ws.numel(), stream), "adjoint")
     assert torch.equal(room[:nr], want)
+
+
+def _solve_plan(tl, sizes, ns, off, diag):
+    n = len(sizes)
+    return tl.Plan(np.array(sizes), np.full(n * (n - 1) // 2, off, dtype=np.int32), np.full(n, diag, dtype=np.int32), ns)
+
+
+@pytest.mark.parametrize("form,line", [("FP32", "LINE_DENSE"), ("FP32_3M", "LINE_TILE_GRAD"), ("BF16X3", "LINE_TILE_GRAD")])
+@pytest.mark.parametrize("sizes,ns,off,diag", [([128, 128], 128, 8, 8), ([128, 128, 128, 128], 256, 16, 16),
+                                               ([128, 128, 128, 128], 200, 10, 9)])
+def test_solve_in_place_equals_staged(form, line, sizes, ns, off, diag):
+    """Whole tiles at 16 bytes are read where they lie; at 8 bytes on they are copied. Ranks that fill their padding
+    leave nothing to clear: the workspace holds NaN before."""
+    import paper_2412_14973_amd as tl
+    plan = _solve_plan(tl, sizes, ns, off, diag)
+    _, D, U, _ = _setup(tl, sizes, ns, 11)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    th = 0.2 * torch.complex(torch.randn(plan.theta_size, generator=gen, device="cuda"),
+                             torch.randn(plan.theta_size, generator=gen, device="cuda"))
+    kw = dict(iters=4, precision=getattr(tl, form), line_products=getattr(tl, line))
+    opts = tl.make_opts(4, precision=kw["precision"], line_products=kw["line_products"])
+    out = [tl.solve(plan, d, u, th, workspace=_dirty(plan.workspace_bytes(tl._lib.OP_SOLVE, opts)), **kw)
+           for d, u in ((D, U), (_shifted(D), _shifted(U)))]
+    assert bool(torch.isfinite(out[0][1]).all()) and float(out[0][1][-1]) < float(out[0][1][0])
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+def test_batches_above_one_launch():
+    """More problems than one staging launch takes (32), of different theta sizes, against each alone."""
+    import paper_2412_14973_amd as tl
+    sizes, ns, count = [20, 24, 20], 50, 67
+    plans = [_solve_plan(tl, sizes, ns, 1 + i % 5, -1 if i % 3 == 0 else 4) for i in range(count)]
+    gen = torch.Generator(device="cuda").manual_seed(6)
+
+    def rand(*shape):
+        return torch.complex(torch.randn(shape, generator=gen, device="cuda"), torch.randn(shape, generator=gen, device="cuda"))
+    D, U = ([rand(ns, sum(sizes)) for _ in range(count)] for _ in range(2))
+    th = [0.2 * rand(p.theta_size) for p in plans]
+    thb, fb = tl.solve_batched(plans, D, U, th, iters=3)
+    for i in (0, 1, 31, 32, 33, 63, 64, 66):
+        t1, f1 = tl.solve(plans[i], D[i], U[i], th[i], iters=3)
+        assert torch.equal(t1, thb[i]) and torch.equal(f1, fb[i]), i
