@@ -328,11 +328,15 @@ def tile_split(nr, d):
     return np.array([d] * (nr // d) + ([nr % d] if nr % d else []), dtype=np.int32)
 
 
-def _ranks_workspace(nr, d, device):
+def _ranks_workspace_bytes(nr, d):
     n = ctypes.c_size_t()
     _lib.check(_lib.load().tlrmdd_workspace_bytes_ranks(int(nr), int(d), ctypes.byref(n)),
                "tlrmdd_workspace_bytes_ranks")
-    return torch.empty(max(int(n.value), 1), dtype=torch.uint8, device=device)
+    return int(n.value)
+
+
+def _ranks_workspace(nr, d, device, extra=0):
+    return torch.empty(max(_ranks_workspace_bytes(nr, d) + extra, 1), dtype=torch.uint8, device=device)
 
 
 def tile_ranks(X, d, eps=0.01):
@@ -360,7 +364,11 @@ def choose_layout(X, candidates, eps=0.01):
     rd = np.zeros(nmax, dtype=np.int32)
     ent = np.zeros(len(cand), dtype=np.int64)
     dsel = ctypes.c_int32()
-    ws = _ranks_workspace(nr, int(cand.max()), X.device)
+    # the largest candidate's workspace, and room beside it for the others: all of them in one pass then
+    top = int(cand.max())
+    ws = _ranks_workspace(nr, top, X.device, sum(
+        48 * nr * len(tile_split(nr, int(d))) + 4096 if d <= 128 else _ranks_workspace_bytes(nr, int(d))
+        for d in cand if d != top) + 4096)
     _lib.check(_lib.load().tlrmdd_choose_layout(_ptr(X), nr, cand.ctypes.data, len(cand), float(eps),
                                                 ctypes.byref(dsel), ent.ctypes.data, ro.ctypes.data, ro.size,
                                                 rd.ctypes.data, rd.size, _ptr(ws), ws.numel(), _stream()),

@@ -2381,6 +2381,8 @@ namespace {
 
 struct SvdHost {
     std::vector<SvdTile> tiles;
+    std::vector<int32_t> first;     // several grids (svd_grids): the first tile of each, and the total; else empty
+    int gathered = 0;               // tiles (from the first on) that the counts read from W
     std::vector<int32_t> pair_tile;
     int64_t nW = 0, nV = 0, nS = 0;
     int maxnp = 2;
@@ -2390,7 +2392,7 @@ struct SvdHost {
 void svd_add_tile(SvdHost &S, int m, int n, int64_t row0, int64_t col0, bool with_v, bool jacobi = true) {
     SvdTile t;
     t.trans = m < n ? 1 : 0;   // decompose the transpose of a wide tile: A is never wider than tall
-    t.pad = 0;
+    t.grid = 0;
     if (t.trans) std::swap(m, n);
     t.m = m;
     t.n = n;
@@ -2428,6 +2430,34 @@ SvdHost svd_grid(int64_t nr, int d, bool with_v) {
     return S;
 }
 
+// The grids of several tile sizes as one list of tiles, for the counts (no Jacobi tables): the grids of larger tiles
+// first, whose workgroups run longest. order[g]: the candidate that grid g belongs to.
+SvdHost svd_grids(int64_t nr, const int32_t *cand, int ncand, std::vector<int> &order) {
+    order.resize(ncand);
+    for (int c = 0; c < ncand; ++c) order[c] = c;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cand[a] > cand[b]; });
+    SvdHost S;
+    for (int g = 0; g < ncand; ++g) {
+        const SvdHost one = svd_grid(nr, cand[order[g]], false);
+        S.first.push_back((int32_t)S.tiles.size());
+        int mmax = 0;
+        for (const SvdTile &t : one.tiles) mmax = std::max(mmax, t.m);
+        const bool in_w = !bidiag_reads_x(mmax);   // else W only takes the bidiagonals' squares
+        for (SvdTile t : one.tiles) {
+            t.grid = g;
+            t.offW = S.nW;
+            t.offS += S.nS;
+            S.nW += in_w ? (int64_t)t.m * t.n : t.n / 2 + 1;
+            S.tiles.push_back(t);
+        }
+        S.nS += one.nS;
+        if (in_w) S.gathered = (int)S.tiles.size();
+    }
+    S.first.push_back((int32_t)S.tiles.size());
+    S.pair_tile = S.first;   // uploaded in its place
+    return S;
+}
+
 struct SvdWs {
     double2 *W = nullptr, *V = nullptr;
     double *sig = nullptr, *v0 = nullptr;
@@ -2450,7 +2480,7 @@ SvdWs svd_carve(char *base, const SvdHost &S, int nitems) {
     w.sig = (double *)take((size_t)S.nS * sizeof(double));
     w.order = (int32_t *)take((size_t)S.nS * sizeof(int32_t));
     w.kout = (int32_t *)take(S.tiles.size() * sizeof(int32_t));
-    w.v0 = (double *)take(sizeof(double));
+    w.v0 = (double *)take(std::max<size_t>(S.first.size(), 2) / 2 * 2 * sizeof(double));
     w.flags = (int32_t *)take(2 * sizeof(int32_t));
     w.tiles = (SvdTile *)take(S.tiles.size() * sizeof(SvdTile));
     w.pair_tile = (int32_t *)take(S.pair_tile.size() * sizeof(int32_t));
@@ -2499,25 +2529,28 @@ int svd_upload(const SvdHost &S, const SvdWs &w, const std::vector<WarmItem> *it
 // finite tiles of at most BIDIAG_MAX_M rows; done = false leaves the rest to svd_run (a tile with a value that is
 // not finite, where the rotations still give the other columns' values; larger tiles, whose two reads and one write
 // per step of one workgroup would take as long as the rotations spread over the chip).
+// v0: one per grid of S.
 int svd_counts(const SvdHost &S, const SvdWs &w, const float2 *X, int64_t ldx, double eps, std::vector<int32_t> &k,
-               double &v0, bool &done, hipStream_t s) {
+               double *v0, bool &done, hipStream_t s) {
     int mmax = 0;
     for (const SvdTile &t : S.tiles) mmax = std::max(mmax, t.m);
     if (mmax > BIDIAG_MAX_M) return TLRMDD_OK;
     const int nt = (int)S.tiles.size();
-    int st = svd_upload(S, w, nullptr, s, false);
+    const int ngrids = S.first.empty() ? 1 : (int)S.first.size() - 1;
+    const int ng = ngrids > 1 ? S.gathered : bidiag_reads_x(mmax) ? 0 : nt;
+    int st = svd_upload(S, w, nullptr, s, ngrids > 1);
     if (st) return st;
     HIP_TRY(launch_fill_zero(w.flags, 2 * sizeof(int32_t), s));
-    if (!bidiag_in_lds(mmax)) HIP_TRY(launch_svd_gather(w.tiles, nt, X, ldx, w.W, nullptr, w.flags, s));
-    HIP_TRY(launch_bidiag(w.tiles, nt, mmax, X, ldx, w.W, w.sig, w.flags, s));
-    HIP_TRY(launch_svd_counts(w.tiles, nt, w.W, w.sig, eps, w.kout, w.v0, s));
+    HIP_TRY(launch_svd_gather(w.tiles, ng, X, ldx, w.W, nullptr, w.flags, s));
+    HIP_TRY(launch_bidiag(w.tiles, nt, ngrids > 1, mmax, X, ldx, w.W, w.sig, w.flags, s));
+    HIP_TRY(launch_svd_counts(w.tiles, nt, ngrids > 1 ? w.pair_tile : nullptr, ngrids, w.W, w.sig, eps, w.kout, w.v0, s));
     // kout, v0 and the flags lie one after the other: one copy
     std::vector<char> out((char *)(w.flags + 1) - (char *)w.kout);
     HIP_TRY(hipMemcpyAsync(out.data(), w.kout, out.size(), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     int32_t nonfinite = 0;
     std::memcpy(&nonfinite, out.data() + ((char *)w.flags - (char *)w.kout), sizeof(nonfinite));
-    std::memcpy(&v0, out.data() + ((char *)w.v0 - (char *)w.kout), sizeof(v0));
+    std::memcpy(v0, out.data() + ((char *)w.v0 - (char *)w.kout), ngrids * sizeof(double));
     std::memcpy(k.data(), out.data(), k.size() * sizeof(int32_t));
     done = nonfinite == 0;
     return TLRMDD_OK;
@@ -2532,6 +2565,16 @@ int check_rank_args(const void *X, int64_t nr, int32_t d, double eps) {
 }
 
 // ranks of all tiles at size d into host vectors (t order / diagonal order); synchronises the stream
+// counts in tile order to ranks below and on the diagonal
+void split_ranks(const int32_t *k, int N, std::vector<int32_t> &koff, std::vector<int32_t> &kdiag) {
+    koff.clear();
+    kdiag.assign(N, 0);
+    for (int i = 0; i < N; ++i) {
+        for (int j = 0; j < i; ++j) koff.push_back(k[(size_t)i * (i + 1) / 2 + j]);
+        kdiag[i] = k[(size_t)i * (i + 1) / 2 + i];
+    }
+}
+
 int tile_ranks_impl(const void *X, int64_t nr, int32_t d, double eps, std::vector<int32_t> &koff,
                     std::vector<int32_t> &kdiag, double *v0, void *workspace, size_t ws_bytes, hipStream_t s) {
     int st = check_rank_args(X, nr, d, eps);
@@ -2543,7 +2586,7 @@ int tile_ranks_impl(const void *X, int64_t nr, int32_t d, double eps, std::vecto
     std::vector<int32_t> k(S.tiles.size());
     double v = 0.0;
     bool done = false;
-    if ((st = svd_counts(S, w, (const float2 *)X, nr, eps, k, v, done, s))) return st;
+    if ((st = svd_counts(S, w, (const float2 *)X, nr, eps, k, &v, done, s))) return st;
     if (!done) {
         if ((st = svd_upload(S, w, nullptr, s))) return st;
         if ((st = svd_run(S, w, (const float2 *)X, nr, s))) return st;
@@ -2552,14 +2595,35 @@ int tile_ranks_impl(const void *X, int64_t nr, int32_t d, double eps, std::vecto
         HIP_TRY(hipMemcpyAsync(&v, w.v0, sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
     }
-    const int N = (int)split_sizes(nr, d).size();
-    koff.clear();
-    kdiag.assign(N, 0);
-    for (int i = 0; i < N; ++i) {
-        for (int j = 0; j < i; ++j) koff.push_back(k[(size_t)i * (i + 1) / 2 + j]);
-        kdiag[i] = k[(size_t)i * (i + 1) / 2 + i];
-    }
+    split_ranks(k.data(), (int)split_sizes(nr, d).size(), koff, kdiag);
     if (v0) *v0 = v;
+    return TLRMDD_OK;
+}
+
+// Counts for every candidate in one pass over the device, where all of them take the same kernel and the workspace
+// holds them side by side (it need only hold the largest); done = false: one after the other then.
+int all_ranks(const void *X, int64_t nr, const int32_t *cand, int ncand, double eps,
+              std::vector<std::vector<int32_t>> &ko, std::vector<std::vector<int32_t>> &kd, bool &done, void *workspace,
+              size_t ws_bytes, hipStream_t s) {
+    done = false;
+    if (ncand < 2 || !workspace) return TLRMDD_OK;
+    for (int c = 0; c < ncand; ++c)
+        if (check_rank_args(X, nr, cand[c], eps) || !bidiag_shared(std::min<int64_t>(cand[c], nr))) {
+            g_last_error.clear();   // the first bad candidate reports it in its turn
+            return TLRMDD_OK;
+        }
+    std::vector<int> order;
+    const SvdHost S = svd_grids(nr, cand, ncand, order);
+    const SvdWs w = svd_carve((char *)workspace, S, 0);
+    if (w.bytes > ws_bytes) return TLRMDD_OK;
+    std::vector<int32_t> k(S.tiles.size());
+    std::vector<double> v0(ncand);
+    const int st = svd_counts(S, w, (const float2 *)X, nr, eps, k, v0.data(), done, s);
+    if (st || !done) return st;
+    for (int g = 0; g < ncand; ++g) {
+        const int c = order[g];
+        split_ranks(k.data() + S.first[g], (int)split_sizes(nr, cand[c]).size(), ko[c], kd[c]);
+    }
     return TLRMDD_OK;
 }
 
@@ -2596,10 +2660,16 @@ int tlrmdd_choose_layout(const void *X, int64_t nr, const int32_t *candidates, i
     if (!candidates || ncand < 1 || !d_out || !rank_off_out || !rank_diag_out)
         return fail(TLRMDD_INVALID_ARGUMENT, "bad arguments");
     int64_t best = -1;
+    std::vector<std::vector<int32_t>> kos(ncand), kds(ncand);
+    bool done = false;
+    int st = all_ranks(X, nr, candidates, ncand, eps, kos, kds, done, workspace, ws_bytes, stream);
+    if (st) return st;
     for (int c = 0; c < ncand; ++c) {
-        std::vector<int32_t> ko, kd;
-        int st = tile_ranks_impl(X, nr, candidates[c], eps, ko, kd, nullptr, workspace, ws_bytes, stream);
-        if (st) return st;
+        std::vector<int32_t> &ko = kos[c], &kd = kds[c];
+        if (!done) {
+            st = tile_ranks_impl(X, nr, candidates[c], eps, ko, kd, nullptr, workspace, ws_bytes, stream);
+            if (st) return st;
+        }
         const std::vector<int> sz = split_sizes(nr, candidates[c]);
         // layout of the estimate: ranks >= 1; dense diagonal when k_ii >= d_i / 2
         int64_t n = 0;

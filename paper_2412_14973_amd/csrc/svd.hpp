@@ -12,7 +12,7 @@ namespace tlr {
 struct SvdTile {
     int32_t m, n;    // rows / columns of A
     int32_t trans;
-    int32_t pad;
+    int32_t grid;    // of several grids in one list of tiles (counts): which
     int64_t row0, col0;
     int64_t offW;    // W: m x n
     int64_t offV;    // V: n x n (warm start of a factored tile), -1 without V
@@ -49,15 +49,18 @@ hipError_t launch_svd_factors(const SvdTile *tiles, const WarmItem *items, int n
                               const double2 *V, const double *sig, const int32_t *order, const float2 *X,
                               int64_t ldx, float2 *theta, hipStream_t s);
 
-// Counts without vectors (bidiag.hip), tiles of at most BIDIAG_MAX_M rows (mmax: the largest). Up to 64 rows the
+// Counts without vectors (bidiag.hip), tiles of at most BIDIAG_MAX_M rows (mmax: the largest). Up to 128 rows the
 // tiles are read from X, else from W (gathered before). The squares of the bidiagonal go to d2 (sigma slots) and,
-// with the tile's largest singular value, to the start of its W.
+// with the tile's largest singular value, to the start of its W. mixed: tiles of several grids, all of which
+// bidiag_shared() says can share a launch.
 constexpr int BIDIAG_MAX_M = 512;
-bool bidiag_in_lds(int mmax);
-hipError_t launch_bidiag(const SvdTile *tiles, int ntiles, int mmax, const float2 *X, int64_t ldx, double2 *W,
+bool bidiag_reads_x(int mmax);
+bool bidiag_shared(int64_t mmax);
+hipError_t launch_bidiag(const SvdTile *tiles, int ntiles, bool mixed, int mmax, const float2 *X, int64_t ldx, double2 *W,
                          double *d2, int32_t *nonfinite, hipStream_t s);
-// v0 = the largest of them, k = #{sigma >= eps v0} per tile
-hipError_t launch_svd_counts(const SvdTile *tiles, int ntiles, const double2 *W, const double *d2, double eps,
-                             int32_t *kout, double *v0, hipStream_t s);
+// v0 = the largest of them, k = #{sigma >= eps v0} per tile, for each of ngrids lists of tiles: list g goes from
+// first[g] to first[g + 1] (first null: one list)
+hipError_t launch_svd_counts(const SvdTile *tiles, int ntiles, const int32_t *first, int ngrids, const double2 *W,
+                             const double *d2, double eps, int32_t *kout, double *v0, hipStream_t s);
 
 }  // namespace tlr

@@ -56,3 +56,56 @@ def test_rank_counts_zero_and_nonfinite():
     Y[40, 2] = np.nan
     ko, kd, v0 = tl.tile_ranks(torch.from_numpy(Y).cuda(), 32, 0.05)
     assert kd.tolist() == ref[1] and ko.tolist()[1:] == ref[0][1:] and abs(v0 - ref[2]) <= 1e-12 * ref[2]
+
+
+@pytest.mark.parametrize("nr,d", [(64, 64), (128, 128), (229, 129), (200, 200), (356, 256), (256, 192)])
+@pytest.mark.parametrize("scale", [1.0, 1e-18, 1e18])
+def test_rank_counts_in_registers(nr, d, scale):
+    """Tiles held in registers whole (to 128 rows) or from the last 128 rows on; squares of the entries' noise near the
+    ends of the range of FP64's exponents when they are scaled are not reached."""
+    import paper_2412_14973_amd as tl
+    X = (_symmetric(nr, 11 * nr + d) * scale).astype(np.complex64)
+    ko, kd, v0 = tl.tile_ranks(torch.from_numpy(X).cuda(), d, 0.02)
+    ro, rd, v0r = _reference(X, d, 0.02)
+    assert ko.tolist() == ro and kd.tolist() == rd and abs(v0 - v0r) <= 1e-13 * v0r
+
+
+@pytest.mark.parametrize("d", [48, 100, 200])
+def test_rank_counts_of_exact_low_rank(d):
+    """Rank one, and a tile of one entry: the reflections meet columns that are zero."""
+    import paper_2412_14973_amd as tl
+    a = np.exp(1j * np.arange(200)).astype(np.complex64)
+    X = np.outer(a, a).astype(np.complex64)
+    ko, kd, _ = tl.tile_ranks(torch.from_numpy(X).cuda(), d, 0.01)
+    assert set(ko.tolist()) <= {1} and set(kd.tolist()) == {1}
+    X = np.zeros((200, 200), dtype=np.complex64)
+    X[7, 7] = 3j
+    ko, kd, v0 = tl.tile_ranks(torch.from_numpy(X).cuda(), d, 0.01)
+    assert not np.any(ko) and kd.tolist() == [1] + [0] * (len(kd) - 1) and v0 == 3.0
+
+
+@pytest.mark.parametrize("nr,cand", [(300, [64, 128, 256]), (300, [100, 40]), (410, [200, 64, 256, 200]), (97, [33, 97]),
+                                     (300, [32, 64]), (600, [64, 300])])
+@pytest.mark.parametrize("bad", [False, True])
+def test_layouts_together_and_one_by_one(nr, cand, bad):
+    """All candidates in one pass (33 to 256 rows, room for all), or one after the other in the documented workspace."""
+    import ctypes
+    import paper_2412_14973_amd as tl
+    X = _symmetric(nr, 5 * nr)
+    if bad:
+        X[3, 1] = X[1, 3] = np.inf
+    X = torch.from_numpy(X).cuda()
+    d, sizes, ro, rd, ent = tl.choose_layout(X, cand, 0.02)
+    lib = tl._lib.load()
+    c = np.array(cand, dtype=np.int32)
+    ws = tl._ranks_workspace(nr, int(c.max()), X.device)
+    ro1, rd1, ent1 = np.zeros(nr * nr, dtype=np.int32), np.zeros(nr, dtype=np.int32), np.zeros(len(cand), dtype=np.int64)
+    d1 = ctypes.c_int32()
+    tl._lib.check(lib.tlrmdd_choose_layout(tl._ptr(X), nr, c.ctypes.data, len(cand), 0.02, ctypes.byref(d1),
+                                           ent1.ctypes.data, ro1.ctypes.data, ro1.size, rd1.ctypes.data, rd1.size,
+                                           tl._ptr(ws), ws.numel(), tl._stream()), "choose_layout")
+    assert d == d1.value and ent.tolist() == ent1.tolist()
+    assert ro.tolist() == ro1[:ro.size].tolist() and rd.tolist() == rd1[:rd.size].tolist()
+    ko, kd, _ = tl.tile_ranks(X, d, 0.02)
+    assert ro.tolist() == np.maximum(1, ko).tolist()
+    assert rd.tolist() == [-1 if k >= (s + 1) // 2 else max(1, k) for k, s in zip(kd.tolist(), sizes.tolist())]
