@@ -43,11 +43,16 @@ __device__ __forceinline__ void put(float2 *X, int64_t row, int64_t col, int64_t
         X[row * ldx + col] = v;
     }
 }
-// entry e of a 64 x 64 block in the order of the output: along its rows, or four entries of each row in turn
+// entry e of a 64 x 64 block in the order of the output: along its rows, or four entries of each row in turn; and how
+// many of them reach the last of the block's true rows and columns (the blocks of small tiles are mostly empty)
 template <bool OUTB>
 __device__ __forceinline__ void out_entry(int e, int &row, int &col) {
     row = OUTB ? (e >> 2) & 63 : e >> 6;
     col = OUTB ? ((e >> 8) << 2) + (e & 3) : e & 63;
+}
+template <bool OUTB>
+__device__ __forceinline__ int out_entries(int rows, int cols) {
+    return OUTB ? (cols + 3) / 4 * 256 : rows * 64;
 }
 
 constexpr int AB = ASM_B;            // block edge (rows and columns)
@@ -151,7 +156,7 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
     const float2 *PRf = DIR ? (qq ? PLf : pv + td.offB) : nullptr;
     for (int kc0 = 0; kc0 < k; kc0 += AKC) {
         const int kn = min(AKC, k - kc0);
-        for (int e = t; e < AB * AKC; e += 256) {    // row factors: rows r0.., k contiguous in theta
+        for (int e = t; e < nrow * AKC; e += 256) {    // row factors: rows r0.., k contiguous in theta
             const int rr = e / AKC, kk = e % AKC;
             const bool ok = rr < nrow && kk < kn;
             const int64_t o = (int64_t)(r0 + rr) * k + kc0 + kk;
@@ -222,13 +227,13 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
                 sTf[2 * ((32 * i + acc_row(r, lane)) * ST_P + ccol) + comp] = acc[f][i][r];
         __syncthreads();
         float2 *dst = f ? X2 : X;
-        for (int e = t; e < AB * AB; e += 256) {
+        for (int e = t; e < out_entries<OUTB>(nrow, ncol); e += 256) {
             int rr, cc;
             out_entry<OUTB>(e, rr, cc);
             if (rr < nrow && cc < ncol && (!qq || r0 + rr >= c0 + cc))
                 put<OUTB>(dst, td.row0 + r0 + rr, td.col0 + c0 + cc, ldx, low, sT[rr * ST_P + cc]);
         }
-        for (int e = t; e < AB * AB; e += 256) {
+        for (int e = t; e < out_entries<OUTB>(ncol, nrow); e += 256) {
             int rr, cc;
             out_entry<OUTB>(e, cc, rr);
             if (cc < ncol && rr < nrow && (!qq || r0 + rr > c0 + cc))
