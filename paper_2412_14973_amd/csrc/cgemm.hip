@@ -10,7 +10,7 @@
 // (AHEAD). The matrix core rate is what bounds it. Measured, TFLOP/s counted 8mnk with
 // the 128 x 128 tiles staged through LDS that this replaces in brackets: one problem of 1024^2, three
 // products: r = D X - U 58 us (252), D^H r 56 (223), [a | b] 107 (234); one of 4096 x 2048: 1500 us (1678),
-// 1537 (1547), 2957 (3077); 34 of 1024^2, four-product form 144 (144), three-product form 132 (125).
+// 1432 (1547), 2834 (3077); 34 of 1024^2, four-product form 144 (144), three-product form 136 (125).
 //   KS = 1: a workgroup is 4 waves (2 x 2) on a 64 x 64 tile, which share its operands through L1.
 //   KS = 4: a workgroup's 4 waves share one 32 x 32 block and each takes every fourth chunk of k; their
 //     sums are added in LDS in a fixed order. Four times as many waves, each a quarter as long, for
@@ -74,6 +74,9 @@ __global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
     // complex k per chunk (one round of loads). GM_LINE takes 8: its accumulators and two column blocks then
     // fit three waves per SIMD instead of two (64 problems of 512^2, split: 892 us, with 16: 957)
     constexpr int CH = BIG && M3 ? 4 : NB == 2 ? 8 : 16;
+    // k that a wave of a split contraction takes at a time, in chunks: the same for every tile, as the order of the sums
+    constexpr int UNIT = KS == 1 ? CH : MODE == GM_LINE ? 8 : 16;
+    constexpr int SUB = UNIT / CH;
 
     // workgroup -> batch entry and tile. Consecutive workgroups go to the eight XCDs in turn. Dense products:
     // contiguous tile ranges of an entry per XCD; tile stages, whose entries are small: whole entries per XCD,
@@ -210,38 +213,39 @@ __global__ __launch_bounds__(256, BIG ? 2 : 3) void cgemm_kernel(GemmArgs g) {
         }
     };
 
-    // the chunks of this wave: first, first + KS, ...; GM_LINE tile stages: b over the first K2 k only
+    // the chunks of this wave: every KS-th unit's; GM_LINE tile stages: b over the first K2 k only
     constexpr bool SPLIT_K2 = MODE == GM_LINE && STAGE;
     const bool inside = m0 < g.Mt && n0 < g.Nt;
-    const int nc = inside ? g.K / CH : 0;
+    const int own = KS == 1 ? 0 : wave;
+    const int nc = inside ? (g.K / UNIT - own + KS - 1) / KS * SUB : 0;
     const int nc2 = (SPLIT_K2 && g.K2 > 0) ? g.K2 / CH : nc;
-    const int first = KS == 1 ? 0 : wave;
+    auto k_at = [&](int c) { return KS == 1 ? c * CH : (c / SUB * KS + own) * UNIT + c % SUB * CH; };
     auto chunks = [&](int c, int end, auto nb_tag) {
         Chunk<TA, HB, NB, CH> r0, r1;
         constexpr bool B2 = decltype(nb_tag)::value > 1;
-        if (c < end) load(r0, c * CH, B2);
+        if (c < end) load(r0, k_at(c), B2);
         if constexpr (AHEAD) {
-            for (; c + KS < end; c += 2 * KS) {
-                load(r1, (c + KS) * CH, B2);
+            for (; c + 1 < end; c += 2) {
+                load(r1, k_at(c + 1), B2);
                 __builtin_amdgcn_sched_barrier(SCHED_ALU);
                 compute(r0, nb_tag);
-                load(r0, min(c + 2 * KS, end - 1) * CH, B2);
+                load(r0, k_at(min(c + 2, end - 1)), B2);
                 __builtin_amdgcn_sched_barrier(SCHED_ALU);
                 compute(r1, nb_tag);
             }
             if (c < end) compute(r0, nb_tag);
         } else {
-            for (; c < end; c += 2 * KS) {
-                if (c + KS < end) load(r1, (c + KS) * CH, B2);
+            for (; c < end; c += 2) {
+                if (c + 1 < end) load(r1, k_at(c + 1), B2);
                 compute(r0, nb_tag);
-                if (c + KS < end) {
-                    if (c + 2 * KS < end) load(r0, (c + 2 * KS) * CH, B2);
+                if (c + 1 < end) {
+                    if (c + 2 < end) load(r0, k_at(c + 2), B2);
                     compute(r1, nb_tag);
                 }
             }
         }
     };
-    chunks(first, nc2, std::integral_constant<int, NB>{});
+    chunks(0, nc2, std::integral_constant<int, NB>{});
     if constexpr (SPLIT_K2) chunks(nc2, nc, std::integral_constant<int, 1>{});
 
     EpiArgs ea;
@@ -293,32 +297,43 @@ hipError_t go(const GemmArgs &a, int batch, hipStream_t s) {
     return hipGetLastError();
 }
 
-// C = AB in wave tiles of 2 x 2 blocks (128 x 128 per workgroup, the same results): half the operand traffic
-// per product, for two waves per SIMD instead of four. Pays where the k loop is long against prologue and
-// epilogue and the workgroups fill the chip twice (two per CU): D^H r of 8 problems of 4096 x 2048 11.6 ms
-// (12.2), of one 1.455 (1.508), but the stages of 12 tile-128 problems (K = 128) 870 us (852). The other
-// epilogues lose with it: r = D X - U 13.6 ms (12.2), [a | b] 23.6 (23.1).
-constexpr int64_t BIG_MIN_WG = 1024;
+// Wave tiles of 2 x 2 blocks, in GM_LINE of two row blocks of a and of b: half the operand traffic per product, for two
+// waves per SIMD instead of three or four. They pay where the workgroups fill the chip more than twice (KS = 1; two
+// per CU, and a split block's are shorter: four times) and the k loop is long against prologue and epilogue. The results
+// are the same. us without and with them, three products:
+//   GM_STORE: D^H r of 8 problems of 4096 x 2048 12.2 and 11.6 ms, of one 1.508 and 1.455, but the stages of 12 problems of
+//     tiles 128 (K = 128) 852 and 870 us; split, 16 problems of 1024^2 789 and 748, 64 of 512^2 437 and 410.
+//   GM_RESID, split only: 812 and 773, 468 and 437. (A wave alone has too few registers for its epilogue: 1490 and 1488
+//     for 4096 x 2048, four products 996 and 1020 for 16 problems of 1024^2.)
+//   GM_LINE: 4096 x 2048 2930 and 2834; split 1560 and 1505, 875 and 825, one problem of 1600^2 (1250 workgroups) 407
+//     and 429. Tile stages 940 and 930 at most, four products within 1 %.
+constexpr int64_t BIG_MIN_WG = 1024, BIG_MIN_WG_SPLIT = 2048;
 constexpr int BIG_MIN_K = 256;
-template <bool M3, int ROLE>
-hipError_t go_store(GemmArgs a, int batch, hipStream_t s) {
-    if (a.M % 128 == 0 && a.N % 128 == 0 && a.K >= BIG_MIN_K &&
-        (int64_t)(a.tiles_m / 2) * (a.tiles_n / 2) * batch >= BIG_MIN_WG) {
-        a.tiles_m /= 2;
-        a.tiles_n /= 2;
-        return go<GM_STORE, M3, ROLE, 1, true>(a, batch, s);
+template <int MODE, bool M3, int ROLE, int KS>
+hipError_t go_big(GemmArgs a, int batch, hipStream_t s) {
+    constexpr int WT = KS == 1 ? 64 : 32;   // the launcher's tiles
+    constexpr bool DENSE3 = M3 && (ROLE == GR_DENSE || ROLE == GR_ADJOINT);
+    if constexpr (MODE == GM_STORE ? KS == 1 || DENSE3 : DENSE3 && (MODE == GM_LINE || KS > 1)) {
+        const bool wide = MODE != GM_LINE;   // two blocks of columns too; GM_LINE has a's and b's
+        if (a.M % (2 * WT) == 0 && a.N % (wide ? 2 * WT : WT) == 0 && a.K >= BIG_MIN_K &&
+            (int64_t)(a.tiles_m / 2) * (wide ? a.tiles_n / 2 : a.tiles_n) * batch >=
+                (KS == 1 ? BIG_MIN_WG : BIG_MIN_WG_SPLIT)) {
+            a.tiles_m /= 2;
+            if (wide) a.tiles_n /= 2;
+            return go<MODE, M3, ROLE, KS, true>(a, batch, s);
+        }
     }
-    return go<GM_STORE, M3, ROLE, 1>(a, batch, s);
+    return go<MODE, M3, ROLE, KS>(a, batch, s);
 }
 
 template <bool M3>
 hipError_t go_dense(int mode, const GemmArgs &a, int batch, hipStream_t s, int role, bool split) {
     if (role == GR_ADJOINT)
-        return split ? go<GM_STORE, M3, GR_ADJOINT, 4>(a, batch, s) : go_store<M3, GR_ADJOINT>(a, batch, s);
+        return split ? go_big<GM_STORE, M3, GR_ADJOINT, 4>(a, batch, s) : go_big<GM_STORE, M3, GR_ADJOINT, 1>(a, batch, s);
     switch (mode) {
-        case GM_STORE: return split ? hipErrorInvalidValue : go_store<M3, GR_DENSE>(a, batch, s);
-        case GM_RESID: return split ? go<GM_RESID, M3, GR_DENSE, 4>(a, batch, s) : go<GM_RESID, M3, GR_DENSE, 1>(a, batch, s);
-        case GM_LINE: return split ? go<GM_LINE, M3, GR_DENSE, 4>(a, batch, s) : go<GM_LINE, M3, GR_DENSE, 1>(a, batch, s);
+        case GM_STORE: return split ? hipErrorInvalidValue : go_big<GM_STORE, M3, GR_DENSE, 1>(a, batch, s);
+        case GM_RESID: return split ? go_big<GM_RESID, M3, GR_DENSE, 4>(a, batch, s) : go<GM_RESID, M3, GR_DENSE, 1>(a, batch, s);
+        case GM_LINE: return split ? go_big<GM_LINE, M3, GR_DENSE, 4>(a, batch, s) : go_big<GM_LINE, M3, GR_DENSE, 1>(a, batch, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -365,9 +380,9 @@ hipError_t launch_cgemm(int mode, const GemmArgs &a0, int batch, hipStream_t s, 
     a.bytesA = (uint32_t)bytesA;
     a.bytesB = (uint32_t)bytesB;
     if (!stage) return m3 ? go_dense<true>(mode, a, batch, s, role, split) : go_dense<false>(mode, a, batch, s, role, split);
-    if (role == GR_TILE_TA_CB) return go_store<true, GR_TILE_TA_CB>(a, batch, s);
+    if (role == GR_TILE_TA_CB) return go_big<GM_STORE, true, GR_TILE_TA_CB, 1>(a, batch, s);
     switch (mode) {
-        case GM_STORE: return go_store<true, GR_TILE>(a, batch, s);
+        case GM_STORE: return go_big<GM_STORE, true, GR_TILE, 1>(a, batch, s);
         case GM_RESID: return go<GM_RESID, true, GR_TILE, 1>(a, batch, s);
         case GM_LINE: return go<GM_LINE, true, GR_TILE, 1>(a, batch, s);
         default: return hipErrorInvalidValue;

@@ -92,10 +92,14 @@ def test_bf16_products_entry_by_entry(nr, ns):
     assert bool((err <= bound).all()), float((err / bound).max())
 
 
-def test_bf16_tiles_agree_bit_for_bit():
+# one block per wave alone, two by two in the batch (BF16: from 256 tiles of 64 x 64 on, here 56 a problem; three
+# FP32 products: from 2048 workgroups on, here 128 a problem for [a | b])
+@pytest.mark.parametrize("form,count", [("BF16X3", 8), ("FP32_3M", 33), ("FP32", 33)])
+def test_tiles_agree_bit_for_bit(form, count):
     """A wave's tile (one block of 32 x 32, or two by two) follows the launch; the sums do not."""
     import paper_2412_14973_amd as tl
-    nr, ns, count = 450, 420, 8   # 49 tiles of 64 x 64 a problem: one block per wave alone, two by two in the batch
+    nr, ns = 450, 420
+    prec = getattr(tl, form)
     plans = [tl.Plan(np.array([150, 150, 150]), np.full(3, 4, dtype=np.int32), np.full(3, 5, dtype=np.int32), ns)
              for _ in range(count)]
     gen = torch.Generator(device="cuda").manual_seed(3)
@@ -104,10 +108,10 @@ def test_bf16_tiles_agree_bit_for_bit():
         return torch.complex(torch.randn(shape, generator=gen, device="cuda"), torch.randn(shape, generator=gen, device="cuda"))
     D, U = ([rand(ns, nr) for _ in range(count)] for _ in range(2))
     th = [0.1 * rand(plans[0].theta_size) for _ in range(count)]
-    alone = [tl.solve(p, d, u, t, iters=4, precision=tl.BF16X3) for p, d, u, t in zip(plans, D, U, th)]
-    thb, fb = tl.solve_batched(plans, D, U, th, iters=4, precision=tl.BF16X3)
-    for i in range(count):
-        assert torch.equal(alone[i][0], thb[i]) and torch.equal(alone[i][1], fb[i])
+    thb, fb = tl.solve_batched(plans, D, U, th, iters=4, precision=prec, resid_refresh=2)
+    for i in range(0, count, 7):
+        t1, f1 = tl.solve(plans[i], D[i], U[i], th[i], iters=4, precision=prec, resid_refresh=2)
+        assert torch.equal(t1, thb[i]) and torch.equal(f1, fb[i])
 
 
 def test_bf16_unsplit_solve():
