@@ -298,17 +298,17 @@ hipError_t go(const GemmArgs &a, int batch, hipStream_t s) {
 }
 
 // Wave tiles of 2 x 2 blocks, in GM_LINE of two row blocks of a and of b: half the operand traffic per product, for two
-// waves per SIMD instead of three or four. They pay where the workgroups fill the chip more than twice (KS = 1; two
-// per CU, and a split block's are shorter: four times) and the k loop is long against prologue and epilogue. The results
-// are the same. us without and with them, three products:
-//   GM_STORE: D^H r of 8 problems of 4096 x 2048 12.2 and 11.6 ms, of one 1.508 and 1.455, but the stages of 12 problems of
-//     tiles 128 (K = 128) 852 and 870 us; split, 16 problems of 1024^2 789 and 748, 64 of 512^2 437 and 410.
+// waves per SIMD instead of three or four. They pay where the workgroups fill the chip (KS = 1: two per CU; a split
+// block's are shorter: four times) and the k loop is long against prologue and epilogue. The results are the same. us without and with them, three products:
+//   GM_STORE: D^H r of 8 problems of 4096 x 2048 12.2 and 11.6 ms, of one 1.508 and 1.455; the gradient
+//     stages of 8 problems of 1024^2, tiles 128, rank 16 (512 workgroups, K = 128 and 256) 184 and 171 us, stage 1 of the
+//     line products with rank 24 (K = 128) 13 of 550 us less; split, 16 problems of 1024^2 789 and 748, 64 of 512^2 437 and 410.
 //   GM_RESID, split only: 812 and 773, 468 and 437. (A wave alone has too few registers for its epilogue: 1490 and 1488
 //     for 4096 x 2048, four products 996 and 1020 for 16 problems of 1024^2.)
 //   GM_LINE: 4096 x 2048 2930 and 2834; split 1560 and 1505, 875 and 825, one problem of 1600^2 (1250 workgroups) 407
 //     and 429. Tile stages 940 and 930 at most, four products within 1 %.
-constexpr int64_t BIG_MIN_WG = 1024, BIG_MIN_WG_SPLIT = 2048;
-constexpr int BIG_MIN_K = 256;
+constexpr int64_t BIG_MIN_WG = 512, BIG_MIN_WG_SPLIT = 2048;
+constexpr int BIG_MIN_K = 128;
 template <int MODE, bool M3, int ROLE, int KS>
 hipError_t go_big(GemmArgs a, int batch, hipStream_t s) {
     constexpr int WT = KS == 1 ? 64 : 32;   // the launcher's tiles
