@@ -493,7 +493,7 @@ struct Ws {
     float *th = nullptr, *g0 = nullptr, *g1 = nullptr, *p = nullptr, *S = nullptr, *Y = nullptr;
     double *gram = nullptr;   // per problem: Gram matrix of the L-BFGS basis and direction coefficients
     float *z = nullptr, *u = nullptr, *cen = nullptr;   // ADMM
-    double *partials = nullptr;
+    double *partials = nullptr, *fpartials = nullptr;
     SolveScalars *sc = nullptr;
     char *tables = nullptr;
     size_t bytes = 0;
@@ -542,6 +542,7 @@ Ws carve(char *base, int op, int nprob, int64_t ldk, int64_t lds, int64_t theta_
     }
     // sums per slot: one (objective) or, in a solve, up to five (line search) and 6 m1 (Gram pass)
     w.partials = (double *)take((size_t)nprob * pstride * (op >= 2 ? std::max(5, 6 * m1) : 1) * sizeof(double));
+    if (op >= 2) w.fpartials = (double *)take((size_t)nprob * pstride * sizeof(double));   // of the residual update
     w.sc = (SolveScalars *)take((size_t)nprob * sizeof(SolveScalars));
     w.tables = take(tbytes);
     w.bytes = o;
@@ -1229,8 +1230,8 @@ void set_precision(Ctx &c, int precision) {
     c.split = gemm_split_k(c.nr, c.ns);
 }
 
-int fin(const Ctx &c, FinArgs f, const int32_t *counts, int ucount, int nsum) {
-    f.partials = c.w.partials;
+int fin(const Ctx &c, FinArgs f, const int32_t *counts, int ucount, int nsum, const double *partials = nullptr) {
+    f.partials = partials ? partials : c.w.partials;
     f.pstride = c.pstride;
     f.counts = counts;
     f.ucount = ucount;
@@ -1528,7 +1529,8 @@ int line_products_tile(Run &R, const LineSeg &sg, bool dir_only = false) {
 
 // Gradient of the problems of a tile range in tile form (see GRAD_TILE_MAX_COST), into g. Needs the
 // theta half of Pcol for the current theta.
-int tile_gradient(Run &R, const LineSeg &sg, float *g) {
+// packed: the B^H blocks of the current theta are in place (tile_pcol_update).
+int tile_gradient(Run &R, const LineSeg &sg, float *g, bool packed) {
     const Ctx c = line_ctx(R.c, sg.p0, sg.np);
     const LineTile &L = sg.lt;
     const LineClass &lc = L.lc;
@@ -1536,9 +1538,10 @@ int tile_gradient(Run &R, const LineSeg &sg, float *g) {
     const int KS = GRAD_TILE_KS;
     const int64_t Kc = c.lds / KS;
     const double ks = L.ksum, dd = (double)d, ns = (double)c.ns, nr = (double)c.nr, np = c.nprob;
-    HIP_TRY(timed(TLRMDD_K_LINE_PACK, c.s, bytes_work(16.0 * dd * ks), [&] {
-        return launch_tlr_pack(L.gpack, L.ngpack, (const float2 *)c.w.th, L.PBH, c.s, nullptr, 2);
-    }));
+    if (!packed)
+        HIP_TRY(timed(TLRMDD_K_LINE_PACK, c.s, bytes_work(16.0 * dd * ks), [&] {
+            return launch_tlr_pack(L.gpack, L.ngpack, (const float2 *)c.w.th, L.PBH, c.s, nullptr, 2);
+        }));
     GemmArgs g1 = gemm_args();   // G1: S_(p,j) = r_p[:, j d ...] PBH_(p,j), stored as Scol_(p,i)[:, j kp ...]
     g1.A = c.w.r; g1.lda = c.ldk; g1.sA = c.lds * c.ldk; g1.sA2 = d;
     g1.B = L.PBH; g1.ldb = Wg; g1.sB = nt * d * Wg; g1.sB2 = d * Wg;
@@ -1601,14 +1604,16 @@ int tile_resid(Run &R, const LineSeg &sg) {
     return TLRMDD_OK;
 }
 
-// After the update theta += step p: the theta half of Pcol follows (P_th += step P_p).
-int tile_pcol_update(Run &R, const LineSeg &sg) {
+// After the update theta += step p: the theta half of Pcol follows (P_th += step P_p), and with pack the B^H blocks
+// for the next gradient.
+int tile_pcol_update(Run &R, const LineSeg &sg, bool pack) {
     const Ctx c = line_ctx(R.c, sg.p0, sg.np);
     const LineTile &L = sg.lt;
     const int64_t nt = L.lc.nt;
-    HIP_TRY(timed(TLRMDD_K_LINE_PACK, c.s, bytes_work(24.0 * (double)c.ns * L.ksum), [&] {
+    const double bytes = 24.0 * (double)c.ns * L.ksum + (pack ? 16.0 * (double)L.lc.d * L.ksum : 0.0);
+    HIP_TRY(timed(TLRMDD_K_LINE_PACK, c.s, bytes_work(bytes), [&] {
         return launch_tlr_paxpy(L.Pcol, (int)(c.nprob * nt), (int)nt, c.lds * L.NA, c.lds, L.NA, nt * L.lc.kpad,
-                                c.w.sc + sg.p0, c.s);
+                                c.w.sc + sg.p0, L.gpack, pack ? L.ngpack : 0, (const float2 *)c.w.th, L.PBH, c.s);
     }));
     return TLRMDD_OK;
 }
@@ -1623,15 +1628,18 @@ int clear_plane_padding(Run &R) {
 }
 
 // record < 0: no f-history entry
-int fin_f(Run &R, int record, double lam, int nsum_parts) {
+void set_record(const Run &R, FinArgs &f, int record) {
+    if (record < 0) return;
+    f.fhist = R.single ? nullptr : R.c.D.fhist;
+    f.fhist0 = R.fhist0;
+    f.t = record;
+}
+
+int fin_f(Run &R, int record, double lam, int nsum_parts, const double *partials = nullptr) {
     FinArgs f = fin_args(FIN_F, R.c.w.sc);
-    if (record >= 0) {
-        f.fhist = R.single ? nullptr : R.c.D.fhist;
-        f.fhist0 = R.fhist0;
-        f.t = record;
-    }
+    set_record(R, f, record);
     f.lam = lam;
-    return fin(R.c, f, nullptr, nsum_parts, 1);
+    return fin(R.c, f, nullptr, nsum_parts, 1, partials);
 }
 
 // r = D C(theta) - U afresh: assembly and the dense product for the problems before the tile-form
@@ -1799,6 +1807,10 @@ int run_setup(Run &R, int op, int nprob, const tlrmdd_plan *plans, const void *c
     return TLRMDD_OK;
 }
 
+// Up to so many segments of r (4096 floats each: 16 MB) r and theta are updated by one launch: a launch that waits for
+// the one before takes about 5 us, more than theta's update. Above, each has its own (and its own statistics).
+constexpr int UPDATE_TOGETHER = 1024;
+
 // `iters` iterations of L-BFGS (or steepest descent) with exact line search on
 //   f(theta) + lam ||theta - cen||^2     (cen == NULL: the plain Frobenius term; lam == 0: f alone)
 // from the current theta and tracked residual, with fresh pair memory. f-history entries go to
@@ -1819,6 +1831,8 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
     for (const LineSeg &sg : R.segs)
         if (sg.tile && sg.lt.lc.grad && iters > 0 && !R.fresh_p)   // (just formed with the residual otherwise)
             if ((st = tile_stage1(R, sg, c.w.th))) return st;
+    constexpr int F_NONE = INT32_MIN;
+    int f_due = F_NONE;   // the record of an objective whose partial sums wait in fpartials
     for (int t = 0; t < iters; ++t) {
         // gradient from the tracked residual (eqs. DXLR): W = D^H r and the tile blocks of W' for the
         // problems before the tile-form gradient ranges, the tile form for those
@@ -1826,7 +1840,7 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
         // push each other out of the caches - 16 problems of 1024^2, 11.1 ms a solve against 10.0)
         for (const LineSeg &sg : R.segs)
             if (sg.tile && sg.lt.lc.grad)
-                if ((st = tile_gradient(R, sg, R.gcur))) return st;
+                if ((st = tile_gradient(R, sg, R.gcur, t > 0))) return st;
         if (R.n_adj > 0) {
             const Ctx ca = R.n_adj == c.nprob ? c : line_ctx(c, 0, R.n_adj);
             if ((st = gemm_adjoint(ca, c.w.r, c.ldk, R.X1, c.ldk, R.xstride))) return st;
@@ -1856,6 +1870,12 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
             f.m1 = m1;
             f.gram = c.w.gram;
             f.gstride = gram_stride(m1);
+            if (f_due != F_NONE) {
+                set_record(R, f, f_due);
+                f.fpartials = c.w.fpartials;
+                f.fcount = R.T.rseg_per_prob;
+                f_due = F_NONE;
+            }
             if ((st = fin(c, f, c.D.tcount, 0, 6 * m1))) return st;
             HIP_TRY(timed(TLRMDD_K_COMBINE, s, bytes_work(8.0 * th_all * (2.0 + 2.0 * std::min(t, R.m))), [&] {
                 return launch_combine(c.D.tsegs, nt, m1, c.w.p, R.gcur, c.w.S, c.w.Y, R.stride2, c.w.sc,
@@ -1897,30 +1917,45 @@ int run_iterate(Run &R, int iters, double lam, const float *cen, int record_base
             f.lam = lam;
             if ((st = fin(c, f, nullptr, partial_slots(c), 5))) return st;
         }
-        // updates
-        HIP_TRY(timed(TLRMDD_K_THETA_UPDATE, s,
-                      bytes_work(8.0 * R.theta_pre.back() * ((R.lbfgs ? 4.0 : 3.0) + (cen ? 1.0 : 0.0))), [&] {
-                          return launch_theta_update(c.D.tsegs, nt, c.w.th, c.w.p, R.lbfgs ? c.w.S : nullptr,
-                                                     R.stride2, cen, c.w.sc, c.w.partials, s);
-                      }));
+        // updates. The residual is recomputed from theta every resid_refresh iterations, else updated in place; the
+        // B^H blocks for the next gradient are packed where P_th follows theta; without a penalty term f goes on
+        // record beside the next Gram sums
+        const bool refresh = R.opts->resid_refresh > 0 && (t + 1) % R.opts->resid_refresh == 0;
+        const int rec = record_base >= 0 ? record_base + t + 1 : -1;
+        const bool last = t + 1 == iters;
+        const bool together = !refresh && lam == 0.0 && R.nrs <= UPDATE_TOGETHER;
+        const double rbytes = 32.0 * (double)c.ns * (double)c.nr * c.nprob;
+        const double tbytes = 8.0 * R.theta_pre.back() * ((R.lbfgs ? 4.0 : 3.0) + (cen ? 1.0 : 0.0));
+        if (together) {
+            HIP_TRY(timed(TLRMDD_K_RESID_UPDATE, s, bytes_work(rbytes + tbytes), [&] {
+                return launch_update(c.D.rsegs, R.nrs, c.D.tsegs, nt, (float *)c.w.r, (const float *)c.w.a,
+                                     (const float *)c.w.b, c.w.th, c.w.p, R.lbfgs ? c.w.S : nullptr, R.stride2, c.w.sc,
+                                     c.w.fpartials, s);
+            }));
+        } else {
+            HIP_TRY(timed(TLRMDD_K_THETA_UPDATE, s, bytes_work(tbytes), [&] {
+                return launch_theta_update(c.D.tsegs, nt, c.w.th, c.w.p, R.lbfgs ? c.w.S : nullptr, R.stride2, cen,
+                                           c.w.sc, c.w.partials, s);
+            }));
+        }
         for (const LineSeg &sg : R.segs)
             if (sg.tile && sg.lt.lc.grad)
-                if ((st = tile_pcol_update(R, sg))) return st;
+                if ((st = tile_pcol_update(R, sg, !last))) return st;
         if (lam != 0.0)
             if ((st = fin(c, fin_args(FIN_THNORM, c.w.sc), c.D.tcount, 0, 1))) return st;
-        // residual: recomputed from theta every resid_refresh iterations, else updated in place
-        const bool refresh = R.opts->resid_refresh > 0 && (t + 1) % R.opts->resid_refresh == 0;
         if (refresh) {
-            if ((st = objective_fresh(R, record_base >= 0 ? record_base + t + 1 : -1, lam))) return st;
+            if ((st = objective_fresh(R, rec, lam))) return st;
         } else {
-            HIP_TRY(timed(TLRMDD_K_RESID_UPDATE, s, bytes_work(32.0 * (double)c.ns * (double)c.nr * c.nprob), [&] {
-                return launch_resid_update(c.D.rsegs, R.nrs, (float *)c.w.r, (const float *)c.w.a,
-                                           (const float *)c.w.b, c.w.sc, c.w.partials, s);
-            }));
+            if (!together)
+                HIP_TRY(timed(TLRMDD_K_RESID_UPDATE, s, bytes_work(rbytes), [&] {
+                    return launch_resid_update(c.D.rsegs, R.nrs, (float *)c.w.r, (const float *)c.w.a,
+                                               (const float *)c.w.b, c.w.sc, c.w.fpartials, s);
+                }));
             Ctx ca = c;   // the problems whose gradient is the dense adjoint product
             ca.nprob = R.n_adj;
             if (ca.nprob > 0 && (st = split_r_transpose(ca))) return st;
-            if ((st = fin_f(R, record_base >= 0 ? record_base + t + 1 : -1, lam, R.T.rseg_per_prob))) return st;
+            if (R.lbfgs && lam == 0.0 && !last) f_due = rec;
+            else if ((st = fin_f(R, rec, lam, R.T.rseg_per_prob, c.w.fpartials))) return st;
         }
         std::swap(R.gcur, R.gprev);
     }

@@ -23,11 +23,8 @@ namespace tlr {
 namespace {
 
 // one packed block per work item: dst[r * ldd + c] = op(src) for r < rows, c < cols
-__global__ __launch_bounds__(256) void tlr_pack_kernel(const PackItem *__restrict__ items,
-                                                       const float2 *__restrict__ theta,
-                                                       const float2 *__restrict__ theta2,
-                                                       float2 *__restrict__ dst_base) {
-    const PackItem it = items[blockIdx.x];
+__device__ __forceinline__ void pack_item(const PackItem &it, const float2 *__restrict__ theta,
+                                          const float2 *__restrict__ theta2, float2 *__restrict__ dst_base, int by, int gy) {
     float2 *dst = dst_base + it.dst;
     const float2 *src = (it.from ? theta2 : theta) + it.src;
     if (it.op == PACK_TRANS || it.op == PACK_CTRANS) {
@@ -36,7 +33,7 @@ __global__ __launch_bounds__(256) void tlr_pack_kernel(const PackItem *__restric
         const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
         const int ntr = (it.rows + 31) / 32, ntc = (it.cols + 31) / 32;
         const float sgn = it.op == PACK_CTRANS ? -1.f : 1.f;
-        for (int q = blockIdx.y; q < ntr * ntc; q += gridDim.y) {
+        for (int q = by; q < ntr * ntc; q += gy) {
             const int r0 = (q / ntc) * 32, c0 = (q % ntc) * 32;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -57,7 +54,7 @@ __global__ __launch_bounds__(256) void tlr_pack_kernel(const PackItem *__restric
         return;
     }
     const int64_t n = (int64_t)it.rows * it.cols;
-    for (int64_t e = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.y * blockDim.x) {
+    for (int64_t e = (int64_t)by * 256 + threadIdx.x; e < n; e += (int64_t)gy * 256) {
         const int r = (int)(e / it.cols), c = (int)(e % it.cols);
         float2 v;
         switch (it.op) {
@@ -72,6 +69,13 @@ __global__ __launch_bounds__(256) void tlr_pack_kernel(const PackItem *__restric
         }
         dst[(int64_t)r * it.ldd + c] = v;
     }
+}
+
+__global__ __launch_bounds__(256) void tlr_pack_kernel(const PackItem *__restrict__ items,
+                                                       const float2 *__restrict__ theta,
+                                                       const float2 *__restrict__ theta2,
+                                                       float2 *__restrict__ dst_base) {
+    pack_item(items[blockIdx.x], theta, theta2, dst_base, blockIdx.y, gridDim.y);
 }
 
 // Gradient blocks of the tile form from the partial planes of its two products (fixed summation
@@ -141,10 +145,9 @@ __global__ __launch_bounds__(256) void tlr_grad_kernel(const TGradItem *__restri
 // A read-modify-write over Pcol: enough workgroups for the bandwidth (16 per entry before: 13 us at nr 1024, tiles 128,
 // rank 24, now 6).
 constexpr int PX_LOADS = 4;
-__global__ __launch_bounds__(256) void tlr_paxpy_kernel(float2 *__restrict__ Pcol, int nt, int64_t entry_stride,
-                                                        int64_t rows, int64_t ld, int64_t half_cols,
-                                                        const SolveScalars *__restrict__ sc) {
-    const int e = blockIdx.x;
+__device__ __forceinline__ void paxpy(float2 *__restrict__ Pcol, int nt, int64_t entry_stride, int64_t rows, int64_t ld,
+                                      int64_t half_cols, const SolveScalars *__restrict__ sc, int e, uint32_t by,
+                                      uint32_t gy) {
     const SolveScalars &st = sc[e / nt];
     if (st.frozen) return;   // theta was not updated
     const float a = (float)st.step;
@@ -152,7 +155,7 @@ __global__ __launch_bounds__(256) void tlr_paxpy_kernel(float2 *__restrict__ Pco
     const uint32_t h = (uint32_t)(half_cols >> 1);   // float4 per row and half
     const uint32_t n = (uint32_t)rows * h;
     // PX_LOADS entries per thread, all loads ahead of the stores
-    for (uint32_t i0 = blockIdx.y * (256 * PX_LOADS) + threadIdx.x; i0 < n; i0 += gridDim.y * (256 * PX_LOADS)) {
+    for (uint32_t i0 = by * (256 * PX_LOADS) + threadIdx.x; i0 < n; i0 += gy * (256 * PX_LOADS)) {
         float4 pv[PX_LOADS], tv[PX_LOADS];
         float4 *tp[PX_LOADS];
 #pragma unroll
@@ -176,6 +179,18 @@ __global__ __launch_bounds__(256) void tlr_paxpy_kernel(float2 *__restrict__ Pco
     }
 }
 
+// with the packing of the next gradient's operands from the updated theta in the same launch (npx blocks of the
+// update, then two per packing item)
+__global__ __launch_bounds__(256) void tlr_paxpy_kernel(float2 *__restrict__ Pcol, int nt, int64_t entry_stride,
+                                                        int64_t rows, int64_t ld, int64_t half_cols,
+                                                        const SolveScalars *__restrict__ sc, int npx, int per_entry,
+                                                        const PackItem *__restrict__ items,
+                                                        const float2 *__restrict__ theta, float2 *__restrict__ dst) {
+    const int b = blockIdx.x;
+    if (b < npx) paxpy(Pcol, nt, entry_stride, rows, ld, half_cols, sc, b / per_entry, b % per_entry, per_entry);
+    else pack_item(items[(b - npx) >> 1], theta, theta, dst, (b - npx) & 1, 2);
+}
+
 }  // namespace
 
 hipError_t launch_tlr_grad(const TGradItem *items, int nitems, const float2 *H1, const float2 *H2, int nparts,
@@ -188,14 +203,16 @@ hipError_t launch_tlr_grad(const TGradItem *items, int nitems, const float2 *H1,
 }
 
 hipError_t launch_tlr_paxpy(float2 *Pcol, int nentries, int nt, int64_t entry_stride, int64_t rows, int64_t ld,
-                            int64_t half_cols, const SolveScalars *sc, hipStream_t s) {
+                            int64_t half_cols, const SolveScalars *sc, const PackItem *items, int nitems,
+                            const float2 *theta, float2 *dst, hipStream_t s) {
     if (nentries <= 0 || rows <= 0) return hipSuccess;
     if ((half_cols & 1) || (ld & 1) || (entry_stride & 1)) return hipErrorInvalidValue;
     const int64_t n = rows * (half_cols >> 1);
     if (n > INT32_MAX) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)std::min<int64_t>((n + 256 * PX_LOADS - 1) / (256 * PX_LOADS), 65535);
-    hipLaunchKernelGGL(tlr_paxpy_kernel, dim3((unsigned)nentries, blocks), dim3(256), 0, s, Pcol, nt, entry_stride,
-                       rows, ld, half_cols, sc);
+    const int64_t blocks = std::min<int64_t>((n + 256 * PX_LOADS - 1) / (256 * PX_LOADS), 65535), npx = nentries * blocks;
+    if (npx + 2 * (int64_t)nitems > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(tlr_paxpy_kernel, dim3((unsigned)(npx + 2 * nitems)), dim3(256), 0, s, Pcol, nt, entry_stride, rows,
+                       ld, half_cols, sc, (int)npx, (int)blocks, items, theta, dst);
     return hipGetLastError();
 }
 

@@ -37,8 +37,10 @@ hipError_t launch_tlr_grad(const TGradItem *items, int nitems, const float2 *H1,
 // (nt kpad) per entry at Pcol + e * entry_stride (direction half at column 0, theta half at column
 // half_cols, row pitch ld); entry e belongs to problem e / nt, whose step and frozen flag are in sc.
 struct SolveScalars;
+// In the same launch nitems packing items (as launch_tlr_pack with two blocks each; 0: none) from theta to dst.
 hipError_t launch_tlr_paxpy(float2 *Pcol, int nentries, int nt, int64_t entry_stride, int64_t rows, int64_t ld,
-                            int64_t half_cols, const SolveScalars *sc, hipStream_t s);
+                            int64_t half_cols, const SolveScalars *sc, const PackItem *items, int nitems,
+                            const float2 *theta, float2 *dst, hipStream_t s);
 
 // blocks_per_item: workgroups that share one item (grid-stride over its elements or 32 x 32 tiles)
 hipError_t launch_tlr_pack(const PackItem *items, int nitems, const float2 *theta, float2 *dst, hipStream_t s,

@@ -3,6 +3,8 @@
 // search, updates). All reductions are FP64, deterministic (fixed-order
 // per-segment partials, then one fixed-order tree per problem), with no
 // atomics. Scalars never leave the device.
+#include <cstddef>
+
 #include "common.hpp"
 #include "exact_step.hpp"
 #include "vec.hpp"
@@ -469,13 +471,10 @@ __global__ __launch_bounds__(256) void admm_update_kernel(const VecSeg *__restri
 }
 
 // theta += step p ; S[head] = step p ; partial ||theta - c||^2 (c = 0 when cen is NULL)
-__global__ __launch_bounds__(256) void theta_update_kernel(const VecSeg *__restrict__ segs, float *__restrict__ th,
-                                                           const float *__restrict__ p, float *__restrict__ Sb,
-                                                           int64_t stride2, const float *__restrict__ cen,
-                                                           const SolveScalars *__restrict__ sc,
-                                                           double *__restrict__ part) {
-    __shared__ double red[4];
-    const VecSeg sg = segs[blockIdx.x];
+// theta += step p (and the newest s pair); part: |theta - cen|^2 of the segment, or null
+__device__ __forceinline__ void theta_update(const VecSeg &sg, float *__restrict__ th, const float *__restrict__ p,
+                                             float *__restrict__ Sb, int64_t stride2, const float *__restrict__ cen,
+                                             const SolveScalars *__restrict__ sc, double *__restrict__ part, double *red) {
     // the vector loads need the segment only: they are in flight while the step is read
     V16 v = ld16(th, sg);
     V16 sp = ld16(p, sg);
@@ -492,6 +491,7 @@ __global__ __launch_bounds__(256) void theta_update_kernel(const VecSeg *__restr
         st16(th, sg, v);
         if (Sb) st16(Sb + s.head * stride2, sg, sp);
     }
+    if (!part) return;
     if (cen) {
         const V16 c = ld16(cen, sg);
 #pragma unroll
@@ -502,13 +502,10 @@ __global__ __launch_bounds__(256) void theta_update_kernel(const VecSeg *__restr
     if (threadIdx.x == 0) part[sg.part] = acc[0];
 }
 
-// r += step a + step^2 b ; partial ||r||^2
-__global__ __launch_bounds__(256) void resid_update_kernel(const VecSeg *__restrict__ segs, float *__restrict__ r,
-                                                           const float *__restrict__ a, const float *__restrict__ b,
-                                                           const SolveScalars *__restrict__ sc,
-                                                           double *__restrict__ part) {
-    __shared__ double red[4];
-    const VecSeg sg = segs[blockIdx.x];
+// r += step a + step^2 b; part: |r|^2 of the segment
+__device__ __forceinline__ void resid_update(const VecSeg &sg, float *__restrict__ r, const float *__restrict__ a,
+                                             const float *__restrict__ b, const SolveScalars *__restrict__ sc,
+                                             double *__restrict__ part, double *red) {
     // the vector loads need the segment only: they are in flight while the step is read
     V16 v = ld16(r, sg);
     const V16 va = ld16(a, sg), vb = ld16(b, sg);
@@ -528,22 +525,67 @@ __global__ __launch_bounds__(256) void resid_update_kernel(const VecSeg *__restr
     if (threadIdx.x == 0) part[sg.part] = acc[0];
 }
 
+__global__ __launch_bounds__(256) void theta_update_kernel(const VecSeg *__restrict__ segs, float *__restrict__ th,
+                                                           const float *__restrict__ p, float *__restrict__ Sb,
+                                                           int64_t stride2, const float *__restrict__ cen,
+                                                           const SolveScalars *__restrict__ sc,
+                                                           double *__restrict__ part) {
+    __shared__ double red[4];
+    theta_update(segs[blockIdx.x], th, p, Sb, stride2, cen, sc, part, red);
+}
+
+__global__ __launch_bounds__(256) void resid_update_kernel(const VecSeg *__restrict__ segs, float *__restrict__ r,
+                                                           const float *__restrict__ a, const float *__restrict__ b,
+                                                           const SolveScalars *__restrict__ sc,
+                                                           double *__restrict__ part) {
+    __shared__ double red[4];
+    resid_update(segs[blockIdx.x], r, a, b, sc, part, red);
+}
+
+// both in one launch (no penalty term: the sums of theta are not wanted), the first nr blocks for r
+__global__ __launch_bounds__(256) void update_kernel(const VecSeg *__restrict__ rsegs, int nr, const VecSeg *__restrict__ tsegs,
+                                                     float *__restrict__ r, const float *__restrict__ a,
+                                                     const float *__restrict__ b, float *__restrict__ th,
+                                                     const float *__restrict__ p, float *__restrict__ Sb, int64_t stride2,
+                                                     const SolveScalars *__restrict__ sc, double *__restrict__ part) {
+    __shared__ double red[4];
+    if ((int)blockIdx.x < nr) resid_update(rsegs[blockIdx.x], r, a, b, sc, part, red);
+    else theta_update(tsegs[blockIdx.x - nr], th, p, Sb, stride2, nullptr, sc, nullptr, red);
+}
+
 // ---------------------------------------------------------------------------
 // per-problem finalisation (one block per problem)
 // ---------------------------------------------------------------------------
 // the scalar work of one problem (thread 0); G: the staged Gram matrix and coefficients (FIN_GRAM)
+// rr = ||r||^2
+__device__ __forceinline__ void record_f(const FinArgs &fa, int prob, double rr, SolveScalars &s) {
+    const double f = 0.5 * rr + fa.lam * s.thnorm2;
+    s.f = f;
+    s.fdata = 0.5 * rr;
+    if (fa.fhist) fa.fhist[prob][fa.t] = f;
+    else if (fa.fhist0) fa.fhist0[fa.t] = f;
+}
+
+// the sum of count partials by the first 256 threads, in thread 0 (the order of the products' sums in finalize_kernel)
+__device__ __forceinline__ double first_sum(const double *base, int count, double *red) {
+    const int t = threadIdx.x;
+    if (t < 256) {
+        double v = 0.0;
+        for (int i = t; i < count; i += 256) v += base[i];
+        v = wave_sum64(v);
+        if ((t & 63) == 0) red[t >> 6] = v;
+    }
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
 __device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, const double *tot, double *Gs,
                                                  SolveScalars &s) {
     const int m1 = fa.m1;
     switch (fa.op) {
-        case FIN_F: {  // tot[0] = ||r||^2
-            const double f = 0.5 * tot[0] + fa.lam * s.thnorm2;
-            s.f = f;
-            s.fdata = 0.5 * tot[0];
-            if (fa.fhist) fa.fhist[prob][fa.t] = f;
-            else if (fa.fhist0) fa.fhist0[fa.t] = f;
+        case FIN_F:
+            record_f(fa, prob, tot[0], s);
             break;
-        }
         case FIN_F_OUT: {  // plain objective into fout[prob]
             if (fa.fout) fa.fout[prob] = 0.5 * tot[0];
             break;
@@ -674,6 +716,13 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinArgs fa) {
     constexpr int SW = sizeof(SolveScalars) / 8;
     const int prob = blockIdx.x;
     const int t = threadIdx.x;
+    if constexpr (NT > 256) {
+        if (blockIdx.y == 1) {   // the objective of the update before, beside the Gram sums: its two scalars only
+            const double s = first_sum(fa.fpartials + (int64_t)prob * fa.pstride, fa.fcount, red);
+            if (t == 0) record_f(fa, prob, s, fa.sc[prob]);
+            return;
+        }
+    }
     const bool scalars = fa.op != FIN_F_OUT;   // the plain objective has none
     double *gs = reinterpret_cast<double *>(fa.sc + prob), *ls = reinterpret_cast<double *>(&ss);
     if (scalars && t < SW) ls[t] = gs[t];
@@ -723,7 +772,9 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinArgs fa) {
     __syncthreads();
     if (t == 0) finalize_scalars(fa, prob, tot, sG, ss);
     __syncthreads();
-    if (scalars && t < SW) gs[t] = ls[t];
+    // (all but the objective, the first two, which the other workgroup may write)
+    static_assert(offsetof(SolveScalars, f) == 0 && offsetof(SolveScalars, fdata) == 8, "the objective's words");
+    if (scalars && t < SW && (NT == 256 || t > 1)) gs[t] = ls[t];
     if constexpr (NT > 256)
         if (Gg)
             for (int i = t; i < gwords; i += NT) Gg[i] = sG[i];
@@ -863,10 +914,18 @@ hipError_t launch_resid_update(const VecSeg *segs, int nseg, float *r, const flo
                                const SolveScalars *sc, double *part, hipStream_t s) {
     SEGS_LAUNCH(resid_update_kernel, nseg, s, segs, r, a, b, sc, part);
 }
+hipError_t launch_update(const VecSeg *rsegs, int nrseg, const VecSeg *tsegs, int ntseg, float *r, const float *a,
+                         const float *b, float *th, const float *p, float *Sb, int64_t stride2, const SolveScalars *sc,
+                         double *part, hipStream_t s) {
+    if (nrseg + ntseg <= 0) return hipSuccess;
+    hipLaunchKernelGGL(update_kernel, dim3((unsigned)(nrseg + ntseg)), dim3(256), 0, s, rsegs, nrseg, tsegs, r, a, b, th, p,
+                       Sb, stride2, sc, part);
+    return hipGetLastError();
+}
 hipError_t launch_finalize(const FinArgs &fa, int nprob, hipStream_t s) {
     if (nprob <= 0) return hipSuccess;
     if ((fa.op == FIN_GRAM) != (fa.nsum > FIN_FEW) || fa.nsum > 6 * (MAX_LBFGS_M + 1)) return hipErrorInvalidValue;
-    if (fa.op == FIN_GRAM) hipLaunchKernelGGL(finalize_kernel<1024>, dim3((unsigned)nprob), dim3(1024), 0, s, fa);
+    if (fa.op == FIN_GRAM) hipLaunchKernelGGL(finalize_kernel<1024>, dim3((unsigned)nprob, fa.fpartials ? 2 : 1), dim3(1024), 0, s, fa);
     else hipLaunchKernelGGL(finalize_kernel<256>, dim3((unsigned)nprob), dim3(256), 0, s, fa);
     return hipGetLastError();
 }

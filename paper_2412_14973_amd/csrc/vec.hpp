@@ -34,6 +34,8 @@ struct FinArgs {
     double lam;
     double *gram;          // FIN_GRAM: per-problem Gram matrix and direction coefficients
     int64_t gstride;       // doubles per problem in gram: (2 m1 + 1)^2 + 2 m1 + 1
+    const double *fpartials;   // FIN_GRAM: |r|^2 partials (pstride per problem, fcount used) of an objective to record
+    int32_t fcount;            // beside it as FIN_F does, or null
 };
 
 hipError_t launch_gram(const VecSeg *segs, int nseg, int m1, const float *g, const float *gprev, float *Yb,
@@ -53,6 +55,10 @@ hipError_t launch_theta_update(const VecSeg *segs, int nseg, float *th, const fl
                                hipStream_t s);
 hipError_t launch_resid_update(const VecSeg *segs, int nseg, float *r, const float *a, const float *b,
                                const SolveScalars *sc, double *part, hipStream_t s);
+// r and theta together, without a penalty term (the sums of theta are not formed)
+hipError_t launch_update(const VecSeg *rsegs, int nrseg, const VecSeg *tsegs, int ntseg, float *r, const float *a,
+                         const float *b, float *th, const float *p, float *Sb, int64_t stride2, const SolveScalars *sc,
+                         double *part, hipStream_t s);
 hipError_t launch_finalize(const FinArgs &fa, int nprob, hipStream_t s);
 
 }  // namespace tlr
