@@ -311,7 +311,8 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
  * nullable); the candidate with the fewest entries (first on ties) is written
  * to d_out, rank_off_out (capacity off_capacity) and rank_diag_out (capacity
  * diag_capacity); status 1 when a chosen layout does not fit. Workspace: the
- * largest candidate's tlrmdd_workspace_bytes_ranks. Synchronises `stream`.
+ * largest candidate's tlrmdd_workspace_bytes_ranks (with room for all of them
+ * the candidates of 33 to 256 rows share one pass). Synchronises `stream`.
  *
  * tlrmdd_warm_start: theta_out (device, theta_size complex64 of the plan's
  * layout) from X: L = U_k S_k^(1/2), R = S_k^(1/2) V_k^H of every off-diagonal

@@ -9,12 +9,13 @@
 //
 // One workgroup per tile. Step k: the reflection u of column k; all columns c > k take the right reflection
 // of step k - 1, A -= zt v^H, and the left one, A -= conj(tau) u (u^H A), in one pass (32 lanes per column, its
-// rows in registers); the reflection v of row k; zt = tau A v in a second, reading pass (a wave per column, its
-// rows over the lanes). Two reads and one write of the trailing matrix and five barriers per step: what bounds
-// it is the latency of the phases in small tiles (2.7 us a step at 64 rows, LDS) and the one CU's path to L2 in
-// large ones (11 us a step at 128 rows, 17 at 256; the traffic alone is 1.7 and 7). Tiles up to 64 rows are held
-// in LDS and read from X once. Tile sizes 64, 128 and 256 of a 1024 x 1024 matrix: 0.23 + 1.4 + 4.3 ms, 6.0 ms in
-// all, where one-sided Jacobi with a launch per round of rotations took 48.6 ms (6104 launches of 8 us).
+// rows in registers); the reflection v of row k; zt = tau A v in a second, reading pass. What bounds it is the
+// latency of a step's five phases: about 5 us a step with the tile in registers (up to 128 rows, and the last 128
+// rows of tiles up to 256) and 24 to 26 with it in memory (the first steps of a 256-row tile: through one CU, two
+// reads and one write of the rest of the tile; half the bytes gave 7 %). Tiles up to 32 rows in a launch of their
+// own are held in LDS. Tile sizes 64, 128 and 256 of a 1024 x 1024 matrix, in one launch: 4.0 ms (6.0 with a launch
+// each and all steps in memory), where one-sided Jacobi with a launch per round of rotations took 48.6 ms (6104
+// launches of 8 us).
 #include "svd.hpp"
 
 #include "common.hpp"
