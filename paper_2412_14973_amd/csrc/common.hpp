@@ -163,7 +163,6 @@ struct SolveScalars {
     double pnorm2, tp;           // lambda terms: ||p||^2, Re<theta,p>
     double thnorm2;              // ||theta||^2 after update (lambda term of f)
     double rho[MAX_LBFGS_M + 1];
-    double alpha[MAX_LBFGS_M];
     int32_t head, count, restart, frozen;
 };
 

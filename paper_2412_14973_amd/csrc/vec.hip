@@ -306,12 +306,12 @@ __device__ __forceinline__ void block_sums(double (&v)[N], double *red) {
 //   j == h : <s_h,s_h> <s_h,y_h> <y_h,y_h> <g,s_h> <g,y_h> <g,g>
 //   j valid: <s_j,s_h> <s_j,y_h> <s_j,g>   <y_j,s_h> <y_j,y_h> <y_j,g>
 //   else   : zeros
-__global__ __launch_bounds__(256) void gram_kernel(const VecSeg *__restrict__ segs, int m1,
+__global__ __launch_bounds__(256, 3) void gram_kernel(const VecSeg *__restrict__ segs, int m1,
                                                    const float *__restrict__ g, const float *__restrict__ gprev,
                                                    float *__restrict__ Yb, const float *__restrict__ Sb,
                                                    int64_t stride2, const SolveScalars *__restrict__ sc,
                                                    double *__restrict__ part) {
-    __shared__ double red[4 * 6];
+    __shared__ double red[6 * (MAX_LBFGS_M + 1)][4];
     const VecSeg sg = segs[blockIdx.x];
     const SolveScalars &s = sc[sg.prob];
     const int h = s.head, count = s.count;
@@ -328,14 +328,20 @@ __global__ __launch_bounds__(256) void gram_kernel(const VecSeg *__restrict__ se
 #pragma unroll
     for (int u = 0; u < 4 * VQ; ++u) vy.v[u] = vg.v[u] - vy.v[u];
     st16(Yb + h * stride2, sg, vy);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto wave_sums = [&](int j, double (&a)[6]) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) a[k] = wave_sum64(a[k]);
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int k = 0; k < 6; ++k) red[6 * j + k][wave] = a[k];
+    };
     {
         double a[6] = {dot16(vs, vs), dot16(vs, vy), dot16(vy, vy), dot16(vg, vs), dot16(vg, vy), dot16(vg, vg)};
-        block_sums<6>(a, red);
-        if (threadIdx.x == 0)
-#pragma unroll
-            for (int k = 0; k < 6; ++k) pp[6 * h + k] = a[k];
+        wave_sums(h, a);
     }
-    // the held pairs, each one's loads issued before the block reduction of the previous one
+    // the held pairs, each one's loads issued before the sums of the previous one; the waves' sums are added at the
+    // end, so no wave waits for another on the way
     for (int i = 0; i < count; ++i) {
         const int j = ring_slot(s, i, m1);
         VecSeg sgn = sg;   // past the last pair: an empty range, the loads return 0 and move no data
@@ -344,18 +350,15 @@ __global__ __launch_bounds__(256) void gram_kernel(const VecSeg *__restrict__ se
         const V16 sn = ld16(Sb + jn * stride2, sgn);
         const V16 yn = ld16(Yb + jn * stride2, sgn);
         double a[6] = {dot16(sj, vs), dot16(sj, vy), dot16(sj, vg), dot16(yj, vs), dot16(yj, vy), dot16(yj, vg)};
-        block_sums<6>(a, red);
-        if (threadIdx.x == 0)
-#pragma unroll
-            for (int k = 0; k < 6; ++k) pp[6 * j + k] = a[k];
+        wave_sums(j, a);
         sj = sn;
         yj = yn;
     }
-    if (threadIdx.x < 6 * m1) {   // slots that are neither h nor valid
-        const int j = threadIdx.x / 6;
-        bool used = (j == h);
-        for (int i = 0; i < count; ++i) used = used || (ring_slot(s, i, m1) == j);
-        if (!used) pp[threadIdx.x] = 0.0;
+    __syncthreads();
+    if (threadIdx.x < 6 * m1) {
+        const int j = threadIdx.x / 6, back = h - 1 - j < 0 ? h - 1 - j + m1 : h - 1 - j;   // how many pairs ago
+        const double *w = red[threadIdx.x];
+        pp[threadIdx.x] = j == h || back < count ? ((w[0] + w[1]) + w[2]) + w[3] : 0.0;   // else: no pair
     }
 }
 
@@ -566,12 +569,29 @@ __device__ __forceinline__ void record_f(const FinArgs &fa, int prob, double rr,
     else if (fa.fhist0) fa.fhist0[fa.t] = f;
 }
 
+// One problem's partial sums, n to a slot, through a buffer as long as they are: what lies past the end reads zero, so
+// the loads of several slots carry no conditions and are all in flight together.
+constexpr uint32_t NO_SUM = 0xffffff00u;   // an offset past every end
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t sums_rsrc(const double *base, int count, int n) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(base), (short)0, count * n * 8, 0x00020000);
+}
+__device__ __forceinline__ double ld_sum(__amdgpu_buffer_rsrc_t rs, uint32_t at) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)at, 0, 0));
+}
+
 // the sum of count partials by the first 256 threads, in thread 0 (the order of the products' sums in finalize_kernel)
 __device__ __forceinline__ double first_sum(const double *base, int count, double *red) {
     const int t = threadIdx.x;
     if (t < 256) {
+        const auto rs = sums_rsrc(base, count, 1);
         double v = 0.0;
-        for (int i = t; i < count; i += 256) v += base[i];
+        for (int i0 = t; i0 < count; i0 += 1024) {
+            double x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = ld_sum(rs, 8u * (uint32_t)(i0 + 256 * u));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v += x[u];
+        }
         v = wave_sum64(v);
         if ((t & 63) == 0) red[t >> 6] = v;
     }
@@ -579,9 +599,126 @@ __device__ __forceinline__ double first_sum(const double *base, int count, doubl
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-__device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, const double *tot, double *Gs,
-                                                 SolveScalars &s) {
-    const int m1 = fa.m1;
+__device__ __forceinline__ double of_lane(double v, int l) {   // l uniform
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | lo);
+}
+
+// Gram entries of the newest pair and of g, and the direction's coefficients: by one wave, lane i works for the i-th
+// newest pair held. G: the staged Gram matrix nb x nb, then nb coefficients, basis (s_j, y_j, g).
+__device__ __forceinline__ void gram_scalars(const FinArgs &fa, const double *tot, double *G, SolveScalars &s) {
+    const int lane = threadIdx.x;
+    const int m1 = fa.m1, nb = 2 * m1 + 1, ig = 2 * m1;
+    double *cf = G + nb * nb;
+    const int h = s.head;
+    int head = h, cnt = s.count;
+    double gamma = s.gamma;
+    auto slot = [&](int i) {   // i < m1
+        const int j = head - 1 - i;
+        return j < 0 ? j + m1 : j;
+    };
+    const double *th = tot + 6 * h;
+    const double sy = th[1], yy = th[2];
+    const bool take = sy > 0.0 && yy > 0.0 && isfinite(sy) && isfinite(yy) && !s.frozen;
+    if (lane < cnt) {
+        const int j = slot(lane);
+        const double *tj = tot + 6 * j;
+        // g against the pairs already held (before the newest one is taken in)
+        G[ig * nb + j] = G[j * nb + ig] = tj[2];
+        G[ig * nb + m1 + j] = G[(m1 + j) * nb + ig] = tj[5];
+        if (take) {
+            G[j * nb + h] = G[h * nb + j] = tj[0];
+            G[j * nb + m1 + h] = G[(m1 + h) * nb + j] = tj[1];
+            G[(m1 + j) * nb + h] = G[h * nb + m1 + j] = tj[3];
+            G[(m1 + j) * nb + m1 + h] = G[(m1 + h) * nb + m1 + j] = tj[4];
+        }
+    }
+    if (take) {
+        gamma = sy / yy;
+        head = h + 1 == m1 ? 0 : h + 1;
+        cnt = min(cnt + 1, m1 - 1);
+    }
+    if (lane == 0) {
+        G[ig * nb + ig] = th[5];
+        s.sy = sy;
+        s.yy = yy;
+        if (take) {
+            G[h * nb + h] = th[0];
+            G[h * nb + m1 + h] = G[(m1 + h) * nb + h] = sy;
+            G[(m1 + h) * nb + m1 + h] = yy;
+            G[ig * nb + h] = G[h * nb + ig] = th[3];
+            G[ig * nb + m1 + h] = G[(m1 + h) * nb + ig] = th[4];
+            s.rho[h] = 1.0 / sy;
+        }
+    }
+    for (int b = lane; b < nb; b += 64) cf[b] = 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // the other lanes' entries
+    // Two-loop recursion on coefficient vectors over the basis: q = sum_b d_b v_b, so <v_a, q> = sum_b G_ab d_b, the
+    // pairs' terms formed by their lanes and added newest first. A row is read while the one before is worked on.
+    struct Row {
+        double s, y, g;
+    };
+    const bool mine = lane < cnt;
+    const int j = mine ? slot(lane) : 0;
+    const double rho = mine ? s.rho[j] : 0.0;
+    double cs = 0.0, cy = 0.0, cg = 1.0, al = 0.0;
+    auto row = [&](int a) {
+        const double *r = G + a * nb;
+        return Row{r[j], r[m1 + j], r[ig]};
+    };
+    auto dot = [&](const Row &r) {
+        const double t = mine ? r.s * cs + r.y * cy : 0.0;
+        double v = r.g * cg;
+        for (int i = 0; i < cnt; ++i) v += of_lane(t, i);
+        return v;
+    };
+    Row next = row(cnt > 0 ? slot(0) : ig);
+    for (int i = 0; i < cnt; ++i) {   // newest first
+        const Row r = next;
+        next = row(i + 1 < cnt ? slot(i + 1) : m1 + slot(i));
+        const double a = of_lane(rho, i) * dot(r);
+        if (lane == i) {
+            al = a;
+            cy -= a;
+        }
+    }
+    if (cnt > 0) {
+        cy *= gamma;
+        cg *= gamma;
+    }
+    for (int i = cnt - 1; i >= 0; --i) {   // oldest first
+        const Row r = next;
+        next = row(i > 0 ? m1 + slot(i - 1) : ig);
+        const double beta = of_lane(rho, i) * dot(r);
+        if (lane == i) cs += al - beta;
+    }
+    cs = -cs;
+    cy = -cy;
+    cg = -cg;
+    double gp = dot(next);
+    const bool restart = gp >= 0.0 || !isfinite(gp);
+    if (restart) {   // not a descent direction: p = -g and the history is dropped
+        cs = cy = 0.0;
+        cg = -1.0;
+        gp = -next.g;
+    }
+    if (mine) {
+        cf[j] = cs;
+        cf[m1 + j] = cy;
+    }
+    if (lane == 0) {
+        cf[ig] = cg;
+        s.head = head;
+        s.count = restart ? 0 : cnt;
+        s.gamma = restart ? 1.0 : gamma;
+        s.restart = restart ? 1 : 0;
+        s.gp = gp;
+    }
+}
+
+__device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, const double *tot, SolveScalars &s) {
     switch (fa.op) {
         case FIN_F:
             record_f(fa, prob, tot[0], s);
@@ -600,78 +737,6 @@ __device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, co
         case FIN_RESET:  // fresh pair memory (a new sub-problem starts from the current theta)
             s.head = 0; s.count = 0; s.restart = 0; s.gamma = 1.0;
             break;
-        case FIN_GRAM: {  // Gram entries of the newest pair and of g; direction coefficients
-            const int nb = 2 * m1 + 1, ig = 2 * m1;
-            double *G = Gs;   // nb x nb, then nb coefficients
-            double *cf = G + nb * nb;
-            const int h = s.head;
-            const double *th = tot + 6 * h;
-            const double sy = th[1], yy = th[2];
-            // g against the pairs already held (before the newest one is taken in)
-            for (int i = 0; i < s.count; ++i) {
-                const int j = ring_slot(s, i, m1);
-                G[ig * nb + j] = G[j * nb + ig] = tot[6 * j + 2];
-                G[ig * nb + m1 + j] = G[(m1 + j) * nb + ig] = tot[6 * j + 5];
-            }
-            G[ig * nb + ig] = th[5];
-            s.sy = sy; s.yy = yy;
-            if (sy > 0.0 && yy > 0.0 && isfinite(sy) && isfinite(yy) && !s.frozen) {
-                for (int i = 0; i < s.count; ++i) {
-                    const int j = ring_slot(s, i, m1);
-                    const double *tj = tot + 6 * j;
-                    G[j * nb + h] = G[h * nb + j] = tj[0];
-                    G[j * nb + m1 + h] = G[(m1 + h) * nb + j] = tj[1];
-                    G[(m1 + j) * nb + h] = G[h * nb + m1 + j] = tj[3];
-                    G[(m1 + j) * nb + m1 + h] = G[(m1 + h) * nb + m1 + j] = tj[4];
-                }
-                G[h * nb + h] = th[0];
-                G[h * nb + m1 + h] = G[(m1 + h) * nb + h] = sy;
-                G[(m1 + h) * nb + m1 + h] = yy;
-                G[ig * nb + h] = G[h * nb + ig] = th[3];
-                G[ig * nb + m1 + h] = G[(m1 + h) * nb + ig] = th[4];
-                s.rho[h] = 1.0 / sy;
-                s.gamma = sy / yy;
-                s.head = (h + 1) % m1;
-                s.count = min(s.count + 1, m1 - 1);
-            }
-            // two-loop recursion on coefficient vectors over the basis (s_j, y_j, g):
-            // q = sum_b d_b v_b, so <v_a, q> = sum_b G_ab d_b
-            for (int b2 = 0; b2 < nb; ++b2) cf[b2] = 0.0;
-            cf[ig] = 1.0;
-            const int cnt = s.count;
-            auto dotG = [&](int a_) {
-                double v = G[a_ * nb + ig] * cf[ig];
-                for (int i = 0; i < cnt; ++i) {
-                    const int j = ring_slot(s, i, m1);
-                    v += G[a_ * nb + j] * cf[j] + G[a_ * nb + m1 + j] * cf[m1 + j];
-                }
-                return v;
-            };
-            for (int i = 0; i < cnt; ++i) {   // newest first
-                const int j = ring_slot(s, i, m1);
-                s.alpha[i] = s.rho[j] * dotG(j);
-                cf[m1 + j] -= s.alpha[i];
-            }
-            if (cnt > 0)
-                for (int b2 = 0; b2 < nb; ++b2) cf[b2] *= s.gamma;
-            for (int i = cnt - 1; i >= 0; --i) {   // oldest first
-                const int j = ring_slot(s, i, m1);
-                const double beta = s.rho[j] * dotG(m1 + j);
-                cf[j] += s.alpha[i] - beta;
-            }
-            for (int b2 = 0; b2 < nb; ++b2) cf[b2] = -cf[b2];
-            const double gp = dotG(ig);
-            s.gp = gp;
-            s.restart = (gp >= 0.0 || !isfinite(gp)) ? 1 : 0;
-            if (s.restart) {   // not a descent direction: p = -g and the history is dropped
-                s.count = 0;
-                s.gamma = 1.0;
-                for (int b2 = 0; b2 < nb; ++b2) cf[b2] = 0.0;
-                cf[ig] = -1.0;
-                s.gp = -G[ig * nb + ig];
-            }
-            break;
-        }
         case FIN_LAMTERMS:  // (Re<theta - c, p>, ||p||^2)
             s.tp = tot[0];
             s.pnorm2 = tot[1];
@@ -695,17 +760,15 @@ __device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, co
     }
 }
 
-// The scalar work runs on one thread and is a chain of dependent steps, so everything it touches sits
-// in LDS first: the partial sums are reduced by the four waves at once (wave w takes sums w, w + 4,
-// ...: lanes stride over the slots, then one DPP wave reduction, a fixed order), and the Gram pass
-// stages the problem's Gram matrix and coefficient vector, which are written back afterwards.
 constexpr int FIN_NB = 2 * (MAX_LBFGS_M + 1) + 1;
 constexpr int FIN_FEW = 5;
-// One workgroup per problem: the sums, then the scalars by one thread. The launch lies between two others that wait
-// for it, so its latency is what counts: the scalars are worked on in LDS (they are read and written there and in
-// global memory by all threads at once), and the Gram pass's 6 m1 sums are added by 1024 threads (NT), each every
-// (1024 / 6 m1)-th segment of one sum. us at nr 1024, tiles 128, one to five pairs held,
-// before and now: Gram 10.5 to 14, 6.6 to 8; of 4.7 that any launch in the chain takes.
+// One workgroup per problem: the sums, then the scalars by one thread, or the Gram pass's by one wave. The launch lies
+// between two others that wait for it, so its latency is what counts: the loads of several slots are in flight
+// together, the scalars are worked on in LDS (they are read and written there and in global memory by all threads at
+// once), and the Gram pass's 6 m1 sums are added by 1024 threads (NT), each every (1024 / 6 m1)-th segment of one sum.
+// us at nr 1024, tiles 128, of 4.7 that any launch in the chain takes: the line sums (1024 slots) 9.7 with a slot's
+// loads after another's, now 4.6; Gram with none to four pairs held 10.5 to 14 by 256 threads in global memory, 6.6 to
+// 8 with one thread's recursion, now 5.1 to 7.2.
 template <int NT>
 __global__ __launch_bounds__(NT) void finalize_kernel(FinArgs fa) {
     __shared__ double tot[6 * (MAX_LBFGS_M + 1)];
@@ -727,7 +790,7 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinArgs fa) {
     double *gs = reinterpret_cast<double *>(fa.sc + prob), *ls = reinterpret_cast<double *>(&ss);
     if (scalars && t < SW) ls[t] = gs[t];
     const int count = fa.counts ? fa.counts[prob] : fa.ucount;
-    const double *base = fa.partials + (int64_t)prob * fa.pstride * fa.nsum;
+    const auto rs = sums_rsrc(fa.partials + (int64_t)prob * fa.pstride * fa.nsum, count, fa.nsum);
     const int lane = t & 63, wv = t >> 6;
     if constexpr (NT == 256) {
         // products' sums, up to thousands of slots: a thread adds every 256th slot, all sums of a slot at once
@@ -735,10 +798,18 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinArgs fa) {
         double v[FIN_FEW];
 #pragma unroll
         for (int k = 0; k < FIN_FEW; ++k) v[k] = 0.0;
-        for (int i = t; i < count; i += 256)
+        for (int i0 = t; i0 < count; i0 += 1024) {
+            double x[4][FIN_FEW];
 #pragma unroll
-            for (int k = 0; k < FIN_FEW; ++k)
-                if (k < fa.nsum) v[k] += base[(int64_t)i * fa.nsum + k];
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < FIN_FEW; ++k)
+                    x[u][k] = ld_sum(rs, k < fa.nsum ? 8u * (uint32_t)((i0 + 256 * u) * fa.nsum + k) : NO_SUM);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < FIN_FEW; ++k) v[k] += x[u][k];
+        }
 #pragma unroll
         for (int k = 0; k < FIN_FEW; ++k) {
             if (k >= fa.nsum) break;
@@ -752,32 +823,47 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinArgs fa) {
         const int parts = NT / fa.nsum;   // fa.nsum <= 6 (MAX_LBFGS_M + 1)
         const int q = t / fa.nsum;
         double v = 0.0;
-        if (q < parts)
-#pragma unroll 8
-            for (int i = q; i < count; i += parts) v += base[(int64_t)i * fa.nsum + (t - q * fa.nsum)];
+        for (int i0 = q; i0 < count; i0 += 8 * parts) {
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * parts;
+                x[u] = ld_sum(rs, q < parts ? 8u * (uint32_t)(i * fa.nsum + (t - q * fa.nsum)) : NO_SUM);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v += x[u];
+        }
         red[t] = v;
         __syncthreads();
         if (t < fa.nsum) {
             double a = 0.0;
-            for (int i = 0; i < parts; ++i) a += red[i * fa.nsum + t];
+            for (int i0 = 0; i0 < parts; i0 += 8) {
+                double x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = red[i0 + u < parts ? (i0 + u) * fa.nsum + t : 0];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) a += i0 + u < parts ? x[u] : 0.0;
+            }
             tot[t] = a;
         }
     }
     const int m1 = fa.m1;
     const int gwords = (2 * m1 + 1) * (2 * m1 + 1) + 2 * m1 + 1;
-    double *Gg = fa.op == FIN_GRAM ? fa.gram + (int64_t)prob * fa.gstride : nullptr;
-    if constexpr (NT > 256)
-        if (Gg)
-            for (int i = t; i < gwords; i += NT) sG[i] = Gg[i];
+    double *Gg = fa.gram + (int64_t)prob * fa.gstride;
+    if constexpr (NT > 256)   // FIN_GRAM
+        for (int i = t; i < gwords; i += NT) sG[i] = Gg[i];
     __syncthreads();
-    if (t == 0) finalize_scalars(fa, prob, tot, sG, ss);
+    if constexpr (NT > 256) {
+        if (t < 64) gram_scalars(fa, tot, sG, ss);
+    } else {
+        if (t == 0) finalize_scalars(fa, prob, tot, ss);
+    }
     __syncthreads();
     // (all but the objective, the first two, which the other workgroup may write)
     static_assert(offsetof(SolveScalars, f) == 0 && offsetof(SolveScalars, fdata) == 8, "the objective's words");
     if (scalars && t < SW && (NT == 256 || t > 1)) gs[t] = ls[t];
     if constexpr (NT > 256)
-        if (Gg)
-            for (int i = t; i < gwords; i += NT) Gg[i] = sG[i];
+        for (int i = t; i < gwords; i += NT) Gg[i] = sG[i];
 }
 
 
