@@ -55,6 +55,10 @@ __device__ __forceinline__ int out_entries(int rows, int cols) {
     return OUTB ? (cols + 3) / 4 * 256 : rows * 64;
 }
 
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t OUTSIDE = 0xffffff00u;   // a buffer offset past every end
+
 constexpr int AB = ASM_B;            // block edge (rows and columns)
 constexpr int AKC = ASM_KC;          // rank entries staged per step
 constexpr int AAP = AB + 1;          // row-factor planes [AKC][AAP] floats (k-major: rows fastest)
@@ -72,7 +76,11 @@ constexpr int B_ST = AKC * ABP;      // complex per column-factor stage
 // The row factors sit in LDS as separate real and imaginary planes, k-major, so a lane's A entry
 // is one conflict-free float read; the column factors stay interleaved complex. 33 KB of LDS and
 // at most 128 VGPRs (launch bound: 4 waves per SIMD) keep four workgroups on a CU, so the write
-// phases of some overlap the loads and products of others.
+// phases of some overlap the loads and products of others. The latency of the phases is what bounds it, so a chunk's
+// loads are in flight together, and so are the LDS reads of whole blocks before their stores: us of 8 problems of nr
+// 1024 (k 25 to 48) X 48.6 with a condition at each, 34.7 with the loads so, 33.1 with both, [X1 | X2] 81.8, 67.9 and
+// 66.4 (its writes take 26, its products 54), X in BF16 planes of nr 2304 33.6 and 30.3 (loads, both). A chunk ahead
+// during the products takes registers that spill: 71.7.
 template <bool DIR, bool OUTB>
 __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__restrict__ tiles,
                                                        const AsmItem *__restrict__ items,
@@ -154,33 +162,49 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
     const float2 *Rf = qq ? Lf : theta + td.offB;       // R (k x dj) or Q again
     const float2 *PLf = DIR ? pv + td.offA : nullptr;
     const float2 *PRf = DIR ? (qq ? PLf : pv + td.offB) : nullptr;
-    for (int kc0 = 0; kc0 < k; kc0 += AKC) {
-        const int kn = min(AKC, k - kc0);
-        for (int e = t; e < nrow * AKC; e += 256) {    // row factors: rows r0.., k contiguous in theta
-            const int rr = e / AKC, kk = e % AKC;
-            const bool ok = rr < nrow && kk < kn;
-            const int64_t o = (int64_t)(r0 + rr) * k + kc0 + kk;
+    // A chunk of the factors: an entry outside them is past its buffer's end and reads zero, so the loads carry no
+    // conditions and are in flight together.
+    constexpr int NE = AB * AKC / 256;
+    auto buffer = [&](const float2 *p, int cols) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(p), (short)0, cols * k * 8, 0x00020000);
+    };
+    const auto La = buffer(Lf, td.di), Ra = buffer(Rf, td.dj);
+    const auto Pl = buffer(DIR ? PLf : Lf, td.di), Pr = buffer(DIR ? PRf : Rf, td.dj);
+    u32x2 va[NE][NF], vb[NE][NF];
+    auto load = [&](int kc0) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int e = t + 256 * i;
+            // row factors: rows r0.., k contiguous in theta; column factors G[kk][cc] = R[kc0+kk][c0+cc] or
+            // Q[c0+cc][kc0+kk]
+            const int rr = e / AKC, kr = kc0 + e % AKC;
+            const int cc = qq ? e / AKC : e & 63, kk = kc0 + (qq ? e % AKC : e >> 6);
+            const uint32_t oa = rr < nrow && kr < k ? 8u * (uint32_t)((r0 + rr) * k + kr) : OUTSIDE;
+            const uint32_t ob = cc < ncol && kk < k ? 8u * (uint32_t)(qq ? (c0 + cc) * k + kk : kk * td.dj + c0 + cc) : OUTSIDE;
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                const float2 v = ok ? (f ? PLf : Lf)[o] : make_float2(0.f, 0.f);
-                float *pl = sA + f * 2 * A_PL + kk * AAP + rr;
-                pl[0] = v.x;
-                pl[A_PL] = v.y;
+                va[i][f] = __builtin_amdgcn_raw_buffer_load_b64(f ? Pl : La, (int)oa, 0, 0);
+                vb[i][f] = __builtin_amdgcn_raw_buffer_load_b64(f ? Pr : Ra, (int)ob, 0, 0);
             }
         }
-        for (int e = t; e < AKC * AB; e += 256) {    // column factors G[kk][cc] = R[kc0+kk][c0+cc] or Q[c0+cc][kc0+kk]
-            int kk, cc;
-            int64_t o;
-            if (qq) { cc = e / AKC; kk = e % AKC; o = (int64_t)(c0 + cc) * k + kc0 + kk; }
-            else { kk = e >> 6; cc = e & 63; o = (int64_t)(kc0 + kk) * td.dj + c0 + cc; }
-            const bool ok = cc < ncol && kk < kn;
+    };
+    for (int kc0 = 0; kc0 < k; kc0 += AKC) {
+        const int kn = min(AKC, k - kc0);
+        load(kc0);
 #pragma unroll
-            for (int f = 0; f < NF; ++f)
-                sB[f * B_ST + kk * ABP + cc] = ok ? (f ? PRf : Rf)[o] : make_float2(0.f, 0.f);
+        for (int i = 0; i < NE; ++i) {
+            const int e = t + 256 * i;
+            const int cc = qq ? e / AKC : e & 63, kk = qq ? e % AKC : e >> 6;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                float *pl = sA + f * 2 * A_PL + e % AKC * AAP + e / AKC;
+                pl[0] = __uint_as_float(va[i][f].x);
+                pl[A_PL] = __uint_as_float(va[i][f].y);
+                sB[f * B_ST + kk * ABP + cc] = make_float2(__uint_as_float(vb[i][f].x), __uint_as_float(vb[i][f].y));
+            }
         }
         __syncthreads();
         const float *bf = reinterpret_cast<const float *>(sB);
-#pragma unroll 2
         for (int kk = 0; kk < kn; ++kk) {
             float a[NF][2], b[NF];
 #pragma unroll
@@ -217,6 +241,7 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
     const int ccol = cb + (j32 >> 1);
     const int comp = j32 & 1;
     float *sTf = smem;   // [row][ST_P] complex
+    const bool whole = nrow == AB && ncol == AB && (!qq || r0 != c0);
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         __syncthreads();
@@ -227,6 +252,21 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
                 sTf[2 * ((32 * i + acc_row(r, lane)) * ST_P + ccol) + comp] = acc[f][i][r];
         __syncthreads();
         float2 *dst = f ? X2 : X;
+        if (whole) {   // no conditions: the reads of several entries are in flight together
+#pragma unroll 8
+            for (int e = t; e < AB * AB; e += 256) {
+                int rr, cc;
+                out_entry<OUTB>(e, rr, cc);
+                put<OUTB>(dst, td.row0 + r0 + rr, td.col0 + c0 + cc, ldx, low, sT[rr * ST_P + cc]);
+            }
+#pragma unroll 8
+            for (int e = t; e < AB * AB; e += 256) {
+                int rr, cc;
+                out_entry<OUTB>(e, cc, rr);
+                put<OUTB>(dst, td.col0 + c0 + cc, td.row0 + r0 + rr, ldx, low, sT[rr * ST_P + cc]);
+            }
+            continue;
+        }
         for (int e = t; e < out_entries<OUTB>(nrow, ncol); e += 256) {
             int rr, cc;
             out_entry<OUTB>(e, rr, cc);
@@ -259,7 +299,6 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
 // rank 40) 166, now 49.
 constexpr int GR_CH = 8;               // contraction entries per chunk: four per half of a wave
 constexpr int GP_P = 66;               // partial blocks [4 waves][16][GP_P] floats
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 template <int KQ>
