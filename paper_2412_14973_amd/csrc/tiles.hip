@@ -321,39 +321,49 @@ __device__ __forceinline__ void grad_block(const GradItem &it, const TileDesc &t
     const int ncon = colside ? td.di : td.dj;                        // contraction length
     // W'[m][c] = w1[m ldw + c] + w2[c ldw + m]. Buffer loads: an offset past the end gives zero, so the chunks at
     // the end of the contraction need no branch (a branch would make each load wait for the ones before it).
-    const uint32_t ld8 = (uint32_t)ldw * 8;
-    const auto rsW = __builtin_amdgcn_make_buffer_rsrc((void *)W, (short)0, (int)(uint32_t)min(ldw * ldw * 8, (int64_t)0xfffffff0), 0x00020000);
-    const auto rsF = __builtin_amdgcn_make_buffer_rsrc((void *)(theta + (FROW ? td.offB : td.offA)), (short)0,
-                                                       (int)(8 * k * (FROW ? td.dj : td.di)), 0x00020000);
-    const uint32_t row1 = (uint32_t)(colside ? td.col0 : td.row0) + a0, col1 = (uint32_t)(colside ? td.row0 : td.col0);
-    const uint32_t row2 = (uint32_t)(colside ? td.row0 : td.col0), col2 = (uint32_t)(colside ? td.col0 : td.row0) + a0;
+    // W and a factor Q can hold 4 GiB and more (the BF16 products' planes of X are half as large), so offsets of 32 bits
+    // count from the item's first row and, where the contraction runs over rows, from the chunk's.
+    const uint32_t ld8 = (uint32_t)ldw * 8, k8 = (uint32_t)k * 8;
+    const int64_t row1 = (colside ? td.col0 : td.row0) + a0, col1 = colside ? td.row0 : td.col0;
+    const int64_t row2 = col1, col2 = row1;
+    const float2 *W1 = W + row1 * ldw + col1, *W2 = W + row2 * ldw + col2;
+    const float2 *F = theta + (FROW ? td.offB : td.offA);
+    const uint32_t end1 = (uint32_t)min((ldw * ldw - row1 * ldw - col1) * 8, (int64_t)0xfffffff0);
+    auto buffer = [](const float2 *p, uint32_t bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(scalar(p), (short)0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+    };
+    const auto rsW1 = buffer(W1, end1), rsR = buffer(F, k8 * (uint32_t)td.dj);   // FROW: R is k x dj
+    auto rows = [&](const float2 *p, int left, uint32_t pitch) {   // of a chunk: what lies past the last one reads zero
+        return buffer(p, (uint32_t)min(max(left, 0), GR_CH) * pitch);
+    };
     const uint32_t m = min(j32, nout - 1);   // rows and rank entries past the item repeat its last one and are dropped
-    const uint32_t o1 = (row1 + m) * ld8 + (col1 + 4 * half) * 8, o2 = (row2 + 4 * half) * ld8 + (col2 + m) * 8;
+    const uint32_t o1 = m * ld8 + 32 * half, o2 = 4 * half * ld8 + m * 8;
     const int comp = j32 & 1;
-    const uint32_t fs = FROW ? 8 : 8 * k;
     uint32_t of[KQ];
 #pragma unroll
     for (int q = 0; q < KQ; ++q) {
         const uint32_t n = b0 + min(16 * q + (j32 >> 1), kn - 1);
-        of[q] = (FROW ? n * td.dj * 8 : n * 8) + 4 * half * fs;
+        of[q] = FROW ? n * td.dj * 8 + 32 * half : n * 8 + 4 * half * k8;
     }
 
     auto load = [&](GradChunk<KQ> &x, int ch) {
-        const uint32_t c = ch * GR_CH;
+        const int c = ch * GR_CH;
 #pragma unroll
         for (int i = 0; i < 4; i += 2) {   // the second entry may lie past the tile: dropped in compute()
-            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsW, (int)(o1 + 8 * i), (int)(8 * c), 0);
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsW1, (int)(o1 + 8 * i), 8 * min(c, ncon - 1), 0);
             x.w1[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
             x.w1[i + 1] = make_float2(__uint_as_float(v[2]), __uint_as_float(v[3]));
         }
+        const auto rsW2 = rows(W2 + c * ldw, ncon - c, ld8);
+        const auto rsF = FROW ? rsR : rows(F + (int64_t)c * k, ncon - c, k8);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const bool in = (int)c + 4 * half + i < ncon;
-            u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsW, in ? (int)(o2 + (c + i) * ld8) : -1, 0, 0);
+            u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsW2, (int)(o2 + i * ld8), 0, 0);
             x.w2[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+            const bool in = !FROW || c + 4 * half + i < ncon;   // past a row of R its next one follows
 #pragma unroll
             for (int q = 0; q < KQ; ++q) {
-                v = __builtin_amdgcn_raw_buffer_load_b64(rsF, in ? (int)(of[q] + (c + i) * fs) : -1, 0, 0);
+                v = __builtin_amdgcn_raw_buffer_load_b64(rsF, in ? (int)(of[q] + (FROW ? 8 * (c + i) : i * k8)) : -1, 0, 0);
                 x.f[q][i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
             }
         }
