@@ -163,13 +163,16 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
     const float2 *PLf = DIR ? pv + td.offA : nullptr;
     const float2 *PRf = DIR ? (qq ? PLf : pv + td.offB) : nullptr;
     // A chunk of the factors: an entry outside them is past its buffer's end and reads zero, so the loads carry no
-    // conditions and are in flight together.
+    // conditions and are in flight together. A factor Q can hold 4 GiB and more, so offsets count from the block's first
+    // row (of R: column).
     constexpr int NE = AB * AKC / 256;
-    auto buffer = [&](const float2 *p, int cols) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(p), (short)0, cols * k * 8, 0x00020000);
+    auto buffer = [&](const float2 *p, uint32_t entries) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(p), (short)0, (int)(8u * entries), 0x00020000);
     };
-    const auto La = buffer(Lf, td.di), Ra = buffer(Rf, td.dj);
-    const auto Pl = buffer(DIR ? PLf : Lf, td.di), Pr = buffer(DIR ? PRf : Rf, td.dj);
+    const int64_t oL = (int64_t)r0 * k, oR = qq ? (int64_t)c0 * k : c0;
+    const uint32_t nL = (uint32_t)nrow * k, nR = qq ? (uint32_t)ncol * k : (uint32_t)k * td.dj - c0;
+    const auto La = buffer(Lf + oL, nL), Ra = buffer(Rf + oR, nR);
+    const auto Pl = buffer((DIR ? PLf : Lf) + oL, nL), Pr = buffer((DIR ? PRf : Rf) + oR, nR);
     u32x2 va[NE][NF], vb[NE][NF];
     auto load = [&](int kc0) {
 #pragma unroll
@@ -179,8 +182,8 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
             // Q[c0+cc][kc0+kk]
             const int rr = e / AKC, kr = kc0 + e % AKC;
             const int cc = qq ? e / AKC : e & 63, kk = kc0 + (qq ? e % AKC : e >> 6);
-            const uint32_t oa = rr < nrow && kr < k ? 8u * (uint32_t)((r0 + rr) * k + kr) : OUTSIDE;
-            const uint32_t ob = cc < ncol && kk < k ? 8u * (uint32_t)(qq ? (c0 + cc) * k + kk : kk * td.dj + c0 + cc) : OUTSIDE;
+            const uint32_t oa = rr < nrow && kr < k ? 8u * (uint32_t)(rr * k + kr) : OUTSIDE;
+            const uint32_t ob = cc < ncol && kk < k ? 8u * (uint32_t)(qq ? cc * k + kk : kk * td.dj + cc) : OUTSIDE;
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 va[i][f] = __builtin_amdgcn_raw_buffer_load_b64(f ? Pl : La, (int)oa, 0, 0);

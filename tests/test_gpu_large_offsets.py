@@ -1,6 +1,6 @@
-"""Gradient where a matrix passes 4 GiB, which byte offsets of 32 bits do not reach: nr 23296 in
+"""Gradient and assembly where a matrix or a factor passes 4 GiB, which byte offsets of 32 bits do not reach: nr 23296 in
 the BF16 split, whose planes of X are half as large as W = D^H r (4.3 GB). Tiles beyond the first 4 GiB of W; one tile
-that W's rows leave in the middle of its contraction.
+that W's rows leave in the middle of its contraction; a factor Q of 4.3 GB.
 
 The factors are zero but for some rows and rank entries (the first, the last, and those around 2^31 and 2^32 bytes), so
 every sum has few terms that are not zero and the bounds stay narrow. They are those of the entry-by-entry tests of the
@@ -28,7 +28,7 @@ def _some(n, gen):
     return sorted(x for x in at if 0 <= x < n)
 
 
-@pytest.mark.parametrize("sizes,off,diag", [([8192, 8192, 6912], 5, 7), ([NR], 0, 3)])
+@pytest.mark.parametrize("sizes,off,diag", [([8192, 8192, 6912], 5, 7), ([NR], 0, 3), ([NR], 0, NR)])
 def test_gradient_beyond_4_gib(sizes, off, diag):
     import paper_2412_14973_amd as tl
     n = len(sizes)
