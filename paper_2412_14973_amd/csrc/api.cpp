@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "extents.hpp"
 #include "tlrmdd.h"
 #include "svd.hpp"
 #include "tlr.hpp"
@@ -1240,6 +1241,12 @@ int fin(const Ctx &c, FinArgs f, const int32_t *counts, int ucount, int nsum, co
     return TLRMDD_OK;
 }
 
+// An FP32 call whose (padded) fields the products' offsets do not reach ends here
+int check_field(int64_t lds, int64_t ldk) {
+    if (field_fits(lds, ldk)) return TLRMDD_OK;
+    return fail(TLRMDD_HIP_ERROR, "invalid argument: FP32 products take fields below 4 GiB (ns and nr rounded up to 128)");
+}
+
 // The dense products contract over the true length rounded up to the kernel's k step (16 complex,
 // 32 in BF16), not over the padded one: the padding is zero and would only add stages.
 // r_true: r is ns x nr (or null: not wanted), else padded
@@ -1272,6 +1279,7 @@ int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64
         HIP_TRY(timed(TLRMDD_K_GEMM_RESID, c.s, wk, [&] { return launch_cgemm_bf16(GM_RESID, g, c.nprob, c.s, c.split); }));
         return TLRMDD_OK;
     }
+    if (int st = check_field(c.lds, c.ldk)) return st;
     GemmArgs g = gemm_args();
     g.A = c.dmat(); g.lda = c.ldd(); g.sA = c.lds * c.ldk;
     g.B = X; g.ldb = c.ldk; g.sB = sX;
@@ -1308,6 +1316,7 @@ int gemm_adjoint(const Ctx &c, const float2 *r, int64_t ldr, float2 *W, int64_t 
         HIP_TRY(timed(TLRMDD_K_GEMM_ADJOINT, c.s, wk, [&] { return launch_cgemm_bf16(GM_STORE, g, c.nprob, c.s, c.split); }));
         return TLRMDD_OK;
     }
+    if (int st = check_field(c.lds, c.ldk)) return st;
     GemmArgs g = gemm_args();
     g.A = c.dmat(); g.lda = c.ldd(); g.sA = c.lds * c.ldk;   // read transposed and conjugated
     g.B = r; g.ldb = ldr; g.sB = c.lds * c.ldk;
@@ -2932,6 +2941,7 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
     TlrHost T = tlr_plan(H, lds);
     const TlrWs w = tlr_carve((char *)workspace, T, lds, ldk);
     if (w.bytes > ws_bytes) return fail(TLRMDD_WORKSPACE, "workspace too small");
+    if (int st = check_field(lds, ldk)) return st;
     hipStream_t s = stream;
     for (PackItem b : T.packB) {   // one list, relative to A
         b.dst += w.B - w.A;

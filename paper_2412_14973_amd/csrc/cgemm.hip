@@ -33,6 +33,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "extents.hpp"
 #include "gemm_common.hpp"
 
 namespace tlr {
@@ -364,21 +365,13 @@ hipError_t launch_cgemm(int mode, const GemmArgs &a0, int batch, hipStream_t s, 
     a.tiles_n = a.N / wt;
     a.Mt = a.Mt > 0 ? std::min(a.Mt, a.M) : a.M;
     a.Nt = a.Nt > 0 ? std::min(a.Nt, a.N) : a.N;
-    // byte extents of the buffer resources (32-bit): A is Mt x lda (transposed source: Kt x lda), B is Kt x ldb
-    // (GM_LINE: B2 follows B)
     if (ta && a.lda < a.Mt) return hipErrorInvalidValue;
-    const int kt = a.Kt > 0 ? std::min(a.Kt, a.K) : a.K;
-    const int64_t bytesA = (int64_t)(ta ? kt : a.Mt) * a.lda * 8;
-    int64_t bytesB = (int64_t)kt * a.ldb * 8;
-    a.b2_off = 0;
-    if (mode == GM_LINE) {
-        a.b2_off = a.B2 - a.B;
-        if (a.b2_off < 0) return hipErrorInvalidValue;
-        bytesB += a.b2_off * 8;
-    }
-    if (bytesA >= (int64_t)1 << 32 || bytesB >= (int64_t)1 << 32) return hipErrorInvalidValue;
-    a.bytesA = (uint32_t)bytesA;
-    a.bytesB = (uint32_t)bytesB;
+    a.b2_off = mode == GM_LINE ? a.B2 - a.B : 0;
+    if (a.b2_off < 0) return hipErrorInvalidValue;
+    const Extents ex = gemm_extents(a.M, a.N, a.K, a.Mt, a.Kt > 0 ? std::min(a.Kt, a.K) : a.K, ta, a.lda, a.ldb, a.b2_off);
+    if (!ex.fit) return hipErrorInvalidValue;
+    a.bytesA = ex.bytesA;
+    a.bytesB = ex.bytesB;
     if (!stage) return m3 ? go_dense<true>(mode, a, batch, s, role, split) : go_dense<false>(mode, a, batch, s, role, split);
     if (role == GR_TILE_TA_CB) return go_big<GM_STORE, true, GR_TILE_TA_CB, 1>(a, batch, s);
     switch (mode) {

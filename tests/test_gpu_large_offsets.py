@@ -100,3 +100,17 @@ def test_gradient_beyond_4_gib(sizes, off, diag):
     for (i, j), a, b, ga, gb in zip(pairs, L, R, gL, gR):
         grad_block(ga, i, j, b.mH.conj(), False, ("L", i, j))     # W' R^H: F = R^T
         grad_block(gb, j, i, a, True, ("R", i, j))               # (L^H W')^T = W'^T conj(L)
+
+
+def test_fields_of_4_gib_are_refused():
+    """A field below 4 GiB that its padding takes past it: an error from every FP32 call, not the field's first rows
+    again in place of the padding."""
+    import paper_2412_14973_amd as tl
+    nr, ns = 1000, 536870
+    plan = tl.Plan(np.array([nr]), np.zeros(0, dtype=np.int32), np.ones(1, dtype=np.int32), ns)
+    D = torch.zeros(ns, nr, dtype=torch.complex64, device="cuda")
+    theta = torch.zeros(plan.theta_size, dtype=torch.complex64, device="cuda")
+    for call in (lambda: tl.adjoint(plan, D, D), lambda: tl.forward(plan, D, D, theta), lambda: tl.grad(plan, D, D, theta),
+                 lambda: tl.forward_tlr(plan, D, D, theta), lambda: tl.solve(plan, D, D, theta, iters=1)):
+        with pytest.raises(tl._lib.TLRMDDError, match="invalid argument"):
+            call()
