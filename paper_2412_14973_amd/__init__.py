@@ -519,7 +519,7 @@ class TLRMDDObjective(torch.autograd.Function):
     def backward(ctx, gout):
         (theta,) = ctx.saved_tensors
         _, g = grad(ctx.plan, ctx.D, ctx.U, theta, ctx.precision)
-        return g.mul_(gout), None, None, None, None   # g is this call's own
+        return g * gout, None, None, None, None   # (not in place: gout may be batched)
 
 
 def objective(theta, D, U, plan, precision=FP32):
