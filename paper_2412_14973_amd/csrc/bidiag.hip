@@ -521,7 +521,8 @@ struct Steps {
             hi = b == NS ? hi : fma(step, b + 1, lo);
             lo = nlo;
         }
-        if (tid == 0) e2[n] = 0.5 * (lo + hi) / sc;
+        // the lower end: counted as reached, so that a threshold of v0 itself counts the value it comes from
+        if (tid == 0) e2[n] = lo / sc;
         for (int i = tid; i < n; i += NT) {
             d2[i] = sd2[i] / (sc * sc);
             e2[i] = se2[i] / (sc * sc);

@@ -109,3 +109,21 @@ def test_layouts_together_and_one_by_one(nr, cand, bad):
     ko, kd, _ = tl.tile_ranks(X, d, 0.02)
     assert ro.tolist() == np.maximum(1, ko).tolist()
     assert rd.tolist() == [-1 if k >= (s + 1) // 2 else max(1, k) for k, s in zip(kd.tolist(), sizes.tolist())]
+
+
+@pytest.mark.parametrize("nr,d", [(1, 1), (33, 16), (64, 32), (97, 33), (64, 64), (300, 100), (356, 256), (530, 257), (600, 560)])
+def test_rank_counts_at_the_largest_singular_value(nr, d):
+    """eps = 1: v0 counts in its own tile and in no other; where all singular values are alike, all of them do."""
+    import paper_2412_14973_amd as tl
+    X = _symmetric(nr, 13 * nr + d)
+    ko, kd, _ = tl.tile_ranks(torch.from_numpy(X).cuda(), d, 1.0)
+    cut = list(range(0, nr, d)) + [nr]
+    top = {(i, j): np.linalg.norm(X[cut[i]:cut[i + 1], cut[j]:cut[j + 1]].astype(np.complex128), 2)
+           for i in range(len(cut) - 1) for j in range(i + 1)}
+    best = max(top.values())
+    assert sum(s > (1 - 1e-9) * best for s in top.values()) == 1
+    n = len(cut) - 1
+    want = {ij: int(s == best) for ij, s in top.items()}
+    assert ko.tolist() == [want[i, j] for i in range(n) for j in range(i)] and kd.tolist() == [want[i, i] for i in range(n)]
+    ko, kd, v0 = tl.tile_ranks(torch.eye(nr, dtype=torch.complex64, device="cuda") * 2.5, d, 1.0)
+    assert not np.any(ko[:n * (n - 1) // 2]) and kd.tolist() == np.diff(cut).tolist() and abs(v0 - 2.5) <= 1e-13
