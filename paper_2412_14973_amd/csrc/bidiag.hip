@@ -112,10 +112,12 @@ __device__ __forceinline__ Reflect reflect(double2 alpha, double xnorm2) {
 }
 
 // how many singular values of the bidiagonal are >= t (d2, e2: squares, scaled with t so that the largest is of
-// the order of 1: no step over- or underflows)
+// the order of 1: no step over- or underflows; nor do a t far above all of them, which needs no count, and one whose
+// square vanishes, which only an exact zero is below)
 __device__ __forceinline__ int at_least(const double *d2, const double *e2, int n, double t) {
     if (!(t > 0.0)) return n;
-    const double t2 = t * t;
+    if (t >= 4.0) return 0;
+    const double t2 = fmax(t * t, 2.3e-308);
     double s = -t2;
     int below = 0;
     for (int i = 0; i < n; ++i) {

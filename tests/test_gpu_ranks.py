@@ -127,3 +127,19 @@ def test_rank_counts_at_the_largest_singular_value(nr, d):
     assert ko.tolist() == [want[i, j] for i in range(n) for j in range(i)] and kd.tolist() == [want[i, i] for i in range(n)]
     ko, kd, v0 = tl.tile_ranks(torch.eye(nr, dtype=torch.complex64, device="cuda") * 2.5, d, 1.0)
     assert not np.any(ko[:n * (n - 1) // 2]) and kd.tolist() == np.diff(cut).tolist() and abs(v0 - 2.5) <= 1e-13
+
+
+@pytest.mark.parametrize("nr,d", [(64, 32), (128, 64), (200, 100), (400, 200), (600, 300), (1200, 600)])
+@pytest.mark.parametrize("scale", [1.0, 1e-30, 1e30])
+def test_rank_counts_at_extreme_thresholds(nr, d, scale):
+    """Thresholds whose squares leave the range of FP64: none of the values is above, and all but exact zeros are."""
+    import paper_2412_14973_amd as tl
+    X = torch.eye(nr, dtype=torch.complex64, device="cuda") * scale
+    for eps in (1e300, 1e200, 1e160, 1e20, 5.0, 1.5):
+        ko, kd, _ = tl.tile_ranks(X, d, eps)
+        assert ko.tolist() == [0] and kd.tolist() == [0, 0], eps
+    for eps in (1e-250, 1e-190, 1e-155, 1e-110, 1e-60):
+        ko, kd, _ = tl.tile_ranks(X, d, eps)
+        assert ko.tolist() == [0] and kd.tolist() == [d, d], eps
+    ko, kd, _ = tl.tile_ranks(X, d, 0.0)
+    assert ko.tolist() == [d] and kd.tolist() == [d, d]
