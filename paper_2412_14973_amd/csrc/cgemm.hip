@@ -24,7 +24,9 @@
 // complex entries of one column.
 //
 // Epilogues: GM_STORE (C = AB), GM_RESID (C = AB - U plus FP64 partial sums of |C|^2) and GM_LINE (a and b
-// plus FP64 partial sums of Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2 for the exact line search).
+// plus FP64 partial sums of Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2 for the exact line search). GM_LINE unsplit, three
+// products, has two registers too few for three waves per SIMD in its epilogue: they go through scratch once a wave,
+// outside the k loop.
 //
 // Operands are padded to whole 64-tiles with zeros, or read where the caller has them: no load carries a bounds
 // check (they are buffer loads: anything past an operand's last row reads zero), and what a row-major operand

@@ -29,13 +29,13 @@ __device__ __forceinline__ void *scalar(const void *p) {
     return reinterpret_cast<void *>(lo | hi << 32);
 }
 
-// the five products of the line-search sums: Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2
-__device__ __forceinline__ void line_terms(float (&blk)[5], float2 r, float2 a, float2 b) {
-    blk[0] = fmaf(r.x, a.x, fmaf(r.y, a.y, blk[0]));
-    blk[1] = fmaf(a.x, a.x, fmaf(a.y, a.y, blk[1]));
-    blk[2] = fmaf(r.x, b.x, fmaf(r.y, b.y, blk[2]));
-    blk[3] = fmaf(a.x, b.x, fmaf(a.y, b.y, blk[3]));
-    blk[4] = fmaf(b.x, b.x, fmaf(b.y, b.y, blk[4]));
+// one component's products of the line-search sums: Re<r,a>, |a|^2, Re<r,b>, Re<a,b>, |b|^2
+__device__ __forceinline__ void line_terms(float (&blk)[5], float r, float a, float b) {
+    blk[0] = fmaf(r, a, blk[0]);
+    blk[1] = fmaf(a, a, blk[1]);
+    blk[2] = fmaf(r, b, blk[2]);
+    blk[3] = fmaf(a, b, blk[3]);
+    blk[4] = fmaf(b, b, blk[4]);
 }
 
 // One batch entry's epilogue operands.
@@ -59,7 +59,8 @@ enum ColumnsOfC { COL_PLAIN, COL_SCAT, COL_MAP };
 // is a and n = 1 is b at the same columns). GM_STORE: C = AB. GM_RESID: C = AB - E and the sum of |C|^2. GM_LINE:
 // the five line sums. KS > 1: the workgroup's KS waves hold shares of the same blocks; they are added in LDS in a
 // fixed order, each wave finishing 16 / KS rows of every lane. A block's sums are its lanes' FP32 sums over the
-// rows, added in FP64, one partial slot per 32 x 32 block, numbered by block row and column whatever the tile.
+// rows, real and imaginary parts apart (16 products at most), added in FP64, one partial slot per 32 x 32 block,
+// numbered by block row and column whatever the tile.
 // GM_RESID: also(h, cb, v) gets the finished rows of a lane (KS > 1: rows wave * 16 / KS and on of its registers).
 struct Nothing {
     template <class V>
@@ -129,9 +130,9 @@ __device__ __forceinline__ void block_epilogue(const EpiArgs &ea, F &&cval, int 
                     }
                 }
             }
-            float blk[NS];
+            float blk[2][NS];
 #pragma unroll
-            for (int q = 0; q < NS; ++q) blk[q] = 0.f;
+            for (int q = 0; q < NS; ++q) blk[0][q] = blk[1][q] = 0.f;
             if constexpr (MODE == GM_STORE) {
                 int64_t ccol = cc;
                 if (COLS == COL_SCAT && ea.scat_kp > 0) {
@@ -149,7 +150,8 @@ __device__ __forceinline__ void block_epilogue(const EpiArgs &ea, F &&cval, int 
                     // zero outside E: an operand read in place has other entries there than zeros
                     const bool in = row_of(h, r) < ea.Me && cc < ea.Ne;
                     const float2 d = in ? make_float2(v[0][r].x - e[r].x, v[0][r].y - e[r].y) : make_float2(0.f, 0.f);
-                    blk[0] = fmaf(d.x, d.x, fmaf(d.y, d.y, blk[0]));
+                    blk[0][0] = fmaf(d.x, d.x, blk[0][0]);
+                    blk[1][0] = fmaf(d.y, d.y, blk[1][0]);
                     v[0][r] = d;
                 }
                 put(cc, v[0]);
@@ -159,14 +161,15 @@ __device__ __forceinline__ void block_epilogue(const EpiArgs &ea, F &&cval, int 
                 for (int r = 0; r < NR; ++r) {
                     ea.C[(int64_t)row_of(h, r) * ea.ldc + cc] = v[0][r];
                     ea.C2[(int64_t)row_of(h, r) * ea.ldc + cc] = v[NV - 1][r];
-                    line_terms(blk, e[r], v[0][r], v[NV - 1][r]);
+                    line_terms(blk[0], e[r].x, v[0][r].x, v[NV - 1][r].x);
+                    line_terms(blk[1], e[r].y, v[0][r].y, v[NV - 1][r].y);
                 }
             }
             if constexpr (MODE != GM_STORE) {
                 const int64_t slot = (int64_t)((m0 >> 5) + h) * ea.nblk + (cc >> 5);
 #pragma unroll
                 for (int q = 0; q < NS; ++q) {
-                    const double s = wave_sum((double)blk[q]);
+                    const double s = wave_sum((double)blk[0][q] + (double)blk[1][q]);
                     if (lane == 0) {
                         if constexpr (KS == 1) ea.partials[slot * NS + q] = s;
                         else red[wave][q] = s;

@@ -128,3 +128,24 @@ def test_bf16_unsplit_solve():
     (t0, f0), (t1, f1) = out
     assert float(((f0 - f1).abs() / f0).max()) <= 5e-3
     assert float((t0 - t1).norm() / t0.norm()) <= 5e-3
+
+
+# the contraction split over waves, and (above 8191 blocks) not
+@pytest.mark.parametrize("nr,ns", [(96, 70), (2912, 2912)])
+@pytest.mark.parametrize("form", ["FP32", "FP32_3M", "BF16X3"])
+def test_objective_sums_of_few_products(nr, ns, form):
+    """theta = 0, so r = -U exactly, with |Re u|^2 = 1 and |Im u|^2 = 2^-26. A lane's FP32 sums hold one component of 16
+    rows at most: 16 and 16 2^-26 are exact there, and the FP64 additions from there on, under 2^10 in a row, err by
+    2^10 2^-53 = 1.2e-13 at the most. With both components in one FP32 sum the small ones vanish, 1.5e-8 of f."""
+    import paper_2412_14973_amd as tl
+    plan = tl.Plan(np.array([nr]), np.zeros(0, dtype=np.int32), np.ones(1, dtype=np.int32), ns)
+    D = torch.ones(ns, nr, dtype=torch.complex64, device="cuda")
+    U = torch.full((ns, nr), complex(1.0, 2.0 ** -13), dtype=torch.complex64, device="cuda")
+    theta = torch.zeros(plan.theta_size, dtype=torch.complex64, device="cuda")
+    want = 0.5 * ns * nr * (1 + 2.0 ** -26)
+    tol = 1.2e-13 * want
+    f, r, _ = tl.forward(plan, D, U, theta, getattr(tl, form), want_r=True)
+    assert torch.equal(r, -U) and abs(float(f) - want) <= tol
+    if form == "FP32":   # the tile low-rank product's second stage, never split
+        f, r = tl.forward_tlr(plan, D, U, theta, want_r=True)
+        assert torch.equal(r, -U) and abs(float(f) - want) <= tol
