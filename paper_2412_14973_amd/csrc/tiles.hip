@@ -296,11 +296,13 @@ __global__ __launch_bounds__(256, 4) void assemble_kernel(const TileDesc *__rest
 // The item's four waves take chunks of 8 c in turn and their sums are added in LDS at the end; until then a wave waits
 // for nobody.
 //
-// What bounds it: the matrix cores in full launches, where a rank is padded to 16 (4096^2 of tiles 256, rank 32: 66 us,
-// 130 TFLOP/s of 8 d d k a product), else the chain of chunks. Before, a workgroup of 64 rows staged W' and F in LDS,
-// 4 c and three barriers at a time: 113 us; nr 1024 (tiles 128, rank 20) 43 us, now 8.2; nr 2304 (tiles 512,
+// What bounds it: the matrix cores in full launches, where a rank is padded to 16 (4096^2 of tiles 256, rank 32: 67 us,
+// 128 TFLOP/s of 8 d d k a product), else the chain of chunks. Before, a workgroup of 64 rows staged W' and F in LDS,
+// 4 c and three barriers at a time: 113 us; nr 1024 (tiles 128, rank 20) 43 us, now 7.7; nr 2304 (tiles 512,
 // rank 40) 166, now 49.
 constexpr int GR_CH = 8;               // contraction entries per chunk: four per half of a wave
+constexpr int GR_FAR = 8192;           // contraction rows that 32-bit offsets span (of up to 2^16 entries each)
+static_assert(GR_FAR % (4 * GR_CH) == 0, "each wave's share of the contraction goes on where it ended");
 constexpr int GP_P = 66;               // partial blocks [4 waves][16][GP_P] floats
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -325,19 +327,15 @@ __device__ __forceinline__ void grad_block(const GradItem &it, const TileDesc &t
     // W'[m][c] = w1[m ldw + c] + w2[c ldw + m]. Buffer loads: an offset past the end gives zero, so the chunks at
     // the end of the contraction need no branch (a branch would make each load wait for the ones before it).
     // W and a factor Q can hold 4 GiB and more (the BF16 products' planes of X are half as large), so offsets of 32 bits
-    // count from the item's first row and, where the contraction runs over rows, from the chunk's.
+    // count from the item's first row and, where the contraction runs over rows, from the first of GR_FAR of them (a base
+    // for every chunk took nr 1024 from 7.7 us to 8.3, nr 4096 from 66 to 71).
     const uint32_t ld8 = (uint32_t)ldw * 8, k8 = (uint32_t)k * 8;
     const int64_t row1 = (colside ? td.col0 : td.row0) + a0, col1 = colside ? td.row0 : td.col0;
     const int64_t row2 = col1, col2 = row1;
     const float2 *W1 = W + row1 * ldw + col1, *W2 = W + row2 * ldw + col2;
     const float2 *F = theta + (FROW ? td.offB : td.offA);
-    const uint32_t end1 = (uint32_t)min((ldw * ldw - row1 * ldw - col1) * 8, (int64_t)0xfffffff0);
     auto buffer = [](const float2 *p, uint32_t bytes) {
         return __builtin_amdgcn_make_buffer_rsrc(scalar(p), (short)0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
-    };
-    const auto rsW1 = buffer(W1, end1), rsR = buffer(F, k8 * (uint32_t)td.dj);   // FROW: R is k x dj
-    auto rows = [&](const float2 *p, int left, uint32_t pitch) {   // of a chunk: what lies past the last one reads zero
-        return buffer(p, (uint32_t)min(max(left, 0), GR_CH) * pitch);
     };
     const uint32_t m = min(j32, nout - 1);   // rows and rank entries past the item repeat its last one and are dropped
     const uint32_t o1 = m * ld8 + 32 * half, o2 = 4 * half * ld8 + m * 8;
@@ -348,61 +346,65 @@ __device__ __forceinline__ void grad_block(const GradItem &it, const TileDesc &t
         const uint32_t n = b0 + min(16 * q + (j32 >> 1), kn - 1);
         of[q] = FROW ? n * td.dj * 8 + 32 * half : n * 8 + 4 * half * k8;
     }
-
-    auto load = [&](GradChunk<KQ> &x, int ch) {
-        const int c = ch * GR_CH;
-#pragma unroll
-        for (int i = 0; i < 4; i += 2) {   // the second entry may lie past the tile: dropped in compute()
-            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsW1, (int)(o1 + 8 * i), 8 * min(c, ncon - 1), 0);
-            x.w1[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
-            x.w1[i + 1] = make_float2(__uint_as_float(v[2]), __uint_as_float(v[3]));
-        }
-        const auto rsW2 = rows(W2 + c * ldw, ncon - c, ld8);
-        const auto rsF = FROW ? rsR : rows(F + (int64_t)c * k, ncon - c, k8);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsW2, (int)(o2 + i * ld8), 0, 0);
-            x.w2[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
-            const bool in = !FROW || c + 4 * half + i < ncon;   // past a row of R its next one follows
-#pragma unroll
-            for (int q = 0; q < KQ; ++q) {
-                v = __builtin_amdgcn_raw_buffer_load_b64(rsF, in ? (int)(of[q] + (FROW ? 8 * (c + i) : i * k8)) : -1, 0, 0);
-                x.f[q][i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
-            }
-        }
-    };
     floatx16 acc[KQ];
 #pragma unroll
     for (int q = 0; q < KQ; ++q)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
-    auto compute = [&](const GradChunk<KQ> &x, int ch) {
+    for (int far = 0; far < ncon; far += GR_FAR) {
+        const int n = min(ncon - far, GR_FAR);   // entries of the contraction from far on
+        const auto rsW1 = buffer(W1 + far, (uint32_t)nout * ld8 - (uint32_t)(col1 + far) * 8);
+        const auto rsW2 = buffer(W2 + far * ldw, n * ld8);   // what lies past the last row reads zero
+        const auto rsF = FROW ? buffer(F + far, k8 * (uint32_t)td.dj - 8 * far) : buffer(F + (int64_t)far * k, n * k8);
+        auto load = [&](GradChunk<KQ> &x, int ch) {
+            const uint32_t c = ch * GR_CH, row = min(ch * GR_CH, n);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bool in = ch * GR_CH + 4 * half + i < ncon;
-            const float wx = in ? x.w1[i].x + x.w2[i].x : 0.f, wy = in ? x.w1[i].y + x.w2[i].y : 0.f;
+            for (int i = 0; i < 4; i += 2) {   // the second entry may lie past the tile: dropped in compute()
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsW1, (int)(o1 + 8 * i), (int)(8 * row), 0);
+                x.w1[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+                x.w1[i + 1] = make_float2(__uint_as_float(v[2]), __uint_as_float(v[3]));
+            }
 #pragma unroll
-            for (int q = 0; q < KQ; ++q)
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(wx, comp ? -x.f[q][i].y : x.f[q][i].x, acc[q], 0, 0, 0);
+            for (int i = 0; i < 4; ++i) {
+                u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsW2, (int)(o2 + i * ld8), (int)(row * ld8), 0);
+                x.w2[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+                const bool in = !FROW || (int)c + 4 * half + i < n;   // past a row of R its next one follows
 #pragma unroll
-            for (int q = 0; q < KQ; ++q)
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(wy, comp ? x.f[q][i].x : x.f[q][i].y, acc[q], 0, 0, 0);
+                for (int q = 0; q < KQ; ++q) {
+                    v = FROW ? __builtin_amdgcn_raw_buffer_load_b64(rsF, in ? (int)(of[q] + 8 * (c + i)) : -1, 0, 0)
+                             : __builtin_amdgcn_raw_buffer_load_b64(rsF, (int)(of[q] + i * k8), (int)(row * k8), 0);
+                    x.f[q][i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+                }
+            }
+        };
+        auto compute = [&](const GradChunk<KQ> &x, int ch) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool in = ch * GR_CH + 4 * half + i < n;
+                const float wx = in ? x.w1[i].x + x.w2[i].x : 0.f, wy = in ? x.w1[i].y + x.w2[i].y : 0.f;
+#pragma unroll
+                for (int q = 0; q < KQ; ++q)
+                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(wx, comp ? -x.f[q][i].y : x.f[q][i].x, acc[q], 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < KQ; ++q)
+                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(wy, comp ? x.f[q][i].x : x.f[q][i].y, acc[q], 0, 0, 0);
+            }
+        };
+        const int nch = (n + GR_CH - 1) / GR_CH;
+        GradChunk<KQ> x0, x1;
+        int ch = wave;
+        if (ch < nch) {
+            load(x0, ch);
+            for (; ch + 4 < nch; ch += 8) {
+                load(x1, ch + 4);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(x0, ch);
+                load(x0, ch + 8);   // past the end: reads nothing or is not used
+                __builtin_amdgcn_sched_barrier(0);
+                compute(x1, ch + 4);
+            }
+            if (ch < nch) compute(x0, ch);
         }
-    };
-    const int nch = (ncon + GR_CH - 1) / GR_CH;
-    GradChunk<KQ> x0, x1;
-    int ch = wave;
-    if (ch < nch) {
-        load(x0, ch);
-        for (; ch + 4 < nch; ch += 8) {
-            load(x1, ch + 4);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(x0, ch);
-            load(x0, ch + 8);   // past the end: reads nothing (see rsW) or is not used
-            __builtin_amdgcn_sched_barrier(0);
-            compute(x1, ch + 4);
-        }
-        if (ch < nch) compute(x0, ch);
     }
 
     // lane (j32, half) holds component comp of rank entry 16 q + j32 / 2 for out-rows acc_row(r, lane)

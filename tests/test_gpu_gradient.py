@@ -84,3 +84,10 @@ def test_gradient_entry_by_entry(sizes, off, diag):
         s, e, m = S[a, b].contiguous(), ES[a, b].contiguous(), aS[a, b].contiguous()
         check(dL, s @ R.mH.contiguous(), (e + (2 * sizes[j] + 8) * U32 * m) @ R.abs().T.contiguous(), ("L", i, j))
         check(dR, L.mH.contiguous() @ s, L.abs().T.contiguous() @ (e + (2 * sizes[i] + 8) * U32 * m), ("R", i, j))
+
+
+# nr a multiple of 128, so W has no padding, and tiles that begin at an odd column and end with the last one: the pairs of
+# entries that a load takes reach past the end of W's rows, and of W
+@pytest.mark.parametrize("sizes,off,diag", [([1, 127], 1, 5), ([63, 65], 20, 17), ([3, 252, 1], 1, 1), ([127, 129], 40, -1)])
+def test_gradient_to_the_end_of_w(sizes, off, diag):
+    test_gradient_entry_by_entry(sizes, off, diag)
