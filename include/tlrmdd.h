@@ -382,8 +382,9 @@ int tlrmdd_permute_columns(const void *in, const int64_t *perm, void *out,
 #define TLRMDD_K_PERMUTE      11  /* column gather D S (tlrmdd_permute_columns)               */
 #define TLRMDD_K_GRAM         12  /* L-BFGS Gram pass                                        */
 #define TLRMDD_K_COMBINE      13  /* L-BFGS direction p = sum_b c_b v_b                       */
-#define TLRMDD_K_THETA_UPDATE 14  /* theta += a* p (and the newest s pair)                  */
-#define TLRMDD_K_RESID_UPDATE 15  /* r += a* a + a*^2 b                                     */
+#define TLRMDD_K_THETA_UPDATE 14  /* theta += a* p (and the newest s pair), its own launches */
+#define TLRMDD_K_RESID_UPDATE 15  /* r += a* a + a*^2 b; with theta's update, bytes included, where
+                                     one launch does both (no penalty, r not recomputed, 16 MB of r) */
 #define TLRMDD_K_NKINDS       16
 
 #define TLRMDD_DT_NONE  (-1)      /* no matrix-core flops counted (memory-bound kind)        */

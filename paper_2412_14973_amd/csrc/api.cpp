@@ -518,6 +518,7 @@ Ws carve(char *base, int op, int nprob, int64_t ldk, int64_t lds, int64_t theta_
     const size_t xsz = (size_t)nprob * ldk * ldk * c8;
     const size_t rsz = (size_t)nprob * lds * ldk * c8;
     w.Ds = (float2 *)take(rsz);
+    // (D^H and r^T planes: BF16 products only; a workspace asked for with one precision serves another)
     if (op >= 1) w.DHs = (float2 *)take((size_t)nprob * ldk * lds * c8);
     w.XW = (float2 *)take(op >= 2 ? 2 * xsz : xsz);
     w.r = (float2 *)take(rsz);
@@ -1286,7 +1287,7 @@ int gemm_resid(const Ctx &c, const float2 *X, int64_t sX, const float2 *U, int64
     g.C = r; g.ldc = ldr; g.sC = c.lds * c.ldk;
     g.Mc = Mc; g.Nc = Nc;
     g.E = U; g.lde = ldu; g.sE = sU;
-    g.partials = c.w.partials; g.sP = (int64_t)c.pstride;   // one sum per workgroup
+    g.partials = c.w.partials; g.sP = (int64_t)c.pstride;   // one sum per 32 x 32 block
     g.M = (int)c.lds; g.N = (int)c.ldk; g.K = (int)round_up(c.nr, GEMM_BK);
     g.Me = g.Mt = (int)c.ns; g.Ne = g.Nt = (int)c.nr;
     HIP_TRY(timed(TLRMDD_K_GEMM_RESID, c.s, wk, [&] {
@@ -1424,7 +1425,7 @@ int stage_split(const Ctx &c, const Problems &in, int p0, int count, bool with_d
 int stage(const Ctx &c, const void *D, bool with_dh) {
     if (c.bf16) return stage_split(c, problems(0, 1, nullptr, &D, nullptr, nullptr), 0, 1, true, with_dh);
     HIP_TRY(timed(TLRMDD_K_STAGE, c.s, bytes_work(16.0 * (double)c.ns * (double)c.nr), [&] {
-        return launch_stage_d((const float2 *)D, c.ns, c.nr, c.w.Ds, c.ldk, nullptr, c.lds, c.s);
+        return launch_stage_d((const float2 *)D, c.ns, c.nr, c.w.Ds, c.ldk, c.lds, c.s);
     }));
     return TLRMDD_OK;
 }
@@ -2571,8 +2572,8 @@ int svd_upload(const SvdHost &S, const SvdWs &w, const std::vector<WarmItem> *it
 
 // Ranks and v0 from bidiagonals (bidiag.hip) instead of Jacobi rotations, which only the singular vectors need:
 // finite tiles of at most BIDIAG_MAX_M rows; done = false leaves the rest to svd_run (a tile with a value that is
-// not finite, where the rotations still give the other columns' values; larger tiles, whose two reads and one write
-// per step of one workgroup would take as long as the rotations spread over the chip).
+// not finite, where the rotations still give the other columns' values; larger tiles, for which no kernel is built: one
+// workgroup per tile gains less the larger its tile is, see svd.hpp).
 // v0: one per grid of S.
 int svd_counts(const SvdHost &S, const SvdWs &w, const float2 *X, int64_t ldx, double eps, std::vector<int32_t> &k,
                double *v0, bool &done, hipStream_t s) {
@@ -2608,8 +2609,7 @@ int check_rank_args(const void *X, int64_t nr, int32_t d, double eps) {
     return TLRMDD_OK;
 }
 
-// ranks of all tiles at size d into host vectors (t order / diagonal order); synchronises the stream
-// counts in tile order to ranks below and on the diagonal
+// counts in tile order to ranks below the diagonal (t order) and on it
 void split_ranks(const int32_t *k, int N, std::vector<int32_t> &koff, std::vector<int32_t> &kdiag) {
     koff.clear();
     kdiag.assign(N, 0);
@@ -2619,6 +2619,7 @@ void split_ranks(const int32_t *k, int N, std::vector<int32_t> &koff, std::vecto
     }
 }
 
+// ranks of all tiles at size d into host vectors (t order / diagonal order); synchronises the stream
 int tile_ranks_impl(const void *X, int64_t nr, int32_t d, double eps, std::vector<int32_t> &koff,
                     std::vector<int32_t> &kdiag, double *v0, void *workspace, size_t ws_bytes, hipStream_t s) {
     int st = check_rank_args(X, nr, d, eps);
@@ -2958,7 +2959,7 @@ int tlrmdd_forward_tlr(tlrmdd_plan plan, const void *D, const void *U, const voi
     for (int i = 0; i < T.N; ++i) in_place = in_place && H.d[i] % GEMM_BK == 0;
     const float2 *Dm = in_place ? (const float2 *)D : w.Ds;
     const int64_t ldd = in_place ? nr : ldk;
-    if (!in_place) HIP_TRY(launch_stage_d((const float2 *)D, ns, nr, w.Ds, ldk, nullptr, lds, s));
+    if (!in_place) HIP_TRY(launch_stage_d((const float2 *)D, ns, nr, w.Ds, ldk, lds, s));
     HIP_TRY(launch_tlr_pack(w.pack, (int)T.packA.size(), (const float2 *)theta, w.A, s));
     for (const auto &run : T.runs) {   // stage 1: P_i = D_:,i A_i, stored as the column blocks of every Pcol_j
         const int i0 = run.first, cnt = run.second - run.first + 1, di = H.d[i0];

@@ -66,8 +66,9 @@ struct GemmArgs {
     float2 *C;        int64_t ldc;   // M x N output
     float2 *C2;                      // GM_LINE: second output (same ldc)
     const float2 *E;  int64_t lde;   // GM_RESID: U (C = AB - U); GM_LINE: residual r
-    double *partials;                // per-workgroup FP64 sums (GM_RESID: 1, GM_LINE: 5)
-    int32_t M, N, K;                 // padded sizes: M, N multiples of 64, K of 16 (zero padding)
+    double *partials;                // FP64 sums per 32 x 32 block of C (GM_RESID: 1, GM_LINE: 5)
+    int32_t M, N, K;                 // padded sizes: M, N multiples of 64, K of 16 (zeros, or an operand read in place:
+                                     // what its rows hold past its last column reaches nothing that is kept)
     int32_t Me, Ne;                  // GM_RESID: true shape of E (reads outside are zero)
     int32_t Mt, Nt;                  // true shape of C (blocks outside are zero; 0: M, N)
     int32_t Kt;                      // true K: rows of B, and of a transposed A, from Kt on read zero (0: K)
@@ -184,8 +185,7 @@ hipError_t launch_grad(const TileDesc *tiles, const GradItem *items, int nitems,
                        const ProbOff *probs, const float2 *W, const float2 *theta, float2 *g,
                        hipStream_t s);
 
-hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, int64_t ldk,
-                          float2 *DHs, int64_t lds, hipStream_t s);
+hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, int64_t ldk, int64_t lds, hipStream_t s);
 // The callers' arrays of up to PROBLEMS_MAX problems of a launch, by value: nothing to upload, and a captured launch
 // keeps them.
 constexpr int PROBLEMS_MAX = 32;

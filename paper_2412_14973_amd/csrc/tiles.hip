@@ -22,14 +22,6 @@
 namespace tlr {
 namespace {
 
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ float2 cmulc(float2 a, float2 b) {  // a * conj(b)
-    return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
-}
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-
 // Output: complex64 (OUTB = false) or split BF16 planes (OUTB = true, see launch_assemble).
 template <bool OUTB>
 __device__ __forceinline__ void put(float2 *X, int64_t row, int64_t col, int64_t ldx, int64_t low, float2 v) {

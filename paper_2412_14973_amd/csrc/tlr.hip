@@ -11,9 +11,9 @@
 // factor blocks into the GEMM operands (and zero their padding); the products themselves run
 // on the FP32 MFMA GEMM, whose first stage stores the P blocks where the second reads them and
 // whose second writes r in place. D is read in place where its rows allow it. nr 4096, ns 2048, tiles 256, rank 32:
-// 608 us, of which the products 580; 758 with a gather of the P blocks, a padded r and its copies. The solver's
-// tile forms of the line search and the gradient use the same factorisation; for them this file also holds the summation of the gradient's partial planes into
-// the factor gradients and the update of the carried theta half of stage 1.
+// 572 us; 758 with a gather of the P blocks, a padded r and its copies. The solver's tile forms of the line search and
+// the gradient use the same factorisation; for them this file also holds the summation of the gradient's partial
+// planes into the factor gradients and the update of the carried theta half of stage 1.
 #include <algorithm>
 
 #include "common.hpp"

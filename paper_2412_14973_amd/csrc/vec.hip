@@ -13,30 +13,14 @@ namespace tlr {
 namespace {
 
 // ---------------------------------------------------------------------------
-// staging: Ds = D (padded rows), DHs = conj(D)^T  (32 x 32 tiles through LDS)
+// staging: Ds = D, padded with zeros to lds x ldk (32 x 32 entries per workgroup)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void stage_d_kernel(const float2 *__restrict__ D, int64_t ns, int64_t nr,
-                                                      float2 *__restrict__ Ds, int64_t ldk,
-                                                      float2 *__restrict__ DHs, int64_t lds) {
-    // grid covers the padded lds x ldk block; padding is written as zeros
-    __shared__ float2 tile[32][33];
-    const int64_t s0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-    for (int r = ty; r < 32; r += 8) {
-        const int64_t s = s0 + r, c = c0 + tx;
-        float2 v = make_float2(0.f, 0.f);
-        if (s < ns && c < nr) v = D[s * nr + c];
-        if (Ds && s < lds && c < ldk) Ds[s * ldk + c] = v;
-        tile[r][tx] = v;
-    }
-    if (!DHs) return;
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int64_t c = c0 + r, s = s0 + tx;
-        if (s < lds && c < ldk) {
-            const float2 v = tile[tx][r];
-            DHs[c * lds + s] = make_float2(v.x, -v.y);
-        }
+                                                      float2 *__restrict__ Ds, int64_t ldk, int64_t lds) {
+    const int64_t s0 = (int64_t)blockIdx.y * 32, c = (int64_t)blockIdx.x * 32 + (threadIdx.x & 31);
+    for (int r = threadIdx.x >> 5; r < 32; r += 8) {
+        const int64_t s = s0 + r;
+        if (s < lds && c < ldk) Ds[s * ldk + c] = s < ns && c < nr ? D[s * nr + c] : make_float2(0.f, 0.f);
     }
 }
 
@@ -216,17 +200,6 @@ namespace {
 
 __device__ __forceinline__ double wave_sum64(double v) { return __ockl_wfred_add_f64(v); }
 
-__device__ __forceinline__ double block_sum(double v, double *red) {
-    v = wave_sum64(v);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0) r = ((red[0] + red[1]) + red[2]) + red[3];
-    __syncthreads();
-    return r;  // valid on thread 0
-}
-
 __device__ __forceinline__ int ring_slot(const SolveScalars &sc, int i, int m1) {
     int s = sc.head - 1 - i;
     s %= m1;
@@ -284,7 +257,7 @@ __device__ __forceinline__ double dot16(const V16 &x, const V16 &y) {
     return a;
 }
 
-// N block sums at once (thread 0 gets the totals); same fixed order as block_sum
+// N sums over a block of four waves at once, in a fixed order (thread 0 gets the totals)
 template <int N>
 __device__ __forceinline__ void block_sums(double (&v)[N], double *red) {
 #pragma unroll
@@ -473,8 +446,7 @@ __global__ __launch_bounds__(256) void admm_update_kernel(const VecSeg *__restri
     st16(cen, sg, vz);
 }
 
-// theta += step p ; S[head] = step p ; partial ||theta - c||^2 (c = 0 when cen is NULL)
-// theta += step p (and the newest s pair); part: |theta - cen|^2 of the segment, or null
+// theta += step p, S[head] = step p (Sb not null); part (or null): ||theta - cen||^2 of the segment (cen null: 0)
 __device__ __forceinline__ void theta_update(const VecSeg &sg, float *__restrict__ th, const float *__restrict__ p,
                                              float *__restrict__ Sb, int64_t stride2, const float *__restrict__ cen,
                                              const SolveScalars *__restrict__ sc, double *__restrict__ part, double *red) {
@@ -559,8 +531,7 @@ __global__ __launch_bounds__(256) void update_kernel(const VecSeg *__restrict__ 
 // ---------------------------------------------------------------------------
 // per-problem finalisation (one block per problem)
 // ---------------------------------------------------------------------------
-// the scalar work of one problem (thread 0); G: the staged Gram matrix and coefficients (FIN_GRAM)
-// rr = ||r||^2
+// the objective of one problem into its scalars and the history; rr = ||r||^2
 __device__ __forceinline__ void record_f(const FinArgs &fa, int prob, double rr, SolveScalars &s) {
     const double f = 0.5 * rr + fa.lam * s.thnorm2;
     s.f = f;
@@ -718,6 +689,7 @@ __device__ __forceinline__ void gram_scalars(const FinArgs &fa, const double *to
     }
 }
 
+// the scalar work of one problem (thread 0), all but the Gram pass's
 __device__ __forceinline__ void finalize_scalars(const FinArgs &fa, int prob, const double *tot, SolveScalars &s) {
     switch (fa.op) {
         case FIN_F:
@@ -872,10 +844,9 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinArgs fa) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, int64_t ldk,
-                          float2 *DHs, int64_t lds, hipStream_t s) {
+hipError_t launch_stage_d(const float2 *D, int64_t ns, int64_t nr, float2 *Ds, int64_t ldk, int64_t lds, hipStream_t s) {
     dim3 grid((unsigned)((ldk + 31) / 32), (unsigned)((lds + 31) / 32));
-    hipLaunchKernelGGL(stage_d_kernel, grid, dim3(256), 0, s, D, ns, nr, Ds, ldk, DHs, lds);
+    hipLaunchKernelGGL(stage_d_kernel, grid, dim3(256), 0, s, D, ns, nr, Ds, ldk, lds);
     return hipGetLastError();
 }
 
