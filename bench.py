@@ -657,7 +657,7 @@ def copy_reference(torch, mib=1024, reps=5):
 
 def grad_calls(tl, torch, inputs, prec, passes=3):
     """tlrmdd_grad called once per frequency of the workload (objective and gradient of one problem per
-    call: assembly, r = D X - U, W = D^H r, tile contractions, with D staged per call), calls per second
+    call: assembly, r = D X - U, W = D^H r, tile contractions, with D read in place), calls per second
     of wall time over `passes` passes of all frequencies."""
     geom, Ds, Us, ths, plans = inputs
     dev = torch.device("cuda")
@@ -679,7 +679,7 @@ def grad_calls(tl, torch, inputs, prec, passes=3):
     return {"calls_per_s": n / dt, "ms_per_call": dt / n * 1e3, "calls": n,
             "dense_products_per_call": 2,
             "complex_equiv_tflops_of_the_two_products": 2 * 8.0 * ns * nr * nr * n / dt / 1e12,
-            "note": "one frequency per call, D staged per call; inputs resident in HBM"}
+            "note": "one frequency per call; inputs resident in HBM"}
 
 
 def small_latency(tl, torch, prec, args):

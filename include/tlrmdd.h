@@ -62,6 +62,8 @@ extern "C" {
 #define TLRMDD_BF16X3    1  /* BF16 hi+lo split (hi*hi + hi*lo + lo*hi), FP32 accumulate */
 #define TLRMDD_FP32_3M   2  /* FP32 MFMA, three real products per complex product (3M form):
                                Re = ArBr - AiBi, Im = (Ar+Ai)(Br+Bi) - ArBr - AiBi; 3/4 of the flops */
+/* The products address a matrix (ns x nr, nr x nr, in a solve two of these; sizes rounded up to 128) with 32-bit
+ * byte offsets: it has to be below 4 GiB at 8 bytes an entry, in TLRMDD_BF16X3 at 4. TLRMDD_HIP_ERROR beyond. */
 
 /* ---- optimisers ------------------------------------------------------------ */
 #define TLRMDD_LBFGS 0
